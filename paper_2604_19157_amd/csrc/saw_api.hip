@@ -76,7 +76,7 @@ static bool make_plan(const saw_cache_t* c, int B, int max_pages, int max_seq_le
   int S = num_splits;
   bool block_of_eight = false;
   if (S == 0) {
-    const int64_t items = (int64_t)B * decode_items_per_seq(c->head_dim, c->n_kv_heads);
+    const int64_t items = (int64_t)B * (kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads));
     // one wavefront per (item, partition), about 8 per compute unit; a quarter more for 257 to 511 items,
     // the zone of mid-size ragged batches, where many partitions of the shorter sequences are empty
     // (48 ragged sequences x 8 kv heads: 6 partitions 37.1 us, 7: 34.4 us, 8: 34.2 us; 33 x 8: 8 partitions

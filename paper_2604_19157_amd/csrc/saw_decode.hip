@@ -1,5 +1,5 @@
-// Paged decode attention over the INT4 cache (and over a 16-bit cache for comparison),
-// split-KV with a log-sum-exp merge.  Paper: Sec. 2 (decode step), Sec. 4.1 and App. A.4
+// Paged decode attention over the INT4 cache on the vector ALU, and the
+// log-sum-exp merge of split-KV partitions for every decode kernel.  Paper: Sec. 2 (decode step), Sec. 4.1 and App. A.4
 // (q is rotated once, K is consumed in the rotated space, the output is rotated back
 // once for V), App. A.1 (x^ = s (c - z)).
 //
@@ -194,147 +194,6 @@ __global__ __launch_bounds__(256) void decode_int4_kernel(DecodeParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// 16-bit KV decode (comparison path).  Same decomposition; a token row of D 16-bit values is
-// split over LPT lanes.
-template <int D, int G, int LPT, int DT>
-__global__ __launch_bounds__(256) void decode_kv16_kernel(DecodeParams p) {
-  constexpr int TPW = 64 / LPT;
-  constexpr int CPL = D / LPT;         // elements per lane
-  constexpr int WPL = CPL / 2;         // dwords per lane
-  // (the partition index is rotated by kv head and sequence, so that no XCD serves a fixed set of partitions)
-  const int split = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x, kvh = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int L = min(p.seq_lens[b] + p.len_bias, p.bound);
-  const int t_begin = split * p.chunk_tokens;
-  const int t_end = min(L, t_begin + p.chunk_tokens);
-  if (t_begin >= t_end) return;
-
-  __shared__ float qs[G * D];
-  __shared__ float red[4][G][D + 4];
-  for (int i = tid; i < G * D; i += 256)
-    qs[i] = p.q_scale * load_elem(p.q, p.q_dtype, ((int64_t)b * p.n_q_heads + kvh * G) * D + i);
-  __syncthreads();
-
-  const int part = lane % LPT;
-  float m[G], lsum[G], acc[G][CPL];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -INFINITY; lsum[g] = 0.f;
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) acc[g][j] = 0.f;
-  }
-  const uint16_t* kpages = (const uint16_t*)p.k_codes;
-  const uint16_t* vpages = (const uint16_t*)p.v_codes;
-  const int64_t pt_row = (int64_t)b * p.max_pages;
-  for (int t0 = t_begin + wave * TPW; t0 < t_end; t0 += 4 * TPW) {
-    const int t = t0 + lane / LPT;
-    const bool valid = t < t_end;
-    const int tt = valid ? t : t_end - 1;
-    int32_t page = p.page_table[pt_row + (tt >> 4)];
-    page = (page < 0 || page >= p.num_pages) ? 0 : page;
-    const int64_t vec = ((int64_t)page * p.n_kv_heads + kvh) * 16 + (tt & 15);
-    const uint4* kp = (const uint4*)(kpages + vec * D + part * CPL);
-    const uint4* vp = (const uint4*)(vpages + vec * D + part * CPL);
-    float dot[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) dot[g] = 0.f;
-#pragma unroll
-    for (int i = 0; i < WPL / 4; ++i) {
-      const uint4 w4 = kp[i];
-      const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float lo, hi;
-        widen2<DT>(ww[j], lo, hi);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          dot[g] = fmaf(qs[g * D + part * CPL + i * 8 + 2 * j], lo, dot[g]);
-          dot[g] = fmaf(qs[g * D + part * CPL + i * 8 + 2 * j + 1], hi, dot[g]);
-        }
-      }
-    }
-    float w[G], mnew[G];
-    bool grow = false;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-      for (int mk = 1; mk < LPT; mk <<= 1) dot[g] += __shfl_xor(dot[g], mk, SAW_WAVE);
-      const float logit = valid ? dot[g] : -INFINITY;
-      float mt = logit;
-#pragma unroll
-      for (int mk = LPT; mk < 64; mk <<= 1) mt = fmaxf(mt, __shfl_xor(mt, mk, SAW_WAVE));
-      mnew[g] = fmaxf(m[g], mt);
-      grow |= mnew[g] > m[g];
-      w[g] = logit;
-    }
-    if (grow) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const float a = fast_exp2(m[g] - mnew[g]);
-        lsum[g] *= a;
-#pragma unroll
-        for (int j = 0; j < CPL; ++j) acc[g][j] *= a;
-        m[g] = mnew[g];
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      w[g] = valid ? fast_exp2(w[g] - m[g]) : 0.f;
-      lsum[g] += w[g];
-    }
-#pragma unroll
-    for (int i = 0; i < WPL / 4; ++i) {
-      const uint4 w4 = vp[i];
-      const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float lo, hi;
-        widen2<DT>(ww[j], lo, hi);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          acc[g][i * 8 + 2 * j] = fmaf(w[g], lo, acc[g][i * 8 + 2 * j]);
-          acc[g][i * 8 + 2 * j + 1] = fmaf(w[g], hi, acc[g][i * 8 + 2 * j + 1]);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-#pragma unroll
-    for (int mk = LPT; mk < 64; mk <<= 1) {
-      lsum[g] += __shfl_xor(lsum[g], mk, SAW_WAVE);
-#pragma unroll
-      for (int j = 0; j < CPL; ++j) acc[g][j] += __shfl_xor(acc[g][j], mk, SAW_WAVE);
-    }
-  }
-  if (lane < LPT) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-      for (int j = 0; j < CPL; ++j) red[wave][g][part * CPL + j] = acc[g][j];
-      if (part == 0) { red[wave][g][D] = m[g]; red[wave][g][D + 1] = lsum[g]; }
-    }
-  }
-  __syncthreads();
-  for (int idx = tid; idx < G * (D + 2); idx += 256) {
-    const int g = idx / (D + 2), c = idx % (D + 2);
-    float mm = -INFINITY;
-#pragma unroll
-    for (int wv = 0; wv < 4; ++wv) mm = fmaxf(mm, red[wv][g][D]);
-    float v;
-    if (c == 0) {
-      v = mm;
-    } else {
-      const int src = (c == 1) ? D + 1 : c - 2;
-      v = 0.f;
-#pragma unroll
-      for (int wv = 0; wv < 4; ++wv) v += fast_exp2(red[wv][g][D] - mm) * red[wv][g][src];
-    }
-    p.ws[(((int64_t)b * p.n_q_heads + kvh * G + g) * p.num_splits + split) * (D + 2) + c] = v;
-  }
-}
-
-// ---------------------------------------------------------------------------------------
 // Merge the splits of one (sequence, query head), rotate the output back, write it.
 template <int D, int NT>
 __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
@@ -427,13 +286,6 @@ static void launch_int4(const DecodeParams& p, dim3 grid, hipStream_t st) {
   constexpr int LPT = (G >= 8) ? 8 : 4;
   decode_int4_kernel<D, G, LPT><<<grid, dim3(256), 0, st>>>(p);
 }
-template <int D, int G, int DT>
-static void launch_kv16(const DecodeParams& p, dim3 grid, hipStream_t st) {
-  constexpr int LPT = (G >= 8 || D == 128) ? 8 : 4;
-  constexpr int LPT2 = (G >= 8 && D == 128) ? 16 : LPT;
-  decode_kv16_kernel<D, G, LPT2, DT><<<grid, dim3(256), 0, st>>>(p);
-}
-
 int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_dtype, hipStream_t st) {
   dim3 grid(p.num_splits, p.n_kv_heads, B);
   const bool head_pairs = !kv16 && decode_head_pairs(D, p.n_kv_heads, G);
@@ -442,19 +294,20 @@ int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_
     if (launch_decode_int4_mfma(p, G, B, p.waves_per_item, head_pairs, mgrid, st) != SAW_OK) return SAW_EINVAL;
     if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
     if (p.num_splits == 1) return SAW_OK;       // the kernel wrote the output itself
-  } else if (kv16 && D == 128 && launch_decode_kv16_mfma(p, G, kv_dtype, grid, st)) {
+  } else if (kv16) {
+    if (launch_decode_kv16_mfma(p, D, G, kv_dtype, grid, st) != SAW_OK) return SAW_EINVAL;
     if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
     if (p.num_splits == 1) return SAW_OK;       // the kernel wrote the output itself
   } else {
 #define SAW_DISPATCH_G(DD)                                                          \
   switch (G) {                                                                      \
-    case 1: if (kv16) { if (kv_dtype == SAW_BF16) launch_kv16<DD, 1, SAW_BF16>(p, grid, st); else launch_kv16<DD, 1, SAW_F16>(p, grid, st); } else launch_int4<DD, 1>(p, grid, st); break; \
-    case 2: if (kv16) { if (kv_dtype == SAW_BF16) launch_kv16<DD, 2, SAW_BF16>(p, grid, st); else launch_kv16<DD, 2, SAW_F16>(p, grid, st); } else launch_int4<DD, 2>(p, grid, st); break; \
-    case 4: if (kv16) { if (kv_dtype == SAW_BF16) launch_kv16<DD, 4, SAW_BF16>(p, grid, st); else launch_kv16<DD, 4, SAW_F16>(p, grid, st); } else launch_int4<DD, 4>(p, grid, st); break; \
-    case 8: if (kv16) { if (kv_dtype == SAW_BF16) launch_kv16<DD, 8, SAW_BF16>(p, grid, st); else launch_kv16<DD, 8, SAW_F16>(p, grid, st); } else launch_int4<DD, 8>(p, grid, st); break; \
+    case 1: launch_int4<DD, 1>(p, grid, st); break;                                 \
+    case 2: launch_int4<DD, 2>(p, grid, st); break;                                 \
+    case 4: launch_int4<DD, 4>(p, grid, st); break;                                 \
+    case 8: launch_int4<DD, 8>(p, grid, st); break;                                 \
     default: return SAW_EINVAL;                                                     \
   }
-  if (D == 128) { SAW_DISPATCH_G(128) } else { SAW_DISPATCH_G(64) }
+  SAW_DISPATCH_G(64)                            // (head_dim 128 is always on the matrix cores)
 #undef SAW_DISPATCH_G
   }
   if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
@@ -566,7 +419,7 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
   }
   // the 16-bit matrix-core kernel has the two-wavefront pair mode as well (same conditions), so that
   // the comparison on a ragged batch is between formats and not between schedules
-  if (kv16 && c->head_dim == 128 && G <= 4 && plan.num_splits == 1 && B <= 1024 &&
+  if (kv16 && plan.num_splits == 1 && B <= 1024 &&
       (int64_t)B * c->n_kv_heads > 256 && (int64_t)((B + 1) / 2) * c->n_kv_heads <= 1024)
     p.pair = 2;
   return launch_decode(p, B, c->head_dim, G, kv16, kv_dtype, st);

@@ -178,6 +178,52 @@ def test_kv16_comparison_path(saw, dtype, Hq, Hkv, d):
         assert err < TOL
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("G,Hkv,d", [(8, 2, 128), (1, 3, 64), (2, 1, 64), (4, 2, 64), (8, 3, 64), (4, 2, 128)])
+@pytest.mark.parametrize("big", [False, True])
+def test_kv16_batch_edges(saw, dtype, G, Hkv, d, big):
+    """Lengths around the batches (32 tokens of head_dim 128, 64 of head_dim 64), every slot that holds no
+    token filled with NaN, partitions forced and automatic, pair blocks (`big`), a query beyond the fp16 range.
+    Bound: with 24 (fp16 cache: 22) bits of q and P what is left are fp32 sums: a logit of a few units carries
+    2^-23 of itself, an output likewise; 4e-6 of the largest output (two bf16 limbs, four heads of 128: 2^-16
+    each of q and P, 1e-4)."""
+    rng = np.random.default_rng(G * d + Hkv)
+    lens = [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 127, 128, 129, 300]
+    if big:
+        lens = (lens * (260 // (16 * Hkv) + 1))[: 260 // Hkv + 1]
+    B = len(lens)
+    n_pages = sum((n + 15) // 16 for n in lens) + 1
+    perm, o = rng.permutation(n_pages).astype(np.int32), 0
+    pt = np.zeros((B, 20), np.int32)
+    k16 = torch.full((n_pages, Hkv, 16, d), float("nan"), dtype=dtype)
+    v16 = k16.clone()
+    for b, n in enumerate(lens):
+        for i in range((n + 15) // 16):
+            pt[b, i] = perm[o]
+            m = min(16, n - 16 * i)
+            for t in (k16, v16):
+                t[perm[o], :, :m] = torch.from_numpy(rng.standard_normal((Hkv, m, d))).to(dtype)
+            o += 1
+    q = torch.from_numpy(rng.standard_normal((B, Hkv * G, d)).astype(np.float32))
+    q[2] *= 3e6                                                        # (a one-hot softmax: any 16-bit limb of it overflows)
+    ref = O.kv16_paged_decode_attn(k16.float().nan_to_num(0.0).numpy(), v16.float().nan_to_num(0.0).numpy(), q.numpy(), pt,
+                                   np.asarray(lens))
+    kc = saw.Kv16Cache(n_pages, Hkv, d, dtype)
+    kc.k_pages.copy_(k16)
+    kc.v_pages.copy_(v16)
+    rows = [b for b in range(B) if b != 2]
+    limit = 1e-4 if (G <= 4 and d == 128 and dtype == torch.bfloat16) else 4e-6
+    for splits in (1, 2, 0):
+        out = torch.full((B, Hkv * G, d), float("nan"), device="cuda")
+        saw.kv16_paged_decode_attn(kc, q.cuda(), torch.from_numpy(pt).cuda(), torch.tensor(lens, dtype=torch.int32).cuda(),
+                                   num_splits=splits, out=out)
+        got = out.cpu().numpy()
+        err, err2 = parity.attn_error(got[rows], ref[rows]), parity.attn_error(got[2:3], ref[2:3])
+        print(f"[kv16 edges {dtype} G={G} Hkv={Hkv} d={d} splits={splits}] err={err:.2e} large q {err2:.2e}", flush=True)
+        assert np.isfinite(got).all() and err < limit and err2 < TOL
+        assert not got[0].any()
+
+
 @pytest.mark.parametrize("lens", [[0] * 64, [1] * 64, [0] * 40 + [1] * 24, [64] * 63 + [0], [65] * 32 + [63] * 32,
                                   [200] * 2 + [1] * 62, [129] * 33 + [0] * 32, [256] + [0] * 63,
                                   list(range(64)), [128] * 64, [64 * (i % 5) for i in range(64)]])
