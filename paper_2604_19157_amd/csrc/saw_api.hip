@@ -14,8 +14,6 @@ static __device__ __align__(256) unsigned char scratch[SAW_STATIC_SCRATCH_BYTES]
 namespace saw {
 
 
-int launch_store(const saw_cache_t*, const void*, const void*, int, int64_t, int64_t, const int32_t*,
-                 int32_t, int32_t, const int32_t*, const int32_t*, int32_t, hipStream_t);
 int launch_prepare_dense(const float*, void*, hipStream_t);
 int launch_decode_order(const int32_t*, int, int, int32_t*, hipStream_t);
 int launch_read_probe(const saw_cache_t*, const int32_t*, int64_t, void*, int32_t, hipStream_t);
@@ -32,7 +30,7 @@ int launch_kv16_store(const saw_cache_t*, void*, void*, const void*, const void*
 int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void* v_pages, int kv_dtype,
                const void* q, int q_dtype, int B, int Hq, const int32_t* pt, int max_pages,
                const int32_t* seq_lens, float sm_scale, void* out, int out_dtype, void* ws,
-               const SplitPlan& plan, const void* k_new, const void* v_new, int kv_new_dtype, int len_bias,
+               const SplitPlan& plan, const void* k_new, const void* v_new, int kv_new_dtype,
                const int32_t* order, hipStream_t st);
 
 static bool aligned16(const void* p) { return (((uintptr_t)p) & 15u) == 0; }
@@ -41,6 +39,26 @@ static bool shape_ok(const saw_cache_t* c) {
   if (c->page_size != 16) return false;
   if (c->head_dim != 64 && c->head_dim != 128) return false;
   if (c->n_kv_heads < 1 || c->num_pages < 1) return false;
+  return true;
+}
+
+// A batch cut by its own lengths (saw_cut.h) into at most `slots` partitions per kv head, of at least four 64-token batches:
+// a shorter one costs more in prologue and merge pass than it brings.  Very many partitions per sequence (few long
+// sequences) become a quarter of them with four wavefronts each, whose states are folded in LDS: the merge pass then
+// reads a quarter of the partial records.  False if a sequence would not get two partitions on average.
+constexpr int kMaxCutSequences = 256;           // (as many lengths as a wavefront keeps in registers)
+static bool cut_plan(int B, int units, int slots, SplitPlan* plan) {
+  constexpr int kMin = 4;
+  if (B > kMaxCutSequences || (int64_t)B * units >= (1 << 23)) return false;   // (counts are divided in fp32)
+  int64_t most = (int64_t)B * ((units + kMin - 1) / kMin);
+  int w = slots < most ? slots : (int)most;
+  int waves = 1;
+  if (w > 64 * B && units / (w / (4 * B)) >= 32) { waves = 4; w /= 4; }
+  if (w > 1024) w = 1024;                       // (the merge pass keeps a weight per slot of a sequence)
+  if (w < 2 * B) return false;
+  plan->cut = w;
+  plan->cut_min = kMin;
+  plan->cut_waves = waves;
   return true;
 }
 
@@ -57,6 +75,28 @@ static bool block_ok(const saw_cache_t* c) {
 }
 
 
+// The kernel that takes 64-channel heads one at a time (saw_decode_split.hip).  Its registers allow 12 wavefronts on a
+// compute unit and a batch is only 5 KiB, so it wants 3072 of them.  Small batches of short contexts: one block of eight
+// wavefronts per (sequence, kv head), a single launch.  Otherwise the batch is cut by its own lengths, as long as that
+// gives a sequence two slots on average; beyond that one partition per sequence, of four wavefronts while they fit.
+static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan) {
+  const int64_t items = (int64_t)B * c->n_kv_heads;
+  constexpr int kWaves = 3072;
+  const int per_wave = (units + 7) / 8;
+  plan->waves_per_item = 1;
+  if (items <= 256 && (per_wave <= 5 || (items >= 192 && per_wave <= 8))) {
+    plan->num_splits = 1;
+    plan->chunk_tokens = units * 64;
+    plan->waves_per_item = 8;
+    return;
+  }
+  if (cut_plan(B, units, kWaves / c->n_kv_heads, plan)) return;
+  if (B > kMaxCutSequences && items < kWaves / 2) return;             // (fixed partitions, as planned)
+  plan->num_splits = 1;
+  plan->chunk_tokens = units * 64;
+  plan->waves_per_item = items * 4 <= kWaves ? 4 : 1;
+}
+
 // Split-KV plan.  Partitions are whole multiples of 64 tokens so every wavefront pass
 // starts on a page boundary.  The automatic choice aims at about 2048 wavefronts (8 per compute
 // unit): one partition per sequence once the batch alone provides them, otherwise partitions of
@@ -65,7 +105,8 @@ static bool block_ok(const saw_cache_t* c) {
 // their pair mode evens out ragged lengths inside the launch at any occupancy, and the merge
 // pass costs more than the extra wavefronts bring (256 sequences x 4 kv heads, 2304 tokens each:
 // 61 us against 66 us with two partitions; ragged 80 against 84; at 320 items partitions win).
-static bool make_plan(const saw_cache_t* c, int B, int max_pages, int max_seq_len, int num_splits,
+// `G`: query heads per kv head (0: not known, the plan of a batch in fixed partitions is wanted).
+static bool make_plan(const saw_cache_t* c, int B, int G, int max_pages, int max_seq_len, int num_splits,
                       bool kv16, SplitPlan* plan) {
   const int64_t cap = (int64_t)max_pages * c->page_size;
   if (cap <= 0 || cap > 0x7fffffffLL) return false;
@@ -122,6 +163,9 @@ static bool make_plan(const saw_cache_t* c, int B, int max_pages, int max_seq_le
   while (nw < 4 && blocks * nw * 2 <= 2560 && plan->chunk_tokens / (nw * 2) >= 512) nw *= 2;
   if (block_of_eight && plan->num_splits == 1) nw = 8;
   plan->waves_per_item = nw;
+  plan->cut = plan->cut_min = plan->cut_waves = 0;
+  if (num_splits != 0 || G == 0) return true;
+  if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G)) plan_split64(c, B, units, plan);
   return true;
 }
 
@@ -169,8 +213,8 @@ int saw_rotate_quant_store(const saw_cache_t* c, const void* K, const void* V, i
   if (!aligned16(K) || !aligned16(V) || !aligned16(c->k_codes) || !aligned16(c->v_codes) ||
       (((uintptr_t)c->k_meta) & 7u) || (((uintptr_t)c->v_meta) & 7u) || (((uintptr_t)slots) & 7u))
     return SAW_EINVAL;
-  return launch_store(c, K, V, in_dtype, T, token_stride_elems, page_table, n_seqs, max_pages_per_seq,
-                      slots, nullptr, 0, (hipStream_t)stream);
+  return launch_store_layers(c, &K, &V, 1, in_dtype, T, token_stride_elems, page_table, n_seqs, max_pages_per_seq,
+                             slots, (hipStream_t)stream);
 }
 
 int saw_rotate_quant_store_layers(const saw_cache_t* caches, const void* const* K, const void* const* V,
@@ -247,11 +291,15 @@ size_t saw_decode_workspace_bytes(const saw_cache_t* c, int32_t B, int32_t n_q_h
   const int max_pages = (max_seq_len + c->page_size - 1) / c->page_size;
   // (the INT4 and the 16-bit calls may choose different partition counts: enough for either)
   SplitPlan plan16;
-  if (!make_plan(c, B, max_pages, max_seq_len, num_splits, false, &plan) ||
-      !make_plan(c, B, max_pages, max_seq_len, num_splits, true, &plan16))
+  SplitPlan fixed;
+  const int G = n_q_heads % c->n_kv_heads ? 0 : n_q_heads / c->n_kv_heads;
+  if (!make_plan(c, B, G, max_pages, max_seq_len, num_splits, false, &plan) ||
+      !make_plan(c, B, G, max_pages, max_seq_len, num_splits, true, &plan16) ||
+      !make_plan(c, B, 0, max_pages, max_seq_len, num_splits, false, &fixed))
     return 0;
-  return partial_bytes(B, n_q_heads, plan.num_splits > plan16.num_splits ? plan.num_splits : plan16.num_splits,
-                       c->head_dim);
+  const size_t a = plan_bytes(plan, B, n_q_heads, c->head_dim), b = plan_bytes(plan16, B, n_q_heads, c->head_dim);
+  const size_t f = plan_bytes(fixed, B, n_q_heads, c->head_dim);
+  return a > b ? (a > f ? a : f) : (b > f ? b : f);
 }
 
 int saw_decode_plan(const saw_cache_t* c, int32_t B, int32_t max_seq_len, int32_t num_splits,
@@ -260,7 +308,7 @@ int saw_decode_plan(const saw_cache_t* c, int32_t B, int32_t max_seq_len, int32_
   if (!shape_ok(c) || B < 1 || max_seq_len < 1) return SAW_EINVAL;
   SplitPlan plan;
   const int max_pages = (max_seq_len + c->page_size - 1) / c->page_size;
-  if (!make_plan(c, B, max_pages, max_seq_len, num_splits, false, &plan)) return SAW_EINVAL;
+  if (!make_plan(c, B, 0, max_pages, max_seq_len, num_splits, false, &plan)) return SAW_EINVAL;
   if (splits_out) *splits_out = plan.num_splits;
   if (chunk_tokens_out) *chunk_tokens_out = plan.chunk_tokens;
   return SAW_OK;
@@ -293,6 +341,15 @@ int saw_decode_order(const int32_t* seq_lens, int32_t B, int32_t max_seq_len, in
   return launch_decode_order(seq_lens, B, max_seq_len <= 0 ? 0x7fffffff : max_seq_len, order_out, (hipStream_t)stream);
 }
 
+// The plan of one call: a batch is cut by its own lengths only where the caller's workspace holds that (it does if it was
+// sized by saw_decode_workspace_bytes); one sized for the partitions of saw_decode_plan gets those.
+static bool plan_call(const saw_cache_t* c, int B, int Hq, int max_pages, int max_seq_len, int num_splits, bool kv16,
+                      size_t ws_bytes, SplitPlan* plan) {
+  if (!make_plan(c, B, Hq / c->n_kv_heads, max_pages, max_seq_len, num_splits, kv16, plan)) return false;
+  if (ws_bytes >= plan_bytes(*plan, B, Hq, c->head_dim)) return true;
+  return make_plan(c, B, 0, max_pages, max_seq_len, num_splits, kv16, plan);
+}
+
 static int decode_common(const saw_cache_t* c, bool kv16, const void* kp, const void* vp, int kv_dtype,
                          const void* q, int32_t q_dtype, int32_t B, int32_t Hq, const int32_t* pt,
                          int32_t max_pages, const int32_t* seq_lens, int32_t max_seq_len, float sm_scale,
@@ -316,11 +373,10 @@ static int decode_common(const saw_cache_t* c, bool kv16, const void* kp, const 
   if (!kv16 && (!aligned16(c->k_meta) || !aligned16(c->v_meta))) return SAW_EINVAL;
   if (!isfinite(sm_scale)) return SAW_EINVAL;
   SplitPlan plan;
-  if (!make_plan(c, B, max_pages, max_seq_len, num_splits, kv16, &plan)) return SAW_EINVAL;
-  const size_t need = partial_bytes(B, Hq, plan.num_splits, c->head_dim);
-  if (ws_bytes < need) return SAW_EWORKSPACE;
+  if (!plan_call(c, B, Hq, max_pages, max_seq_len, num_splits, kv16, ws_bytes, &plan)) return SAW_EINVAL;
+  if (ws_bytes < plan_bytes(plan, B, Hq, c->head_dim)) return SAW_EWORKSPACE;
   return run_decode(c, kv16, kp, vp, kv_dtype, q, q_dtype, B, Hq, pt, max_pages, seq_lens, sm_scale, out,
-                    out_dtype, ws, plan, nullptr, nullptr, 0, 0, hints ? hints->order : nullptr, (hipStream_t)stream);
+                    out_dtype, ws, plan, nullptr, nullptr, 0, hints ? hints->order : nullptr, (hipStream_t)stream);
 }
 
 int saw_paged_decode_attn(const saw_cache_t* c, const void* q, int32_t q_dtype, int32_t B,
@@ -371,8 +427,9 @@ int saw_paged_decode_attn_static(const saw_cache_t* c, const void* q, int32_t q_
   if (!shape_ok(c) || B < 1 || n_q_heads < 1 || max_pages_per_seq < 1) return SAW_EINVAL;
   // the scratch the plan needs, before anything else: too large is an error of its own
   SplitPlan plan;
-  if (!make_plan(c, B, max_pages_per_seq, max_seq_len, num_splits, false, &plan)) return SAW_EINVAL;
-  if (partial_bytes(B, n_q_heads, plan.num_splits, c->head_dim) > (size_t)SAW_STATIC_SCRATCH_BYTES) return SAW_ESCRATCH;
+  if (!plan_call(c, B, n_q_heads, max_pages_per_seq, max_seq_len, num_splits, false, (size_t)SAW_STATIC_SCRATCH_BYTES, &plan))
+    return SAW_EINVAL;
+  if (plan_bytes(plan, B, n_q_heads, c->head_dim) > (size_t)SAW_STATIC_SCRATCH_BYTES) return SAW_ESCRATCH;
   void* ws = nullptr;
   const int rc = static_scratch_ptr(&ws);
   if (rc != SAW_OK) return rc;
@@ -409,26 +466,14 @@ static int append_common(const saw_cache_t* c, const void* K_new, const void* V_
   const int64_t after = (max_seq_len <= 0 ? cap - 1 : (int64_t)max_seq_len) + 1;
   if (after > cap) return SAW_EINVAL;
   SplitPlan plan;
-  const bool fused_kernel = c->head_dim == 128 || decode_head_pairs(c->head_dim, c->n_kv_heads, G);
-  if (!make_plan(c, B, max_pages, (int)after, 0, false, &plan)) return SAW_EINVAL;
-  const size_t need = partial_bytes(B, Hq, plan.num_splits, c->head_dim);
-  if (ws_bytes < need) return SAW_EWORKSPACE;
-  if (fused_kernel) {
-    // the decode kernel stores the new token itself and attends to it from registers (with several
-    // partitions per sequence the one that starts the sequence does, and the merge kernel follows);
-    // the cached range is [0, seq_lens[b]), bounded by max_seq_len as given
-    plan.bound = (int)(after - 1);
-    return run_decode(c, false, c->k_codes, c->v_codes, 0, q, q_dtype, B, Hq, page_table, max_pages, seq_lens,
-                      sm_scale, out, out_dtype, ws, plan, K_new, V_new, kv_dtype, 0, hints ? hints->order : nullptr,
-                      (hipStream_t)stream);
-  }
-  // head_dim 64 outside the head-pair kernel: two launches from the same call: append (token b -> sequence b at seq_lens[b]),
-  // then decode over seq_lens[b] + 1 tokens
-  const int rc = launch_store(c, K_new, V_new, kv_dtype, B, (int64_t)c->n_kv_heads * c->head_dim, page_table, B,
-                              max_pages, nullptr, seq_lens, (int32_t)(after - 1), (hipStream_t)stream);
-  if (rc != SAW_OK) return rc;
+  if (!plan_call(c, B, Hq, max_pages, (int)after, 0, false, ws_bytes, &plan)) return SAW_EINVAL;
+  if (ws_bytes < plan_bytes(plan, B, Hq, c->head_dim)) return SAW_EWORKSPACE;
+  // the decode kernel stores the new token itself and attends to it from on-chip memory (with several
+  // partitions per sequence one of them does, and the merge kernel follows);
+  // the cached range is [0, seq_lens[b]), bounded by max_seq_len as given
+  plan.bound = (int)(after - 1);
   return run_decode(c, false, c->k_codes, c->v_codes, 0, q, q_dtype, B, Hq, page_table, max_pages, seq_lens,
-                    sm_scale, out, out_dtype, ws, plan, nullptr, nullptr, 0, 1, hints ? hints->order : nullptr,
+                    sm_scale, out, out_dtype, ws, plan, K_new, V_new, kv_dtype, hints ? hints->order : nullptr,
                     (hipStream_t)stream);
 }
 

@@ -100,6 +100,9 @@ struct SplitPlan {
   int32_t chunk_tokens;   // tokens per partition (multiple of 64)
   int32_t bound;          // clamp for seq_lens
   int32_t waves_per_item; // wavefronts that share one partition in the MFMA decode kernel
+  int32_t cut;            // partition slots per kv head if the kernel cuts the batch by its own lengths (saw_cut.h); 0: as above
+  int32_t cut_min;        // 64-token batches such a partition has at least
+  int32_t cut_waves;      // wavefronts that share one
 };
 
 }  // namespace saw

@@ -23,12 +23,13 @@ struct DecodeParams {
   const void* k_new;    // fused append (matrix-core INT4 path): the step's K, V [B][Hkv][d], else null
   const void* v_new;
   int32_t kv_new_dtype, append;
-  int32_t len_bias;     // added to every seq_lens entry (1 when a separate store launch appended a token)
   int32_t sorted;           // matrix-core path, one block per (sequence, kv head): block z takes the sequence of length rank z
   int32_t pair;             // matrix-core path: blocks of this many wavefronts (2 or 4) over (long, short) sequence pairs; 0: off
   int32_t pair_seqs;        // matrix-core path, pair mode: sequences per block, 2 or (with pair == 4) 3
   const int32_t* order;     // matrix-core INT4 path: the caller's longest-first order of the sequences, or null (ranked in the kernel)
   int32_t batch;
+  int32_t cut;              // partition slots per kv head of a batch that the kernel cuts by its own lengths (saw_cut.h); 0: fixed partitions
+  int32_t cut_min;          // ... 64-token batches a partition has at least
   int32_t waves_per_item;   // matrix-core path: wavefronts sharing one partition (1, 2, 4 or 8)
   const float* dense;       // learned rotation R_l (App. A.3): fp32 [128][128], its transpose right behind it; null: none
   int32_t dense_k, dense_v; // R_l applies to K and the query / to V and the output
@@ -57,6 +58,10 @@ int launch_decode_int4_mfma(const DecodeParams& p, int G, int B, int nw, bool he
 inline bool decode_head_pairs(int head_dim, int n_kv_heads, int G) {
   return head_dim == 64 && n_kv_heads % 2 == 0 && (G == 1 || G == 2 || G == 4);
 }
+// the head_dim 64 shapes that leaves go one 64-channel head at a time (saw_decode_split.hip):
+// grid = (splits, kv heads, batch), or (slots, kv heads) for a batch cut by its own lengths
+int launch_decode_int4_split64(const DecodeParams& p, int G, int nw, dim3 grid, hipStream_t st);
+
 // (sequence, kv head) work items per sequence as the INT4 decode kernels see them
 inline int decode_items_per_seq(int head_dim, int n_kv_heads) {
   return (head_dim == 64 && n_kv_heads % 2 == 0) ? n_kv_heads / 2 : n_kv_heads;
@@ -67,6 +72,10 @@ int launch_decode_kv16_mfma(const DecodeParams& p, int D, int G, int kv_dtype, d
 
 inline size_t partial_bytes(int B, int Hq, int splits, int D) {
   return (((size_t)B * Hq * splits * (D + 2) * sizeof(float)) + 15) & ~(size_t)15;
+}
+// scratch of a call as planned: partial results per (sequence, split), or per slot of a batch cut by its own lengths
+inline size_t plan_bytes(const SplitPlan& plan, int B, int Hq, int D) {
+  return plan.cut ? partial_bytes(1, Hq, plan.cut, D) : partial_bytes(B, Hq, plan.num_splits, D);
 }
 
 }  // namespace saw

@@ -1,197 +1,10 @@
-// Paged decode attention over the INT4 cache on the vector ALU, and the
-// log-sum-exp merge of split-KV partitions for every decode kernel.  Paper: Sec. 2 (decode step), Sec. 4.1 and App. A.4
-// (q is rotated once, K is consumed in the rotated space, the output is rotated back
-// once for V), App. A.1 (x^ = s (c - z)).
-//
-// The zero-point never enters the inner loop:
-//   q~ . k^_t      = s_t (q~ . c_t) - s_t z_t sum(q~)
-//   sum_t p_t v^_t = sum_t (p_t s_t) c_t - sum_t p_t s_t z_t
-// Logits are kept in base-2 units (log2 e folded into q~) so the softmax uses exp2.
+// Split-KV merge (log-sum-exp) of the decode kernels' partial results, and the dispatch of the decode calls.
+// Paper: Sec. 2 (decode step), Sec. 4.1 and App. A.4 (the output is rotated back once for V).
 #include "saw_decode.h"
 #include "saw_wave_util.h"
+#include "saw_cut.h"
 
 namespace saw {
-
-
-// In-place un-normalised block Walsh-Hadamard over `n_vec` vectors of length D held in LDS.
-template <int D>
-__device__ __forceinline__ void lds_fwht(float* x, int n_vec, int h, int tid, int nthreads) {
-  for (int st = 1; st < h; st <<= 1) {
-    for (int idx = tid; idx < n_vec * (D / 2); idx += nthreads) {
-      const int v = idx / (D / 2);
-      const int r = idx % (D / 2);
-      const int i = v * D + (r / st) * 2 * st + (r % st);
-      const float a = x[i], b = x[i + st];
-      x[i] = a + b;
-      x[i + st] = a - b;
-    }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------------------
-// INT4 decode, VALU formulation.  One 256-thread block per (sequence, kv head, split).
-// A wavefront covers 64/LPT tokens per pass; a token's code row is split over LPT lanes.
-template <int D, int G, int LPT>
-__global__ __launch_bounds__(256) void decode_int4_kernel(DecodeParams p) {
-  constexpr int TPW = 64 / LPT;        // tokens per wave pass
-  constexpr int CPL = D / LPT;         // codes per lane
-  constexpr int WPL = CPL / 8;         // dwords per lane
-  // (the partition index is rotated by kv head and sequence, so that no XCD serves a fixed set of partitions)
-  const int split = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x, kvh = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int L = min(p.seq_lens[b] + p.len_bias, p.bound);
-  const int t_begin = split * p.chunk_tokens;
-  const int t_end = min(L, t_begin + p.chunk_tokens);
-  if (t_begin >= t_end) return;
-
-  __shared__ float qs[G * D];
-  __shared__ float qsum[G];
-  __shared__ float red[4][G][D + 4];
-
-  // ---- q~ = (q H_blk) * sm_scale * log2 e ----
-  for (int i = tid; i < G * D; i += 256) {
-    const float v = load_elem(p.q, p.q_dtype, ((int64_t)b * p.n_q_heads + kvh * G) * D + i);
-    qs[i] = (p.rot_k && p.has_signs) ? apply_sign(p.signs, i % D, v) : v;       // q diag(sigma), then H_blk
-  }
-  __syncthreads();
-  float qmul = p.q_scale;
-  if (p.rot_k) {
-    lds_fwht<D>(qs, G, p.had_block, tid, 256);
-    qmul *= had_norm(p.had_block);
-  }
-  for (int i = tid; i < G * D; i += 256) qs[i] *= qmul;
-  __syncthreads();
-  if (tid < G) {
-    float s = 0.f;
-    for (int c = 0; c < D; ++c) s += qs[tid * D + c];
-    qsum[tid] = s;
-  }
-  __syncthreads();
-
-  const int part = lane % LPT;
-  float m[G], lsum[G], zsum[G], acc[G][CPL];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -INFINITY; lsum[g] = 0.f; zsum[g] = 0.f;
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) acc[g][j] = 0.f;
-  }
-
-  const int64_t pt_row = (int64_t)b * p.max_pages;
-  for (int t0 = t_begin + wave * TPW; t0 < t_end; t0 += 4 * TPW) {
-    const int t = t0 + lane / LPT;
-    const bool valid = t < t_end;
-    const int tt = valid ? t : t_end - 1;
-    int32_t page = p.page_table[pt_row + (tt >> 4)];
-    page = (page < 0 || page >= p.num_pages) ? 0 : page;
-    const int64_t vec = ((int64_t)page * p.n_kv_heads + kvh) * 16 + (tt & 15);
-    uint32_t kw[WPL], vw[WPL];
-    {
-      const uint32_t* kp = (const uint32_t*)(p.k_codes + vec * (D / 2)) + part * WPL;
-      const uint32_t* vp = (const uint32_t*)(p.v_codes + vec * (D / 2)) + part * WPL;
-#pragma unroll
-      for (int i = 0; i < WPL; ++i) { kw[i] = kp[i]; vw[i] = vp[i]; }
-    }
-    const float2 ksz = *(const float2*)(p.k_meta + vec * 2);
-    const float2 vsz = *(const float2*)(p.v_meta + vec * 2);
-
-    float dot[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) dot[g] = 0.f;
-#pragma unroll
-    for (int i = 0; i < WPL; ++i) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float c = (float)((kw[i] >> (4 * j)) & 15u);
-#pragma unroll
-        for (int g = 0; g < G; ++g) dot[g] = fmaf(qs[g * D + part * CPL + i * 8 + j], c, dot[g]);
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-      for (int mk = 1; mk < LPT; mk <<= 1) dot[g] += __shfl_xor(dot[g], mk, SAW_WAVE);
-    }
-    float w[G];
-    bool grow = false;
-    float mnew[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float logit = valid ? ksz.x * (dot[g] - ksz.y * qsum[g]) : -INFINITY;
-      float mt = logit;
-#pragma unroll
-      for (int mk = LPT; mk < 64; mk <<= 1) mt = fmaxf(mt, __shfl_xor(mt, mk, SAW_WAVE));
-      mnew[g] = fmaxf(m[g], mt);
-      grow |= mnew[g] > m[g];
-      w[g] = logit;
-    }
-    if (grow) {  // wave-uniform: m and mt are identical in every lane
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const float a = fast_exp2(m[g] - mnew[g]);   // exp2(-inf) = 0 on the first pass
-        lsum[g] *= a; zsum[g] *= a;
-#pragma unroll
-        for (int j = 0; j < CPL; ++j) acc[g][j] *= a;
-        m[g] = mnew[g];
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float pr = valid ? fast_exp2(w[g] - m[g]) : 0.f;
-      lsum[g] += pr;
-      w[g] = pr * vsz.x;
-      zsum[g] = fmaf(w[g], vsz.y, zsum[g]);
-    }
-#pragma unroll
-    for (int i = 0; i < WPL; ++i) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float c = (float)((vw[i] >> (4 * j)) & 15u);
-#pragma unroll
-        for (int g = 0; g < G; ++g) acc[g][i * 8 + j] = fmaf(w[g], c, acc[g][i * 8 + j]);
-      }
-    }
-  }
-
-  // ---- reduce over the token lanes of the wave ----
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-#pragma unroll
-    for (int mk = LPT; mk < 64; mk <<= 1) {
-      lsum[g] += __shfl_xor(lsum[g], mk, SAW_WAVE);
-      zsum[g] += __shfl_xor(zsum[g], mk, SAW_WAVE);
-#pragma unroll
-      for (int j = 0; j < CPL; ++j) acc[g][j] += __shfl_xor(acc[g][j], mk, SAW_WAVE);
-    }
-  }
-  if (lane < LPT) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-      for (int j = 0; j < CPL; ++j) red[wave][g][part * CPL + j] = acc[g][j] - zsum[g];
-      if (part == 0) { red[wave][g][D] = m[g]; red[wave][g][D + 1] = lsum[g]; }
-    }
-  }
-  __syncthreads();
-  // ---- merge the four waves, write the split's partial ----
-  for (int idx = tid; idx < G * (D + 2); idx += 256) {
-    const int g = idx / (D + 2), c = idx % (D + 2);
-    float mm = -INFINITY;
-#pragma unroll
-    for (int wv = 0; wv < 4; ++wv) mm = fmaxf(mm, red[wv][g][D]);
-    float v;
-    if (c == 0) {
-      v = mm;
-    } else {
-      const int src = (c == 1) ? D + 1 : c - 2;
-      v = 0.f;
-#pragma unroll
-      for (int wv = 0; wv < 4; ++wv) v += fast_exp2(red[wv][g][D] - mm) * red[wv][g][src];
-    }
-    p.ws[(((int64_t)b * p.n_q_heads + kvh * G + g) * p.num_splits + split) * (D + 2) + c] = v;
-  }
-}
 
 // ---------------------------------------------------------------------------------------
 // Merge the splits of one (sequence, query head), rotate the output back, write it.
@@ -202,11 +15,21 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
   const int j = blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = tid % D, g = tid / D;
-  const int L = min(p.seq_lens[b] + p.len_bias, p.bound);
   const int64_t o_idx = ((int64_t)b * p.n_q_heads + j) * D + c;
-  // partitions that ran: those that start inside the cached tokens, and with a fused append the
-  // first one in any case (it carries the step's own token)
-  const int ns = max((max(L, 0) + p.chunk_tokens - 1) / p.chunk_tokens, p.append ? 1 : 0);
+  int ns;                                     // partitions that ran
+  const float* base = p.ws;                   // their records
+  if (p.cut) {
+    int first;
+    const BatchCut cut = cut_batch(p, lane);
+    cut_slots_of(cut, b, first, ns);
+    base += ((int64_t)j * p.cut + first) * (D + 2);
+  } else {
+    // those that start inside the cached tokens, and with a fused append the first one in any case (it
+    // carries the step's own token)
+    const int L = min(p.seq_lens[b], p.bound);
+    ns = max((max(L, 0) + p.chunk_tokens - 1) / p.chunk_tokens, p.append ? 1 : 0);
+    base += ((int64_t)b * p.n_q_heads + j) * p.num_splits * (D + 2);
+  }
   if (ns == 0) {
     if (g == 0) store_elem(p.out, p.out_dtype, o_idx, 0.f);
     return;
@@ -214,20 +37,32 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
   __shared__ float wgt[1024];
   __shared__ __attribute__((aligned(16))) float red[NG][D];
   __shared__ float wred[2][NW];
-  const float* base = p.ws + ((int64_t)b * p.n_q_heads + j) * p.num_splits * (D + 2);
-  // Every split's (max, sum) pair is read once, by thread s (the launch gives the block at least as
-  // many threads as there are splits): reference maximum, then weights and the denominator.
-  float2 ml = make_float2(-INFINITY, 0.f);
-  if (tid < ns) ml = *(const float2*)(base + (int64_t)tid * (D + 2));
-  float mm = max_xor32(max_xor16(row_allmax(ml.x)));
+  // Every split's (max, sum) pair is read once, by thread s, s + NT, ... (at most 1024 splits): reference
+  // maximum, then weights and the denominator.
+  constexpr int NM = 1024 / NT;
+  float2 ml[NM];
+  float mm = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < NM; ++k) {
+    ml[k] = make_float2(-INFINITY, 0.f);
+    if (tid + k * NT < ns) ml[k] = *(const float2*)(base + (int64_t)(tid + k * NT) * (D + 2));
+    mm = fmaxf(mm, ml[k].x);
+  }
+  mm = max_xor32(max_xor16(row_allmax(mm)));
   if (lane == 0) wred[0][wave] = mm;
   __syncthreads();
   mm = wred[0][0];
 #pragma unroll
   for (int k = 1; k < NW; ++k) mm = fmaxf(mm, wred[0][k]);
-  const float a_mine = (tid < ns) ? fast_exp2(ml.x - mm) : 0.f;
-  if (tid < ns) wgt[tid] = a_mine;
-  float den = add_xor32(add_xor16(row_allsum(a_mine * ml.y)));
+  float den = 0.f;
+#pragma unroll
+  for (int k = 0; k < NM; ++k)
+    if (tid + k * NT < ns) {
+      const float a = fast_exp2(ml[k].x - mm);
+      wgt[tid + k * NT] = a;
+      den = fmaf(a, ml[k].y, den);
+    }
+  den = add_xor32(add_xor16(row_allsum(den)));
   if (lane == 0) wred[1][wave] = den;
   __syncthreads();
   den = wred[1][0];
@@ -281,11 +116,6 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-template <int D, int G>
-static void launch_int4(const DecodeParams& p, dim3 grid, hipStream_t st) {
-  constexpr int LPT = (G >= 8) ? 8 : 4;
-  decode_int4_kernel<D, G, LPT><<<grid, dim3(256), 0, st>>>(p);
-}
 int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_dtype, hipStream_t st) {
   dim3 grid(p.num_splits, p.n_kv_heads, B);
   const bool head_pairs = !kv16 && decode_head_pairs(D, p.n_kv_heads, G);
@@ -299,20 +129,15 @@ int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_
     if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
     if (p.num_splits == 1) return SAW_OK;       // the kernel wrote the output itself
   } else {
-#define SAW_DISPATCH_G(DD)                                                          \
-  switch (G) {                                                                      \
-    case 1: launch_int4<DD, 1>(p, grid, st); break;                                 \
-    case 2: launch_int4<DD, 2>(p, grid, st); break;                                 \
-    case 4: launch_int4<DD, 4>(p, grid, st); break;                                 \
-    case 8: launch_int4<DD, 8>(p, grid, st); break;                                 \
-    default: return SAW_EINVAL;                                                     \
-  }
-  SAW_DISPATCH_G(64)                            // (head_dim 128 is always on the matrix cores)
-#undef SAW_DISPATCH_G
+    const dim3 sgrid = p.cut ? dim3(p.cut, p.n_kv_heads) : grid;
+    if (launch_decode_int4_split64(p, G, p.waves_per_item, sgrid, st) != SAW_OK) return SAW_EINVAL;
+    if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
+    if (!p.cut && p.num_splits == 1) return SAW_OK;
   }
   if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
   dim3 mgrid(p.n_q_heads, B);
-  if (p.num_splits > 16) {
+  // (a block per row: 1024 threads where a sequence has more than 16 partitions, on average if the lengths cut the batch)
+  if ((p.cut ? p.cut / B : p.num_splits) > 16) {
     if (D == 128) decode_merge_kernel<128, 1024><<<mgrid, dim3(1024), 0, st>>>(p);
     else decode_merge_kernel<64, 1024><<<mgrid, dim3(1024), 0, st>>>(p);
   } else {
@@ -325,7 +150,7 @@ int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_
 int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void* v_pages, int kv_dtype,
                const void* q, int q_dtype, int B, int Hq, const int32_t* pt, int max_pages,
                const int32_t* seq_lens, float sm_scale, void* out, int out_dtype, void* ws,
-               const SplitPlan& plan, const void* k_new, const void* v_new, int kv_new_dtype, int len_bias,
+               const SplitPlan& plan, const void* k_new, const void* v_new, int kv_new_dtype,
                const int32_t* order, hipStream_t st) {
   DecodeParams p;
   p.order = kv16 ? nullptr : order;
@@ -357,14 +182,15 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
   p.num_splits = plan.num_splits;
   p.chunk_tokens = plan.chunk_tokens;
   p.bound = plan.bound;
-  p.waves_per_item = plan.waves_per_item;
+  p.waves_per_item = plan.cut ? plan.cut_waves : plan.waves_per_item;
+  p.cut = plan.cut;
+  p.cut_min = plan.cut_min;
   // Pair mode: one partition per sequence, enough (sequence, kv head) items that every compute
   // unit gets several, and at most 16 lengths per lane for the in-kernel ranking.
   p.k_new = k_new;
   p.v_new = v_new;
   p.kv_new_dtype = kv_new_dtype;
   p.append = k_new != nullptr;
-  p.len_bias = len_bias;
   p.batch = B;
   // How the matrix-core INT4 kernel hands out work when one partition covers each sequence and the
   // batch provides more (sequence, kv head) items than compute units (and at most 16 lengths per
@@ -417,6 +243,10 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
       else p.sorted = 1;
     }
   }
+  // one 64-channel head at a time: the caller's order, if there is one (and one partition covers a sequence)
+  if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G) && !plan.cut && plan.num_splits == 1 &&
+      order && B <= 1024 && (int64_t)B * c->n_kv_heads > 256)
+    p.sorted = 1;
   // the 16-bit matrix-core kernel has the two-wavefront pair mode as well (same conditions), so that
   // the comparison on a ragged batch is between formats and not between schedules
   if (kv16 && plan.num_splits == 1 && B <= 1024 &&

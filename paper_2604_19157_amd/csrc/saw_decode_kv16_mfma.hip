@@ -154,7 +154,7 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
     }
     wave_sync();                                        // the ranking's scratch lived in vbuf_a
   } else {
-    const int L = min(p.seq_lens[sg_b[0]] + p.len_bias, p.bound);
+    const int L = min(p.seq_lens[sg_b[0]], p.bound);
     sg_t0[0] = split * p.chunk_tokens;
     sg_t1[0] = min(L, sg_t0[0] + p.chunk_tokens);
     if (sg_t0[0] >= sg_t1[0]) {

@@ -390,7 +390,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
 #pragma unroll
       for (int k = 0; k < K; ++k) raw[k] = present[k] ? p.seq_lens[bk[k]] : 0;
 #pragma unroll
-      for (int k = 0; k < K; ++k) lk[k] = present[k] ? max(min(raw[k] + p.len_bias, p.bound), 0) : 0;
+      for (int k = 0; k < K; ++k) lk[k] = present[k] ? max(min(raw[k], p.bound), 0) : 0;
     } else {
       const LenClasses lc = build_len_classes(p, B, lane, (int*)kbuf);
 #pragma unroll
@@ -519,7 +519,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     t_end = __builtin_amdgcn_readfirstlane(SAW_SEG(sg_t1));
     seq_len_b = __builtin_amdgcn_readfirstlane(SAW_SEQ(lk));
   } else {
-    seq_len_b = max(min(p.seq_lens[b] + p.len_bias, p.bound), 0);
+    seq_len_b = max(min(p.seq_lens[b], p.bound), 0);
     t_end = min(seq_len_b, t_begin + p.chunk_tokens);
     if (t_begin >= t_end && !(p.append && t_begin == 0)) {            // block-uniform
       if (p.num_splits == 1)           // empty sequence and no merge pass: the output row is zero

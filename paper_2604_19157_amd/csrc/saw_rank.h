@@ -48,7 +48,7 @@ __device__ __forceinline__ LenClasses build_len_classes(const DecodeParams& p, i
 #pragma unroll
   for (int v = 0; v < kMaxRanked / 64; ++v) {
     if (v < lc.V) {
-      mine[v] = (64 * v + lane < B) ? max(min(mine[v] + p.len_bias, p.bound), 0) : 0;
+      mine[v] = (64 * v + lane < B) ? max(min(mine[v], p.bound), 0) : 0;
       nbmax = max(nbmax, (mine[v] + 63) >> 6);
     }
   }

@@ -40,9 +40,7 @@ struct StoreLayerPtrs {
 struct StoreMfmaParams {
   StoreLayerPtrs layer[kMaxStoreLayers];
   const int32_t* page_table;
-  const int32_t* slots;         // [T][2] (sequence, position), or null:
-  const int32_t* append_lens;   // then token t goes to sequence t at position append_lens[t],
-  int32_t append_bound;         // unless that exceeds append_bound (the caller's bound on the lengths): skipped
+  const int32_t* slots;         // [T][2] (sequence, position)
   int64_t T;
   int64_t token_stride;
   int32_t n_seqs, max_pages, num_pages, n_kv_heads;
@@ -130,9 +128,7 @@ __global__ __launch_bounds__(256) void rotate_quant_store_mfma_kernel(StoreMfmaP
     // this lane's token (column n16 of the tile) and where it goes
     const int64_t t_mine = t0 + 16 * tile + n16;
     slot[tile] = make_int2(-1, -1);
-    if (wave_live && t_mine < p.T)
-      slot[tile] = p.slots ? *(const int2*)(p.slots + 2 * t_mine) : make_int2((int)t_mine, p.append_lens[t_mine]);
-    if (!p.slots && slot[tile].y > p.append_bound) slot[tile] = make_int2(-1, -1);
+    if (wave_live && t_mine < p.T) slot[tile] = *(const int2*)(p.slots + 2 * t_mine);
   }
 
   // ---- the +/-1 matrix: A[m][k], m = output row, k = input channel (low five bits) ----
@@ -368,7 +364,6 @@ __global__ __launch_bounds__(256) void rotate_quant_store_mfma_kernel(StoreMfmaP
 int launch_store_mfma(const saw_cache_t* c, const void* const* K, const void* const* V, int n_layers, int dt,
                       int64_t T, int64_t stride,
                       const int32_t* pt, int32_t n_seqs, int32_t max_pages, const int32_t* slots,
-                      const int32_t* append_lens, int32_t append_bound,
                       hipStream_t st) {
   StoreMfmaParams p;
   for (int l = 0; l < n_layers; ++l) {
@@ -378,7 +373,7 @@ int launch_store_mfma(const saw_cache_t* c, const void* const* K, const void* co
     lp.in[0] = K[l]; lp.in[1] = V[l];
     lp.dense_limbs = c[l].dense_rot ? (const uint8_t*)c[l].dense_rot + kDenseLimbOffset : nullptr;
   }
-  p.page_table = pt; p.slots = slots; p.append_lens = append_lens; p.append_bound = append_bound; p.T = T; p.token_stride = stride;
+  p.page_table = pt; p.slots = slots; p.T = T; p.token_stride = stride;
   p.n_seqs = n_seqs; p.max_pages = max_pages; p.num_pages = c->num_pages; p.n_kv_heads = c->n_kv_heads;
   p.had_block = c->had_block;
   p.rot[0] = (c->had_block > 1) && (c->rotate_mask & SAW_ROT_K);

@@ -2,7 +2,7 @@
 rotation only needs h | d, so 64-channel heads are served too).
 
 With an even number of kv heads and at most 4 query heads per kv head the matrix-core kernel runs on
-pairs of kv heads; other shapes take the vector-ALU kernel.  Every way the kernel hands out work is
+pairs of kv heads; other shapes take the kernel of one 64-channel head at a time.  Every way the kernel hands out work is
 driven here at head_dim 64: one partition, split-KV with the merge pass, several wavefronts per
 partition, pair mode, longest-first order, and the append entry point (store launch + decode).
 """
@@ -37,7 +37,7 @@ def test_head_pairs_group_sizes(saw, Hq, Hkv):
 
 @pytest.mark.parametrize("Hq,Hkv", [(3, 3), (6, 3), (16, 2), (5, 5)])
 def test_shapes_outside_the_pair_kernel(saw, Hq, Hkv):
-    """Odd kv head counts and 8 query heads per kv head: the vector-ALU kernel."""
+    """Odd kv head counts and 8 query heads per kv head: the kernel of one 64-channel head at a time."""
     TD._decode_case(saw, _w(batch=3, ctx=(20, 150), n_q_heads=Hq, n_kv_heads=Hkv))
 
 
@@ -116,3 +116,59 @@ def test_append_unmapped_page_and_odd_kv_heads(saw):
     # (the unmapped token must open a page of its own, or cached tokens would lose their page with it)
     TA._case(saw, _w(batch=3, seq_lens=[40, 64, 95], n_q_heads=8, n_kv_heads=4), unmapped=(1,))
     TA._case(saw, _w(batch=3, ctx=(20, 150), n_q_heads=6, n_kv_heads=3))        # store launch + decode
+
+
+@pytest.mark.parametrize("Hq,Hkv,dtype,kw", [(8, 1, torch.bfloat16, {}), (3, 3, torch.float16, {"rotate_mask": 1}),
+                                             (6, 3, torch.bfloat16, {"sign_seed": 3, "had_block": 16}),
+                                             (4, 1, torch.float16, {"rotate_mask": 2, "sign_seed": 4}),
+                                             (64, 8, torch.float16, {"had_block": 1})])
+@pytest.mark.parametrize("B", [1, 16, 70, 300])
+def test_one_head_at_a_time_batch_edges(saw, Hq, Hkv, dtype, kw, B):
+    """Lengths around the 64-token batches and the pages, empty sequences, a long one: fixed partitions, a batch cut by
+    its own lengths (automatic, up to 256 sequences; under a tight and a loose bound), one partition, and the fused
+    append against store + decode.  The query and the weights carry 24 bits and the codes are exact, so what is left is
+    the rounding of fp32 sums: Sum w c of up to 15 s, from which about half is taken away again with the zero-points
+    (2^-24 a step of that, tens of steps: 2^-20 s), against outputs of a few s that shrink with sqrt(L) as the values
+    average out: 4e-6 sqrt(max(L / 300, 1)) of the largest output."""
+    import gpu_cases as gc
+    from oracle import saw_oracle as O
+    import parity
+    rng = np.random.default_rng(B + Hq)
+    limit = 4e-6 * (5000 / 300 if B == 1 else 1) ** 0.5
+    edges = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 300, 1030, 255, 256, 257]
+    lens = (edges * (B // 16 + 1))[:B] if B > 1 else [5000]
+    w = _w(batch=B, seq_lens=lens, n_q_heads=Hq, n_kv_heads=Hkv, dtype=dtype, table_width=400, **kw)
+    ref = gc.oracle_fill(w)
+    cache = gc.upload_cache(ref, w, saw)
+    pt, sl = torch.from_numpy(w.page_table).cuda(), torch.from_numpy(w.seq_lens).cuda()
+    q = synth.gen_q(w).float() * 0.5
+    want = O.paged_decode_attn(ref, q.numpy(), w.page_table, w.seq_lens, w.had_block, w.rotate_mask, signs=w.signs)
+    for splits, bound in ((0, max(lens)), (0, 0), (1, 0), (3, 0)):
+        out = torch.full((B, Hq, 64), float("nan"), device="cuda")
+        saw.paged_decode_attn(cache, q.cuda(), pt, sl, max_seq_len=bound, out=out, num_splits=splits)
+        err = parity.attn_error(out.cpu().numpy(), want)
+        print(f"[one head at a time B={B} Hq={Hq}/{Hkv} splits={splits} bound={bound}] err={err:.2e}", flush=True)
+        assert err < limit
+        assert not out[[b for b in range(B) if lens[b] == 0]].any()
+    # a scratch sized for the fixed partitions of the plan is enough
+    s, _ = saw.decode_plan(cache, B, max(lens))
+    ws = torch.empty(max(16, B * Hq * s * 66 * 4), dtype=torch.uint8, device="cuda")
+    out = saw.paged_decode_attn(cache, q.cuda(), pt, sl, max_seq_len=max(lens), workspace=ws)
+    assert parity.attn_error(out.cpu().numpy(), want) < limit
+    # fused append: the attention of store + decode (a code on a rounding boundary may differ: one step of one value of
+    # one token), and every stored token under the store criterion
+    K = torch.from_numpy(rng.standard_normal((B, Hkv, 64))).to(dtype).cuda()
+    V = torch.from_numpy(rng.standard_normal((B, Hkv, 64))).to(dtype).cuda()
+    two = gc.upload_cache(ref, w, saw)
+    slots = torch.from_numpy(np.stack([np.arange(B), w.seq_lens], 1).astype(np.int32)).cuda()
+    saw.rotate_quant_store(two, K, V, pt, slots)
+    o2 = saw.paged_decode_attn(two, q.cuda(), pt, sl + 1, num_splits=1)
+    for bound in (max(lens), 0):
+        o1 = saw.append_decode_attn(cache, K, V, q.cuda(), pt, sl, max_seq_len=bound)
+        same = (cache.k_codes == two.k_codes).flatten(1).all(1) & (cache.v_codes == two.v_codes).flatten(1).all(1)
+        assert (~same).sum() <= 2
+        last = torch.tensor([w.page_table[b, n // 16] for b, n in enumerate(lens)]).cuda()
+        rows = same[last].cpu().numpy()
+        assert parity.attn_error(o1.cpu().numpy()[rows], o2.cpu().numpy()[rows]) < 2 * limit
+    if B <= 70:
+        TA._case(saw, w)
