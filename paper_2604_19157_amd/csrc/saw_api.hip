@@ -42,18 +42,17 @@ static bool shape_ok(const saw_cache_t* c) {
   return true;
 }
 
-// A batch cut by its own lengths (saw_cut.h) into at most `slots` partitions per kv head, of at least four 64-token batches:
-// a shorter one costs more in prologue and merge pass than it brings.  Very many partitions per sequence (few long
-// sequences) become a quarter of them with four wavefronts each, whose states are folded in LDS: the merge pass then
-// reads a quarter of the partial records.  False if a sequence would not get two partitions on average.
+// A batch cut by its own lengths (saw_cut.h) into at most `slots` partitions per kv head, of `waves` wavefronts and at least
+// four 64-token batches each: a shorter one costs more in prologue and merge pass than it brings.  False if a sequence
+// would not get two partitions on average (the rounding of a sequence's share to whole partitions then costs too much), and
+// for a single sequence, whose fixed partitions can request their page ids before the length is there (1 x 131072 tokens,
+// 64 query heads: 36.5 against 38.6 us).
 constexpr int kMaxCutSequences = 256;           // (as many lengths as a wavefront keeps in registers)
-static bool cut_plan(int B, int units, int slots, SplitPlan* plan) {
+static bool cut_plan(int B, int units, int slots, int waves, SplitPlan* plan) {
   constexpr int kMin = 4;
-  if (B > kMaxCutSequences || (int64_t)B * units >= (1 << 23)) return false;   // (counts are divided in fp32)
-  int64_t most = (int64_t)B * ((units + kMin - 1) / kMin);
+  if (B == 1 || B > kMaxCutSequences || (int64_t)B * units >= (1 << 23)) return false;   // (counts are divided in fp32)
+  const int64_t most = (int64_t)B * ((units + kMin - 1) / kMin);
   int w = slots < most ? slots : (int)most;
-  int waves = 1;
-  if (w > 64 * B && units / (w / (4 * B)) >= 32) { waves = 4; w /= 4; }
   if (w > 1024) w = 1024;                       // (the merge pass keeps a weight per slot of a sequence)
   if (w < 2 * B) return false;
   plan->cut = w;
@@ -75,10 +74,34 @@ static bool block_ok(const saw_cache_t* c) {
 }
 
 
+// The matrix-core INT4 kernel for rows of 128 channels holds 2048 wavefronts.  `per_seq`: (kv head, or pair of heads) items of a
+// sequence.  What was measured, decode or fused step, 32 query / 8 kv heads, against the fixed partitions (in brackets):
+//   * partitions of four wavefronts, which fold in LDS, leave the merge pass a quarter of the records, where that still gives
+//     a sequence four partitions on average: 16 x 4096 tokens 24.0 us (25.8; two wavefronts 24.2, one 26.2), 4 x 131072
+//     108.7 (111.5), 8 ragged up to 3000 under a loose bound 17.0 (22.8);
+//   * two wavefronts otherwise: 48 ragged up to 4096 34.3 (37.5, with a loose bound 54; four wavefronts 39.7), 32 ragged 26.7
+//     (27.8, loose 47), 200 ragged x 2 heads 35.2 (37.0);
+//   * from 512 items on one partition per sequence stays ahead or level (64 ragged 43.0 against 43.2, equal lengths 35.0
+//     against 39.8, 96 ragged 57.3 against 59.6);
+//   * the block of eight stays ahead where its wavefronts have at most four batches, or five when the blocks fill most of
+//     the chip (4 x 256 12.7 against 16.4, 4 ragged up to 1100 14.3 against 16.4, 16 ragged up to 1000 under a bound of 2000
+//     14.7 against 16.7, 32 x 2304 22.0 against 25.3; behind it 25 x 4096 40.8 against 30.1, 32 x 4096 38.4 against 36.2).
+static void plan_cut(int B, int units, int per_seq, SplitPlan* plan) {
+  const int64_t items = (int64_t)B * per_seq;
+  const int per_wave = (units + 7) / 8;
+  if (plan->waves_per_item == 8 && (per_wave <= 4 || (items >= 192 && per_wave <= 5))) return;
+  if (items >= 512) return;
+  if (cut_plan(B, units, 512 / per_seq, 4, plan) && plan->cut >= 4 * B) return;
+  plan->cut = 0;
+  cut_plan(B, units, 1024 / per_seq, 2, plan);
+}
+
 // The kernel that takes 64-channel heads one at a time (saw_decode_split.hip).  Its registers allow 12 wavefronts on a
 // compute unit and a batch is only 5 KiB, so it wants 3072 of them.  Small batches of short contexts: one block of eight
 // wavefronts per (sequence, kv head), a single launch.  Otherwise the batch is cut by its own lengths, as long as that
-// gives a sequence two slots on average; beyond that one partition per sequence, of four wavefronts while they fit.
+// gives a sequence two slots on average; beyond that one partition per sequence, of four wavefronts while they fit.  Four
+// wavefronts a slot, 2048 in all, where a sequence gets four slots of those (16 ragged x 8 heads of 300-3000 tokens 17.5 us, 19.1
+// with 3072, 22.4 and 25.3 with one wavefront a slot; 64 ragged 40.0, with one wavefront 32.1, which is why it needs the four).
 static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan) {
   const int64_t items = (int64_t)B * c->n_kv_heads;
   constexpr int kWaves = 3072;
@@ -90,7 +113,17 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
     plan->waves_per_item = 8;
     return;
   }
-  if (cut_plan(B, units, kWaves / c->n_kv_heads, plan)) return;
+  if (cut_plan(B, units, 2048 / 4 / c->n_kv_heads, 4, plan) && plan->cut >= 4 * B) return;
+  plan->cut = 0;
+  if (B == 1) {
+    const int s = 512 / c->n_kv_heads < (units + 3) / 4 ? 512 / c->n_kv_heads : (units + 3) / 4;
+    const int chunk = (units + (s > 1 ? s : 1) - 1) / (s > 1 ? s : 1);
+    plan->num_splits = (units + chunk - 1) / chunk;
+    plan->chunk_tokens = chunk * 64;
+    plan->waves_per_item = 4;
+    return;
+  }
+  if (cut_plan(B, units, kWaves / c->n_kv_heads, 1, plan)) return;
   if (B > kMaxCutSequences && items < kWaves / 2) return;             // (fixed partitions, as planned)
   plan->num_splits = 1;
   plan->chunk_tokens = units * 64;
@@ -165,7 +198,10 @@ static bool make_plan(const saw_cache_t* c, int B, int G, int max_pages, int max
   plan->waves_per_item = nw;
   plan->cut = plan->cut_min = plan->cut_waves = 0;
   if (num_splits != 0 || G == 0) return true;
+  const int per_seq = kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads);
   if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G)) plan_split64(c, B, units, plan);
+  else if (kv16) { if (plan->num_splits > 1) cut_plan(B, units, 2048 / per_seq, 1, plan); }
+  else plan_cut(B, units, per_seq, plan);
   return true;
 }
 

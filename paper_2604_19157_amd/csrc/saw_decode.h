@@ -30,6 +30,7 @@ struct DecodeParams {
   int32_t batch;
   int32_t cut;              // partition slots per kv head of a batch that the kernel cuts by its own lengths (saw_cut.h); 0: fixed partitions
   int32_t cut_min;          // ... 64-token batches a partition has at least
+  int2* cut_of;             // ... behind the partial results: first slot and slots of each sequence that has any, for the merge pass
   int32_t waves_per_item;   // matrix-core path: wavefronts sharing one partition (1, 2, 4 or 8)
   const float* dense;       // learned rotation R_l (App. A.3): fp32 [128][128], its transpose right behind it; null: none
   int32_t dense_k, dense_v; // R_l applies to K and the query / to V and the output
@@ -73,9 +74,10 @@ int launch_decode_kv16_mfma(const DecodeParams& p, int D, int G, int kv_dtype, d
 inline size_t partial_bytes(int B, int Hq, int splits, int D) {
   return (((size_t)B * Hq * splits * (D + 2) * sizeof(float)) + 15) & ~(size_t)15;
 }
-// scratch of a call as planned: partial results per (sequence, split), or per slot of a batch cut by its own lengths
+// scratch of a call as planned: partial results per (sequence, split); or of a batch cut by its own lengths: per slot, and
+// which slots are whose
 inline size_t plan_bytes(const SplitPlan& plan, int B, int Hq, int D) {
-  return plan.cut ? partial_bytes(1, Hq, plan.cut, D) : partial_bytes(B, Hq, plan.num_splits, D);
+  return plan.cut ? partial_bytes(1, Hq, plan.cut, D) + (size_t)B * sizeof(int2) : partial_bytes(B, Hq, plan.num_splits, D);
 }
 
 }  // namespace saw

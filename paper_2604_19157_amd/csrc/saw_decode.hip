@@ -6,8 +6,147 @@
 
 namespace saw {
 
+// The partial results of one (sequence, query head): how many, and where the first one is.
+template <int D>
+__device__ __forceinline__ int row_records(const DecodeParams& p, int b, int j, const float*& base) {
+  if (p.cut) {
+    const int2 own = p.cut_of[b];             // (requested with the length; not written, and not used, if nothing ran)
+    const int L = min(p.seq_lens[b], p.bound);
+    base = p.ws + ((int64_t)j * p.cut + own.x) * (D + 2);
+    return (L > 0 || p.append) ? own.y : 0;
+  }
+  // partitions that ran: those that start inside the cached tokens, and with a fused append the first one
+  // in any case (it carries the step's own token)
+  const int L = min(p.seq_lens[b], p.bound);
+  base = p.ws + ((int64_t)b * p.n_q_heads + j) * p.num_splits * (D + 2);
+  return max((max(L, 0) + p.chunk_tokens - 1) / p.chunk_tokens, p.append ? 1 : 0);
+}
+
+// y[r][j] = sum_i x[r][i] M[i][j] for four rows of 128 floats in LDS, run by a block of four wavefronts: wavefront w takes
+// columns 32 w .. + 31, lane l four of them and 16 of the 128 terms.  M (64 KiB, from L2) is read once per four rows.
+__device__ __forceinline__ void block_lds_matvec4(const float* x, float* y, const float* __restrict__ M, int wave, int lane) {
+  const int col = 32 * wave + 4 * (lane & 7), k0 = 16 * (lane >> 3);
+  f32x4 m[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) m[u] = *(const f32x4*)(M + (k0 + u) * 128 + col);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u4 = 0; u4 < 4; ++u4) {
+      const f32x4 xv = *(const f32x4*)(x + 128 * r + k0 + 4 * u4);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] = fmaf(xv[k], m[4 * u4 + k][c], acc[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      acc[c] += dpp_f<0x128>(acc[c]);           // row_ror:8: the other eight lanes of the row
+      acc[c] = add_xor32(add_xor16(acc[c]));
+    }
+    if (lane < 8) *(f32x4*)(y + 128 * r + col) = f32x4{acc[0], acc[1], acc[2], acc[3]};
+  }
+}
+
 // ---------------------------------------------------------------------------------------
-// Merge the splits of one (sequence, query head), rotate the output back, write it.
+// Merge of the partitions of a (sequence, query head) by one wavefront, four rows per block: up to 16 records are requested
+// at once, so a row of few partitions costs one trip to memory and no block barrier (64 x 64 rows of 64 channels, 6 partitions
+// each: 5.1 us, 7.0 with a block of 256 threads per row; 48 x 32 rows of 128 channels: 4.0 and 4.6 us; 16 x 32: 3.9 and 4.0).
+template <int D>
+__global__ __launch_bounds__(256) void decode_merge_rows_kernel(DecodeParams p) {
+  constexpr int E = D / 64;                   // channels per lane
+  constexpr int CH = 16;                      // records per trip
+  const int b = blockIdx.y, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool live = (int)blockIdx.x * 4 + wave < p.n_q_heads;                 // (an idle wavefront shadows the last row)
+  const int j = min((int)blockIdx.x * 4 + wave, p.n_q_heads - 1);
+  __shared__ __attribute__((aligned(16))) float rows[2][4][128];
+  const float* base;
+  const int ns = row_records<D>(p, b, j, base);
+  float mm = -INFINITY, den = 0.f, num[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) num[e] = 0.f;
+  for (int s0 = 0; s0 < ns; s0 += CH) {
+    const int n = min(CH, ns - s0);
+    const float* const at = base + (int64_t)s0 * (D + 2);
+    float2 ml = make_float2(-INFINITY, 0.f);
+    if (lane < n) ml = *(const float2*)(at + lane * (D + 2));
+    float v[CH][E];
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      if (k % 4 == 0 && k >= n) {             // (wavefront-uniform)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < E; ++e) v[k + u][e] = 0.f;
+      } else if (k % 4 == 0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float* const src = at + min(k + u, n - 1) * (D + 2) + 2 + E * lane;
+          if (E == 2) {
+            const f32x2 w = *(const f32x2*)src;
+            v[k + u][0] = w.x; v[k + u][E - 1] = w.y;
+          } else {
+            v[k + u][0] = src[0];
+          }
+        }
+      }
+    }
+    const float mnew = fmaxf(mm, __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(row_allmax(ml.x)))));
+    const float alpha = fast_exp2(mm - mnew);
+    const float a = fast_exp2(ml.x - mnew);   // 0 from lane n on
+    den = fmaf(den, alpha, __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(row_allsum(a * ml.y)))));
+#pragma unroll
+    for (int e = 0; e < E; ++e) num[e] *= alpha;
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(a), k));
+#pragma unroll
+      for (int e = 0; e < E; ++e) num[e] = fmaf(w, v[k][e], num[e]);
+    }
+    mm = mnew;
+  }
+  float o[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) o[e] = ns ? num[e] / den : 0.f;
+  const bool dense = D == 128 && p.dense_v;   // the learned rotation's transpose first (App. A.3)
+  if (dense || p.rot_v) {
+    float* x = rows[0][wave];
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[E * lane + e] = o[e];
+    if (dense) {                              // block-uniform
+      __syncthreads();
+      block_lds_matvec4(rows[0][0], rows[1][0], p.dense + kDenseD * kDenseD, wave, lane);
+      __syncthreads();
+      x = rows[1][wave];
+    }
+    wave_sync();
+    float onorm = 1.f;
+    if (p.rot_v) {                            // (64 channels: half of a vector, the other half is nobody's)
+      wave_lds_fwht128<1>(x, p.had_block, lane);
+      onorm = had_norm(p.had_block);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      o[e] = x[E * lane + e] * onorm;
+      if (p.rot_v && p.has_signs) o[e] = apply_sign(p.signs, E * lane + e, o[e]);         // (o~ H_blk) diag(sigma) = o~ R^T
+    }
+  }
+  if (!live) return;
+  const int64_t at = ((int64_t)b * p.n_q_heads + j) * D + E * lane;
+  if (E == 2 && p.out_dtype == SAW_F32) {
+    *(f32x2*)((float*)p.out + at) = f32x2{o[0], o[E - 1]};
+  } else if (E == 2) {
+    const uint32_t w = p.out_dtype == SAW_BF16 ? f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[E - 1]) << 16)
+                                               : f32_to_f16(o[0]) | ((uint32_t)f32_to_f16(o[E - 1]) << 16);
+    *(uint32_t*)((uint16_t*)p.out + at) = w;
+  } else {
+    store_elem(p.out, p.out_dtype, at, o[0]);
+  }
+}
+
+// Merge by a block of NT threads per row: rows of very many partitions (long contexts, small batches).
 template <int D, int NT>
 __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
   constexpr int NG = NT / D;                  // channel groups working on different splits
@@ -16,20 +155,8 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = tid % D, g = tid / D;
   const int64_t o_idx = ((int64_t)b * p.n_q_heads + j) * D + c;
-  int ns;                                     // partitions that ran
-  const float* base = p.ws;                   // their records
-  if (p.cut) {
-    int first;
-    const BatchCut cut = cut_batch(p, lane);
-    cut_slots_of(cut, b, first, ns);
-    base += ((int64_t)j * p.cut + first) * (D + 2);
-  } else {
-    // those that start inside the cached tokens, and with a fused append the first one in any case (it
-    // carries the step's own token)
-    const int L = min(p.seq_lens[b], p.bound);
-    ns = max((max(L, 0) + p.chunk_tokens - 1) / p.chunk_tokens, p.append ? 1 : 0);
-    base += ((int64_t)b * p.n_q_heads + j) * p.num_splits * (D + 2);
-  }
+  const float* base;
+  const int ns = row_records<D>(p, b, j, base);
   if (ns == 0) {
     if (g == 0) store_elem(p.out, p.out_dtype, o_idx, 0.f);
     return;
@@ -37,32 +164,20 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
   __shared__ float wgt[1024];
   __shared__ __attribute__((aligned(16))) float red[NG][D];
   __shared__ float wred[2][NW];
-  // Every split's (max, sum) pair is read once, by thread s, s + NT, ... (at most 1024 splits): reference
+  // Every split's (max, sum) pair is read once, by thread s (at most 1024 splits): reference
   // maximum, then weights and the denominator.
-  constexpr int NM = 1024 / NT;
-  float2 ml[NM];
-  float mm = -INFINITY;
-#pragma unroll
-  for (int k = 0; k < NM; ++k) {
-    ml[k] = make_float2(-INFINITY, 0.f);
-    if (tid + k * NT < ns) ml[k] = *(const float2*)(base + (int64_t)(tid + k * NT) * (D + 2));
-    mm = fmaxf(mm, ml[k].x);
-  }
-  mm = max_xor32(max_xor16(row_allmax(mm)));
+  static_assert(NT == 1024, "a thread per split");
+  float2 ml = make_float2(-INFINITY, 0.f);
+  if (tid < ns) ml = *(const float2*)(base + (int64_t)tid * (D + 2));
+  float mm = max_xor32(max_xor16(row_allmax(ml.x)));
   if (lane == 0) wred[0][wave] = mm;
   __syncthreads();
   mm = wred[0][0];
 #pragma unroll
   for (int k = 1; k < NW; ++k) mm = fmaxf(mm, wred[0][k]);
-  float den = 0.f;
-#pragma unroll
-  for (int k = 0; k < NM; ++k)
-    if (tid + k * NT < ns) {
-      const float a = fast_exp2(ml[k].x - mm);
-      wgt[tid + k * NT] = a;
-      den = fmaf(a, ml[k].y, den);
-    }
-  den = add_xor32(add_xor16(row_allsum(den)));
+  const float a_mine = (tid < ns) ? fast_exp2(ml.x - mm) : 0.f;
+  if (tid < ns) wgt[tid] = a_mine;
+  float den = add_xor32(add_xor16(row_allsum(a_mine * ml.y)));
   if (lane == 0) wred[1][wave] = den;
   __syncthreads();
   den = wred[1][0];
@@ -117,32 +232,29 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
 
 // ---------------------------------------------------------------------------------------
 int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_dtype, hipStream_t st) {
-  dim3 grid(p.num_splits, p.n_kv_heads, B);
+  const dim3 grid = p.cut ? dim3(p.cut, p.n_kv_heads) : dim3(p.num_splits, p.n_kv_heads, B);
   const bool head_pairs = !kv16 && decode_head_pairs(D, p.n_kv_heads, G);
   if (!kv16 && (D == 128 || head_pairs)) {
-    const dim3 mgrid(grid.x, head_pairs ? grid.y / 2 : grid.y, grid.z);
+    const int ny = head_pairs ? p.n_kv_heads / 2 : p.n_kv_heads;
+    const dim3 mgrid = p.cut ? dim3(p.cut, ny) : dim3(p.num_splits, ny, B);
     if (launch_decode_int4_mfma(p, G, B, p.waves_per_item, head_pairs, mgrid, st) != SAW_OK) return SAW_EINVAL;
-    if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
-    if (p.num_splits == 1) return SAW_OK;       // the kernel wrote the output itself
   } else if (kv16) {
     if (launch_decode_kv16_mfma(p, D, G, kv_dtype, grid, st) != SAW_OK) return SAW_EINVAL;
-    if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
-    if (p.num_splits == 1) return SAW_OK;       // the kernel wrote the output itself
   } else {
-    const dim3 sgrid = p.cut ? dim3(p.cut, p.n_kv_heads) : grid;
-    if (launch_decode_int4_split64(p, G, p.waves_per_item, sgrid, st) != SAW_OK) return SAW_EINVAL;
-    if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
-    if (!p.cut && p.num_splits == 1) return SAW_OK;
+    if (launch_decode_int4_split64(p, G, p.waves_per_item, grid, st) != SAW_OK) return SAW_EINVAL;
   }
   if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
-  dim3 mgrid(p.n_q_heads, B);
-  // (a block per row: 1024 threads where a sequence has more than 16 partitions, on average if the lengths cut the batch)
+  if (!p.cut && p.num_splits == 1) return SAW_OK;             // the kernel wrote the output itself
+  // (a sequence has more than 16 partitions - on average, if the lengths cut the batch -: a block of 1024 threads per row;
+  // otherwise a wavefront per row)
   if ((p.cut ? p.cut / B : p.num_splits) > 16) {
+    const dim3 mgrid(p.n_q_heads, B);
     if (D == 128) decode_merge_kernel<128, 1024><<<mgrid, dim3(1024), 0, st>>>(p);
     else decode_merge_kernel<64, 1024><<<mgrid, dim3(1024), 0, st>>>(p);
   } else {
-    if (D == 128) decode_merge_kernel<128, 256><<<mgrid, dim3(256), 0, st>>>(p);
-    else decode_merge_kernel<64, 256><<<mgrid, dim3(256), 0, st>>>(p);
+    const dim3 mgrid((p.n_q_heads + 3) / 4, B);
+    if (D == 128) decode_merge_rows_kernel<128><<<mgrid, dim3(256), 0, st>>>(p);
+    else decode_merge_rows_kernel<64><<<mgrid, dim3(256), 0, st>>>(p);
   }
   return hipGetLastError() == hipSuccess ? SAW_OK : SAW_ELAUNCH;
 }
@@ -185,6 +297,7 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
   p.waves_per_item = plan.cut ? plan.cut_waves : plan.waves_per_item;
   p.cut = plan.cut;
   p.cut_min = plan.cut_min;
+  p.cut_of = plan.cut ? (int2*)((uint8_t*)ws + partial_bytes(1, Hq, plan.cut, c->head_dim)) : nullptr;
   // Pair mode: one partition per sequence, enough (sequence, kv head) items that every compute
   // unit gets several, and at most 16 lengths per lane for the in-kernel ranking.
   p.k_new = k_new;
@@ -219,7 +332,7 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
   const int G = Hq / c->n_kv_heads;
   const int items = decode_items_per_seq(c->head_dim, c->n_kv_heads);   // head_dim 64: pairs of kv heads
   if (!kv16 && (c->head_dim == 128 || decode_head_pairs(c->head_dim, c->n_kv_heads, G)) &&
-      plan.num_splits == 1 && B <= 1024) {
+      !plan.cut && plan.num_splits == 1 && B <= 1024) {
     const int64_t blocks = (int64_t)((B + 1) / 2) * items;
     const int64_t blocks3 = (int64_t)((B + 2) / 3) * items;
     if ((int64_t)B * items >= 576 && blocks <= 512) p.pair = 4;
@@ -249,7 +362,7 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
     p.sorted = 1;
   // the 16-bit matrix-core kernel has the two-wavefront pair mode as well (same conditions), so that
   // the comparison on a ragged batch is between formats and not between schedules
-  if (kv16 && plan.num_splits == 1 && B <= 1024 &&
+  if (kv16 && !plan.cut && plan.num_splits == 1 && B <= 1024 &&
       (int64_t)B * c->n_kv_heads > 256 && (int64_t)((B + 1) / 2) * c->n_kv_heads <= 1024)
     p.pair = 2;
   return launch_decode(p, B, c->head_dim, G, kv16, kv_dtype, st);

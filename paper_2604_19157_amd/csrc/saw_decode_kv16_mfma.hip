@@ -32,6 +32,7 @@
 #include "saw_decode.h"
 #include "saw_wave_util.h"
 #include "saw_rank.h"
+#include "saw_cut.h"
 
 namespace saw {
 
@@ -98,7 +99,9 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
   constexpr int NS = (G > 4 && NP == 4) ? 2 : 1;
   constexpr int NWV = PAIR ? 2 : 1;
   // (the partition index is rotated by kv head and sequence, so that no XCD serves a fixed set of partitions)
-  const int split = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x, kvh = blockIdx.y;
+  // (a batch cut by its own lengths has one block per slot: see saw_cut.h)
+  const int split = (!PAIR && p.cut) ? (int)blockIdx.x : (int)((blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x);
+  const int kvh = blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row16 = lane & 15, grp = lane >> 4;
@@ -153,6 +156,15 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
       }
     }
     wave_sync();                                        // the ranking's scratch lived in vbuf_a
+  } else if (p.cut) {
+    const BatchCut cut = cut_batch(p, lane);
+    int len, part, parts, first, end;
+    cut_slot(cut, split, sg_b[0], len, part, parts);
+    if (sg_b[0] < 0) return;
+    if (part == 0 && kvh == 0 && lane == 0) p.cut_of[sg_b[0]] = make_int2(split, parts);
+    cut_range((len + 63) >> 6, part, parts, first, end);
+    sg_t0[0] = 64 * first;
+    sg_t1[0] = min(len, 64 * end);
   } else {
     const int L = min(p.seq_lens[sg_b[0]], p.bound);
     sg_t0[0] = split * p.chunk_tokens;
@@ -398,10 +410,8 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
           const int voff = vr_base + 32 * ks * kRowBytes + 16 * ((2 * c) ^ vr_swz);
           const i16x4 t0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS i16x4*)(vcur + voff));
           const i16x4 t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS i16x4*)(vcur + voff + 4 * kRowBytes));
-          const u32x4 bv = u32x4{(uint32_t)(uint16_t)t0[0] | ((uint32_t)(uint16_t)t0[1] << 16),
-                                 (uint32_t)(uint16_t)t0[2] | ((uint32_t)(uint16_t)t0[3] << 16),
-                                 (uint32_t)(uint16_t)t1[0] | ((uint32_t)(uint16_t)t1[1] << 16),
-                                 (uint32_t)(uint16_t)t1[2] | ((uint32_t)(uint16_t)t1[3] << 16)};
+          const u32x2 b0 = __builtin_bit_cast(u32x2, t0), b1 = __builtin_bit_cast(u32x2, t1);
+          const u32x4 bv = u32x4{b0.x, b0.y, b1.x, b1.y};
           if (kThree) oacc[c] = mfma16<DT>(pa3, bv, oacc[c]);
           oacc[c] = mfma16<DT>(pa, bv, oacc[c]);
         }
@@ -464,19 +474,20 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
 #pragma unroll
   for (int i = 0; i < NH; ++i) {
     const int head = kvh * G + head0 + i;
-    float* part = p.ws + (((int64_t)b * p.n_q_heads + head) * p.num_splits + split) * (D + 2);
+    const bool alone = !p.cut && p.num_splits == 1;
+    float* part = p.ws + (p.cut ? (int64_t)head * p.cut + split : ((int64_t)b * p.n_q_heads + head) * p.num_splits + split) * (D + 2);
     const float inv = 1.0f / lsum[i];
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
       const float o = both_limbs(oacc[c][i]);
       if (writer) {
-        if (p.num_splits == 1)
+        if (alone)
           store_elem(p.out, p.out_dtype, ((int64_t)b * p.n_q_heads + head) * D + 16 * c + row16, o * inv);
         else
           part[2 + 16 * c + row16] = o;
       }
     }
-    if (p.num_splits != 1 && writer && row16 == 0) { part[0] = m_ref[i]; part[1] = lsum[i]; }
+    if (!alone && writer && row16 == 0) { part[0] = m_ref[i]; part[1] = lsum[i]; }
   }
   wave_sync();                                   // the next range's prologue reuses the buffers
   }  // ranges of this wavefront

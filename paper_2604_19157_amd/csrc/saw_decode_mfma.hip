@@ -29,6 +29,7 @@
 #include "saw_decode.h"
 #include "saw_wave_util.h"
 #include "saw_rank.h"
+#include "saw_cut.h"
 
 namespace saw {
 
@@ -302,13 +303,16 @@ enum SegMode : int { kSegSplitKV = 0, kSegAlone = 1, kSegShare = 2 };
 // the spread of the lengths).  Four wavefronts over three sequences put 4/3 wavefronts on a (sequence,
 // kv head) item, which fills the chip when there are 1025 to 1536 items - too many for four
 // wavefronts per pair, and with two per pair a quarter to a half of the slots would stay empty.
-template <int G, int NW, bool PAIR, bool HP = false, int PK = 2, bool DN = false>
+// CUT: the batch is cut by its own lengths (saw_cut.h), a block of NW wavefronts per slot; a kernel of its own because the code
+// in front of the first page-id load costs the other modes 2 % even where it is not taken.
+template <int G, int NW, bool PAIR, bool HP = false, int PK = 2, bool DN = false, bool CUT = false>
 // (a launch of this kernel puts at most 8 wavefronts on a compute unit, 2 per SIMD: let the
 // register allocator use the 256 registers that leaves each of them)
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_int4_mfma_kernel(DecodeParams p) {
   static_assert(!PAIR || NW == 2 || NW == 4, "a pair block has two or four wavefronts");
   static_assert(!HP || G >= 2, "a head pair has at least one query head per kv head");
+  static_assert(!(PAIR && CUT), "pair blocks deal out whole sequences");
   static_assert(!(HP && DN), "the learned rotation is built for head_dim 128");
   constexpr int D = 128;                       // channels of a row (a head, or a pair of 64-channel heads)
   constexpr int DH = HP ? 64 : 128;            // channels of one head
@@ -323,7 +327,8 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // that shares a factor with 8 every XCD would serve a fixed set of partition indices - of a ragged
   // batch the later partitions are mostly empty, so some XCDs got most of the work: 33 sequences x 8
   // partitions 41 us against 28-32 us with 7 or 9 partitions)
-  const int split = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
+  // (a batch cut by its own lengths has one block per slot: see saw_cut.h)
+  const int split = CUT ? (int)blockIdx.x : (int)((blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x);
   const int kvh = blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -365,6 +370,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   uint32_t part_mask[MS];                      // PAIR: wavefronts with a share of sequence k of the block
 #pragma unroll
   for (int i = 0; i < MS; ++i) part_mask[i] = 0u;
+  bool cut_new = false;                        // a batch cut by its lengths: this block takes the sequence's new token
   if (PAIR) {
     const int B = p.batch;
     if (threadIdx.x < 4) done_cnt[threadIdx.x] = 0;
@@ -451,6 +457,16 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       }
     }
     wave_sync();                                        // the ranking's scratch lived in kbuf (and on into vbuf_a)
+  } else if (CUT) {
+    const BatchCut cut = cut_batch(p, lane);
+    int b, len, part, parts, first, end;
+    cut_slot(cut, split, b, len, part, parts);
+    if (b < 0) return;                                  // block-uniform
+    if (part == 0 && kvh == 0 && threadIdx.x == 0) p.cut_of[b] = make_int2(split, parts);
+    cut_range((len + 63) >> 6, part, parts, first, end);
+    bk[0] = b; lk[0] = len;
+    sg_t0[0] = 64 * first; sg_t1[0] = min(len, 64 * end);
+    cut_new = part == parts - 1;                        // (the last partition is one with the fewest batches)
   } else if (p.sorted) {
     // one block per (sequence, kv head), more blocks than fit the chip at once: blocks are dispatched
     // in index order as earlier ones finish, so taking the sequences longest first leaves the
@@ -515,7 +531,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   int window = 0;                    // 16-batch window pidv covers
   SAW_LOAD_PIDS(pidv, pg_first)
   int t_end, seq_len_b;                // seq_len_b: cached tokens of the sequence (= position of an appended token)
-  if (PAIR) {
+  if (PAIR || CUT) {
     t_end = __builtin_amdgcn_readfirstlane(SAW_SEG(sg_t1));
     seq_len_b = __builtin_amdgcn_readfirstlane(SAW_SEQ(lk));
   } else {
@@ -544,9 +560,10 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     }
   }
 
-  // fused append: the range that starts the sequence also takes the step's new token (wavefront
-  // 0 of the block when several share the range); its inputs are requested here, with the query
-  const bool takes_new = p.append && t_begin == 0 && first_batch == 0;
+  // fused append: the range that starts the sequence also takes the step's new token (wavefront 0 of the block when
+  // several share the range); of a batch cut by its lengths the one that ends it, there the wavefront with the fewest
+  // batches; its inputs are requested here, with the query
+  const bool takes_new = p.append && (CUT ? cut_new && wave == NW - 1 : t_begin == 0 && first_batch == 0);
   uint32_t new_wk = 0, new_wv = 0;
   int new_pid = -1;
   if (takes_new) {
@@ -618,11 +635,9 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // restrict-qualified pointers: the compiler then orders none of its LDS accesses behind them.
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0)
-  if (nb > 0) {
-    // issued unconditionally: a wavefront without a batch of its own shadows the last batch
-    const int first = min(first_batch, nb - 1);
-    SAW_FETCH_V(first, vbuf_a, mbuf_a)
-    SAW_FETCH_K(first, kbuf)
+  if (first_batch < nb) {
+    SAW_FETCH_V(first_batch, vbuf_a, mbuf_a)
+    SAW_FETCH_K(first_batch, kbuf)
   }
   // query scratch: up to G = 4 in the P buffer (no transfer ever targets it), else the second V
   // buffer for the rows (first written by the second batch's transfers, which leave after this)
@@ -799,10 +814,8 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     if (bi + STEP < nb) body(bi + STEP, t_begin + 64 * (bi + STEP), kbuf, vbuf_b, vbuf_a, pbuf, mbuf_b, mbuf_a);
   }
 
-  // A wavefront without a batch of its own (first_batch >= nb) still has the prologue's transfers of
-  // the last batch in flight.  Everything below reuses those buffers as scratch, so they have to
-  // have landed first: without this wait a transfer can arrive after the scratch has been written
-  // and overwrite it.
+  // Everything below reuses the buffers as scratch, so no transfer may be in flight (every batch's were waited for
+  // when it began, and a wavefront without a batch has requested none: this waits for nothing, it states the rule).
   __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0)
 
   // Fused append: the step's new token is quantised and stored now, placed in the (idle) buffers as
@@ -840,7 +853,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
 #pragma unroll
     for (int i = 0; i < NH; ++i) {
       float mw[NW];
-      float mm = -INFINITY;                                 // (wavefront 0 always has a batch: the maximum is finite)
+      float mm = -INFINITY;                                 // (some wavefront has a batch or the new token: the maximum is finite)
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
         mw[w] = ((const float*)(lds_all + w * kWaveLds))[(32 + i) * 64 + lane];
@@ -901,13 +914,14 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   }
   // (the lanes holding the lo rows sit 16 lanes above the hi rows, 32 for G = 8)
   const bool writer = (G > 4) ? (grp < 2) : (grp == 0);
-  const int emode = PAIR ? mode : (p.num_splits == 1 ? (int)kSegAlone : (int)kSegSplitKV);
+  const int emode = PAIR ? mode : (!CUT && p.num_splits == 1 ? (int)kSegAlone : (int)kSegSplitKV);
   if (emode == kSegSplitKV) {
     // one of several partitions: (max, sum, un-normalised accumulator) for the merge kernel
 #pragma unroll
     for (int i = 0; i < NH; ++i) {
       const int head = head0 + i;
-      float* dst = p.ws + (((int64_t)b * p.n_q_heads + kvh * G + head) * p.num_splits + split) * (DH + 2);
+      float* dst = p.ws + (CUT ? (int64_t)(kvh * G + head) * p.cut + split
+                                 : ((int64_t)b * p.n_q_heads + kvh * G + head) * p.num_splits + split) * (DH + 2);
       const int own = head / GK;                  // head pair: the half of the row that is this head's
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
@@ -1102,6 +1116,11 @@ static void launch_g(const DecodeParams& p, int B, int nw, dim3 grid, hipStream_
   }
   if (p.pair) {
     decode_int4_mfma_kernel<G, 2, true, HP, 2, DN><<<dim3(1, grid.y, (B + 1) / 2), dim3(128), 0, st>>>(p);
+    return;
+  }
+  if (p.cut) {
+    if (nw >= 4) decode_int4_mfma_kernel<G, 4, false, HP, 2, DN, true><<<grid, dim3(256), 0, st>>>(p);
+    else decode_int4_mfma_kernel<G, 2, false, HP, 2, DN, true><<<grid, dim3(128), 0, st>>>(p);
     return;
   }
   if (nw >= 8) decode_int4_mfma_kernel<G, 8, false, HP, 2, DN><<<grid, dim3(512), 0, st>>>(p);

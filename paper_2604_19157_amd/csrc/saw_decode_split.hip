@@ -92,9 +92,9 @@ void decode_int4_split64_kernel(DecodeParams p) {
   if (p.cut) {
     const BatchCut cut = cut_batch(p, lane);
     slot = blockIdx.x;
-    cut_slot(cut, slot, b, part, parts);
+    cut_slot(cut, slot, b, len, part, parts);
     if (b < 0) return;                                        // block-uniform
-    len = max(min(p.seq_lens[b], p.bound), 0);
+    if (part == 0 && kvh == 0 && threadIdx.x == 0) p.cut_of[b] = make_int2(slot, parts);
     cut_range((len + 63) >> 6, part, parts, first, end);
   } else {
     // (the partition index is rotated by kv head and sequence, so that no XCD serves a fixed set of partitions)
