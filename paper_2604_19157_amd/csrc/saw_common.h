@@ -74,8 +74,8 @@ __device__ __forceinline__ float apply_sign(const SignBits& sb, int c, float v) 
 // saw_prepare_dense_rotation lays it out:
 //   [0, 64 KiB)        R_l, fp32 row-major [i][j]                (y = x R_l: query, appended token)
 //   [64 KiB, 128 KiB)  R_l^T, fp32 row-major                     (outputs, read-backs)
-//   [128 KiB, 224 KiB) three bf16 limbs (hi, mid, lo; hi + mid + lo = R_l to 24 bits) as operands of
-//                      v_mfma_f32_16x16x32_bf16 (A and B operands have the same layout) for the store kernel: 16 bytes per (limb L, output tile
+//   [128 KiB, 224 KiB) three bf16 limbs (hi, mid, lo; hi + mid + lo = R_l to 24 bits) as A operands of
+//                      v_mfma_f32_16x16x32_bf16 for the store kernel: 16 bytes per (limb L, output tile
 //                      J < 8, k-step a < 4, lane) at index ((L * 8 + J) * 4 + a) * 64 + lane, holding
 //                      R_l[32 a + 8 (lane / 16) + e][dense_out_channel(J, lane % 16)], e = 0..7.
 constexpr int kDenseD = 128;

@@ -20,11 +20,13 @@
 //     one contiguous 1 KiB tile write, otherwise as per-token dword stores.
 // The transform is un-normalised; 1/sqrt(h) is folded into the stored scale (codes unchanged).
 #include "saw_common.h"
-#include "saw_wave_util.h"
 
 namespace saw {
 
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // One launch can serve several layers (grid.z): the layers share the slots, the page table and the
 // cache shape, and differ in their pools, their inputs and their learned rotation.
@@ -59,28 +61,9 @@ __device__ __forceinline__ f32x4 mfma_pm1(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// ---- the +/-1 matrix: A[m][k], m = output row, k = input channel (low five bits) ----
-// MFMA #1 row m -> output channel (low five bits) 8*(m/4) + m%4, MFMA #2 row m -> that + 4,
-// so lane (n16, rg) receives channels 8*rg .. 8*rg+7 of every 32-channel group.
-// Entry = (-1)^popcount(lo & k & (hm-1)) where the bits above the order hm agree, else 0.
-template <int DT>
-__device__ __forceinline__ void hadamard_operands(int hm, int n16, int rg, u32x4& ha1, u32x4& ha2) {
-  const uint32_t one = (DT == SAW_BF16) ? 0x3F80u : 0x3C00u;
-  const int lo1 = 8 * (n16 >> 2) + (n16 & 3);                  // A operand: lane (m = n16, k-group = rg)
-  uint32_t e1[8], e2[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int cl = 8 * rg + j;
-    const int lo2 = lo1 + 4;
-    const bool on1 = (((lo1 ^ cl) & ~(hm - 1)) & 31) == 0;
-    const bool on2 = (((lo2 ^ cl) & ~(hm - 1)) & 31) == 0;
-    const uint32_t s1 = (__builtin_popcount(lo1 & cl & (hm - 1)) & 1) ? 0x8000u : 0u;
-    const uint32_t s2 = (__builtin_popcount(lo2 & cl & (hm - 1)) & 1) ? 0x8000u : 0u;
-    e1[j] = on1 ? (one | s1) : 0u;
-    e2[j] = on2 ? (one | s2) : 0u;
-  }
-  ha1 = u32x4{e1[0] | (e1[1] << 16), e1[2] | (e1[3] << 16), e1[4] | (e1[5] << 16), e1[6] | (e1[7] << 16)};
-  ha2 = u32x4{e2[0] | (e2[1] << 16), e2[2] | (e2[3] << 16), e2[4] | (e2[5] << 16), e2[6] | (e2[7] << 16)};
+template <int CTRL>
+__device__ __forceinline__ float dppf(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, false));
 }
 
 // XS = number of register-to-register butterfly stages after the MFMA (0: h <= 32 or no rotation,
@@ -91,8 +74,16 @@ __device__ __forceinline__ void hadamard_operands(int hm, int n16, int rg, u32x4
 // and their code tiles and metadata are contiguous in the cache), so that loads, staging and the
 // matrix products run exactly as for head_dim 128; only the min/max, the scales and the addresses
 // are per head.
-template <int D, int DT, int XS, int HP = 1>
+// DENSE (D = 128, one head per wavefront): a learned per-layer rotation follows the Hadamard, y = (x H_blk) R_l
+// (App. A.3).  The Hadamard output of a lane - eight channels of each 32-channel group of one token - is
+// already the B operand of a v_mfma_f32_16x16x32_bf16 over that group, so it is split into three bf16 limbs
+// in registers (hi + mid + lo = the fp32 value to 24 bits) and multiplied by the three limbs of R_l, which
+// arrive as ready-made A operands from the prepared buffer (224 KiB, cache-resident): the six limb products
+// that matter (everything down to 2^-24 of the result), smallest first, accumulated in fp32.  The rows of the
+// A operands are ordered so that the result lands in the very lane layout the quantiser below expects.
+template <int D, int DT, int XS, int HP = 1, bool DENSE = false>
 __global__ __launch_bounds__(256) void rotate_quant_store_mfma_kernel(StoreMfmaParams p) {
+  static_assert(!DENSE || (D == 128 && HP == 1), "the learned rotation is built for head_dim 128");
   constexpr int DH = D / HP;             // channels of one head (D itself unless HP = 2: then 64)
   constexpr int ROWB = D * 2;            // bytes of one token's head vector (or head pair)
   constexpr int XC = ROWB / 16;          // 16-byte chunks per vector (16 | 8)
@@ -111,7 +102,9 @@ __global__ __launch_bounds__(256) void rotate_quant_store_mfma_kernel(StoreMfmaP
   const int kind = wave_live ? kind_raw : 0;                  // an idle wavefront shadows kind 0 and stores nothing
   const int which = kind >= n_heads_w ? 1 : 0;
   const int head = (kind - which * n_heads_w) * HP;           // (first) head of this wavefront
-  constexpr int NT = 1;                  // 16-token tiles of a wavefront
+  // DENSE: a wavefront takes NT = 2 consecutive 16-token tiles, so that one set of limb operands of R_l
+  // (96 KB per wavefront through L1) serves twice the tokens.
+  constexpr int NT = DENSE ? 2 : 1;
   const int64_t t0 = tb_id * (16 * NT);
   const bool rot = p.rot[which] != 0;
   const StoreLayerPtrs& lp = p.layer[blockIdx.z];
@@ -138,9 +131,30 @@ __global__ __launch_bounds__(256) void rotate_quant_store_mfma_kernel(StoreMfmaP
     if (wave_live && t_mine < p.T) slot[tile] = *(const int2*)(p.slots + 2 * t_mine);
   }
 
+  // ---- the +/-1 matrix: A[m][k], m = output row, k = input channel (low five bits) ----
+  // MFMA #1 row m -> output channel (low five bits) 8*(m/4) + m%4, MFMA #2 row m -> that + 4,
+  // so lane (n16, rg) receives channels 8*rg .. 8*rg+7 of every 32-channel group.
+  // Entry = (-1)^popcount(lo & k & (hm-1)) where the bits above the order hm agree, else 0.
   const int hm = rot ? min(p.had_block, 32) : 1;              // order handled inside the MFMA
   u32x4 ha1, ha2;
-  hadamard_operands<DT>(hm, n16, rg, ha1, ha2);
+  {
+    const uint32_t one = (DT == SAW_BF16) ? 0x3F80u : 0x3C00u;
+    const int lo1 = 8 * (n16 >> 2) + (n16 & 3);                // A operand: lane (m = n16, k-group = rg)
+    uint32_t e1[8], e2[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int cl = 8 * rg + j;
+      const int lo2 = lo1 + 4;
+      const bool on1 = (((lo1 ^ cl) & ~(hm - 1)) & 31) == 0;
+      const bool on2 = (((lo2 ^ cl) & ~(hm - 1)) & 31) == 0;
+      const uint32_t s1 = (__builtin_popcount(lo1 & cl & (hm - 1)) & 1) ? 0x8000u : 0u;
+      const uint32_t s2 = (__builtin_popcount(lo2 & cl & (hm - 1)) & 1) ? 0x8000u : 0u;
+      e1[j] = on1 ? (one | s1) : 0u;
+      e2[j] = on2 ? (one | s2) : 0u;
+    }
+    ha1 = u32x4{e1[0] | (e1[1] << 16), e1[2] | (e1[3] << 16), e1[4] | (e1[5] << 16), e1[6] | (e1[7] << 16)};
+    ha2 = u32x4{e2[0] | (e2[1] << 16), e2[2] | (e2[3] << 16), e2[4] | (e2[5] << 16), e2[6] | (e2[7] << 16)};
+  }
 
   // Randomised Hadamard: x . diag(sigma) is a sign flip of the 16-bit inputs (exact), applied at the
   // staging step because a lane's chunk index (lane % (ROWB / 16)) is the same for all of its loads: one mask.
@@ -201,6 +215,60 @@ __global__ __launch_bounds__(256) void rotate_quant_store_mfma_kernel(StoreMfmaP
           y[tile][8 * a + i] = u + v;
           y[tile][8 * a + 16 + i] = u - v;
         }
+    }
+  }
+  if constexpr (DENSE) {
+    if (p.dense_on[which]) {                                    // wavefront-uniform
+      typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+      typedef float f32x2_t __attribute__((ext_vector_type(2)));
+      u32x4 bh[NT][NA], bm[NT][NA], bl[NT][NA];                 // limbs of y as B operands, one per k-step (32 channels)
+#pragma unroll
+      for (int tile = 0; tile < NT; ++tile) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+          uint32_t wh[4], wm[4], wl[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float y0 = y[tile][8 * a + 2 * e], y1 = y[tile][8 * a + 2 * e + 1];
+            wh[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{y0, y1}, bf16x2_t));
+            const float r0 = y0 - __uint_as_float(wh[e] << 16), r1 = y1 - __uint_as_float(wh[e] & 0xffff0000u);
+            wm[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{r0, r1}, bf16x2_t));
+            const float q0 = r0 - __uint_as_float(wm[e] << 16), q1 = r1 - __uint_as_float(wm[e] & 0xffff0000u);
+            wl[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{q0, q1}, bf16x2_t));
+          }
+          bh[tile][a] = u32x4{wh[0], wh[1], wh[2], wh[3]};
+          bm[tile][a] = u32x4{wm[0], wm[1], wm[2], wm[3]};
+          bl[tile][a] = u32x4{wl[0], wl[1], wl[2], wl[3]};
+        }
+      }
+      const u32x4* const A = (const u32x4*)lp.dense_limbs + lane;
+#pragma unroll
+      for (int J = 0; J < 8; ++J) {
+        u32x4 ah[NA], am[NA], al[NA];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+          ah[a] = A[((0 * 8 + J) * 4 + a) * 64];
+          am[a] = A[((1 * 8 + J) * 4 + a) * 64];
+          al[a] = A[((2 * 8 + J) * 4 + a) * 64];
+        }
+#pragma unroll
+        for (int tile = 0; tile < NT; ++tile) {
+          f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#define SAW_LIMB_PRODUCT(RA, YB)                                                                     \
+  _Pragma("unroll") for (int a = 0; a < NA; ++a)                                                     \
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, RA[a]), __builtin_bit_cast(bf16x8, YB[tile][a]), acc, 0, 0, 0);
+          SAW_LIMB_PRODUCT(al, bh)
+          SAW_LIMB_PRODUCT(ah, bl)
+          SAW_LIMB_PRODUCT(am, bm)
+          SAW_LIMB_PRODUCT(am, bh)
+          SAW_LIMB_PRODUCT(ah, bm)
+          SAW_LIMB_PRODUCT(ah, bh)
+#undef SAW_LIMB_PRODUCT
+          // tile J holds channels 32 (J / 2) + 8 rg + 4 (J % 2) + 0..3 of token n16
+#pragma unroll
+          for (int i = 0; i < 4; ++i) y[tile][8 * (J >> 1) + 4 * (J & 1) + i] = acc[i];
+        }
+      }
     }
   }
   const float norm = rot ? had_norm(p.had_block) : 1.0f;
@@ -291,277 +359,6 @@ __global__ __launch_bounds__(256) void rotate_quant_store_mfma_kernel(StoreMfmaP
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// The store of a cache with a learned rotation behind the Hadamard (App. A.3): y = (x H_b) R_l = x M, M = H_b R_l.
-//
-// Taking the two matrices together is what makes this cheap: x is 16-bit and needs no splitting, so with M in three 16-bit
-// limbs a tile takes three products per k-step where (x H_b) and R_l in three limbs each took six, and no Hadamard product in
-// front.  M is worked out by every block from R_l's prepared limbs (96 KiB, from L2) and kept in registers for the
-// block's life: wavefront w of four holds all of M's rows for the 32 output channels 32 w .. + 31 (96 registers a lane).  The
-// block walks groups of 64 tokens of one (K|V, head) each: staged in LDS once, read as B operands by all four wavefronts (16 KiB
-// a group; with M's limbs through LDS or L1 instead it was 96 KiB per 16 or 32 tokens), min / max over the wavefronts' channel
-// groups through LDS, codes gathered in LDS, and wavefront w stores the w-th 16 tokens.  The next group's loads are in flight
-// meanwhile.  Two blocks per compute unit take turns on the matrix cores (floor 20 us for the 32k-token prefill of 8 heads; HBM
-// 35 us).  A tensor that is not rotated (rotate_mask) runs through with M = 1: the products are exact then.
-// Limbs: bf16 for bf16 inputs (24 bits of M).  For fp16 inputs fp16 limbs of M times a power of two that brings the largest entry
-// of the wavefront's channels to 2^13 .. 2^14 (33 bits, small entries keep theirs), taken out of y again.
-// Measured, 8 heads: 32768 tokens 103 -> 62 us, 8209 tokens from inside a page 36.5 -> 23.4, 16 tokens of 4 layers 19.7 -> 18.1.
-// What bounds it now: 2.5 us per group and block of two per compute unit against 1.3 us of matrix products - the vector ALU
-// (quantising 32 values a lane, 12 rounds of row minima and maxima) and three barriers a group.
-template <int DT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void rotate_quant_store_dense_kernel(StoreMfmaParams p) {
-  constexpr int D = kDenseD, TG = 64;          // channels, tokens per group
-  constexpr int ROWB = 2 * D;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n16 = lane & 15, rg = lane >> 4;
-  const int which = blockIdx.y;
-  const StoreLayerPtrs& lp = p.layer[blockIdx.z];
-  const bool rot = p.rot[which] != 0, dense = p.dense_on[which] != 0;
-  __shared__ __attribute__((aligned(16))) uint8_t stage[TG * ROWB];
-  __shared__ __attribute__((aligned(16))) uint32_t codes[TG * (D / 8)];       // [token][16 dwords]
-  __shared__ __attribute__((aligned(16))) float2 ends[4][TG];                 // (min, max) of a wavefront's 32 channels per token
-
-  // items (group of tokens, head), heads fastest: blocks side by side read one token's row
-  const int groups = (int)((p.T + TG - 1) / TG);                              // (the host keeps larger ones away)
-  const int step_g = (int)gridDim.x / p.n_kv_heads, step_h = (int)gridDim.x - step_g * p.n_kv_heads;
-  int group = (int)blockIdx.x / p.n_kv_heads, head = (int)blockIdx.x - group * p.n_kv_heads;
-  // ---- requests of one item: this thread's four 16-byte pieces, this lane's slot ----
-  u32x4 ld[4];
-  int2 slot = make_int2(-1, -1);
-  auto request = [&](int grp, int hd) __attribute__((always_inline)) {
-    const int64_t t0 = (int64_t)grp * TG;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int tok = 16 * r + (tid >> 4);
-      const int64_t t = min(t0 + tok, p.T - 1);                               // tokens past the end shadow the last one; never stored
-      ld[r] = __builtin_nontemporal_load((const u32x4*)((const uint16_t*)lp.in[which] + t * p.token_stride + hd * D + 8 * (tid & 15)));
-    }
-    const int64_t t_mine = t0 + 16 * wave + n16;
-    slot = make_int2(-1, -1);
-    if (t_mine < p.T) slot = *(const int2*)(p.slots + 2 * t_mine);
-  };
-  request(group, head);
-
-  // ---- M's limbs as A operands: lane (m = n16, k-group rg) of tile jj and k-step a holds M[32 a + 8 rg + e][j], e < 8, with
-  // j = dense_out_channel(2 wave + jj, m): the two tiles leave a lane eight contiguous channels of one token.
-  // M = H_b R_l is a product of the +/-1 matrix (rows k, ordered so that a lane ends up with eight consecutive ones) and the
-  // prepared limbs of R_l, which are B operands as they are: within 32 rows by the MFMA, between the groups of 32 by signs.  Each
-  // limb of R_l has sums of its own - 128 numbers of eight bits, so next to nothing is rounded - and their total is rounded
-  // once.  (The loop over the two tiles is kept rolled: the code is run once per block and read from memory every time; unrolled,
-  // with 64-bit butterflies, the launch took 14 us to get to its first token.) ----
-  u32x4 A[2][4][3];
-  float back[2] = {1.f, 1.f};                                                 // 1 / the power of two in the fp16 limbs
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int L = 0; L < 3; ++L) A[0][a][L] = A[1][a][L] = u32x4{0u, 0u, 0u, 0u};
-  u32x4 h1, h2;
-  hadamard_operands<SAW_BF16>(rot ? min(p.had_block, 32) : 1, n16, rg, h1, h2);
-  const int across = rot && p.had_block > 32 ? p.had_block / 32 : 1;          // groups of 32 rows that the Hadamard mixes: 1, 2 or 4
-#pragma unroll 1
-  for (int jj = 0; jj < 2; ++jj) {
-    float m[4][8];
-    if (dense) {                                                              // block-uniform
-      u32x4 R[3][4];
-#pragma unroll
-      for (int L = 0; L < 3; ++L)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) R[L][i] = ((const u32x4*)lp.dense_limbs)[((L * 8 + 2 * wave + jj) * 4 + i) * 64 + lane];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        f32x4 sum[2][3];
-#pragma unroll
-        for (int L = 0; L < 3; ++L) sum[0][L] = sum[1][L] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t on = ((a ^ i) & ~(across - 1)) == 0 ? 0xffffffffu : 0u;                     // wavefront-uniform
-          const uint32_t flip = (__builtin_popcount(a & i & (across - 1)) & 1) ? 0x80008000u : 0u;
-          const u32x4 g1 = (h1 ^ u32x4{flip, flip, flip, flip}) & u32x4{on, on, on, on};
-          const u32x4 g2 = (h2 ^ u32x4{flip, flip, flip, flip}) & u32x4{on, on, on, on};
-#pragma unroll
-          for (int L = 0; L < 3; ++L) {
-            sum[0][L] = mfma_pm1<SAW_BF16>(g1, R[L][i], sum[0][L]);
-            sum[1][L] = mfma_pm1<SAW_BF16>(g2, R[L][i], sum[1][L]);
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) m[a][e] = sum[e >> 2][0][e & 3] + (sum[e >> 2][1][e & 3] + sum[e >> 2][2][e & 3]);
-      }
-    } else {
-      const int j = dense_out_channel(2 * wave + jj, n16);
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) m[a][e] = 32 * a + 8 * rg + e == j ? 1.f : 0.f;
-    }
-    back[0] = back[1];
-    if (DT == SAW_F16) {
-      float top = 0.f;
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(m[a][e]));
-      top = max_xor32(max_xor16(row_allmax(top)));
-      const int up = (top > 0.f && top < INFINITY) ? min(max(14 - __builtin_amdgcn_frexp_expf(top), -100), 100) : 0;
-      back[1] = __builtin_ldexpf(1.f, -up);
-      const float by = __builtin_ldexpf(1.f, up);
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) m[a][e] *= by;
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      uint32_t w[3][4];
-#pragma unroll
-      for (int e2 = 0; e2 < 4; ++e2) {
-        float x0 = m[a][2 * e2], x1 = m[a][2 * e2 + 1];
-#pragma unroll
-        for (int L = 0; L < 3; ++L) {                                         // (what a limb leaves is exact)
-          if (DT == SAW_BF16) {
-            typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-            w[L][e2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, bf16x2_t));
-            x0 -= __uint_as_float(w[L][e2] << 16);
-            x1 -= __uint_as_float(w[L][e2] & 0xffff0000u);
-          } else {
-            const uint32_t u0 = f32_to_f16(x0), u1 = f32_to_f16(x1);
-            w[L][e2] = u0 | (u1 << 16);
-            x0 -= f16_to_f32(u0);
-            x1 -= f16_to_f32(u1);
-          }
-        }
-      }
-#pragma unroll
-      for (int L = 0; L < 3; ++L) {
-        A[0][a][L] = A[1][a][L];                                              // (the first round's limbs move up)
-        A[1][a][L] = u32x4{w[L][0], w[L][1], w[L][2], w[L][3]};
-      }
-    }
-  }
-  // randomised Hadamard: x . diag(sigma) is a sign flip of the 16-bit inputs, the same for all of a thread's pieces
-  u32x4 sflip = u32x4{0u, 0u, 0u, 0u};
-  if (p.has_signs && rot) {
-    uint32_t sx[4];
-    sign_pairs(p.signs, 8 * (tid & 15), sx);
-    sflip = u32x4{sx[0], sx[1], sx[2], sx[3]};
-  }
-  const float norm = rot ? had_norm(p.had_block) : 1.0f;
-
-#pragma unroll 1
-  while (group < groups) {
-    // ---- stage: chunk x of token tok at chunk position x ^ (tok % 16) ----
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int tok = 16 * r + (tid >> 4);
-      *(u32x4*)(stage + tok * ROWB + 16 * ((tid & 15) ^ (tok & 15))) = ld[r] ^ sflip;
-    }
-    const int2 sl = slot;
-    const int this_head = head;
-    __syncthreads();
-    group += step_g;
-    head += step_h;
-    if (head >= p.n_kv_heads) { head -= p.n_kv_heads; ++group; }
-    if (group < groups) request(group, head);
-    // where this wavefront's 16 tokens go (needed at the end)
-    int32_t page = -1;
-    const bool slot_ok = sl.x >= 0 && sl.x < p.n_seqs && sl.y >= 0 && (sl.y >> 4) < p.max_pages;
-    if (slot_ok) page = p.page_table[(int64_t)sl.x * p.max_pages + (sl.y >> 4)];
-
-    // ---- y = x M for this wavefront's 32 channels: tile t, lane (token n16, rg): channels 32 wave + 8 rg + 0 .. 7 ----
-    float y[4][8];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      // four independent sums: two output tiles, two halves of the channels (half as many roundings at full size)
-      f32x4 acc[2][2];
-      u32x4 bv[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) bv[a] = *(const u32x4*)(stage + (16 * t + n16) * ROWB + 16 * ((4 * a + rg) ^ n16));
-#pragma unroll
-      for (int u = 0; u < 2; ++u) acc[u][0] = acc[u][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int L = 2; L >= 0; --L)                                            // smallest limbs first
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj) acc[a & 1][jj] = mfma_pm1<DT>(A[jj][a][L], bv[a], acc[a & 1][jj]);
-      float mn, mx;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float v = acc[0][i >> 2][i & 3] + acc[1][i >> 2][i & 3];
-        y[t][i] = DT == SAW_F16 ? v * back[i >> 2] : v;
-        mn = i ? fminf(mn, y[t][i]) : y[t][i];
-        mx = i ? fmaxf(mx, y[t][i]) : y[t][i];
-      }
-      mn = -max_xor32(max_xor16(-mn));
-      mx = max_xor32(max_xor16(mx));
-      if (rg == 0) ends[wave][16 * t + n16] = make_float2(mn, mx);
-    }
-    __syncthreads();                                                          // (and everybody is done with the stage)
-    // ---- scale / zero (App. A.1): lane l for token l of the group ----
-    float inv, zq, s_store, z_store;
-    {
-      float mn = INFINITY, mx = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float2 e = ends[w][lane];
-        mn = fminf(mn, e.x); mx = fmaxf(mx, e.y);
-      }
-      const float range = mx - mn;
-      if (range > 0.0f) {
-        inv = 15.0f / range;
-        s_store = range * (norm * (1.0f / 15.0f));
-        zq = rintf(-mn * inv);
-        z_store = zq;
-      } else {  // constant vector
-        inv = 0.0f;
-        zq = 0.0f;
-        s_store = (mn != 0.0f) ? fabsf(mn) * norm : 1.0f;
-        z_store = (mn > 0.0f) ? -1.0f : ((mn < 0.0f) ? 1.0f : 0.0f);
-      }
-    }
-    // ---- quantise, pack: c = clip(round(y / s) + z, 0, 15).  With 1.5 2^23 + z added in one fused step the sum is rounded to a
-    // whole number (half to even) as it is formed and its low bits are the code; eight shifted bit patterns add up to the
-    // packed dword plus a constant.  (A zero-point beyond 2^21 - a range a millionth of its offset - goes the long way.) ----
-    constexpr float kMagic = 12582912.f;                                      // bits 0x4B400000
-    constexpr uint32_t kSum = 0x4B400000u * 0x11111111u;
-    const bool far = __any(!(fabsf(zq) < 2097152.f));
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const float inv_t = __shfl(inv, 16 * t + n16, 64), zq_t = __shfl(zq, 16 * t + n16, 64);
-      uint32_t w = 0;
-      if (!far) {                                                             // wavefront-uniform
-        const float zm = kMagic + zq_t;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          w += __float_as_uint(__builtin_amdgcn_fmed3f(fmaf(y[t][i], inv_t, zm), kMagic, kMagic + 15.f)) << (4 * i);
-        w -= kSum;
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          w |= ((uint32_t)__builtin_amdgcn_fmed3f(rintf(y[t][i] * inv_t) + zq_t, 0.0f, 15.0f)) << (4 * i);
-      }
-      codes[(16 * t + n16) * (D / 8) + 4 * wave + rg] = w;
-    }
-    __syncthreads();
-    // ---- paged placement of this wavefront's 16 tokens ----
-    const bool ok = slot_ok && page >= 0 && page < p.num_pages;
-    const int seq0 = __builtin_amdgcn_readfirstlane(sl.x), pos0 = __builtin_amdgcn_readfirstlane(sl.y);
-    const uint32_t* const mine = codes + 16 * wave * (D / 8);
-    if (__all(ok && sl.x == seq0 && sl.y == pos0 + n16) && (pos0 & 15) == 0) {       // one whole page: 1 KiB in one piece
-      const int64_t vec0 = ((int64_t)__builtin_amdgcn_readfirstlane(page) * p.n_kv_heads + this_head) * 16;
-      __builtin_nontemporal_store(*(const u32x4*)(mine + 4 * lane), (u32x4*)(lp.codes[which] + vec0 * (D / 2) + 16 * lane));
-      if (rg == wave) *(float2*)(lp.meta[which] + (vec0 + n16) * 2) = make_float2(s_store, z_store);     // (lane 16 wave + n16: this token's)
-    } else if (ok) {                                                          // per token: four lanes write its 64 bytes
-      const int64_t vec = ((int64_t)page * p.n_kv_heads + this_head) * 16 + (sl.y & 15);
-      *(u32x4*)(lp.codes[which] + vec * (D / 2) + 16 * rg) = *(const u32x4*)(mine + n16 * (D / 8) + 4 * rg);
-      if (rg == wave) *(float2*)(lp.meta[which] + vec * 2) = make_float2(s_store, z_store);
-    }
-    // (the next group's codes are written behind its own two barriers, which this wavefront reaches after reading these)
-  }
-}
-
 // `c`, `K`, `V`: n_layers cache descriptors and input pointers (host arrays); the layers agree in shape,
 // Hadamard block, mask and signs (checked by the caller).
 int launch_store_mfma(const saw_cache_t* c, const void* const* K, const void* const* V, int n_layers, int dt,
@@ -586,17 +383,8 @@ int launch_store_mfma(const saw_cache_t* c, const void* const* K, const void* co
   p.dense_on[0] = c->dense_rot && (c->rotate_mask & SAW_ROT_K);
   p.dense_on[1] = c->dense_rot && (c->rotate_mask & SAW_ROT_V);
   const int D = c->head_dim;
-  if (p.dense_on[0] || p.dense_on[1]) {                         // head_dim 128 (checked by the caller)
-    // two resident blocks of four wavefronts per compute unit, shared by K and V and the layers
-    const int64_t items = ((T + 63) / 64) * c->n_kv_heads;
-    if (items > 0x3fffffffLL) return SAW_EINVAL;
-    const int64_t most = 512 / (2 * n_layers) > 1 ? 512 / (2 * n_layers) : 1;
-    const dim3 dgrid((unsigned)(items < most ? items : most), 2, n_layers);
-    if (dt == SAW_BF16) rotate_quant_store_dense_kernel<SAW_BF16><<<dgrid, dim3(256), 0, st>>>(p);
-    else rotate_quant_store_dense_kernel<SAW_F16><<<dgrid, dim3(256), 0, st>>>(p);
-    return hipGetLastError() == hipSuccess ? SAW_OK : SAW_ELAUNCH;
-  }
-  const int64_t tblocks = (T + 15) / 16;
+  const int tile_tokens = (p.dense_on[0] || p.dense_on[1]) ? 32 : 16;   // tokens per wavefront (the DENSE kernel takes two tiles)
+  const int64_t tblocks = (T + tile_tokens - 1) / tile_tokens;
   if (tblocks > 0x7fffffffLL) return SAW_EINVAL;
   const bool pair64 = D == 64 && (c->n_kv_heads % 2) == 0;      // two 64-channel heads per wavefront
   const int kblocks = (2 * (c->n_kv_heads / (pair64 ? 2 : 1)) + 3) / 4;
@@ -628,7 +416,11 @@ int launch_store_mfma(const saw_cache_t* c, const void* const* K, const void* co
     case 1: case 2: rotate_quant_store_mfma_kernel<128, TT, 1, 2><<<grid, block, 0, st>>>(p); break;   \
     default: rotate_quant_store_mfma_kernel<128, TT, -1, 2><<<grid, block, 0, st>>>(p); break;         \
   }
-  if (pair64 && dt == SAW_BF16) { SAW_LAUNCH_PAIR(SAW_BF16) }
+  if (p.dense_on[0] || p.dense_on[1]) {                         // head_dim 128 (checked by the caller)
+    if (dt == SAW_BF16) rotate_quant_store_mfma_kernel<128, SAW_BF16, -1, 1, true><<<grid, block, 0, st>>>(p);
+    else rotate_quant_store_mfma_kernel<128, SAW_F16, -1, 1, true><<<grid, block, 0, st>>>(p);
+  }
+  else if (pair64 && dt == SAW_BF16) { SAW_LAUNCH_PAIR(SAW_BF16) }
   else if (pair64) { SAW_LAUNCH_PAIR(SAW_F16) }
   else if (D == 128 && dt == SAW_BF16) { SAW_LAUNCH(128, SAW_BF16) }
   else if (D == 128) { SAW_LAUNCH(128, SAW_F16) }

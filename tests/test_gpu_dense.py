@@ -137,25 +137,3 @@ def test_learned_rotation_needs_head_dim_128(saw):
         saw.rotate_quant_store(cache, K, V, torch.from_numpy(w.page_table).cuda(),
                                torch.from_numpy(synth.slots_for(0, 0, 40)).cuda())
     assert e.value.code == -1
-
-
-@pytest.mark.parametrize("T", [1, 15, 17, 63, 64, 65, 129, 1000])
-@pytest.mark.parametrize("dtype,Hkv,kw", [(torch.bfloat16, 8, dict(had_block=128)), (torch.float16, 3, dict(had_block=32, rotate_mask=1)),
-                                          (torch.bfloat16, 1, dict(had_block=64, sign_seed=7)), (torch.float16, 8, dict(had_block=1, rotate_mask=2))])
-def test_store_token_groups(saw, T, dtype, Hkv, kw):
-    """Edges of the store's 64-token groups and 16-token tiles, K and V apart (one of them unrotated), odd head counts; at
-    T = 1000 several groups per block when eight layers share the launch.  Every vector under the store criterion, and the
-    layers' call equal to single calls."""
-    w = synth.make_workload("tiny", batch=1, seq_lens=[T], n_q_heads=Hkv, n_kv_heads=Hkv, dtype=dtype, dense_seed=T, **kw)
-    cache, ref, recs, pt = gc.fill_caches(w, saw)
-    parity.assert_store_ok(gc.compare_store(gc.cache_to_numpy(cache, w), ref, recs))
-    K, V = synth.gen_kv(w, 0, 0, T)
-    K, V, sl = K.cuda(), V.cuda(), torch.from_numpy(synth.slots_for(0, 0, T)).cuda()
-    n = 32 if T == 1000 else 3
-    caches = [saw.Cache(w.num_pages, Hkv, 128, w.had_block, w.rotate_mask, signs=w.signs) for _ in range(n)]
-    for c in caches:
-        c.dense_rot = cache.dense_rot
-    saw.rotate_quant_store_layers(caches, [K] * n, [V] * n, pt, sl)
-    for c in caches:
-        for f in ("k_codes", "v_codes", "k_meta", "v_meta"):
-            assert torch.equal(getattr(c, f), getattr(cache, f)), f
