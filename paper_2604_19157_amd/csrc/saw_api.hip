@@ -77,9 +77,9 @@ static bool block_ok(const saw_cache_t* c) {
 // The matrix-core INT4 kernel for rows of 128 channels holds 2048 wavefronts.  `per_seq`: (kv head, or pair of heads) items of a
 // sequence.  What was measured, decode or fused step, 32 query / 8 kv heads, against the fixed partitions (in brackets):
 //   * partitions of four wavefronts, which fold in LDS, leave the merge pass a quarter of the records, where that still gives
-//     a sequence four partitions on average: 16 x 4096 tokens 24.0 us (25.8; two wavefronts 24.2, one 26.2), 4 x 131072
-//     108.7 (111.5), 8 ragged up to 3000 under a loose bound 17.0 (22.8);
-//   * two wavefronts otherwise: 48 ragged up to 4096 34.3 (37.5, with a loose bound 54; four wavefronts 39.7), 32 ragged 26.7
+//     a sequence eight partitions on average, so that rounding its share to whole ones costs little: 4 x 131072 tokens
+//     108.7 us (111.5; two wavefronts 109.7), 8 ragged up to 3000 under a loose bound 17.0 (22.8; 18.7), 8 x 8192 24.3 (26.0);
+//   * two wavefronts otherwise: 16 x 4096 24.2 (25.8), 43 of 4888-6153 x 2 heads with four 21.7 (21.0), 48 ragged up to 4096 34.3 (37.5, with a loose bound 54; four wavefronts 39.7), 32 ragged 26.7
 //     (27.8, loose 47), 200 ragged x 2 heads 35.2 (37.0);
 //   * from 512 items on one partition per sequence stays ahead or level (64 ragged 43.0 against 43.2, equal lengths 35.0
 //     against 39.8, 96 ragged 57.3 against 59.6);
@@ -91,7 +91,7 @@ static void plan_cut(int B, int units, int per_seq, SplitPlan* plan) {
   const int per_wave = (units + 7) / 8;
   if (plan->waves_per_item == 8 && (per_wave <= 4 || (items >= 192 && per_wave <= 5))) return;
   if (items >= 512) return;
-  if (cut_plan(B, units, 512 / per_seq, 4, plan) && plan->cut >= 4 * B) return;
+  if (cut_plan(B, units, 512 / per_seq, 4, plan) && plan->cut >= 8 * B) return;
   plan->cut = 0;
   cut_plan(B, units, 1024 / per_seq, 2, plan);
 }
