@@ -1,8 +1,9 @@
-"""ctypes binding of the C ABI declared in ``include/saw.h``.
+"""Binding of the C ABI declared in ``include/saw.h``.
 
 Argument marshalling only: torch supplies device memory and the current stream, every
-step of the path runs in the HIP kernels of ``libsaw.so``.  There is no CPU fallback: if
-the library is missing or a call fails, an exception is raised.
+step of the path runs in the HIP kernels of ``libsaw.so``.  The calls of a serving loop go through
+``_marshal`` (``csrc/marshal.cpp``), which reads the tensors natively; the others through ctypes.  There is no CPU
+fallback: if the library is missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
@@ -82,6 +83,22 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_native = None
+
+
+def _marshal():
+    """The native marshalling module; raises if it or the library is absent."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _marshal as m
+        except ImportError as e:
+            raise RuntimeError("_marshal.so not built: build it with `python -c 'import __graft_entry__ as g; g.build()'`") from e
+        _native = m
+    return _native
+
+
 def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
@@ -144,34 +161,13 @@ def prepare_dense_rotation(R, head_dim, device="cuda"):
 def rotate_quant_store(cache: Cache, K, V, page_table, slots):
     """saw_rotate_quant_store: K, V ``[T][Hkv][d]`` fp16/bf16, page_table ``[n_seqs][max_pages]`` int32,
     slots ``[T][2]`` int32, all on the device."""
-    T = K.shape[0]
-    assert K.dtype == V.dtype and K.shape == V.shape and K.stride(2) == 1 and K.stride(1) == cache.head_dim
-    assert V.stride() == K.stride() and page_table.dtype == torch.int32 and slots.dtype == torch.int32
-    assert page_table.is_contiguous() and slots.is_contiguous() and slots.shape == (T, 2)
-    st = cache.struct()
-    _check(lib().saw_rotate_quant_store(ctypes.byref(st), _ptr(K), _ptr(V), _DT[K.dtype], T,
-                                        K.stride(0) if T > 1 else cache.n_kv_heads * cache.head_dim,
-                                        _ptr(page_table), page_table.shape[0], page_table.shape[1],
-                                        _ptr(slots), _stream()), "saw_rotate_quant_store")
+    _check((_native or _marshal()).store(cache, K, V, page_table, slots), "saw_rotate_quant_store")
 
 
 def rotate_quant_store_layers(caches, Ks, Vs, page_table, slots):
     """saw_rotate_quant_store_layers: lists of n_layers caches and ``[T][Hkv][d]`` K / V tensors, one launch
     per 32 layers."""
-    n = len(caches)
-    c0 = caches[0]
-    T = Ks[0].shape[0]
-    stride = Ks[0].stride(0) if T > 1 else c0.n_kv_heads * c0.head_dim
-    for K, V in zip(Ks, Vs):
-        assert K.dtype == Ks[0].dtype and K.shape == Ks[0].shape == V.shape and K.stride(2) == 1 and K.stride(1) == c0.head_dim
-        assert V.stride() == K.stride() and (T <= 1 or K.stride(0) == stride)
-    assert len(Ks) == n == len(Vs) and page_table.is_contiguous() and slots.is_contiguous() and slots.shape == (T, 2)
-    sts = (SawCacheStruct * n)(*[c.struct() for c in caches])
-    kp = (ctypes.c_void_p * n)(*[K.data_ptr() for K in Ks])
-    vp_ = (ctypes.c_void_p * n)(*[V.data_ptr() for V in Vs])
-    _check(lib().saw_rotate_quant_store_layers(sts, kp, vp_, n, _DT[Ks[0].dtype], T, stride, _ptr(page_table),
-                                               page_table.shape[0], page_table.shape[1], _ptr(slots), _stream()),
-           "saw_rotate_quant_store_layers")
+    _check((_native or _marshal()).store_layers(caches, Ks, Vs, page_table, slots), "saw_rotate_quant_store_layers")
 
 
 def decode_order(seq_lens, max_seq_len=0):
@@ -233,26 +229,13 @@ def paged_decode_attn(cache: Cache, q, page_table, seq_lens, max_seq_len=0, sm_s
     """saw_paged_decode_attn: q ``[B][Hq][d]``; returns ``out [B][Hq][d]``.  With ``order`` (int32 device
     tensor, the sequences longest first) the call is saw_paged_decode_attn_hinted."""
     B, Hq, d = q.shape
-    assert q.is_contiguous() and page_table.is_contiguous() and seq_lens.dtype == torch.int32
-    bound = max_seq_len if max_seq_len > 0 else page_table.shape[1] * cache.page_size
     if out is None:
         out = torch.empty((B, Hq, d), dtype=out_dtype, device=q.device)
-    need = decode_workspace_bytes(cache, B, Hq, bound, num_splits)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-    st = cache.struct()
-    if order is not None:
-        assert order.dtype == torch.int32 and order.numel() == B and order.is_contiguous()
-        hints = SawHints(order.data_ptr())
-        _check(lib().saw_paged_decode_attn_hinted(ctypes.byref(st), _ptr(q), _DT[q.dtype], B, Hq, _ptr(page_table),
-                                                  page_table.shape[1], _ptr(seq_lens), max_seq_len, float(sm_scale),
-                                                  _ptr(out), _DT[out.dtype], _ptr(workspace), workspace.numel(),
-                                                  num_splits, ctypes.byref(hints), _stream()), "saw_paged_decode_attn_hinted")
-        return out
-    _check(lib().saw_paged_decode_attn(ctypes.byref(st), _ptr(q), _DT[q.dtype], B, Hq, _ptr(page_table),
-                                       page_table.shape[1], _ptr(seq_lens), max_seq_len, float(sm_scale),
-                                       _ptr(out), _DT[out.dtype], _ptr(workspace), workspace.numel(),
-                                       num_splits, _stream()), "saw_paged_decode_attn")
+        bound = max_seq_len if max_seq_len > 0 else page_table.shape[1] * cache.page_size
+        workspace = torch.empty(max(decode_workspace_bytes(cache, B, Hq, bound, num_splits), 16), dtype=torch.uint8, device=q.device)
+    _check((_native or _marshal()).decode(cache, q, page_table, seq_lens, max_seq_len, sm_scale, out, workspace, num_splits, order),
+           "saw_paged_decode_attn")
     return out
 
 
@@ -275,29 +258,13 @@ def append_decode_attn(cache: Cache, K_new, V_new, q, page_table, seq_lens, max_
     seq_lens[b]), q ``[B][Hq][d]``; stores the tokens and returns ``out [B][Hq][d]`` of the attention
     over seq_lens[b] + 1 tokens.  seq_lens (tokens cached before the call) is not modified."""
     B, Hq, d = q.shape
-    assert q.is_contiguous() and K_new.is_contiguous() and V_new.is_contiguous() and K_new.dtype == V_new.dtype
-    assert page_table.is_contiguous() and seq_lens.dtype == torch.int32
-    cap = page_table.shape[1] * cache.page_size
-    after = (max_seq_len if max_seq_len > 0 else cap - 1) + 1
     if out is None:
         out = torch.empty((B, Hq, d), dtype=out_dtype, device=q.device)
-    need = decode_workspace_bytes(cache, B, Hq, after, 0)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-    st = cache.struct()
-    if order is not None:
-        assert order.dtype == torch.int32 and order.numel() == B and order.is_contiguous()
-        hints = SawHints(order.data_ptr())
-        _check(lib().saw_append_decode_attn_hinted(ctypes.byref(st), _ptr(K_new), _ptr(V_new), _DT[K_new.dtype], _ptr(q),
-                                                   _DT[q.dtype], B, Hq, _ptr(page_table), page_table.shape[1], _ptr(seq_lens),
-                                                   max_seq_len, float(sm_scale), _ptr(out), _DT[out.dtype], _ptr(workspace),
-                                                   workspace.numel(), ctypes.byref(hints), _stream()),
-               "saw_append_decode_attn_hinted")
-        return out
-    _check(lib().saw_append_decode_attn(ctypes.byref(st), _ptr(K_new), _ptr(V_new), _DT[K_new.dtype], _ptr(q),
-                                        _DT[q.dtype], B, Hq, _ptr(page_table), page_table.shape[1], _ptr(seq_lens),
-                                        max_seq_len, float(sm_scale), _ptr(out), _DT[out.dtype], _ptr(workspace),
-                                        workspace.numel(), _stream()), "saw_append_decode_attn")
+        after = (max_seq_len if max_seq_len > 0 else page_table.shape[1] * cache.page_size - 1) + 1
+        workspace = torch.empty(max(decode_workspace_bytes(cache, B, Hq, after, 0), 16), dtype=torch.uint8, device=q.device)
+    _check((_native or _marshal()).append(cache, K_new, V_new, q, page_table, seq_lens, max_seq_len, sm_scale, out, workspace, order),
+           "saw_append_decode_attn")
     return out
 
 
@@ -323,13 +290,13 @@ def flatten_dequant(cache: Cache, page_table, seq, pos_begin, pos_end, unrotate=
         k_out = torch.empty(shape, dtype=out_dtype, device=dev)
     if want_v and v_out is None:
         v_out = torch.empty(shape, dtype=out_dtype, device=dev)
-    ref = k_out if k_out is not None else v_out
-    stride = ref.stride(0) if ref is not None and n > 0 else cache.n_kv_heads * cache.head_dim
-    dt = _DT[ref.dtype] if ref is not None else _DT[out_dtype]
-    st = cache.struct()
-    _check(lib().saw_flatten_dequant(ctypes.byref(st), _ptr(page_table), page_table.shape[1], seq, pos_begin,
-                                     pos_end, int(bool(unrotate)), dt, _ptr(k_out), _ptr(v_out), stride,
-                                     _stream()), "saw_flatten_dequant")
+    if k_out is None and v_out is None:               # nothing wanted: the arguments are still looked at
+        st = cache.struct()
+        _check(lib().saw_flatten_dequant(ctypes.byref(st), _ptr(page_table), page_table.shape[1], seq, pos_begin, pos_end,
+                                         int(bool(unrotate)), _DT[out_dtype], None, None, cache.n_kv_heads * cache.head_dim,
+                                         _stream()), "saw_flatten_dequant")
+        return k_out, v_out
+    _check((_native or _marshal()).flatten(cache, page_table, seq, pos_begin, pos_end, unrotate, k_out, v_out), "saw_flatten_dequant")
     return k_out, v_out
 
 
@@ -362,16 +329,13 @@ def kv16_store(cache: Kv16Cache, K, V, page_table, slots):
 def kv16_paged_decode_attn(cache: Kv16Cache, q, page_table, seq_lens, max_seq_len=0, sm_scale=0.0, out=None,
                            out_dtype=torch.float32, workspace=None, num_splits=0):
     B, Hq, d = q.shape
-    bound = max_seq_len if max_seq_len > 0 else page_table.shape[1] * cache.page_size
     if out is None:
         out = torch.empty((B, Hq, d), dtype=out_dtype, device=q.device)
-    st = cache.struct()
-    need = int(lib().saw_decode_workspace_bytes(ctypes.byref(st), B, Hq, bound, num_splits))
     if workspace is None:
+        st = cache.struct()
+        bound = max_seq_len if max_seq_len > 0 else page_table.shape[1] * cache.page_size
+        need = int(lib().saw_decode_workspace_bytes(ctypes.byref(st), B, Hq, bound, num_splits))
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-    _check(lib().saw_kv16_paged_decode_attn(ctypes.byref(st), _ptr(cache.k_pages), _ptr(cache.v_pages),
-                                            _DT[cache.dtype], _ptr(q), _DT[q.dtype], B, Hq, _ptr(page_table),
-                                            page_table.shape[1], _ptr(seq_lens), max_seq_len, float(sm_scale),
-                                            _ptr(out), _DT[out.dtype], _ptr(workspace), workspace.numel(),
-                                            num_splits, _stream()), "saw_kv16_paged_decode_attn")
+    _check((_native or _marshal()).kv16_decode(cache, q, page_table, seq_lens, max_seq_len, sm_scale, out, workspace, num_splits),
+           "saw_kv16_paged_decode_attn")
     return out

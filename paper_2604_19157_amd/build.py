@@ -8,6 +8,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libsaw.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")     # the binding's argument marshalling (csrc/marshal.cpp)
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
@@ -55,7 +56,25 @@ def build_library(verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + out + err)
     _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB + ".tmp", *objs], verbose)
     os.replace(LIB + ".tmp", LIB)
+    build_marshal(verbose)
     return LIB
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Host code only: a Python extension module against torch's headers, linked to ``libsaw.so`` beside it."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    inc = [os.path.join(ROOT, "include"), os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *["-I" + d for d in inc],
+          os.path.join(HERE, "csrc", "marshal.cpp"), "-o", MARSHAL + ".tmp", "-L" + HERE, "-l:libsaw.so", "-Wl,-rpath,$ORIGIN",
+          "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], verbose)
+    os.replace(MARSHAL + ".tmp", MARSHAL)
+    return MARSHAL
 
 
 if __name__ == "__main__":

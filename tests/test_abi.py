@@ -228,3 +228,38 @@ def test_store_layers_and_dense_rotation_reject_bad_arguments(saw):
     # flatten cannot rotate a learned rotation back
     st = _struct(saw, dense_rot=16)
     assert L.saw_flatten_dequant(ctypes.byref(st), P(16), 4, 0, 0, 8, 1, 2, P(16), P(16), 256, P(0)) == -1
+
+
+def test_native_marshalling_checks_like_the_binding(saw):
+    """The calls that go through the native module refuse on the host what the binding always refused; nothing is launched."""
+    import torch
+    c = saw.Cache(4, 2, 128, 128, device="cpu")
+    K = torch.zeros((3, 2, 128), dtype=torch.bfloat16)
+    pt, sl = torch.zeros((1, 4), dtype=torch.int32), torch.zeros((3, 2), dtype=torch.int32)
+    bad = [(K, K.half(), pt, sl), (K, K[:2], pt, sl), (K.transpose(1, 2), K, pt, sl), (K, K, pt.long(), sl), (K, K, pt, sl.long()),
+           (K, K, pt, sl[:2]), (K[:, :1], K[:, :1].clone(), pt, sl)]
+    for k, v, t, s in bad:
+        with pytest.raises(AssertionError):
+            saw.rotate_quant_store(c, k, v, t, s)
+    with pytest.raises(KeyError):
+        saw.rotate_quant_store(c, K.int(), K.int(), pt, sl)
+    with pytest.raises(TypeError):
+        saw.rotate_quant_store(c, None, K, pt, sl)
+    with pytest.raises(AttributeError):
+        saw.rotate_quant_store(object(), K, K, pt, sl)
+    with pytest.raises(IndexError):
+        saw.rotate_quant_store_layers([], [], [], pt, sl)
+    with pytest.raises(AssertionError):
+        saw.rotate_quant_store_layers([c, c], [K, K[:2]], [K, K[:2]], pt, sl)
+    with pytest.raises(AssertionError):
+        saw.rotate_quant_store_layers([c, c], [K], [K], pt, sl)
+    q, lens = torch.zeros((1, 4, 128), dtype=torch.bfloat16), torch.zeros(1, dtype=torch.int32)
+    out, ws = torch.zeros((1, 4, 128)), torch.zeros(1 << 16, dtype=torch.uint8)
+    with pytest.raises(AssertionError):
+        saw.paged_decode_attn(c, q, pt, lens.long(), out=out, workspace=ws)
+    with pytest.raises(AssertionError):
+        saw.paged_decode_attn(c, q, pt, lens, out=out, workspace=ws, order=lens.long())
+    with pytest.raises(AssertionError):
+        saw.append_decode_attn(c, K[:1], K[:1].half(), q, pt, lens, out=out, workspace=ws)
+    with pytest.raises(AssertionError):
+        saw.append_decode_attn(c, K[:1], K[:1], q.transpose(1, 2), pt, lens, out=out, workspace=ws)
