@@ -7,9 +7,11 @@
 namespace saw {
 
 // The partial results of one (sequence, query head): how many, and where the first one is.
-template <int D>
+// (CUT at compile time: a test of the argument block puts one more scalar-memory latency in front of everything; the decode of 1 x
+// 131072 tokens took 1.016 times as long as with the merge kernel before there were cut batches, and takes 0.987 times.)
+template <int D, bool CUT>
 __device__ __forceinline__ int row_records(const DecodeParams& p, int b, int j, const float*& base) {
-  if (p.cut) {
+  if (CUT) {
     const int2 own = p.cut_of[b];             // (requested with the length; not written, and not used, if nothing ran)
     const int L = min(p.seq_lens[b], p.bound);
     base = p.ws + ((int64_t)j * p.cut + own.x) * (D + 2);
@@ -53,7 +55,7 @@ __device__ __forceinline__ void block_lds_matvec4(const float* x, float* y, cons
 // Merge of the partitions of a (sequence, query head) by one wavefront, four rows per block: up to 16 records are requested
 // at once, so a row of few partitions costs one trip to memory and no block barrier (64 x 64 rows of 64 channels, 6 partitions
 // each: 5.1 us, 7.0 with a block of 256 threads per row; 48 x 32 rows of 128 channels: 4.0 and 4.6 us; 16 x 32: 3.9 and 4.0).
-template <int D>
+template <int D, bool CUT>
 __global__ __launch_bounds__(256) void decode_merge_rows_kernel(DecodeParams p) {
   constexpr int E = D / 64;                   // channels per lane
   constexpr int CH = 16;                      // records per trip
@@ -63,7 +65,7 @@ __global__ __launch_bounds__(256) void decode_merge_rows_kernel(DecodeParams p) 
   const int j = min((int)blockIdx.x * 4 + wave, p.n_q_heads - 1);
   __shared__ __attribute__((aligned(16))) float rows[2][4][128];
   const float* base;
-  const int ns = row_records<D>(p, b, j, base);
+  const int ns = row_records<D, CUT>(p, b, j, base);
   float mm = -INFINITY, den = 0.f, num[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) num[e] = 0.f;
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(256) void decode_merge_rows_kernel(DecodeParams p) 
 }
 
 // Merge by a block of NT threads per row: rows of very many partitions (long contexts, small batches).
-template <int D, int NT>
+template <int D, int NT, bool CUT>
 __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
   constexpr int NG = NT / D;                  // channel groups working on different splits
   constexpr int NW = NT / 64;
@@ -156,7 +158,7 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
   const int c = tid % D, g = tid / D;
   const int64_t o_idx = ((int64_t)b * p.n_q_heads + j) * D + c;
   const float* base;
-  const int ns = row_records<D>(p, b, j, base);
+  const int ns = row_records<D, CUT>(p, b, j, base);
   if (ns == 0) {
     if (g == 0) store_elem(p.out, p.out_dtype, o_idx, 0.f);
     return;
@@ -231,6 +233,19 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
+template <bool CUT>
+static void launch_merge(const DecodeParams& p, int B, int D, bool many, hipStream_t st) {
+  if (many) {
+    const dim3 grid(p.n_q_heads, B);
+    if (D == 128) decode_merge_kernel<128, 1024, CUT><<<grid, dim3(1024), 0, st>>>(p);
+    else decode_merge_kernel<64, 1024, CUT><<<grid, dim3(1024), 0, st>>>(p);
+  } else {
+    const dim3 grid((p.n_q_heads + 3) / 4, B);
+    if (D == 128) decode_merge_rows_kernel<128, CUT><<<grid, dim3(256), 0, st>>>(p);
+    else decode_merge_rows_kernel<64, CUT><<<grid, dim3(256), 0, st>>>(p);
+  }
+}
+
 int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_dtype, hipStream_t st) {
   const dim3 grid = p.cut ? dim3(p.cut, p.n_kv_heads) : dim3(p.num_splits, p.n_kv_heads, B);
   const bool head_pairs = !kv16 && decode_head_pairs(D, p.n_kv_heads, G);
@@ -247,15 +262,8 @@ int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_
   if (!p.cut && p.num_splits == 1) return SAW_OK;             // the kernel wrote the output itself
   // (a sequence has more than 16 partitions - on average, if the lengths cut the batch -: a block of 1024 threads per row;
   // otherwise a wavefront per row)
-  if ((p.cut ? p.cut / B : p.num_splits) > 16) {
-    const dim3 mgrid(p.n_q_heads, B);
-    if (D == 128) decode_merge_kernel<128, 1024><<<mgrid, dim3(1024), 0, st>>>(p);
-    else decode_merge_kernel<64, 1024><<<mgrid, dim3(1024), 0, st>>>(p);
-  } else {
-    const dim3 mgrid((p.n_q_heads + 3) / 4, B);
-    if (D == 128) decode_merge_rows_kernel<128><<<mgrid, dim3(256), 0, st>>>(p);
-    else decode_merge_rows_kernel<64><<<mgrid, dim3(256), 0, st>>>(p);
-  }
+  if (p.cut) launch_merge<true>(p, B, D, p.cut / B > 16, st);
+  else launch_merge<false>(p, B, D, p.num_splits > 16, st);
   return hipGetLastError() == hipSuccess ? SAW_OK : SAW_ELAUNCH;
 }
 
