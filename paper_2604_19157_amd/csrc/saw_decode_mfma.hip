@@ -53,9 +53,11 @@ constexpr float kLazyTau = 8.0f;               // reference max may lag the true
 // the other half, so that the 128-channel products below are the 64-channel ones.
 // DN: a learned rotation R_l follows the Hadamard (App. A.3); a compile-time flag, so that the kernels
 // of caches without one carry none of its code.
-template <int G, int NH, bool HP, bool DN>
+// NWC > 1: all NWC wavefronts of the block prepare the same query, and share the learned rotation's product (`first`: wavefront 0's
+// scratch, `stride` floats apart): each reads its columns of R_l instead of all 64 KiB.
+template <int G, int NH, bool HP, bool DN, int NWC>
 __device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&qraw)[2 * G], int lane,
-                                          float* __restrict__ qs, u32x4 (&a_q)[4],
+                                          float* __restrict__ qs, float* __restrict__ first, int stride, int wave, u32x4 (&a_q)[4],
                                           float (&qsum)[NH], float& qmul_out) {
   constexpr int D = 128;
   constexpr int LO = (G > 4) ? 8 : 4;
@@ -86,7 +88,10 @@ __device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&q
   }
   // learned rotation after the Hadamard (App. A.3: q^ = (q H_b) R_l)
   if constexpr (DN) {
-    if (p.dense_k) wave_lds_matvec128<G>(qs, p.dense, lane);
+    if (p.dense_k) {
+      if constexpr (NWC > 1) block_lds_matvec128<G, NWC>(first, stride, p.dense, wave, lane);
+      else wave_lds_matvec128<G>(qs, p.dense, lane);
+    }
   }
   const bool is_lo = row16 >= LO;
   const int qhead = row16 - (is_lo ? LO : 0);
@@ -657,7 +662,9 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       // randomised Hadamard: q diag(sigma) first (element lane + 64 j is channel lane + 64 (j & 1))
       if (p.rot_k && p.has_signs) qraw[j] = apply_sign(p.signs, HP ? lane : lane + 64 * (j & 1), qraw[j]);
     }
-    prepare_q<G, NH, HP, DN>(p, qraw, lane, qrows, a_q, qsum, qmul);
+    // (the wavefronts of a block that share a range prepare the same query)
+    prepare_q<G, NH, HP, DN, PAIR ? 1 : NW>(p, qraw, lane, qrows, (float*)((uint8_t*)qrows - wave * kWaveLds), kWaveLds / 4, wave,
+                                            a_q, qsum, qmul);
   }
 
   f32x4 oacc[8];
