@@ -10,7 +10,8 @@ namespace saw {
 // usual serving call, which avoids a host read of the lengths) or a ragged batch most of its partitions are empty
 // and the longest sequences decide.  Here the W = p.cut partition slots of a kv head are dealt out by the lengths
 // themselves: c = the smallest number of 64-token batches (at least p.cut_min) for which sum_b ceil(nb_b / c) <= W,
-// sequence b gets P_b = ceil(nb_b / c) consecutive slots and its batches are spread evenly over them.  No wavefront streams more than c batches, and c is within a rounding of the ideal sum / W.  Every wavefront
+// sequence b gets P_b = ceil(nb_b / c) consecutive slots and its batches are spread evenly over them.  No slot streams
+// more than c batches, and c is within a rounding of the ideal sum / W.  Every wavefront
 // works this out for itself from the lengths (one load each, up to kMaxCut sequences); an empty sequence has no slot,
 // with a fused append one slot (its new token).  The wavefront of a sequence's first slot leaves (first slot, slots) for
 // the merge pass, which has thousands of blocks to work it out again in otherwise (64 x 64 rows: 10.4 against 5.1 us).
