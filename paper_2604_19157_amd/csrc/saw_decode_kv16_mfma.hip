@@ -18,8 +18,12 @@
 // The tile holds the heads' first limbs, then their second limbs (rows 0-3 and 4-7 up to four heads, 0-7 and
 // 8-15 for eight).  What bounds the kernel is HBM; the matrix cores are idle most of the time (eight products per
 // 16 KiB of cache), so eight heads and head_dim 64 - which ran on the vector ALU before, in fp32 - afford a
-// third bf16 limb (kThree): a second product per k-step whose rows 0.. hold the third limbs, added into the
-// first limbs' rows.  q~ and P then carry 24 bits, as in fp32; an fp16 cache has 22 bits in two limbs.
+// third limb (kThree): a second product per k-step.  A bf16 limb has fp32's exponents, so the third limbs' rows are
+// 0.., added into the first limbs' rows, and the three sum to the fp32 value.  An fp16 limb has not: numbers below 2^-14
+// lose bits and below 2^-25 everything, while the sum of the weights still counts them in fp32 (one dominant token 25 bits
+// above a long tail: a hundredth of the output).  So q~ is brought to 2^13 .. 2^14 per head and P is kept 2^7 higher, both by powers
+// of two that cancel exactly, the second and third limbs are held 2^12 times as large, in rows of their own, and what is
+// lost of a weight is below 2^-43 of the largest one's.
 // 16 ragged sequences of 4000-12000 tokens, 64 query / 8 kv heads of 128: 433 -> 109 us.
 //
 // PAIR = true gives this kernel the INT4 kernel's way of evening out a ragged batch when all of it
@@ -50,7 +54,8 @@ struct Shape {
   static constexpr int kRowBytes = 2 * D;                  // one token's head vector
   static constexpr int kPageBytes = 16 * kRowBytes;        // one (page, head) tile
   static constexpr int LO = (G > 4) ? 8 : 4;               // first row of the second limbs
-  static constexpr bool kThree = DT == SAW_BF16 && (G > 4 || D == 64);
+  static constexpr bool kThree = G > 4 || D == 64;
+  static constexpr bool kScaled = kThree && DT == SAW_F16; // limbs scaled by powers of two; the third ones in the second ones' rows
   static constexpr int kProw = TB + 8;                     // P row stride in 16-bit elements (8 pad)
   static constexpr int kPbufBytes = (kThree ? 3 : 2) * LO * kProw * 2;
   static constexpr int kWaveLds = 2 * kVbufBytes + kPbufBytes;
@@ -83,6 +88,15 @@ __device__ __forceinline__ void split16x3(float x, uint32_t& hi16, uint32_t& mid
   lo16 = __float_as_uint(r - __uint_as_float(mid16 << 16)) >> 16;
 }
 
+constexpr float kLow = 1.f / 4096.f;           // what the scaled second and third fp16 limbs stand for
+// x as three fp16 values: hi + (mid + lo) kLow
+__device__ __forceinline__ void split16x3_scaled(float x, uint32_t& hi16, uint32_t& mid16, uint32_t& lo16) {
+  hi16 = f32_to_f16(x);
+  const float r = (x - f16_to_f32(hi16)) * 4096.f;
+  mid16 = f32_to_f16(r);
+  lo16 = f32_to_f16(r - f16_to_f32(mid16));
+}
+
 }  // namespace kv16
 
 template <int D, int G, int DT, bool PAIR>
@@ -91,7 +105,8 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
   using Sh = Shape<D, G, DT>;
   constexpr int NP = Sh::NP, TB = Sh::TB, kRowBytes = Sh::kRowBytes, kPageBytes = Sh::kPageBytes;
   constexpr int LO = Sh::LO, kProw = Sh::kProw, kWaveLds = Sh::kWaveLds;
-  constexpr bool kThree = Sh::kThree;
+  constexpr bool kThree = Sh::kThree, kScaled = Sh::kScaled;
+  constexpr float kLift = kScaled ? 7.f : 0.f;                 // P is kept 2^kLift higher: at most 2^(kLift + kLazyTau) = 32768
   constexpr int KK = D / 32, CT = D / 16;                      // k-steps of the logits, 16-channel output tiles
   // The softmax layout.  Up to four heads: a lane holds one token of the batch and every head (32-token batches
   // leave lanes 32.. idle).  Eight heads: a lane holds four of them, for one token (32-token batches) or two.
@@ -193,10 +208,11 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
   const int nb = (t_end - t_begin + TB - 1) / TB;
 
   // ---- q~ = q sm_scale log2(e) as the logit MFMA's A operand: rows 0.. first limbs, LO.. second limbs;
-  // third limbs (kThree) in rows 0.. of a second operand whose other rows are zero ----
-  // An fp16 limb holds at most 65504: a larger q~ is scaled by a power of two first and the logits scaled back.
+  // third limbs (kThree) in rows 0.. (kScaled: LO..) of a second operand whose other rows are zero ----
+  // An fp16 limb holds at most 65504: a larger q~ is scaled by a power of two first (kScaled: every head is) and the logits
+  // scaled back.
   u32x4 a_q[KK], a_q3[kThree ? KK : 1];
-  float q_back = 1.f;
+  float q_back[kScaled ? NH : 1] = {1.f};
   {
     const bool is_lo = (row16 & LO) != 0;
     const int qhead = row16 & (LO - 1);
@@ -211,10 +227,23 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
         x[kk][j] = live ? load_elem(p.q, p.q_dtype, qbase + 32 * kk + 8 * grp + j) * p.q_scale : 0.f;
         big = fmaxf(big, fabsf(x[kk][j]));
       }
-    if (DT == SAW_F16 && __any(big > 32768.f)) {
+    if constexpr (kScaled) {
+      const float top = max_xor32(max_xor16(big));                      // of this lane's head
+      const int e = min(max(14 - __builtin_amdgcn_frexp_expf(top), -100), 100);
+#pragma unroll
+      for (int i = 0; i < NH; ++i) {
+        int of = __builtin_amdgcn_readlane(e, i);                       // (lane i: the first limbs of head i)
+        if (G > 4) of = (grp & 1) ? __builtin_amdgcn_readlane(e, 4 + i) : of;
+        q_back[i] = __builtin_ldexpf(1.f, -of);
+      }
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[kk][j] = __builtin_ldexpf(x[kk][j], e);
+    } else if (DT == SAW_F16 && __any(big > 32768.f)) {
       const float top = max_xor32(max_xor16(row_allmax(big)));          // the same in every lane
       const int e = min(max(15 - __builtin_amdgcn_frexp_expf(top), -100), 0);
-      q_back = __builtin_ldexpf(1.f, -e);
+      q_back[0] = __builtin_ldexpf(1.f, -e);
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
@@ -226,10 +255,11 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         uint32_t h16, l16, t16 = 0;
-        if (kThree) split16x3(x[kk][j], h16, l16, t16);
+        if (kScaled) split16x3_scaled(x[kk][j], h16, l16, t16);
+        else if (kThree) split16x3(x[kk][j], h16, l16, t16);
         else split16<DT>(x[kk][j], h16, l16);
         limb[j] = is_lo ? l16 : h16;
-        third[j] = is_lo ? 0u : t16;
+        third[j] = is_lo == kScaled ? t16 : 0u;
       }
       a_q[kk] = u32x4{limb[0] | (limb[1] << 16), limb[2] | (limb[3] << 16), limb[4] | (limb[5] << 16), limb[6] | (limb[7] << 16)};
       if (kThree) a_q3[kk] = u32x4{third[0] | (third[1] << 16), third[2] | (third[3] << 16), third[4] | (third[5] << 16), third[6] | (third[7] << 16)};
@@ -281,7 +311,7 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
   // 32 ks + 8g .. + 7 of row % (2 LO), of the third limbs row % LO (zeroed for the rows from LO on)
   const uint32_t pa_addr = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)pbuf + ((row16 & (2 * LO - 1)) * kProw + 8 * grp) * 2;
   const uint32_t pa3_addr = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)pbuf + ((2 * LO + (row16 & (LO - 1))) * kProw + 8 * grp) * 2;
-  const uint32_t third_rows = (row16 < LO) ? 0xffffffffu : 0u;
+  const uint32_t third_rows = (kScaled ? (row16 & LO) != 0 : row16 < LO) ? 0xffffffffu : 0u;
   const int head0 = (G > 4) ? 4 * (grp & 1) : 0;                     // first head of this lane
 
   f32x4 oacc[CT];
@@ -340,7 +370,7 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
           for (int s = 0; s < NS; ++s) {
             float hi, lo;
             swap32(dq[2 * s][i], dq[2 * s + 1][i], hi, lo);
-            v[s] = hi + lo;
+            v[s] = kScaled ? fmaf(lo, kLow, hi) : hi + lo;
           }
         } else if constexpr (NP == 4) {                        // first | second | idle | idle
           float h01, l01, h23, l23, hi, lo, junk;
@@ -348,7 +378,7 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
           swap16(dq[2][i], dq[3][i], h23, l23);
           swap32(h01, h23, hi, junk);
           swap32(l01, l23, lo, junk);
-          v[0] = hi + lo;
+          v[0] = kScaled ? fmaf(lo, kLow, hi) : hi + lo;
         } else {
           float hi, lo;
           swap16(dq[0][i], dq[1][i], hi, lo);                  // hi: rows (p0.hi, p1.hi, ..), lo: rows (p0.lo, p1.lo, ..)
@@ -356,9 +386,9 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
         }
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-          if (DT == SAW_F16) v[s] *= q_back;
+          if (DT == SAW_F16) v[s] *= q_back[kScaled ? i : 0];
           lg[s][i] = (!idle && tok0 + col[s] < t_end) ? v[s] : -INFINITY;
-          need |= lg[s][i] > m_ref[i] + kLazyTau;
+          need |= lg[s][i] > m_ref[i] + (kLazyTau + kLift);
         }
       }
       if (__any(need)) {
@@ -369,7 +399,7 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
           mx = row_allmax(mx);
           if (G <= 4) mx = max_xor16(mx);                      // eight heads: neighbouring lane groups hold other heads
           mx = max_xor32(mx);
-          const float mnew = fmaxf(m_ref[i], mx);
+          const float mnew = fmaxf(m_ref[i], mx - kLift);
           const float alpha = fast_exp2(m_ref[i] - mnew);
           lsum[i] *= alpha;
 #pragma unroll
@@ -384,7 +414,8 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
           const float pr = fast_exp2(lg[s][i] - m_ref[i]);     // 0 for masked tokens and idle lanes
           lsum[i] += pr;
           uint32_t h16, l16, t16 = 0;
-          if (kThree) split16x3(pr, h16, l16, t16);
+          if (kScaled) split16x3_scaled(pr, h16, l16, t16);
+          else if (kThree) split16x3(pr, h16, l16, t16);
           else split16<DT>(pr, h16, l16);
           if (!idle) {
             ((uint16_t*)pb)[(head0 + i) * kProw + col[s]] = (uint16_t)h16;
@@ -394,6 +425,12 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
         }
       wave_sync();
       // ---- O[row][channel] += P (rows x tokens) . V ----
+      // (kThree: a batch's sums start at zero and are added to the running ones by the vector ALU, which rounds to nearest; the
+      // matrix cores cut off what does not fit the accumulator, always in the same direction: 8000 tokens of like sign in one
+      // partition came out 6e-6 too small)
+      f32x4 tsum[kThree ? CT : 1];
+#pragma unroll
+      for (int c = 0; c < (kThree ? CT : 0); ++c) tsum[c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < TB / 32; ++ks) {
         u32x4 pa, pa3 = u32x4{0u, 0u, 0u, 0u};
@@ -412,10 +449,16 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
           const i16x4 t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS i16x4*)(vcur + voff + 4 * kRowBytes));
           const u32x2 b0 = __builtin_bit_cast(u32x2, t0), b1 = __builtin_bit_cast(u32x2, t1);
           const u32x4 bv = u32x4{b0.x, b0.y, b1.x, b1.y};
-          if (kThree) oacc[c] = mfma16<DT>(pa3, bv, oacc[c]);
-          oacc[c] = mfma16<DT>(pa, bv, oacc[c]);
+          if constexpr (kThree) {
+            tsum[c] = mfma16<DT>(pa3, bv, tsum[c]);
+            tsum[c] = mfma16<DT>(pa, bv, tsum[c]);
+          } else {
+            oacc[c] = mfma16<DT>(pa, bv, oacc[c]);
+          }
         }
       }
+#pragma unroll
+      for (int c = 0; c < (kThree ? CT : 0); ++c) oacc[c] += tsum[c];
       wave_sync();                                           // P is rewritten by the next batch
     }
   };
@@ -432,7 +475,8 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
   // oacc[c][i] of lane (grp, row16) = O[row 4 grp + i][channel 16c + row16]: up to four heads rows 0..3 (grp 0) hold
   // the first (and third) limbs' part, rows 4..7 (grp 1) the second limbs'; eight heads: grps 0, 1 and 2, 3
   const bool writer = (G > 4) ? grp < 2 : grp == 0;
-  auto both_limbs = [&](float v) { return (G > 4) ? add_xor32(v) : add_xor16(v); };
+  const float limb = kScaled && ((G > 4) ? grp >= 2 : (grp & 1)) ? kLow : 1.f;
+  auto both_limbs = [&](float v) { return (G > 4) ? add_xor32(v * limb) : add_xor16(v * limb); };
   if (PAIR && share) {
     // this wavefront's share of the long sequence as a record in its own V buffer (every read of
     // it is done and nothing is in flight): acc[G][D] un-normalised, then (max, sum) per head

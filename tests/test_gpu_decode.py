@@ -184,9 +184,9 @@ def test_kv16_comparison_path(saw, dtype, Hq, Hkv, d):
 def test_kv16_batch_edges(saw, dtype, G, Hkv, d, big):
     """Lengths around the batches (32 tokens of head_dim 128, 64 of head_dim 64), every slot that holds no
     token filled with NaN, partitions forced and automatic, pair blocks (`big`), a query beyond the fp16 range.
-    Bound: with 24 (fp16 cache: 22) bits of q and P what is left are fp32 sums: a logit of a few units carries
-    2^-23 of itself, an output likewise; 4e-6 of the largest output (two bf16 limbs, four heads of 128: 2^-16
-    each of q and P, 1e-4)."""
+    Bound: with 24 bits of q and P (two fp16 limbs, four heads of 128: 22) what is left are fp32 sums: a logit of a
+    few units carries 2^-23 of itself, an output likewise; 4e-6 of the largest output (two bf16 limbs, four heads of
+    128: 2^-16 each of q and P, 1e-4)."""
     rng = np.random.default_rng(G * d + Hkv)
     lens = [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 127, 128, 129, 300]
     if big:
