@@ -24,6 +24,8 @@
 // above a long tail: a hundredth of the output).  So q~ is brought to 2^13 .. 2^14 per head and P is kept 2^7 higher, both by powers
 // of two that cancel exactly, the second and third limbs are held 2^12 times as large, in rows of their own, and what is
 // lost of a weight is below 2^-43 of the largest one's.
+// An infinity in the cache times a limb that is zero is NaN, where fp32 gives a logit of -inf no weight and hands an infinite
+// value on: a range whose sums are not finite is worked out again in fp32 (range_fp32).
 // 16 ragged sequences of 4000-12000 tokens, 64 query / 8 kv heads of 128: 433 -> 109 us.
 //
 // PAIR = true gives this kernel the INT4 kernel's way of evening out a ragged batch when all of it
@@ -95,6 +97,60 @@ __device__ __forceinline__ void split16x3_scaled(float x, uint32_t& hi16, uint32
   const float r = (x - f16_to_f32(hi16)) * 4096.f;
   mid16 = f32_to_f16(r);
   lo16 = f32_to_f16(r - f16_to_f32(mid16));
+}
+
+// Positions [t_begin, t_end) of one (sequence, kv head) by one wavefront in plain fp32, lane = token for the logits and lane =
+// channel for the outputs: rec = un-normalised sums [G][D], then (max, sum) per head.  For caches that hold infinities or NaN.
+template <int D, int G, int DT>
+__device__ __forceinline__ void range_fp32(const DecodeParams& p, int b, int kvh, int t_begin, int t_end, int lane,
+                                                     float* qs, float* rec) {
+  constexpr int E = D / 64;
+  const int64_t pt_row = (int64_t)b * p.max_pages;
+#pragma unroll 1
+  for (int h = 0; h < G; ++h) {
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      qs[lane + 64 * e] = load_elem(p.q, p.q_dtype, ((int64_t)b * p.n_q_heads + kvh * G + h) * D + lane + 64 * e) * p.q_scale;
+    wave_sync();
+    float m = -INFINITY, l = 0.f, acc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0.f;
+#pragma unroll 1
+    for (int t0 = t_begin; t0 < t_end; t0 += 64) {
+      const int n = min(64, t_end - t0), t = t0 + min(lane, n - 1);
+      int page = p.page_table[pt_row + (t >> 4)];
+      page = (page < 0 || page >= p.num_pages) ? 0 : page;
+      const uint32_t* const k = (const uint32_t*)(p.k_codes + (((int64_t)page * p.n_kv_heads + kvh) * 16 + (t & 15)) * (2 * D));
+      float dot = 0.f;
+#pragma unroll 4
+      for (int i = 0; i < D / 2; ++i) {
+        float lo, hi;
+        widen2<DT>(k[i], lo, hi);
+        dot = fmaf(qs[2 * i], lo, dot);
+        dot = fmaf(qs[2 * i + 1], hi, dot);
+      }
+      const float lg = lane < n ? dot : -INFINITY;
+      const float mnew = fmaxf(m, max_xor32(max_xor16(row_allmax(lg))));
+      const float a = m == mnew ? 1.f : fast_exp2(m - mnew);
+      const float w = lg == -INFINITY ? 0.f : fast_exp2(lg - mnew);
+      l = fmaf(l, a, w);
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[e] *= a;
+      m = mnew;
+#pragma unroll 1
+      for (int j = 0; j < n; ++j) {
+        const float wj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), j));
+        const int64_t row = ((int64_t)__builtin_amdgcn_readlane(page, j) * p.n_kv_heads + kvh) * 16 + ((t0 + j) & 15);
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = fmaf(wj, load_elem(p.v_codes, DT, row * D + lane + 64 * e), acc[e]);
+      }
+    }
+    l = add_xor32(add_xor16(row_allsum(l)));
+#pragma unroll
+    for (int e = 0; e < E; ++e) rec[h * D + lane + 64 * e] = acc[e];
+    if (lane == 0) { rec[G * D + 2 * h] = m; rec[G * D + 2 * h + 1] = l; }
+    wave_sync();
+  }
 }
 
 }  // namespace kv16
@@ -477,6 +533,29 @@ __global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(Decod
   const bool writer = (G > 4) ? grp < 2 : grp == 0;
   const float limb = kScaled && ((G > 4) ? grp >= 2 : (grp & 1)) ? kLow : 1.f;
   auto both_limbs = [&](float v) { return (G > 4) ? add_xor32(v * limb) : add_xor16(v * limb); };
+  if constexpr (kThree) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+      bad |= !(lsum[i] < INFINITY);
+#pragma unroll
+      for (int c = 0; c < CT; ++c) bad |= !(fabsf(oacc[c][i]) < INFINITY);
+    }
+    if (__any(bad)) {
+      static_assert(G * D * 4 + G * 8 <= kVbufBytes, "a record fits a V buffer");
+      const float* const rec = (const float*)vbuf_b;
+      wave_sync();                                                    // (every read of the buffers is done)
+      range_fp32<D, G, DT>(p, b, kvh, t_begin, t_end, lane, (float*)vbuf_a, (float*)vbuf_b);
+#pragma unroll
+      for (int i = 0; i < NH; ++i) {
+        m_ref[i] = rec[G * D + 2 * (head0 + i)];
+        lsum[i] = rec[G * D + 2 * (head0 + i) + 1];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) oacc[c][i] = writer ? rec[(head0 + i) * D + 16 * c + row16] : 0.f;
+      }
+      wave_sync();
+    }
+  }
   if (PAIR && share) {
     // this wavefront's share of the long sequence as a record in its own V buffer (every read of
     // it is done and nothing is in flight): acc[G][D] un-normalised, then (max, sum) per head

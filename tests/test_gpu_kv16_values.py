@@ -82,3 +82,32 @@ def test_weights_far_below_the_largest_one(saw, dtype, G, Hkv, d, L, B):
             err = float((got - want).abs().max() / want.abs().max())
             print(f"[kv16 sink {dtype} G={G} Hkv={Hkv} d={d} L={L} gap={gap} splits={splits}] {err:.2e}", flush=True)
             assert err < (1.5e-6 if gap == 6 else 2e-6 + L / 32 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
+@pytest.mark.parametrize("B", [2, 260])
+def test_infinities_as_in_fp32(saw, dtype, G, Hkv, d, B):
+    """A key with an infinite channel gives logits of -inf, which have no weight, or of +inf, which make the row NaN; an
+    infinite value makes its channel infinite.  Every other row and channel is what it is without them."""
+    g = torch.Generator().manual_seed(G + d)
+    L, lens = 300, [300 - 41 * (b % 7) if b > 1 else 300 for b in range(B)]
+    q = torch.randn((B, Hkv * G, d), generator=g).abs() + 0.1          # (every query has the key's -inf as a logit of -inf)
+    K = [torch.randn((L, Hkv, d), generator=g).to(dtype) for _ in range(2)]
+    V = [torch.randn((L, Hkv, d), generator=g).to(dtype) for _ in range(2)]
+    K[0][7, 0, 3] = K[0][30, 0, d - 1] = K[0][L - 1, 0, 0] = float("-inf")
+    V[0][20, 0, 5], V[0][41, Hkv - 1, d - 2] = float("inf"), float("-inf")
+    V[1][9, 0, 1] = float("inf")
+    idx = [b % 2 for b in range(B)]
+    want = torch.stack([_exact(K[i][:lens[b]], V[i][:lens[b]], q[b], G) for b, i in enumerate(idx)])
+    assert not want.isnan().any()
+    for splits in (1, 0, 2):
+        got = _run(saw, [K[i] for i in idx], [V[i] for i in idx], q, lens, splits, dtype)
+        assert not got.isnan().any() and torch.equal(got.isinf(), want.isinf())
+        assert torch.equal(got[got.isinf()], want[want.isinf()])
+        err = float((got - want)[~want.isinf()].abs().max() / want[~want.isinf()].abs().max())
+        print(f"[kv16 inf {dtype} G={G} Hkv={Hkv} d={d} B={B} splits={splits}] {err:.2e}", flush=True)
+        assert err < 4e-6
+    K[1][33, Hkv - 1, 2] = float("inf")
+    got = _run(saw, [K[i] for i in idx], [V[i] for i in idx], q, lens, 0, dtype)
+    assert got[1, (Hkv - 1) * G:].isnan().all() and not got[0].isnan().any()
