@@ -156,7 +156,8 @@ __device__ __forceinline__ void range_fp32(const DecodeParams& p, int b, int kvh
 }  // namespace kv16
 
 template <int D, int G, int DT, bool PAIR>
-__global__ __launch_bounds__(PAIR ? 128 : 64) void decode_kv16_mfma_kernel(DecodeParams p) {
+__global__ __launch_bounds__(PAIR ? 128 : 64) __attribute__((amdgpu_waves_per_eu(2)))
+void decode_kv16_mfma_kernel(DecodeParams p) {
   using namespace kv16;
   using Sh = Shape<D, G, DT>;
   constexpr int NP = Sh::NP, TB = Sh::TB, kRowBytes = Sh::kRowBytes, kPageBytes = Sh::kPageBytes;
