@@ -138,8 +138,8 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
 // their pair mode evens out ragged lengths inside the launch at any occupancy, and the merge
 // pass costs more than the extra wavefronts bring (256 sequences x 4 kv heads, 2304 tokens each:
 // 61 us against 66 us with two partitions; ragged 80 against 84; at 320 items partitions win).
-// `G`: query heads per kv head (0: not known, the plan of a batch in fixed partitions is wanted).
-static bool make_plan(const saw_cache_t* c, int B, int G, int max_pages, int max_seq_len, int num_splits,
+// `G`: query heads per kv head.  `fixed`: the plan in fixed partitions that saw_decode_plan reports is wanted.
+static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pages, int max_seq_len, int num_splits,
                       bool kv16, SplitPlan* plan) {
   const int64_t cap = (int64_t)max_pages * c->page_size;
   if (cap <= 0 || cap > 0x7fffffffLL) return false;
@@ -150,7 +150,7 @@ static bool make_plan(const saw_cache_t* c, int B, int G, int max_pages, int max
   int S = num_splits;
   bool block_of_eight = false;
   if (S == 0) {
-    const int64_t items = (int64_t)B * (kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads));
+    const int64_t items = (int64_t)B * (kv16 && !fixed ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads));
     // one wavefront per (item, partition), about 8 per compute unit; a quarter more for 257 to 511 items,
     // the zone of mid-size ragged batches, where many partitions of the shorter sequences are empty
     // (48 ragged sequences x 8 kv heads: 6 partitions 37.1 us, 7: 34.4 us, 8: 34.2 us; 33 x 8: 8 partitions
@@ -197,7 +197,7 @@ static bool make_plan(const saw_cache_t* c, int B, int G, int max_pages, int max
   if (block_of_eight && plan->num_splits == 1) nw = 8;
   plan->waves_per_item = nw;
   plan->cut = plan->cut_min = plan->cut_waves = 0;
-  if (num_splits != 0 || G == 0) return true;
+  if (num_splits != 0 || fixed) return true;
   const int per_seq = kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads);
   if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G)) plan_split64(c, B, units, plan);
   else if (kv16) { if (plan->num_splits > 1) cut_plan(B, units, 2048 / per_seq, 1, plan); }
@@ -325,17 +325,16 @@ size_t saw_decode_workspace_bytes(const saw_cache_t* c, int32_t B, int32_t n_q_h
   if (!c || !shape_ok(c) || B < 1 || n_q_heads < 1 || max_seq_len < 1) return 0;
   SplitPlan plan;
   const int max_pages = (max_seq_len + c->page_size - 1) / c->page_size;
-  // (the INT4 and the 16-bit calls may choose different partition counts: enough for either)
-  SplitPlan plan16;
-  SplitPlan fixed;
+  // (the INT4 and the 16-bit calls may choose different partition counts, and either may take its fixed partitions: enough for all)
   const int G = n_q_heads % c->n_kv_heads ? 0 : n_q_heads / c->n_kv_heads;
-  if (!make_plan(c, B, G, max_pages, max_seq_len, num_splits, false, &plan) ||
-      !make_plan(c, B, G, max_pages, max_seq_len, num_splits, true, &plan16) ||
-      !make_plan(c, B, 0, max_pages, max_seq_len, num_splits, false, &fixed))
-    return 0;
-  const size_t a = plan_bytes(plan, B, n_q_heads, c->head_dim), b = plan_bytes(plan16, B, n_q_heads, c->head_dim);
-  const size_t f = plan_bytes(fixed, B, n_q_heads, c->head_dim);
-  return a > b ? (a > f ? a : f) : (b > f ? b : f);
+  size_t most = 0;
+  for (int k = 0; k < 4; ++k) {
+    const bool fixed = G == 0 || (k & 1);
+    if (!make_plan(c, B, G, fixed, max_pages, max_seq_len, num_splits, (k & 2) != 0, &plan)) return 0;
+    const size_t n = plan_bytes(plan, B, n_q_heads, c->head_dim);
+    if (n > most) most = n;
+  }
+  return most;
 }
 
 int saw_decode_plan(const saw_cache_t* c, int32_t B, int32_t max_seq_len, int32_t num_splits,
@@ -344,7 +343,7 @@ int saw_decode_plan(const saw_cache_t* c, int32_t B, int32_t max_seq_len, int32_
   if (!shape_ok(c) || B < 1 || max_seq_len < 1) return SAW_EINVAL;
   SplitPlan plan;
   const int max_pages = (max_seq_len + c->page_size - 1) / c->page_size;
-  if (!make_plan(c, B, 0, max_pages, max_seq_len, num_splits, false, &plan)) return SAW_EINVAL;
+  if (!make_plan(c, B, 0, true, max_pages, max_seq_len, num_splits, false, &plan)) return SAW_EINVAL;
   if (splits_out) *splits_out = plan.num_splits;
   if (chunk_tokens_out) *chunk_tokens_out = plan.chunk_tokens;
   return SAW_OK;
@@ -377,13 +376,18 @@ int saw_decode_order(const int32_t* seq_lens, int32_t B, int32_t max_seq_len, in
   return launch_decode_order(seq_lens, B, max_seq_len <= 0 ? 0x7fffffff : max_seq_len, order_out, (hipStream_t)stream);
 }
 
-// The plan of one call: a batch is cut by its own lengths only where the caller's workspace holds that (it does if it was
-// sized by saw_decode_workspace_bytes); one sized for the partitions of saw_decode_plan gets those.
-static bool plan_call(const saw_cache_t* c, int B, int Hq, int max_pages, int max_seq_len, int num_splits, bool kv16,
-                      size_t ws_bytes, SplitPlan* plan) {
-  if (!make_plan(c, B, Hq / c->n_kv_heads, max_pages, max_seq_len, num_splits, kv16, plan)) return false;
-  if (ws_bytes >= plan_bytes(*plan, B, Hq, c->head_dim)) return true;
-  return make_plan(c, B, 0, max_pages, max_seq_len, num_splits, kv16, plan);
+// The plan of one call.  What the fixed partitions need is what a call has to bring; what the plan for these shapes needs
+// beyond that it gets from a workspace sized by saw_decode_workspace_bytes, and a smaller one gets the fixed partitions.
+static int plan_call(const saw_cache_t* c, int B, int Hq, int max_pages, int max_seq_len, int num_splits, bool kv16,
+                     size_t ws_bytes, SplitPlan* plan) {
+  const int G = Hq % c->n_kv_heads ? 0 : Hq / c->n_kv_heads;
+  SplitPlan fixed;
+  if (!make_plan(c, B, G, true, max_pages, max_seq_len, num_splits, kv16, &fixed) ||
+      !make_plan(c, B, G, G == 0, max_pages, max_seq_len, num_splits, kv16, plan))
+    return SAW_EINVAL;
+  if (ws_bytes < plan_bytes(fixed, B, Hq, c->head_dim)) return SAW_EWORKSPACE;
+  if (ws_bytes < plan_bytes(*plan, B, Hq, c->head_dim)) *plan = fixed;
+  return SAW_OK;
 }
 
 static int decode_common(const saw_cache_t* c, bool kv16, const void* kp, const void* vp, int kv_dtype,
@@ -409,8 +413,8 @@ static int decode_common(const saw_cache_t* c, bool kv16, const void* kp, const 
   if (!kv16 && (!aligned16(c->k_meta) || !aligned16(c->v_meta))) return SAW_EINVAL;
   if (!isfinite(sm_scale)) return SAW_EINVAL;
   SplitPlan plan;
-  if (!plan_call(c, B, Hq, max_pages, max_seq_len, num_splits, kv16, ws_bytes, &plan)) return SAW_EINVAL;
-  if (ws_bytes < plan_bytes(plan, B, Hq, c->head_dim)) return SAW_EWORKSPACE;
+  const int rc = plan_call(c, B, Hq, max_pages, max_seq_len, num_splits, kv16, ws_bytes, &plan);
+  if (rc != SAW_OK) return rc;
   return run_decode(c, kv16, kp, vp, kv_dtype, q, q_dtype, B, Hq, pt, max_pages, seq_lens, sm_scale, out,
                     out_dtype, ws, plan, nullptr, nullptr, 0, hints ? hints->order : nullptr, (hipStream_t)stream);
 }
@@ -463,11 +467,10 @@ int saw_paged_decode_attn_static(const saw_cache_t* c, const void* q, int32_t q_
   if (!shape_ok(c) || B < 1 || n_q_heads < 1 || max_pages_per_seq < 1) return SAW_EINVAL;
   // the scratch the plan needs, before anything else: too large is an error of its own
   SplitPlan plan;
-  if (!plan_call(c, B, n_q_heads, max_pages_per_seq, max_seq_len, num_splits, false, (size_t)SAW_STATIC_SCRATCH_BYTES, &plan))
-    return SAW_EINVAL;
-  if (plan_bytes(plan, B, n_q_heads, c->head_dim) > (size_t)SAW_STATIC_SCRATCH_BYTES) return SAW_ESCRATCH;
+  int rc = plan_call(c, B, n_q_heads, max_pages_per_seq, max_seq_len, num_splits, false, (size_t)SAW_STATIC_SCRATCH_BYTES, &plan);
+  if (rc != SAW_OK) return rc == SAW_EWORKSPACE ? SAW_ESCRATCH : rc;
   void* ws = nullptr;
-  const int rc = static_scratch_ptr(&ws);
+  rc = static_scratch_ptr(&ws);
   if (rc != SAW_OK) return rc;
   // (nothing in the scratch has to start at zero: every partial record the merge pass reads was
   // written by the decode pass of the same call)
@@ -502,8 +505,8 @@ static int append_common(const saw_cache_t* c, const void* K_new, const void* V_
   const int64_t after = (max_seq_len <= 0 ? cap - 1 : (int64_t)max_seq_len) + 1;
   if (after > cap) return SAW_EINVAL;
   SplitPlan plan;
-  if (!plan_call(c, B, Hq, max_pages, (int)after, 0, false, ws_bytes, &plan)) return SAW_EINVAL;
-  if (ws_bytes < plan_bytes(plan, B, Hq, c->head_dim)) return SAW_EWORKSPACE;
+  const int rc = plan_call(c, B, Hq, max_pages, (int)after, 0, false, ws_bytes, &plan);
+  if (rc != SAW_OK) return rc;
   // the decode kernel stores the new token itself and attends to it from on-chip memory (with several
   // partitions per sequence one of them does, and the merge kernel follows);
   // the cached range is [0, seq_lens[b]), bounded by max_seq_len as given

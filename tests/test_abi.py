@@ -263,3 +263,29 @@ def test_native_marshalling_checks_like_the_binding(saw):
         saw.append_decode_attn(c, K[:1], K[:1].half(), q, pt, lens, out=out, workspace=ws)
     with pytest.raises(AssertionError):
         saw.append_decode_attn(c, K[:1], K[:1], q.transpose(1, 2), pt, lens, out=out, workspace=ws)
+
+
+def test_a_workspace_below_the_reported_geometry_is_refused(saw):
+    """What a call has to bring is what the fixed partitions need, [B][n_q_heads][splits][head_dim + 2] floats, also where it
+    would cut the batch by its own lengths and need less; saw_decode_workspace_bytes covers it, and num_splits = the reported
+    count asks for exactly the reported partitions."""
+    L, P = saw.lib(), ctypes.c_void_p
+    for d, n_kv, B, Hq, msl in [(128, 8, 16, 32, 4096), (128, 8, 48, 32, 9000), (64, 8, 40, 64, 3000), (64, 3, 100, 24, 2000), (128, 1, 256, 8, 6000)]:
+        st = _struct(saw, n_kv_heads=n_kv, head_dim=d, had_block=64)
+        s, c, s2, c2 = (ctypes.c_int32() for _ in range(4))
+        assert L.saw_decode_plan(ctypes.byref(st), B, msl, 0, ctypes.byref(s), ctypes.byref(c)) == 0
+        assert L.saw_decode_plan(ctypes.byref(st), B, msl, s.value, ctypes.byref(s2), ctypes.byref(c2)) == 0
+        assert (s.value, c.value) == (s2.value, c2.value) and s.value > 1
+        need = (B * Hq * s.value * (d + 2) * 4 + 15) // 16 * 16
+        assert L.saw_decode_workspace_bytes(ctypes.byref(st), B, Hq, msl, 0) >= need
+        pages = (msl + 15) // 16 + 1
+        for ws in (need - 16, need // 2 // 16 * 16):
+            assert L.saw_paged_decode_attn(ctypes.byref(st), P(16), 1, B, Hq, P(16), pages, P(16), msl, 0.0, P(16), 3, P(16), ws, 0, P(0)) == -3
+            assert L.saw_append_decode_attn(ctypes.byref(st), P(16), P(16), 1, P(16), 1, B, Hq, P(16), pages, P(16), msl - 1, 0.0, P(16), 3,
+                                            P(16), ws, P(0)) == -3
+    # the 16-bit call of 64-channel heads counts pairs of kv heads there
+    st = _struct(saw, n_kv_heads=8, head_dim=64, had_block=64)
+    need = 20 * 32 * 26 * 66 * 4                                     # 2048 / (20 x 4) = 26 partitions, of 256 tokens and more
+    assert L.saw_decode_workspace_bytes(ctypes.byref(st), 20, 32, 26 * 256, 0) >= need
+    assert L.saw_kv16_paged_decode_attn(ctypes.byref(st), P(16), P(16), 1, P(16), 1, 20, 32, P(16), 26 * 16, P(16), 26 * 256, 0.0, P(16), 3,
+                                        P(16), need - 16, 0, P(0)) == -3
