@@ -200,7 +200,9 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   if (num_splits != 0 || fixed) return true;
   const int per_seq = kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads);
   if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G)) plan_split64(c, B, units, plan);
-  else if (kv16) { if (plan->num_splits > 1) cut_plan(B, units, 2048 / per_seq, 1, plan); }
+  // (partitions of 256 tokens are the shortest a cut makes: fixed ones that are no longer have the shorter start - 8 ragged up to 8000
+  // tokens, 32 query / 8 kv heads, 42 us, 49 cut; above that 40 ragged up to 8000 161 and 131)
+  else if (kv16) { if (plan->num_splits > 1 && chunk_units > 4) cut_plan(B, units, 2048 / per_seq, 1, plan); }
   else plan_cut(B, units, per_seq, plan);
   return true;
 }

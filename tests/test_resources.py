@@ -39,6 +39,6 @@ def kernels(tmp_path_factory):
 def test_pair_blocks_of_the_16_bit_kernel_fit_twice_on_a_simd(kernels):
     """The pair rule takes up to 2048 items as resident at once: eight wavefronts on a compute unit, two on a SIMD, 256 registers
     each."""
-    pair = {n: v for n, v in kernels.items() if n.startswith("decode_kv16_mfma_kernel<") and ", true>" in n}
+    pair = {n: v for n, v in kernels.items() if n.startswith("decode_kv16_mfma_kernel<") and ", true, false>" in n}
     assert len(pair) == 16
     assert {n: v for n, v in pair.items() if v[0] > 256 or v[1]} == {}
