@@ -130,6 +130,20 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
   plan->waves_per_item = items * 4 <= kWaves ? 4 : 1;
 }
 
+// Does the vector-ALU kernel take a 16-bit call?  One query head per kv head: always.  Two: unless the batch fills the chip with
+// items several times over (above 2048 items the matrix-core kernel takes 0.60 to 1.01 of its time), or has long contexts for enough
+// items and can be cut by its own lengths (bounds above 1280 tokens, 33 to 1023 items: 0.64 to 1.04).  Elsewhere the matrix-core kernel's
+// start-up decides (2 x 2304 tokens x 8 kv heads 10.7 and 11.4 us) or the ranking of the pair blocks (257 x 1 of up to 250
+// tokens 10.9 and 16.7), and between 1024 and 2048 items the partitions that a bound of the caller's leaves empty (200 ragged x 8 up
+// to 600 tokens under a bound of 1200: 40 and 58).
+static bool takes_valu16(const saw_cache_t* c, int B, int G, int units) {
+  if (c->head_dim != 64 || G < 1 || G > 2) return false;
+  const int64_t items = (int64_t)B * c->n_kv_heads;
+  const bool many = items > 2048;
+  const bool long_ones = units > 20 && items > 32 && items < 1024 && B <= kMaxCutSequences;
+  return G == 1 || !(many || long_ones);
+}
+
 // Split-KV plan.  Partitions are whole multiples of 64 tokens so every wavefront pass
 // starts on a page boundary.  The automatic choice aims at about 2048 wavefronts (8 per compute
 // unit): one partition per sequence once the batch alone provides them, otherwise partitions of
@@ -147,10 +161,11 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   if (bound > cap) return false;
   if (num_splits < 0 || num_splits > 1024) return false;
   const int units = (bound + 63) / 64;                    // 64-token units
+  const bool valu16 = kv16 && takes_valu16(c, B, G, units);
   int S = num_splits;
   bool block_of_eight = false;
   if (S == 0) {
-    const int64_t items = (int64_t)B * (kv16 && !fixed ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads));
+    const int64_t items = (int64_t)B * (kv16 && !fixed && !valu16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads));
     // one wavefront per (item, partition), about 8 per compute unit; a quarter more for 257 to 511 items,
     // the zone of mid-size ragged batches, where many partitions of the shorter sequences are empty
     // (48 ragged sequences x 8 kv heads: 6 partitions 37.1 us, 7: 34.4 us, 8: 34.2 us; 33 x 8: 8 partitions
@@ -197,7 +212,8 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   if (block_of_eight && plan->num_splits == 1) nw = 8;
   plan->waves_per_item = nw;
   plan->cut = plan->cut_min = plan->cut_waves = 0;
-  if (num_splits != 0 || fixed) return true;
+  plan->valu16 = valu16;
+  if (num_splits != 0 || fixed || valu16) return true;
   const int per_seq = kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads);
   if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G)) plan_split64(c, B, units, plan);
   // (partitions of 256 tokens are the shortest a cut makes: fixed ones that are no longer have the shorter start - 8 ragged up to 8000

@@ -103,6 +103,7 @@ struct SplitPlan {
   int32_t cut;            // partition slots per kv head if the kernel cuts the batch by its own lengths (saw_cut.h); 0: as above
   int32_t cut_min;        // 64-token batches such a partition has at least
   int32_t cut_waves;      // wavefronts that share one
+  int32_t valu16;         // 16-bit cache: the vector-ALU kernel (saw_decode_kv16_valu.hip) takes the call
 };
 
 }  // namespace saw

@@ -68,6 +68,10 @@ inline int decode_items_per_seq(int head_dim, int n_kv_heads) {
   return (head_dim == 64 && n_kv_heads % 2 == 0) ? n_kv_heads / 2 : n_kv_heads;
 }
 
+// 16-bit-KV decode of head_dim 64 with one or two query heads per kv head (saw_decode_kv16_valu.hip), grid = (splits, kv heads,
+// batch); every partition leaves a record, also where there is only one
+int launch_decode_kv16_valu(const DecodeParams& p, int G, int kv_dtype, dim3 grid, hipStream_t st);
+
 // MFMA 16-bit-KV decode (saw_decode_kv16_mfma.hip), grid = (splits, kv heads, batch)
 int launch_decode_kv16_mfma(const DecodeParams& p, int D, int G, int kv_dtype, dim3 grid, hipStream_t st);
 

@@ -248,20 +248,22 @@ static void launch_merge(const DecodeParams& p, int B, int D, bool many, hipStre
   }
 }
 
-int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, int kv_dtype, hipStream_t st) {
+int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, bool valu16, int kv_dtype, hipStream_t st) {
   const dim3 grid = p.cut ? dim3(p.cut, p.n_kv_heads) : dim3(p.num_splits, p.n_kv_heads, B);
   const bool head_pairs = !kv16 && decode_head_pairs(D, p.n_kv_heads, G);
   if (!kv16 && (D == 128 || head_pairs)) {
     const int ny = head_pairs ? p.n_kv_heads / 2 : p.n_kv_heads;
     const dim3 mgrid = p.cut ? dim3(p.cut, ny) : dim3(p.num_splits, ny, B);
     if (launch_decode_int4_mfma(p, G, B, p.waves_per_item, head_pairs, mgrid, st) != SAW_OK) return SAW_EINVAL;
+  } else if (kv16 && valu16) {
+    if (launch_decode_kv16_valu(p, G, kv_dtype, grid, st) != SAW_OK) return SAW_EINVAL;
   } else if (kv16) {
     if (launch_decode_kv16_mfma(p, D, G, kv_dtype, grid, st) != SAW_OK) return SAW_EINVAL;
   } else {
     if (launch_decode_int4_split64(p, G, p.waves_per_item, grid, st) != SAW_OK) return SAW_EINVAL;
   }
   if (hipGetLastError() != hipSuccess) return SAW_ELAUNCH;
-  if (!p.cut && p.num_splits == 1) return SAW_OK;             // the kernel wrote the output itself
+  if (!p.cut && p.num_splits == 1 && !valu16) return SAW_OK;  // the kernel wrote the output itself
   // (a sequence has more than 16 partitions - on average, if the lengths cut the batch -: a block of 1024 threads per row;
   // otherwise a wavefront per row)
   if (p.cut) launch_merge<true>(p, B, D, p.cut / B > 16, st);
@@ -375,7 +377,7 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
   if (kv16 && !plan.cut && plan.num_splits == 1 && B <= 1024 &&
       (int64_t)B * c->n_kv_heads > 256 && (int64_t)((B + 1) / 2) * c->n_kv_heads <= 1024)
     p.pair = 2;
-  return launch_decode(p, B, c->head_dim, G, kv16, kv_dtype, st);
+  return launch_decode(p, B, c->head_dim, G, kv16, plan.valu16 != 0, kv_dtype, st);
 }
 
 }  // namespace saw
