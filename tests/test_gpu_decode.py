@@ -194,7 +194,7 @@ def test_kv16_batch_edges(saw, dtype, G, Hkv, d, big):
     B = len(lens)
     n_pages = sum((n + 15) // 16 for n in lens) + 1
     perm, o = rng.permutation(n_pages).astype(np.int32), 0
-    pt = np.zeros((B, 20), np.int32)
+    pt = np.zeros((B, 80 if big else 20), np.int32)                    # (pair blocks of these shapes need a bound above 1024 tokens)
     k16 = torch.full((n_pages, Hkv, 16, d), float("nan"), dtype=dtype)
     v16 = k16.clone()
     for b, n in enumerate(lens):
