@@ -79,17 +79,23 @@ static bool block_ok(const saw_cache_t* c) {
 //   * partitions of four wavefronts, which fold in LDS, leave the merge pass a quarter of the records, where that still gives
 //     a sequence eight partitions on average, so that rounding its share to whole ones costs little: 4 x 131072 tokens
 //     108.7 us (111.5; two wavefronts 109.7), 8 ragged up to 3000 under a loose bound 17.0 (22.8; 18.7), 8 x 8192 24.3 (26.0);
-//   * two wavefronts otherwise: 16 x 4096 24.2 (25.8), 43 of 4888-6153 x 2 heads with four 21.7 (21.0), 48 ragged up to 4096 34.3 (37.5, with a loose bound 54; four wavefronts 39.7), 32 ragged 26.7
-//     (27.8, loose 47), 200 ragged x 2 heads 35.2 (37.0);
+//   * two wavefronts otherwise: 16 x 4096 24.2 (25.8), 48 ragged up to 4096 34.3 (37.5, with a loose bound 54; four wavefronts
+//     39.7), 32 ragged 26.7 (27.8, loose 47), 200 ragged x 2 heads 35.2 (37.0).  Equal lengths under a tight bound, which fixed partitions
+//     serve best, at 43 to 63 sequences: 43 x 4096 52.0 (54.2), 48 x 4096 52.9 (62.9), 63 x 2304 39.3 (51.0), the least 43 x 1100
+//     24.4 (23.8) and 43 x 3000 under a loose bound 38.3 (37.5); 10 x 7000 27.6 (26.7), 60 x 7000 x 3 heads 43.0 (41.7);
 //   * from 512 items on one partition per sequence stays ahead or level (64 ragged 43.0 against 43.2, equal lengths 35.0
 //     against 39.8, 96 ragged 57.3 against 59.6);
-//   * the block of eight stays ahead where its wavefronts have at most four batches, or five when the blocks fill most of
-//     the chip (4 x 256 12.7 against 16.4, 4 ragged up to 1100 14.3 against 16.4, 16 ragged up to 1000 under a bound of 2000
-//     14.7 against 16.7, 32 x 2304 22.0 against 25.3; behind it 25 x 4096 40.8 against 30.1, 32 x 4096 38.4 against 36.2).
-static void plan_cut(int B, int units, int per_seq, SplitPlan* plan) {
+//   * the block of eight, which has no merge pass and follows the lengths too, stays ahead where its wavefronts have at most four
+//     batches (4 x 256 12.7 against 16.4, 16 ragged up to 1000 under a bound of 2000 14.7 against 16.7), five from 129 items on
+//     (20 x 2304 19.0 against 21.4, 16 x 2304 18.9 against 19.3 but ragged 18.3 against 17.4), eight from 192 on (24 x 2560 20.7 against
+//     23.9, 28 x 3584 26.2 against 30.3, 28 of up to 1750 under a bound of 3500 16.6 against 18.6; 28 ragged up to 3500 24.4 against
+//     23.1, 24 ragged up to 4000 26.1 against 23.0).  Pairs of 64-channel heads: five from 192 items on (56 x 3584 31.2
+//     against 33.4, but ragged 29.8 against 25.5).
+static void plan_cut(int B, int units, int per_seq, bool pairs, SplitPlan* plan) {
   const int64_t items = (int64_t)B * per_seq;
   const int per_wave = (units + 7) / 8;
-  if (plan->waves_per_item == 8 && (per_wave <= 4 || (items >= 192 && per_wave <= 5))) return;
+  const int most = pairs ? (items >= 192 ? 5 : 4) : items >= 192 ? 8 : items > 128 ? 5 : 4;
+  if (plan->waves_per_item == 8 && per_wave <= most) return;
   if (items >= 512) return;
   if (cut_plan(B, units, 512 / per_seq, 4, plan) && plan->cut >= 8 * B) return;
   plan->cut = 0;
@@ -219,7 +225,7 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   // (partitions of 256 tokens are the shortest a cut makes: fixed ones that are no longer have the shorter start - 8 ragged up to 8000
   // tokens, 32 query / 8 kv heads, 42 us, 49 cut; above that 40 ragged up to 8000 161 and 131)
   else if (kv16) { if (plan->num_splits > 1 && chunk_units > 4) cut_plan(B, units, 2048 / per_seq, 1, plan); }
-  else plan_cut(B, units, per_seq, plan);
+  else plan_cut(B, units, per_seq, c->head_dim == 64, plan);
   return true;
 }
 
