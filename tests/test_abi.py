@@ -289,3 +289,70 @@ def test_a_workspace_below_the_reported_geometry_is_refused(saw):
     assert L.saw_decode_workspace_bytes(ctypes.byref(st), 20, 32, 26 * 256, 0) >= need
     assert L.saw_kv16_paged_decode_attn(ctypes.byref(st), P(16), P(16), 1, P(16), 1, 20, 32, P(16), 26 * 16, P(16), 26 * 256, 0.0, P(16), 3,
                                         P(16), need - 16, 0, P(0)) == -3
+
+
+_FAKE = r"""
+// a library of the same entry points that waits for another Python thread
+#include <stdint.h>
+#include <time.h>
+static volatile int flag = 0;
+extern "C" void let_go() { flag = 1; }
+static int wait_for_it() {
+  for (int i = 0; i < 3000 && !flag; ++i) { timespec t = {0, 1000000}; nanosleep(&t, 0); }
+  const int seen = flag;
+  flag = 0;
+  return seen ? 0 : -77;
+}
+extern "C" {
+int saw_rotate_quant_store(...) { return wait_for_it(); }
+int saw_rotate_quant_store_layers(...) { return wait_for_it(); }
+int saw_paged_decode_attn_hinted(...) { return wait_for_it(); }
+int saw_append_decode_attn_hinted(...) { return wait_for_it(); }
+int saw_flatten_dequant(...) { return wait_for_it(); }
+int saw_kv16_paged_decode_attn(...) { return wait_for_it(); }
+// (no device here: the current stream is a stand-in too)
+struct two { int64_t a, b; };
+two _ZN3c103hip19getCurrentHIPStreamEa(signed char) { return two{0, 0}; }
+void* _ZNK3c103hip9HIPStream6streamEv(const void*) { return 0; }
+}
+"""
+_DRIVER = r"""
+import ctypes, importlib.util, sys, threading, types
+import torch
+d = sys.argv[1]
+spec = importlib.util.spec_from_file_location("_marshal", d + "/_marshal.so")
+m = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(m)
+fake = ctypes.PyDLL(d + "/libsaw.so")                                # (calls with the lock held, as a host callback into Python does)
+z = torch.zeros
+c = types.SimpleNamespace(k_codes=z(1), v_codes=z(1), k_meta=z(1), v_meta=z(1), num_pages=1, n_kv_heads=2, page_size=16, head_dim=64,
+                          had_block=1, rotate_mask=0, sign_bits=[0] * 4, dense_rot=None, k_pages=z(1), v_pages=z(1), dtype=torch.float16)
+i32 = torch.int32
+K, pt, sl, q, lens, out, ws = z(3, 2, 64).half(), z(1, 4, dtype=i32), z(3, 2, dtype=i32), z(1, 2, 64), z(1, dtype=i32), z(1, 2, 64), z(64, dtype=torch.uint8)
+calls = {"store": (c, K, K, pt, sl), "store_layers": ([c], [K], [K], pt, sl), "decode": (c, q, pt, lens, 0, 0.0, out, ws, 0, None),
+         "append": (c, K[:1], K[:1], q, pt, lens, 0, 0.0, out, ws, None), "flatten": (c, pt, 0, 0, 3, True, K, None),
+         "kv16_decode": (c, q, pt, lens, 0, 0.0, out, ws, 0)}
+for name, args in calls.items():
+    t = threading.Timer(0.05, fake.let_go)
+    t.start()
+    rc = getattr(m, name)(*args)
+    t.join()
+    print(name, rc)
+"""
+
+
+def test_the_interpreter_lock_is_free_during_a_native_call(saw, tmp_path):
+    """A launch that waits for another Python thread must not keep that thread from running (a ctypes call does not)."""
+    import shutil
+    import subprocess
+    import sys
+    from paper_2604_19157_amd import build
+    if not os.path.exists(build.MARSHAL):
+        pytest.skip("the native module is not built")
+    (tmp_path / "fake.cpp").write_text(_FAKE)
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-w", str(tmp_path / "fake.cpp"), "-o", str(tmp_path / "libsaw.so")], check=True)
+    shutil.copy(build.MARSHAL, tmp_path / "_marshal.so")
+    (tmp_path / "drive.py").write_text(_DRIVER)
+    r = subprocess.run([sys.executable, str(tmp_path / "drive.py"), str(tmp_path)], capture_output=True, text=True, timeout=120)
+    got = dict(l.split() for l in r.stdout.splitlines() if len(l.split()) == 2)
+    assert got == {n: "0" for n in ("store", "store_layers", "decode", "append", "flatten", "kv16_decode")}, r.stdout + r.stderr[-800:]
