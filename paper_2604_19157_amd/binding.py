@@ -2,13 +2,15 @@
 
 Argument marshalling only: torch supplies device memory and the current stream, every
 step of the path runs in the HIP kernels of ``libsaw.so``.  The calls of a serving loop go through
-``_marshal`` (``csrc/marshal.cpp``), which reads the tensors natively; the others through ctypes.  There is no CPU
+``_marshal`` (``csrc/marshal.cpp``), which reads the tensors natively, or, with a warning, through
+``marshal_ctypes`` where that module was not built; the others through ctypes.  There is no CPU
 fallback: if the library is missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -87,14 +89,15 @@ _native = None
 
 
 def _marshal():
-    """The native marshalling module; raises if it or the library is absent."""
+    """The native marshalling module, or the ctypes one in its place; raises if the library is absent."""
     global _native
     if _native is None:
         lib()
         try:
             from . import _marshal as m
         except ImportError as e:
-            raise RuntimeError("_marshal.so not built: build it with `python -c 'import __graft_entry__ as g; g.build()'`") from e
+            warnings.warn(f"_marshal.so cannot be loaded ({e}): calls go through ctypes and take longer on the host")
+            from . import marshal_ctypes as m
         _native = m
     return _native
 

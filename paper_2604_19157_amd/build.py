@@ -60,8 +60,9 @@ def build_library(verbose: bool = False) -> str:
     return LIB
 
 
-def build_marshal(verbose: bool = False) -> str:
-    """Host code only: a Python extension module against torch's headers, linked to ``libsaw.so`` beside it."""
+def build_marshal(verbose: bool = False) -> str | None:
+    """Host code only: a Python extension module against torch's headers, linked to ``libsaw.so`` beside it.  Where those headers or
+    Python's are not installed there is none, and the binding goes through ctypes."""
     import sysconfig
 
     import torch
@@ -69,6 +70,11 @@ def build_marshal(verbose: bool = False) -> str:
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     inc = [os.path.join(ROOT, "include"), os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
            os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    if not (os.path.exists(os.path.join(inc[-1], "Python.h")) and os.path.exists(os.path.join(inc[1], "torch"))):
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)                  # (an older one would not fit the library)
+        print("no headers of Python and torch: _marshal.so is not built", flush=True)
+        return None
     _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *["-I" + d for d in inc],
           os.path.join(HERE, "csrc", "marshal.cpp"), "-o", MARSHAL + ".tmp", "-L" + HERE, "-l:libsaw.so", "-Wl,-rpath,$ORIGIN",

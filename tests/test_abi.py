@@ -291,6 +291,35 @@ def test_a_workspace_below_the_reported_geometry_is_refused(saw):
                                         P(16), need - 16, 0, P(0)) == -3
 
 
+def test_calls_go_through_ctypes_without_the_native_module(saw, monkeypatch):
+    """A tree whose native module was not built still works, with a warning; the same arguments are refused."""
+    import sys
+    import paper_2604_19157_amd as pkg
+    monkeypatch.setattr(saw, "_native", None)
+    monkeypatch.delattr(pkg, "_marshal", raising=False)
+    monkeypatch.setitem(sys.modules, pkg.__name__ + "._marshal", None)
+    with pytest.warns(UserWarning, match="ctypes"):
+        m = saw._marshal()
+    assert m.__name__.endswith("marshal_ctypes")
+    native = {"store", "store_layers", "decode", "append", "flatten", "kv16_decode"}
+    assert native <= set(dir(m))
+    import torch
+    c = saw.Cache(4, 2, 128, 128, device="cpu")
+    K = torch.zeros((3, 2, 128), dtype=torch.bfloat16)
+    pt, sl = torch.zeros((1, 4), dtype=torch.int32), torch.zeros((3, 2), dtype=torch.int32)
+    for k, v, t, s in [(K, K.half(), pt, sl), (K, K[:2], pt, sl), (K.transpose(1, 2), K, pt, sl), (K, K, pt.long(), sl), (K, K, pt, sl[:2])]:
+        with pytest.raises(AssertionError):
+            saw.rotate_quant_store(c, k, v, t, s)
+    with pytest.raises(AssertionError):
+        saw.rotate_quant_store_layers([c, c], [K, K[:2]], [K, K[:2]], pt, sl)
+    q, lens = torch.zeros((1, 4, 128), dtype=torch.bfloat16), torch.zeros(1, dtype=torch.int32)
+    out, ws = torch.zeros((1, 4, 128)), torch.zeros(1 << 16, dtype=torch.uint8)
+    with pytest.raises(AssertionError):
+        saw.paged_decode_attn(c, q, pt, lens.long(), out=out, workspace=ws)
+    with pytest.raises(AssertionError):
+        saw.append_decode_attn(c, K[:1], K[:1], q, pt, lens, out=out, workspace=ws, order=lens.long())
+
+
 _FAKE = r"""
 // a library of the same entry points that waits for another Python thread
 #include <stdint.h>
