@@ -47,13 +47,12 @@ static bool shape_ok(const saw_cache_t* c) {
 // would not get two partitions on average (the rounding of a sequence's share to whole partitions then costs too much), and
 // for a single sequence, whose fixed partitions can request their page ids before the length is there (1 x 131072 tokens,
 // 64 query heads: 36.5 against 38.6 us).
-constexpr int kMaxCutSequences = 256;           // (as many lengths as a wavefront keeps in registers)
 static bool cut_plan(int B, int units, int slots, int waves, SplitPlan* plan) {
   constexpr int kMin = 4;
-  if (B == 1 || B > kMaxCutSequences || (int64_t)B * units >= (1 << 23)) return false;   // (counts are divided in fp32)
+  if (B == 1 || B > kMaxCut || (int64_t)B * units >= (1 << 23)) return false;   // (counts are divided in fp32)
   const int64_t most = (int64_t)B * ((units + kMin - 1) / kMin);
   int w = slots < most ? slots : (int)most;
-  if (w > 1024) w = 1024;                       // (the merge pass keeps a weight per slot of a sequence)
+  if (w > kMaxSplits) w = kMaxSplits;
   if (w < 2 * B) return false;
   plan->cut = w;
   plan->cut_min = kMin;
@@ -130,7 +129,7 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
     return;
   }
   if (cut_plan(B, units, kWaves / c->n_kv_heads, 1, plan)) return;
-  if (B > kMaxCutSequences && items < kWaves / 2) return;             // (fixed partitions, as planned)
+  if (B > kMaxCut && items < kWaves / 2) return;             // (fixed partitions, as planned)
   plan->num_splits = 1;
   plan->chunk_tokens = units * 64;
   plan->waves_per_item = items * 4 <= kWaves ? 4 : 1;
@@ -146,7 +145,7 @@ static bool takes_valu16(const saw_cache_t* c, int B, int G, int units) {
   if (c->head_dim != 64 || G < 1 || G > 2) return false;
   const int64_t items = (int64_t)B * c->n_kv_heads;
   const bool many = items > 2048;
-  const bool long_ones = units > 20 && items > 32 && items < 1024 && B <= kMaxCutSequences;
+  const bool long_ones = units > 20 && items > 32 && items < 1024 && B <= kMaxCut;
   return G == 1 || !(many || long_ones);
 }
 
@@ -165,7 +164,7 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   if (cap <= 0 || cap > 0x7fffffffLL) return false;
   int bound = (max_seq_len <= 0) ? (int)cap : max_seq_len;
   if (bound > cap) return false;
-  if (num_splits < 0 || num_splits > 1024) return false;
+  if (num_splits < 0 || num_splits > kMaxSplits) return false;
   const int units = (bound + 63) / 64;                    // 64-token units
   const bool valu16 = kv16 && takes_valu16(c, B, G, units);
   int S = num_splits;
@@ -201,7 +200,7 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
       block_of_eight = true;
     }
     if (s < 1) s = 1;
-    if (s > 1024) s = 1024;
+    if (s > kMaxSplits) s = kMaxSplits;
     S = (int)s;
   }
   if (S > units) S = units;

@@ -11,11 +11,11 @@ namespace saw {
 // and the longest sequences decide.  Here the W = p.cut partition slots of a kv head are dealt out by the lengths
 // themselves: c = the smallest number of 64-token batches (at least p.cut_min) for which sum_b ceil(nb_b / c) <= W,
 // sequence b gets P_b = ceil(nb_b / c) consecutive slots and its batches are spread evenly over them.  No slot streams
-// more than c batches, and c is within a rounding of the ideal sum / W.  Every wavefront
-// works this out for itself from the lengths (one load each, up to kMaxCut sequences); an empty sequence has no slot,
-// with a fused append one slot (its new token).  The wavefront of a sequence's first slot leaves (first slot, slots) for
+// more than c batches, and c <= max(p.cut_min, ceil(sum / (W - B))): up to twice the ideal sum / W where the host gives a batch only
+// twice as many slots as sequences (W = 128: 48 sequences of 64 batches get c = 32 against 24, a quarter of the slots stays empty).
+// Every wavefront works this out for itself from the lengths (one load each, up to kMaxCut sequences); an empty sequence has
+// no slot, with a fused append one slot (its new token).  The wavefront of a sequence's first slot leaves (first slot, slots) for
 // the merge pass, which has thousands of blocks to work it out again in otherwise (64 x 64 rows: 10.4 against 5.1 us).
-constexpr int kMaxCut = 256;
 constexpr int kCutGroups = kMaxCut / 64;
 
 struct BatchCut {

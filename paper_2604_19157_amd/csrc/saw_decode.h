@@ -5,6 +5,9 @@
 
 namespace saw {
 
+constexpr int kMaxCut = 256;        // sequences of a batch that is cut by its own lengths: as many as a wavefront keeps in registers
+constexpr int kMaxSplits = 1024;    // partitions of a sequence, or slots of a cut batch: the merge pass keeps a weight for each
+
 struct DecodeParams {
   const uint8_t* k_codes;
   const uint8_t* v_codes;

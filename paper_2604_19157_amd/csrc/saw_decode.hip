@@ -165,12 +165,12 @@ __global__ __launch_bounds__(NT) void decode_merge_kernel(DecodeParams p) {
     if (g == 0) store_elem(p.out, p.out_dtype, o_idx, 0.f);
     return;
   }
-  __shared__ float wgt[1024];
+  __shared__ float wgt[kMaxSplits];
   __shared__ __attribute__((aligned(16))) float red[NG][D];
   __shared__ float wred[2][NW];
   // Every split's (max, sum) pair is read once, by thread s (at most 1024 splits): reference
   // maximum, then weights and the denominator.
-  static_assert(NT == 1024, "a thread per split");
+  static_assert(NT == kMaxSplits, "a thread per split");
   float2 ml = make_float2(-INFINITY, 0.f);
   if (tid < ns) ml = *(const float2*)(base + (int64_t)tid * (D + 2));
   float mm = max_xor32(max_xor16(row_allmax(ml.x)));
@@ -249,6 +249,9 @@ static void launch_merge(const DecodeParams& p, int B, int D, bool many, hipStre
 }
 
 int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, bool valu16, int kv_dtype, hipStream_t st) {
+  // (the device's cut divides by p.cut - B and keeps kMaxCut lengths, the merge pass kMaxSplits weights: a plan that breaks this
+  // would turn into reads out of range)
+  if (p.cut && (p.cut < 2 * B || B > kMaxCut || p.cut > kMaxSplits)) return SAW_EINVAL;
   const dim3 grid = p.cut ? dim3(p.cut, p.n_kv_heads) : dim3(p.num_splits, p.n_kv_heads, B);
   const bool head_pairs = !kv16 && decode_head_pairs(D, p.n_kv_heads, G);
   if (!kv16 && (D == 128 || head_pairs)) {

@@ -291,6 +291,26 @@ def test_a_workspace_below_the_reported_geometry_is_refused(saw):
                                         P(16), need - 16, 0, P(0)) == -3
 
 
+class _SplitPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("num_splits", "chunk_tokens", "bound", "waves_per_item", "cut", "cut_min", "cut_waves", "valu16")]
+
+
+def test_a_cut_that_the_device_cannot_hold_is_refused_on_the_host(saw):
+    """The kernels divide by (slots - sequences) and keep 256 lengths and 1024 weights: a plan beyond that must not be launched."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("drives an internal function with pointers that stand for nothing")
+    P = ctypes.c_void_p
+    f = saw.lib()["_ZN3saw10run_decodeEPK9saw_cachebPKvS4_iS4_iiiPKiiS6_fPviS7_RKNS_9SplitPlanES4_S4_iS6_P12ihipStream_t"]
+    st = _struct(saw, n_kv_heads=8)
+    for B, cut in [(64, 64), (64, 65), (64, 127), (257, 600), (16, 1025)]:
+        plan = _SplitPlan(1, 4096, 4096, 1, cut, 4, 2, 0)
+        for kv16 in (False, True):
+            rc = f(ctypes.byref(st), ctypes.c_bool(kv16), P(16), P(16), 1, P(16), 1, B, 32, P(16), 256, P(16), ctypes.c_float(0), P(16), 3,
+                   P(16), ctypes.byref(plan), P(0), P(0), 0, P(0), P(0))
+            assert rc == -1, (B, cut, kv16)
+
+
 def test_calls_go_through_ctypes_without_the_native_module(saw, monkeypatch):
     """A tree whose native module was not built still works, with a warning; the same arguments are refused."""
     import sys
