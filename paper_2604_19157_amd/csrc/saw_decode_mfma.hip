@@ -57,8 +57,9 @@ constexpr float kLazyTau = 8.0f;               // reference max may lag the true
 // scratch, `stride` floats apart): each reads its columns of R_l instead of all 64 KiB.
 template <int G, int NH, bool HP, bool DN, int NWC>
 __device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&qraw)[2 * G], int lane,
-                                          float* __restrict__ qs, float* __restrict__ first, int stride, int wave, u32x4 (&a_q)[4],
+                                          float* __restrict__ first, int stride, int wave, u32x4 (&a_q)[4],
                                           float (&qsum)[NH], float& qmul_out) {
+  float* const qs = first + stride * wave;     // (one restrict-qualified pointer: the block's product reaches this row through it too)
   constexpr int D = 128;
   constexpr int LO = (G > 4) ? 8 : 4;
   const int row16 = lane & 15, grp = lane >> 4;
@@ -663,7 +664,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       if (p.rot_k && p.has_signs) qraw[j] = apply_sign(p.signs, HP ? lane : lane + 64 * (j & 1), qraw[j]);
     }
     // (the wavefronts of a block that share a range prepare the same query)
-    prepare_q<G, NH, HP, DN, PAIR ? 1 : NW>(p, qraw, lane, qrows, (float*)((uint8_t*)qrows - wave * kWaveLds), kWaveLds / 4, wave,
+    prepare_q<G, NH, HP, DN, PAIR ? 1 : NW>(p, qraw, lane, (float*)((uint8_t*)qrows - wave * kWaveLds), kWaveLds / 4, wave,
                                             a_q, qsum, qmul);
   }
 
