@@ -157,8 +157,9 @@ void decode_int4_split64_kernel(DecodeParams p) {
     new_wk = ((const uint32_t*)p.k_new)[e];
     new_wv = ((const uint32_t*)p.v_new)[e];
     // (a length beyond the caller's bound was clamped for the attention; storing at the clamped
-    // position would overwrite a cached token, so such a token is attended to but not stored)
-    if ((len >> 4) < p.max_pages && p.seq_lens[b] <= p.bound) new_pid = p.page_table[pt_row + (len >> 4)];
+    // position would overwrite a cached token, so such a token is attended to but not stored; nor is one of a length below
+    // zero, whose position is no position)
+    if ((len >> 4) < p.max_pages && (uint32_t)p.seq_lens[b] <= (uint32_t)p.bound) new_pid = p.page_table[pt_row + (len >> 4)];
   }
   pidv = clamp_pid(pidv);
 

@@ -172,3 +172,25 @@ def test_one_head_at_a_time_batch_edges(saw, Hq, Hkv, dtype, kw, B):
         assert parity.attn_error(o1.cpu().numpy()[rows], o2.cpu().numpy()[rows]) < 2 * limit
     if B <= 70:
         TA._case(saw, w)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 1), (3, 3), (16, 2)])
+@pytest.mark.parametrize("B", [2, 40, 300])
+def test_append_of_a_length_below_zero_stores_nothing(saw, Hq, Hkv, B):
+    """Such a sequence has no position for its token: its pages stay as they are, and the others' tokens are stored."""
+    import gpu_cases as gc
+    lens = [50 + (37 * b) % 900 for b in range(B)]
+    w = _w(batch=B, seq_lens=lens, n_q_heads=Hq, n_kv_heads=Hkv, table_width=400)
+    cache = gc.upload_cache(gc.oracle_fill(w), w, saw)
+    pt = torch.from_numpy(w.page_table).cuda()
+    sl = torch.tensor([-1 - b % 5 if b % 3 == 1 else n for b, n in enumerate(lens)], dtype=torch.int32).cuda()
+    before = cache.k_codes.clone(), cache.v_codes.clone(), cache.k_meta.clone(), cache.v_meta.clone()
+    K = torch.randn((B, Hkv, 64), device="cuda").to(w.dtype)
+    saw.append_decode_attn(cache, K, K, synth.gen_q(w).cuda(), pt, sl)
+    same = [(a == b).flatten(1).all(1).cpu() for a, b in zip(before, (cache.k_codes, cache.v_codes, cache.k_meta, cache.v_meta))]
+    for b, n in enumerate(lens):
+        mine = torch.from_numpy(w.page_table[b, : (n + 15) // 16]).long()
+        if b % 3 == 1:
+            assert all(s[mine].all() for s in same)
+        else:
+            assert not same[2][int(w.page_table[b, n // 16])]
