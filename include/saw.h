@@ -166,10 +166,11 @@ size_t saw_decode_workspace_bytes(const saw_cache_t* cache, int32_t B, int32_t n
 
 /*
  * The split-KV geometry of these arguments (host-side helper for reporting): partitions per sequence and tokens per
- * partition.  Either output may be NULL.  With num_splits 0 the decode calls may instead cut the batch into partitions
- * by its own lengths, on the device, when the workspace is as large as saw_decode_workspace_bytes says; with a
- * workspace of [B][n_q_heads][splits][head_dim + 2] float32 they use the geometry reported here.
- * (The 16-bit comparison call may choose more partitions for the same arguments;
+ * partition.  Either output may be NULL.  The decode calls need a workspace of at least
+ * [B][n_q_heads][splits][head_dim + 2] float32 (SAW_EWORKSPACE otherwise).  With num_splits 0 they may instead deal the batch
+ * out by its own lengths, on the device, or use another number of partitions, where the workspace holds that;
+ * passing the reported count as num_splits gives exactly the geometry reported here.
+ * (The 16-bit comparison call may choose, and need, more partitions for the same arguments;
  * saw_decode_workspace_bytes covers everything.)
  */
 int saw_decode_plan(const saw_cache_t* cache, int32_t B, int32_t max_seq_len, int32_t num_splits,
@@ -342,6 +343,9 @@ int saw_flatten_dequant(const saw_cache_t* cache, const int32_t* page_table,
  * pages are [num_pages][n_kv_heads][page_size][head_dim] of `dtype` (SAW_F16 | SAW_BF16),
  * no rotation, no metadata.  Same argument meaning as the INT4 calls; `cache` supplies
  * only the shape fields (pointers and had_block / rotate_mask are ignored).
+ * The arithmetic is fp32's for head_dim 64 and for eight query heads per kv head, infinities included (a logit of
+ * -inf has no weight, an infinite value makes its channel infinite); head_dim 128 with up to four query heads
+ * carries q and the weights in two 16-bit limbs, and there a row that meets an infinity is NaN.
  */
 int saw_kv16_store(const saw_cache_t* shape, void* k_pages, void* v_pages, int32_t dtype,
                    const void* K, const void* V, int64_t T, int64_t token_stride_elems,

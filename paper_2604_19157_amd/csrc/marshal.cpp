@@ -3,7 +3,7 @@
 // The checks and conversions are those of binding.py, one Python-level attribute or method at a time there (13-17 us a
 // decode call, 2.4 us per layer of a store for many layers: 77 us for 32 layers, whose kernel takes 5.6).  Here a call reads
 // the cache object's attributes, looks at the tensors directly and launches (32 layers 8.4 us in all, a small store 10.6 -> 4.5, a
-// fused step of four 256-token sequences 12.0 -> 10.8, which is its kernel's time); nothing is kept between calls, because a caller may
+// fused step of four 256-token sequences 12.3 -> 10.8); nothing is kept between calls, because a caller may
 // replace a cache's tensors at any time.  Functions return the C call's code; a failed check raises AssertionError.
 // The C call itself runs without the interpreter lock, as a ctypes call does: a launch can wait - for room in the stream's queue, for
 // its code object - and what it waits for can need another Python thread.  Everything Python is read before, and what the call's

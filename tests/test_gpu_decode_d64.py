@@ -4,7 +4,7 @@ rotation only needs h | d, so 64-channel heads are served too).
 With an even number of kv heads and at most 4 query heads per kv head the matrix-core kernel runs on
 pairs of kv heads; other shapes take the kernel of one 64-channel head at a time.  Every way the kernel hands out work is
 driven here at head_dim 64: one partition, split-KV with the merge pass, several wavefronts per
-partition, pair mode, longest-first order, and the append entry point (store launch + decode).
+partition, pair mode, longest-first order, and the append entry point.
 """
 import numpy as np
 import pytest
@@ -100,7 +100,7 @@ def test_head_pairs_fp16_cache_input(saw):
 @pytest.mark.parametrize("B,Hq,Hkv,ctx", [(3, 8, 4, (20, 150)), (70, 32, 8, (1, 120)), (150, 16, 8, (0, 200)),
                                           (2, 8, 2, (700, 900))])
 def test_append_then_attend(saw, B, Hq, Hkv, ctx):
-    """saw_append_decode_attn at head_dim 64: the store launch, then the decode over one more token."""
+    """saw_append_decode_attn at head_dim 64: what a store followed by a decode over one more token gives."""
     TA._case(saw, _w(batch=B, ctx=ctx, n_q_heads=Hq, n_kv_heads=Hkv))
 
 
@@ -115,7 +115,7 @@ def test_append_block_sizes_masks_signs(saw, h, mask, sign_seed, Hq, Hkv):
 def test_append_unmapped_page_and_odd_kv_heads(saw):
     # (the unmapped token must open a page of its own, or cached tokens would lose their page with it)
     TA._case(saw, _w(batch=3, seq_lens=[40, 64, 95], n_q_heads=8, n_kv_heads=4), unmapped=(1,))
-    TA._case(saw, _w(batch=3, ctx=(20, 150), n_q_heads=6, n_kv_heads=3))        # store launch + decode
+    TA._case(saw, _w(batch=3, ctx=(20, 150), n_q_heads=6, n_kv_heads=3))
 
 
 @pytest.mark.parametrize("Hq,Hkv,dtype,kw", [(8, 1, torch.bfloat16, {}), (3, 3, torch.float16, {"rotate_mask": 1}),
