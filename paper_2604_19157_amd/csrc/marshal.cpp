@@ -39,7 +39,8 @@ struct Ref {                                                 // an owned referen
 class Held {                                                 // references kept until the C call is back
   std::vector<PyObject*> v_;
  public:
-  Held() { v_.reserve(16); }
+  Held() { v_.reserve(8); }
+  void room(size_t n) { v_.reserve(n); }
   ~Held() { for (PyObject* o : v_) Py_DECREF(o); }
   Held(const Held&) = delete;
   Held& operator=(const Held&) = delete;
@@ -180,6 +181,7 @@ PyObject* store_layers(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     if (n < 1) { PyErr_SetString(PyExc_IndexError, "no caches"); throw Raised(); }
     check(PyTuple_GET_SIZE(ks.o) == n && PyTuple_GET_SIZE(vs.o) == n, "one K and one V per cache");
     const at::Tensor &pt = tensor(a[3]), &slots = tensor(a[4]);
+    held.room(5 * (size_t)n);
     std::vector<saw_cache_t> c(n);
     std::vector<const void*> K(n), V(n);
     const at::Tensor& K0 = tensor(PyTuple_GET_ITEM(ks.o, 0));

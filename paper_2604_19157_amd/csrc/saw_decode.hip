@@ -56,7 +56,7 @@ __device__ __forceinline__ void block_lds_matvec4(const float* x, float* y, cons
 // at once, so a row of few partitions costs one trip to memory and no block barrier (64 x 64 rows of 64 channels, 6 partitions
 // each: 5.1 us, 7.0 with a block of 256 threads per row; 48 x 32 rows of 128 channels: 4.0 and 4.6 us; 16 x 32: 3.9 and 4.0).
 // (what a trip reads in the place of records past the last one: 0 times an infinite sum would be NaN)
-__device__ const float no_record[128 + 2] = {0.f};
+__device__ const __attribute__((aligned(16))) float no_record[128 + 2] = {0.f};
 template <int D, bool CUT>
 __global__ __launch_bounds__(256) void decode_merge_rows_kernel(DecodeParams p) {
   constexpr int E = D / 64;                   // channels per lane
