@@ -129,7 +129,8 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
     return;
   }
   if (cut_plan(B, units, kWaves / c->n_kv_heads, 1, plan)) return;
-  if (B > kMaxCut && items < kWaves / 2) return;             // (fixed partitions, as planned)
+  // (fixed partitions, as planned, where a batch of long contexts or bounds is beyond what can be cut)
+  if ((B > kMaxCut || (int64_t)B * units >= (1 << 23)) && items < kWaves / 2) return;
   plan->num_splits = 1;
   plan->chunk_tokens = units * 64;
   plan->waves_per_item = items * 4 <= kWaves ? 4 : 1;
@@ -138,7 +139,7 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
 // Does the vector-ALU kernel take a 16-bit call?  One query head per kv head: always.  Two: unless the batch fills the chip with
 // items several times over (above 2048 items the matrix-core kernel takes 0.60 to 1.01 of its time), or has long contexts for enough
 // items and can be cut by its own lengths (bounds above 1280 tokens, 33 to 1023 items: 0.64 to 1.04).  Elsewhere the matrix-core kernel's
-// start-up decides (2 x 2304 tokens x 8 kv heads 10.7 and 11.4 us) or the ranking of the pair blocks (257 x 1 of up to 250
+// start-up decides (2 x 2304 tokens x 8 kv heads 11.2 and 12.0 us) or the ranking of the pair blocks (257 x 1 of up to 250
 // tokens 10.9 and 16.7), and between 1024 and 2048 items the partitions that a bound of the caller's leaves empty (200 ragged x 8 up
 // to 600 tokens under a bound of 1200: 40 and 58).
 static bool takes_valu16(const saw_cache_t* c, int B, int G, int units) {

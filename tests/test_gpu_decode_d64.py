@@ -194,3 +194,21 @@ def test_append_of_a_length_below_zero_stores_nothing(saw, Hq, Hkv, B):
             assert all(s[mine].all() for s in same)
         else:
             assert not same[2][int(w.page_table[b, n // 16])]
+
+
+def test_a_bound_beyond_what_can_be_cut_keeps_partitions(saw):
+    """256 sequences under the bound of a page table of two million tokens: more 64-token batches than the device's cut
+    counts, so the batch is split by that bound, and every partition that runs leaves a record in the workspace."""
+    import gpu_cases as gc
+    B, Hq, width = 256, 8, 131072
+    w = _w(batch=B, seq_lens=[100 + b for b in range(B)], n_q_heads=Hq, n_kv_heads=1, table_width=32)
+    cache = gc.upload_cache(gc.oracle_fill(w), w, saw)
+    pt = torch.zeros((B, width), dtype=torch.int32, device="cuda")
+    pt[:, :32] = torch.from_numpy(w.page_table).cuda()
+    sl, q = torch.from_numpy(w.seq_lens).cuda(), synth.gen_q(w).cuda()
+    ws = torch.full((saw.decode_workspace_bytes(cache, B, Hq, 16 * width),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = saw.paged_decode_attn(cache, q, pt, sl, workspace=ws)
+    assert saw.decode_plan(cache, B, 16 * width)[0] > 1 and (ws != 0xFF).any()
+    want = saw.paged_decode_attn(cache, q, pt[:, :32].contiguous(), sl, num_splits=1)
+    import parity
+    assert parity.attn_error(out.cpu().numpy(), want.cpu().numpy()) < 1e-5
