@@ -1,4 +1,4 @@
-"""What the compiler reports of the built kernels, where a launch rule counts on it.  Read from the code objects in libsaw.so."""
+"""What the compiler reports of the built kernels, where a launch rule counts on it.  Read from the build's objects."""
 import os
 import re
 import shutil
@@ -15,13 +15,13 @@ LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
 def kernels(tmp_path_factory):
     """demangled name without its arguments -> (vector registers with the accumulators, bytes of scratch per lane)"""
     tools = [os.path.join(LLVM, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf")] + [shutil.which("c++filt")]
-    if not all(t and os.path.exists(t) for t in tools) or not os.path.exists(build.LIB):
-        pytest.skip("needs the built library and the tools of ROCm's llvm")
+    objs = [os.path.join(build.HERE, "_build", os.path.basename(src) + ".o") for src in build.sources()]
+    if not all(t and os.path.exists(t) for t in tools + objs):
+        pytest.skip("needs the objects of a build and the tools of ROCm's llvm")
     objcopy, bundler, readelf, cxxfilt = tools
     d = tmp_path_factory.mktemp("co")
     got = {}
-    for src in build.sources():
-        obj = os.path.join(build.HERE, "_build", os.path.basename(src) + ".o")
+    for obj in objs:
         fat, co = str(d / "fat"), str(d / "co")
         subprocess.run([objcopy, f"--dump-section=.hip_fatbin={fat}", obj, os.devnull], check=True)
         subprocess.run([bundler, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={fat}",
