@@ -275,11 +275,159 @@ template <bool HP> constexpr int kMetaBytes = HP ? 2048 : 1024;
 // memory a transfer may be writing.
 template <int G, bool HP> constexpr int kWaveLdsG = 12 * kTileBytes + kPbufBytes + 2 * kMetaBytes<HP>;   // per wavefront: K buffer, two V buffers, P buffer, two metadata buffers
 
+// The end of a range that NW wavefronts of a block shared: their running (max, sum, accumulator) states become the partition's
+// record, or the sequence's output.  Every wavefront leaves its state in its own buffers; after one barrier a wavefront takes G / NW
+// heads (some wavefronts none, if there are more of them) and works them out from all states with two channels per lane: weights, hi + lo
+// rows, the lane sums, normalising, the way back through the rotation and the store.  What this costs is instructions of the last
+// wavefront to arrive, one every 4-5 cycles: as a fold of accumulator tiles by all, then the rest by wavefront 0, it took 2.5 us from
+// the last batch to the end of the kernel for a record (16 sequences of 4096 tokens) and 3.2 us for an output (4 of 256); now 1.7 and
+// 2.1.  Whole calls: 4 x 256 tokens 10.8 -> 9.3 us, 16 x 4096 23.7 -> 22.6, 48 ragged 34.2 -> 33.1, 1 x 131072 37.3 -> 35.3, 64 ragged
+// with a learned rotation 50.1 -> 47.9.
+template <int G, int NW, bool HP, bool DN, bool CUT>
+__device__ __forceinline__ void block_epilogue(const DecodeParams& p, uint8_t* const lds_all, int wave, int lane, int b, int kvh,
+                                               int split, const f32x4 (&oacc)[8], const float (&m_ref)[(G > 4) ? 4 : G],
+                                               const float (&lsum)[(G > 4) ? 4 : G], const float (&zs)[(G > 4) ? 4 : G]) {
+  constexpr int DH = HP ? 64 : 128;
+  constexpr int GK = HP ? G / 2 : G;
+  constexpr int NH = (G > 4) ? 4 : G;
+  constexpr int kWaveLds = kWaveLdsG<G, HP>;
+  constexpr int SW = (G > 4) ? 64 : 32;                       // lanes whose accumulator rows are heads' limbs
+  constexpr int SP = SW + 4;                                  // row pitch: the reads below touch every bank once
+  constexpr int kL = 32 * SP, kZ = kL + 64 * NH, kM = kZ + 64 * NH;
+  constexpr int HPW = (G + NW - 1) / NW;                      // heads of a wavefront
+  constexpr int kScr = 12 * kTileBytes;                       // (the P and metadata buffers: no state reaches them)
+  static_assert((kM + G) * 4 <= kScr, "a state fits in front of the P buffer");
+  static_assert(HPW * 512 <= kPbufBytes && G * 512 <= kPbufBytes + 2 * kMetaBytesOf(HP), "the heads' rows fit behind it");
+  const int row16 = lane & 15, grp = lane >> 4;
+  {
+    float* const st = (float*)(lds_all + wave * kWaveLds);
+    if (SW == 64 || lane < SW) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int i = 0; i < NH; ++i) st[(4 * c + i) * SP + lane] = oacc[c][i];
+    }
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+      st[kL + 64 * i + lane] = lsum[i];
+      st[kZ + 64 * i + lane] = zs[i];
+      if (row16 == 0 && grp < (G > 4 ? 2 : 1)) st[kM + (G > 4 ? 4 * grp : 0) + i] = m_ref[i];
+    }
+  }
+  __syncthreads();
+  const int h0 = wave * HPW;
+  const bool alone = !CUT && p.num_splits == 1;
+  if (h0 >= G && !(DN && alone)) return;                      // (wavefronts without a head help with the learned rotation)
+  float* const scr = (float*)(lds_all + wave * kWaveLds + kScr);
+  float o0[HPW], o1[HPW];
+#pragma unroll
+  for (int j = 0; j < HPW; ++j) {
+    const int h = min(h0 + j, G - 1);
+    const int i = h & (NH - 1), hg = (G > 4) ? h >> 2 : 0;    // row of the lane's four, lane group (hi limbs)
+    constexpr int LOF = (G > 4) ? 32 : 16;                    // lanes from the hi to the lo limbs' rows
+    float a[NW], mm = -INFINITY;                              // (some wavefront has a batch or the new token: the maximum is finite)
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      a[w] = ((const float*)(lds_all + w * kWaveLds))[kM + h];
+      mm = fmaxf(mm, a[w]);
+    }
+    // the lane sums: up to four heads every lane has a part of each, with eight the lanes of two groups
+    const int at = (G > 4) ? 64 * i + 32 * ((lane >> 4) & 1) + 16 * hg + row16 : 64 * i + lane;
+    const int cell = (4 * grp + i) * SP + 16 * hg + row16;    // channel `lane`; channel lane + 64 is 16 rows further
+    float l = 0.f, z = 0.f, v0 = 0.f, v1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float* const so = (const float*)(lds_all + w * kWaveLds);
+      const float aw = fast_exp2(a[w] - mm);                  // 0 for a wavefront that had no batch
+      l = fmaf(aw, so[kL + at], l);
+      z = fmaf(aw, so[kZ + at], z);
+      v0 = fmaf(aw, so[cell] + so[cell + LOF], v0);
+      v1 = fmaf(aw, so[cell + 16 * SP] + so[cell + 16 * SP + LOF], v1);
+    }
+    l = add_xor16(row_allsum(l));
+    z = add_xor16(row_allsum(z));
+    if (G <= 4) { l = add_xor32(l); z = add_xor32(z); }
+    v0 -= z;
+    v1 -= z;
+    if (!alone) {
+      // one of several partitions: (max, sum, un-normalised accumulator) for the merge kernel
+      if (h0 + j < G) {
+        const int head = kvh * G + h;
+        float* const dst = p.ws + (CUT ? (int64_t)head * p.cut + split : ((int64_t)b * p.n_q_heads + head) * p.num_splits + split) * (DH + 2);
+        if (HP) {
+          dst[2 + lane] = (h / GK) ? v1 : v0;                 // the half of the row that is this head's
+        } else {
+          dst[2 + lane] = v0;
+          dst[2 + 64 + lane] = v1;
+        }
+        if (lane == 0) { dst[0] = mm; dst[1] = l; }
+      }
+    } else {
+      const float inv = __builtin_amdgcn_rcpf(l);
+      o0[j] = v0 * inv;
+      o1[j] = v1 * inv;
+    }
+  }
+  if (!alone) return;
+  // rotate back once for V (App. A.4; a learned rotation's transpose first, App. A.3), write the output
+  float* rows = scr;
+  if constexpr (DN) {
+    if (p.dense_v) {
+      float* const x = (float*)(lds_all + kScr);
+      float* const y = (float*)(lds_all + kWaveLds + kScr);
+#pragma unroll
+      for (int j = 0; j < HPW; ++j)
+        if (h0 + j < G) {
+          x[128 * (h0 + j) + lane] = o0[j];
+          x[128 * (h0 + j) + 64 + lane] = o1[j];
+        }
+      __syncthreads();
+      block_lds_product128<G, NW>(x, y, p.dense + kDenseD * kDenseD, wave, lane);
+      __syncthreads();
+      rows = y + 128 * h0;
+    }
+  }
+  if (h0 >= G) return;
+  if (!DN || !p.dense_v) {
+#pragma unroll
+    for (int j = 0; j < HPW; ++j) {
+      rows[128 * j + lane] = o0[j];
+      rows[128 * j + 64 + lane] = o1[j];
+    }
+  }
+  wave_sync();
+  float onorm = 1.0f;
+  if (p.rot_v) {
+    wave_lds_fwht128<HPW>(rows, p.had_block, lane);
+    onorm = had_norm(p.had_block);
+  }
+#pragma unroll
+  for (int j = 0; j < HPW; ++j) {
+    const int h = h0 + j;
+    if (h >= G) break;                                        // (three heads or fewer left over: wavefront-uniform)
+    // two consecutive channels per lane: a whole row per store (head pair: the 32 lanes of the head's own half)
+    if (HP && (lane >> 5) != h / GK) continue;
+    const f32x2 o2 = *(const f32x2*)(rows + 128 * j + 2 * lane);
+    const int c = (2 * lane) & (DH - 1);
+    float o[2] = {o2.x * onorm, o2.y * onorm};
+    if (p.rot_v && p.has_signs) {                             // (o~ H_blk) diag(sigma) = o~ R^T
+      o[0] = apply_sign(p.signs, c, o[0]);
+      o[1] = apply_sign(p.signs, c + 1, o[1]);
+    }
+    const int64_t at = ((int64_t)b * p.n_q_heads + kvh * G + h) * DH + c;
+    if (p.out_dtype == SAW_F32)
+      *(f32x2*)((float*)p.out + at) = f32x2{o[0], o[1]};
+    else
+      *(uint32_t*)((uint16_t*)p.out + at) = p.out_dtype == SAW_BF16 ? f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[1]) << 16)
+                                                                   : f32_to_f16(o[0]) | ((uint32_t)f32_to_f16(o[1]) << 16);
+  }
+}
+
 // Two ways of giving wavefronts their work.
 //
 // PAIR = false: NW wavefronts share one (sequence, kv head, partition): wavefront w takes batches
 // w, w + NW, ... and the block folds their running (max, sum, accumulator) states together in LDS
-// at the end; with several partitions the result goes to the workspace for the merge kernel.
+// at the end (block_epilogue); with several partitions the result goes to the workspace for the merge kernel.
 //
 // PAIR = true (one partition per sequence, batch too large for every wavefront to need help):
 // a block of NW = 2 or 4 wavefronts owns the sequences at ranks r and B-1-r of the longest-first
@@ -837,72 +985,10 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     append_store<HP>(p, lane, nt);                         // (nobody waits for these: see append_store)
   }
 
-  // ---- fold the wavefronts of the block together (wavefront 0 keeps the result) ----
-  // Every wavefront leaves its state in its own buffers; then all of them work on the fold together:
-  // each works out the common reference maximum and the NW weights per head, combines its own slice of
-  // the accumulator tiles over all wavefronts into wavefront 0's copy, and wavefront 0 combines the
-  // sums.  Two block barriers whatever NW is, instead of one pass per wavefront by wavefront 0 alone.
-  if (!PAIR && NW > 1) {
-    static_assert(8 % NW == 0, "the accumulator tiles are dealt out evenly");
-    constexpr int CPW = 8 / NW;                             // accumulator tiles per wavefront
-    float* const st = (float*)kbuf;                         // this wavefront's state: [j][lane]
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) st[(4 * c + i) * 64 + lane] = oacc[c][i];
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      st[(32 + i) * 64 + lane] = m_ref[i];
-      st[(36 + i) * 64 + lane] = lsum[i];
-      st[(40 + i) * 64 + lane] = zs[i];
-    }
-    __syncthreads();
-    float aw[NW][NH];
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      float mw[NW];
-      float mm = -INFINITY;                                 // (some wavefront has a batch or the new token: the maximum is finite)
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        mw[w] = ((const float*)(lds_all + w * kWaveLds))[(32 + i) * 64 + lane];
-        mm = fmaxf(mm, mw[w]);
-      }
-#pragma unroll
-      for (int w = 0; w < NW; ++w) aw[w][i] = fast_exp2(mw[w] - mm);   // 0 for a wavefront that had no batch
-      m_ref[i] = mm;
-    }
-    float* const st0 = (float*)lds_all;                     // wavefront 0's state
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      const int c = wave * CPW + cc;
-#pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) v = fmaf(aw[w][i], ((const float*)(lds_all + w * kWaveLds))[(4 * c + i) * 64 + lane], v);
-        st0[(4 * c + i) * 64 + lane] = v;                   // (only this wavefront touches tile c of that copy now)
-      }
-    }
-    if (wave == 0) {
-#pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        float l = 0.f, z = 0.f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          const float* so = (const float*)(lds_all + w * kWaveLds);
-          l = fmaf(aw[w][i], so[(36 + i) * 64 + lane], l);
-          z = fmaf(aw[w][i], so[(40 + i) * 64 + lane], z);
-        }
-        lsum[i] = l;
-        zs[i] = z;
-      }
-    }
-    __syncthreads();
-    if (wave > 0) return;
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-      for (int i = 0; i < NH; ++i) oacc[c][i] = st[(4 * c + i) * 64 + lane];
+  // ---- fold the wavefronts of the block together: heads are dealt out to the wavefronts ----
+  if constexpr (!PAIR && NW > 1) {
+    block_epilogue<G, NW, HP, DN, CUT>(p, lds_all, wave, lane, b, kvh, split, oacc, m_ref, lsum, zs);
+    return;
   }
 
   // ---- epilogue: reduce the per-lane sums, fold hi + lo rows ----
@@ -922,14 +1008,13 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   }
   // (the lanes holding the lo rows sit 16 lanes above the hi rows, 32 for G = 8)
   const bool writer = (G > 4) ? (grp < 2) : (grp == 0);
-  const int emode = PAIR ? mode : (!CUT && p.num_splits == 1 ? (int)kSegAlone : (int)kSegSplitKV);
+  const int emode = PAIR ? mode : (p.num_splits == 1 ? (int)kSegAlone : (int)kSegSplitKV);
   if (emode == kSegSplitKV) {
     // one of several partitions: (max, sum, un-normalised accumulator) for the merge kernel
 #pragma unroll
     for (int i = 0; i < NH; ++i) {
       const int head = head0 + i;
-      float* dst = p.ws + (CUT ? (int64_t)(kvh * G + head) * p.cut + split
-                                 : ((int64_t)b * p.n_q_heads + kvh * G + head) * p.num_splits + split) * (DH + 2);
+      float* dst = p.ws + (((int64_t)b * p.n_q_heads + kvh * G + head) * p.num_splits + split) * (DH + 2);
       const int own = head / GK;                  // head pair: the half of the row that is this head's
 #pragma unroll
       for (int c = 0; c < 8; ++c) {

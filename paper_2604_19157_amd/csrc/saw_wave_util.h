@@ -224,21 +224,16 @@ __device__ __forceinline__ void wave_lds_matvec128(float* x, const float* __rest
   wave_sync();
 }
 
-// The same product for a block of NW (2, 4 or 8) wavefronts that all hold the same NV vectors, each in LDS of its own: wavefront
-// `wave` works out 128 / NW columns - it reads that part of M only - and writes them into every wavefront's copy (the copies are
-// `stride` floats apart, `first` is wavefront 0's): a quarter of the L2 traffic and of the arithmetic with four (64 ragged sequences
-// of 512-4096 tokens with a learned rotation, fused step: 52.5 -> 50.7 us).  The barriers wait for LDS, not for transfers in flight.  Every wavefront of
-// the block must get here.
+// r[v] = this wavefront's columns (four per lane) of x[v] M, v < NV, where NW (2, 4 or 8) wavefronts of a block take 128 / NW columns
+// each; returns the lane's first column.  Lanes whose index agrees below 128 / NW / 4 hold the same columns.
 template <int NV, int NW>
-__device__ __forceinline__ void block_lds_matvec128(float* __restrict__ first, int stride, const float* __restrict__ M, int wave, int lane) {
+__device__ __forceinline__ int block_columns128(const float* __restrict__ x, const float* __restrict__ M, int wave, int lane, f32x4 (&r)[NV]) {
   constexpr int QUADS = 32 / NW;                              // column quads of a wavefront, one per lane of a group
   constexpr int ROWS = 128 / (64 / QUADS);                    // rows of M a lane multiplies
   const int col = 4 * (QUADS * wave + (lane & (QUADS - 1))), row0 = ROWS * (lane / QUADS);
   f32x4 m[ROWS];
 #pragma unroll
   for (int u = 0; u < ROWS; ++u) m[u] = *(const f32x4*)(M + (row0 + u) * 128 + col);
-  float* const x = first + stride * wave;
-  f32x4 r[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     float acc[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
@@ -258,6 +253,19 @@ __device__ __forceinline__ void block_lds_matvec128(float* __restrict__ first, i
       r[v][c] = add_xor32(add_xor16(t));
     }
   }
+  return col;
+}
+
+// The same product for a block of NW (2, 4 or 8) wavefronts that all hold the same NV vectors, each in LDS of its own: wavefront
+// `wave` works out 128 / NW columns - it reads that part of M only - and writes them into every wavefront's copy (the copies are
+// `stride` floats apart, `first` is wavefront 0's): a quarter of the L2 traffic and of the arithmetic with four (64 ragged sequences
+// of 512-4096 tokens with a learned rotation, fused step: 52.5 -> 50.7 us).  The barriers wait for LDS, not for transfers in flight.  Every wavefront of
+// the block must get here.
+template <int NV, int NW>
+__device__ __forceinline__ void block_lds_matvec128(float* __restrict__ first, int stride, const float* __restrict__ M, int wave, int lane) {
+  constexpr int QUADS = 32 / NW;
+  f32x4 r[NV];
+  const int col = block_columns128<NV, NW>(first + stride * wave, M, wave, lane, r);
   __builtin_amdgcn_s_waitcnt(0xC07F);                         // lgkmcnt(0)
   wave_sync();
   __builtin_amdgcn_s_barrier();                               // everybody has read its copy
@@ -269,6 +277,17 @@ __device__ __forceinline__ void block_lds_matvec128(float* __restrict__ first, i
   __builtin_amdgcn_s_waitcnt(0xC07F);
   wave_sync();
   __builtin_amdgcn_s_barrier();                               // every copy is complete
+}
+// The same for NV vectors that the block holds once: y[v] = x[v] M (x and y are different memory; the caller's barriers)
+template <int NV, int NW>
+__device__ __forceinline__ void block_lds_product128(const float* __restrict__ x, float* __restrict__ y, const float* __restrict__ M, int wave, int lane) {
+  constexpr int QUADS = 32 / NW;
+  f32x4 r[NV];
+  const int col = block_columns128<NV, NW>(x, M, wave, lane, r);
+  if (lane < QUADS) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) *(f32x4*)(y + v * 128 + col) = r[v];
+  }
 }
 
 }  // namespace saw
