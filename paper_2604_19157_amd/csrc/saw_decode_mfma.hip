@@ -38,6 +38,48 @@ constexpr int kProw = 72;                      // P row stride in bf16 (64 token
 constexpr int kPbufBytes = 16 * kProw * 2;     // P as bf16 [16 rows][64 tokens]
 constexpr float kLazyTau = 8.0f;               // reference max may lag the true max by 2^8
 
+// the A operand of k-step kk from the rows of q R (in LDS, 128 floats each): see prepare_q
+template <int G>
+__device__ __forceinline__ u32x4 q_operand(const float* qs, int kk, float qmul, int row16, int grp) {
+  constexpr int LO = (G > 4) ? 8 : 4;
+  const bool is_lo = row16 >= LO;
+  const int qhead = row16 - (is_lo ? LO : 0);
+  const bool q_live = qhead < G;
+  const float* const qrow = qs + (q_live ? qhead : 0) * 128 + 32 * grp + 8 * kk;
+  const float qm = q_live ? qmul : 0.f;                      // idle rows of the tile carry zeros
+  const f32x4 va = *(const f32x4*)qrow, vb = *(const f32x4*)(qrow + 4);
+  uint32_t w[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {                              // dword j packs channels j (low half) and j + 4
+    const float x0 = va[j] * qm, x1 = vb[j] * qm;
+    const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
+    // hi limbs: the top 16 bits of both values in one byte permute
+    const uint32_t hi = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+    // lo limbs: the remainders, rounded to nearest even (v_cvt_pk_bf16_f32)
+    const f32x2 rem = f32x2{x0 - __uint_as_float(u0 & 0xffff0000u), x1 - __uint_as_float(u1 & 0xffff0000u)};
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rem, bf16x2_t));
+    w[j] = is_lo ? lo : hi;
+  }
+  return u32x4{w[0], w[1], w[2], w[3]};
+}
+template <int G, int NH>
+__device__ __forceinline__ void q_sums(const u32x4 (&a_q)[4], float (&qsum)[NH]) {
+  // qsum = sum over channels of the limbs as the matrix cores will see them: one product per k-step
+  // with a matrix of ones leaves row m's sum in every column; lane (grp, .) holds rows 4 grp + i,
+  // and the hi and lo rows of a head sit one (G <= 4) or two (G = 8) lane groups apart
+  f32x4 rs = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bf16x8 ones = as_bf16x8(u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) rs = mfma_bf16(as_bf16x8(a_q[kk]), ones, rs);
+#pragma unroll
+  for (int i = 0; i < NH; ++i) {
+    float t = rs[i];
+    if (G <= 4) t = add_xor16(t);                            // rows 0-3 (hi) + rows 4-7 (lo); groups 2, 3 hold zeros
+    qsum[i] = add_xor32(t);                                  // G = 8: rows 4 (grp & 1) + i (hi) + 8 more (lo)
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // q~ = (q H_blk) sm_scale log2(e) for the G query heads of one kv head, in the lane layout of the
 // logit MFMA's A operand, as bf16 hi and lo limbs (Sec. 4.1: the query is rotated once and
@@ -53,13 +95,9 @@ constexpr float kLazyTau = 8.0f;               // reference max may lag the true
 // the other half, so that the 128-channel products below are the 64-channel ones.
 // DN: a learned rotation R_l follows the Hadamard (App. A.3); a compile-time flag, so that the kernels
 // of caches without one carry none of its code.
-// NWC > 1: all NWC wavefronts of the block prepare the same query, and share the learned rotation's product (`first`: wavefront 0's
-// scratch, `stride` floats apart): each reads its columns of R_l instead of all 64 KiB.
-template <int G, int NH, bool HP, bool DN, int NWC>
+template <int G, int NH, bool HP, bool DN>
 __device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&qraw)[2 * G], int lane,
-                                          float* __restrict__ first, int stride, int wave, u32x4 (&a_q)[4],
-                                          float (&qsum)[NH], float& qmul_out) {
-  float* const qs = first + stride * wave;     // (one restrict-qualified pointer: the block's product reaches this row through it too)
+                                          float* __restrict__ qs, u32x4 (&a_q)[4], float (&qsum)[NH]) {
   constexpr int D = 128;
   constexpr int LO = (G > 4) ? 8 : 4;
   const int row16 = lane & 15, grp = lane >> 4;
@@ -89,49 +127,12 @@ __device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&q
   }
   // learned rotation after the Hadamard (App. A.3: q^ = (q H_b) R_l)
   if constexpr (DN) {
-    if (p.dense_k) {
-      if constexpr (NWC > 1) block_lds_matvec128<G, NWC>(first, stride, p.dense, wave, lane);
-      else wave_lds_matvec128<G>(qs, p.dense, lane);
-    }
+    if (p.dense_k) wave_lds_matvec128<G>(qs, p.dense, lane);
   }
-  const bool is_lo = row16 >= LO;
-  const int qhead = row16 - (is_lo ? LO : 0);
-  const bool q_live = qhead < G;
-  const float* qrow = qs + (q_live ? qhead : 0) * D + 32 * grp;
-  const float qm = q_live ? qmul : 0.f;                      // idle rows of the tile carry zeros
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const f32x4 va = *(const f32x4*)(qrow + 8 * kk), vb = *(const f32x4*)(qrow + 8 * kk + 4);
-    uint32_t w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {                            // dword j packs channels j (low half) and j + 4
-      const float x0 = va[j] * qm, x1 = vb[j] * qm;
-      const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
-      // hi limbs: the top 16 bits of both values in one byte permute
-      const uint32_t hi = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
-      // lo limbs: the remainders, rounded to nearest even (v_cvt_pk_bf16_f32)
-      const f32x2 rem = f32x2{x0 - __uint_as_float(u0 & 0xffff0000u), x1 - __uint_as_float(u1 & 0xffff0000u)};
-      typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-      const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rem, bf16x2_t));
-      w[j] = is_lo ? lo : hi;
-    }
-    a_q[kk] = u32x4{w[0], w[1], w[2], w[3]};
-  }
-  // qsum = sum over channels of the limbs as the matrix cores will see them: one product per k-step
-  // with a matrix of ones leaves row m's sum in every column; lane (grp, .) holds rows 4 grp + i,
-  // and the hi and lo rows of a head sit one (G <= 4) or two (G = 8) lane groups apart
-  f32x4 rs = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bf16x8 ones = as_bf16x8(u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) rs = mfma_bf16(as_bf16x8(a_q[kk]), ones, rs);
-#pragma unroll
-  for (int i = 0; i < NH; ++i) {
-    float t = rs[i];
-    if (G <= 4) t = add_xor16(t);                            // rows 0-3 (hi) + rows 4-7 (lo); groups 2, 3 hold zeros
-    qsum[i] = add_xor32(t);                                  // G = 8: rows 4 (grp & 1) + i (hi) + 8 more (lo)
-  }
+  for (int kk = 0; kk < 4; ++kk) a_q[kk] = q_operand<G>(qs, kk, qmul, row16, grp);
+  q_sums<G, NH>(a_q, qsum);
   wave_sync();
-  qmul_out = qmul;
 }
 
 constexpr int kMetaBytesOf(bool hp) { return hp ? 2048 : 1024; }   // one batch's (scale, zero) pairs: K, then V
@@ -158,40 +159,18 @@ __device__ __forceinline__ void append_store(const DecodeParams& p, int lane, co
     if ((lane & (DH / 2 - 1)) == 0) *(f32x2*)(meta + nt.vec * 2) = nt.meta[w];
   }
 }
-// The decode step's own token (fused append, Sec. 4.1's "new KV entries are rotated, quantised
-// and written" folded into the attention launch): rotate and quantise the new K and V vectors of
-// (sequence b, kv head kvh) for position L exactly as the store kernel would (Sec. 3 eqs. 1-3,
-// App. A.1; append_store writes them to the pools), and place its codes and (scale, zero) pairs in LDS as token 0 of page 0 of a
-// batch, in the layout the transfers produce.  The caller then runs one more batch in which only that
-// token is valid, so the new token goes through the very code path of the cached ones (same q~ limbs,
-// same softmax update) and nothing this launch writes to the cache is read back by it.  All of this
-// happens at the END of the range that starts the sequence, when every transfer of the range has
-// landed: at the start of a launch all wavefronts of the chip run their prologues at once and are
-// bound by instruction issue, while later the vector ALU has slack under the memory traffic.
-// One wavefront, two channels per lane.
-//   pid, wk, wv  page id of position L and this lane's two channels of the new K and V vectors,
-//         loaded by the caller at the start of the range
-//   scr   LDS scratch of 256 floats (16-byte aligned) that no buffer below overlaps
-//   kdst, vdst, mdst  the K buffer, a V buffer and its metadata buffer
-// HP: the 128 values are the new vectors of two neighbouring 64-channel kv heads (lanes 0-31 hold
-// the first head's channels), quantised and stored per head; `kvh` counts pairs.
-template <int G, bool HP, bool DN>
-__device__ __forceinline__ void append_token(const DecodeParams& p, int kvh, int lane, int L, int pid,
-                                             uint32_t wk, uint32_t wv, float* __restrict__ scr,
-                                             uint8_t* __restrict__ kdst, uint8_t* __restrict__ vdst,
-                                             uint8_t* __restrict__ mdst, NewToken& nt) {
+// The rotation of the new token's K and V vectors by one wavefront, two channels per lane (a block that prepares its range
+// together has them from there); scr: LDS scratch of 256 floats (16-byte aligned) that no transfer in flight targets.
+template <bool HP, bool DN>
+__device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, uint32_t wk, uint32_t wv, float* __restrict__ scr,
+                                             float (&x)[2][2]) {
   constexpr int D = 128;
   constexpr int DH = HP ? 64 : 128;  // channels of one head
   float* const yb = scr;            // [2][128]: K and V for the rotation
-  const int slot = L & 15;
-  nt.place = pid >= 0 && pid < p.num_pages;                  // otherwise attended to but not stored
-  const int head = HP ? 2 * kvh + (lane >> 5) : kvh;         // kv head of this lane's two channels
-  nt.vec = ((int64_t)pid * p.n_kv_heads + head) * 16 + slot;
   // K and V go through every step together (index 0: K, 1: V): one two-vector transform instead of
   // two single ones, and reductions that overlap each other
   const bool rot[2] = {p.rot_k != 0, p.rot_v != 0};                                // block Hadamard
   const bool dns[2] = {DN && p.dense_k != 0, DN && p.dense_v != 0};                  // learned rotation after it
-  float x[2][2];
   if (p.kv_new_dtype == SAW_BF16) { widen2<SAW_BF16>(wk, x[0][0], x[0][1]); widen2<SAW_BF16>(wv, x[1][0], x[1][1]); }
   else                            { widen2<SAW_F16>(wk, x[0][0], x[0][1]);  widen2<SAW_F16>(wv, x[1][0], x[1][1]); }
   if (p.has_signs) {                                         // x diag(sigma), as the store kernel does
@@ -219,6 +198,32 @@ __device__ __forceinline__ void append_token(const DecodeParams& p, int kvh, int
     x[0][0] = yk.x; x[0][1] = yk.y; x[1][0] = yv.x; x[1][1] = yv.y;
     wave_sync();
   }
+}
+// The decode step's own token (fused append, Sec. 4.1's "new KV entries are rotated, quantised
+// and written" folded into the attention launch): rotate and quantise the new K and V vectors of
+// (sequence b, kv head kvh) for position L exactly as the store kernel would (Sec. 3 eqs. 1-3,
+// App. A.1; append_store writes them to the pools), and place its codes and (scale, zero) pairs in LDS as token 0 of page 0 of a
+// batch, in the layout the transfers produce.  The caller then runs one more batch in which only that
+// token is valid, so the new token goes through the very code path of the cached ones (same q~ limbs,
+// same softmax update) and nothing this launch writes to the cache is read back by it.  All of this
+// happens at the END of the range that starts the sequence, when every transfer of the range has
+// landed: at the start of a launch all wavefronts of the chip run their prologues at once and are
+// bound by instruction issue, while later the vector ALU has slack under the memory traffic.
+// One wavefront, two channels per lane.
+//   pid, x  page id of position L and this lane's two channels of the new K and V vectors, rotated
+//   kdst, vdst, mdst  the K buffer, a V buffer and its metadata buffer
+// HP: the 128 values are the new vectors of two neighbouring 64-channel kv heads (lanes 0-31 hold
+// the first head's channels), quantised and stored per head; `kvh` counts pairs.
+template <bool HP>
+__device__ __forceinline__ void append_token(const DecodeParams& p, int kvh, int lane, int L, int pid, const float (&x)[2][2],
+                                             uint8_t* __restrict__ kdst, uint8_t* __restrict__ vdst,
+                                             uint8_t* __restrict__ mdst, NewToken& nt) {
+  constexpr int DH = HP ? 64 : 128;  // channels of one head
+  const int slot = L & 15;
+  nt.place = pid >= 0 && pid < p.num_pages;                  // otherwise attended to but not stored
+  const int head = HP ? 2 * kvh + (lane >> 5) : kvh;         // kv head of this lane's two channels
+  nt.vec = ((int64_t)pid * p.n_kv_heads + head) * 16 + slot;
+  const bool rot[2] = {p.rot_k != 0, p.rot_v != 0};                                // block Hadamard
   // min and max over each head's values (128: all lanes, 64: half of them): reductions of
   // (max, -min) pairs, rows first (DPP)
   float mx[2], nmn[2];
@@ -275,6 +280,104 @@ template <bool HP> constexpr int kMetaBytes = HP ? 2048 : 1024;
 // memory a transfer may be writing.
 template <int G, bool HP> constexpr int kWaveLdsG = 12 * kTileBytes + kPbufBytes + 2 * kMetaBytes<HP>;   // per wavefront: K buffer, two V buffers, P buffer, two metadata buffers
 
+// The start of a range that NW wavefronts of a block share, where they prepare it together (kBlockPrep): every wavefront rotates its
+// share of the G query rows and of the new token's K and V vectors, a learned rotation's product is the block's, and the A operands are
+// converted once (four wavefronts a k-step each) and handed out.  When each wavefront of a block of eight prepared all of it for itself that
+// was 1.6 us of instructions, two wavefronts a SIMD, in front of the first batch.  With a learned rotation the new token costs its
+// rows in a product that runs anyway, instead of one wavefront's product at the end of the longest range.
+// Blocks of two only do this with a learned rotation: theirs is hidden by the first transfers (16 x 4096 tokens).
+// (fused steps, each wavefront for itself and then together: 4 x 256 tokens 8.9 -> 8.6 us, 64 ragged with a learned rotation 47.8 -> 46.3.)
+template <int NW, bool PAIR, bool HP, bool DN>
+constexpr bool kBlockPrep = !PAIR && (NW == 8 || (NW == 4 && !HP) || (DN && NW > 1));
+// LDS for it beside the wavefronts' buffers, which transfers may target: the rotated rows, then the A operands
+template <int G, int NW, bool PAIR, bool HP, bool DN>
+constexpr int kPrepBytes = kBlockPrep<NW, PAIR, HP, DN> ? (G + 2) * 512 + (NW >= 4 ? 4096 : 0) : 0;
+
+// This wavefront's vectors (wave, wave + NW, ...: below G a query row, then K, then V): elements `lane` and `lane + 64`, as loaded.
+template <int G, int NW, bool HP>
+__device__ __forceinline__ void block_vectors_load(const DecodeParams& p, int b, int kvh, bool with_new, int wave, int lane,
+                                                   uint32_t (&bits)[(G + 1 + NW) / NW][2]) {
+  constexpr int DH = HP ? 64 : 128;
+#pragma unroll
+  for (int u = 0; u < (G + 1 + NW) / NW; ++u) {
+    const int v = wave + NW * u;                             // (wavefront-uniform)
+    bits[u][0] = bits[u][1] = 0u;
+    if (v < G) {
+      const int64_t at = ((int64_t)b * p.n_q_heads + kvh * G + v) * DH + lane;
+      if (p.q_dtype == SAW_F32) {
+        bits[u][0] = ((const uint32_t*)p.q)[at];
+        if (!HP) bits[u][1] = ((const uint32_t*)p.q)[at + 64];
+      } else {
+        bits[u][0] = ((const uint16_t*)p.q)[at];
+        if (!HP) bits[u][1] = ((const uint16_t*)p.q)[at + 64];
+      }
+    } else if (v < G + 2 && with_new) {
+      // (the block's new K|V values are 128 contiguous elements: one head, or a pair of 64-channel heads)
+      const uint16_t* const src = (const uint16_t*)(v == G ? p.k_new : p.v_new) + (int64_t)b * p.n_kv_heads * DH + (int64_t)kvh * 128 + lane;
+      bits[u][0] = src[0];
+      bits[u][1] = src[64];
+    }
+  }
+}
+//   x, y  rows of 128 floats; x is where the vectors are rotated (without a learned rotation it is y), y holds the result; no
+//         transfer in flight may target either, and y stays until the range ends
+//   aq    the A operands, [4][64] of 16 bytes
+template <int G, int NW, int NH, bool HP, bool DN>
+__device__ __forceinline__ void block_prepare(const DecodeParams& p, const uint32_t (&bits)[(G + 1 + NW) / NW][2], bool with_new, int wave,
+                                              int lane, float* __restrict__ x, float* __restrict__ y, u32x4* __restrict__ aq,
+                                              const BlockColumns<DN ? NW : 8>& cols, u32x4 (&a_q)[4], float (&qsum)[NH]) {
+  float* const in = DN ? x : y;
+#pragma unroll
+  for (int u = 0; u < (G + 1 + NW) / NW; ++u) {
+    const int v = wave + NW * u;
+    if (v < G || (v < G + 2 && with_new)) {
+      const int dt = v < G ? p.q_dtype : p.kv_new_dtype;
+      const bool rot = v == G + 1 ? p.rot_v : p.rot_k;
+      float e[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        e[k] = dt == SAW_F32 ? __uint_as_float(bits[u][k]) : dt == SAW_BF16 ? __uint_as_float(bits[u][k] << 16)
+                                                                             : f16_to_f32(bits[u][k] & 0xffffu);
+        if (rot && p.has_signs) e[k] = apply_sign(p.signs, HP ? lane : lane + 64 * k, e[k]);      // x diag(sigma) first
+      }
+      // (head pair: a query row has its 64 values in the half of its own kv head and zeros in the other)
+      const bool second = HP && v < G && v >= G / 2;
+      in[128 * v + lane] = second ? 0.f : e[0];
+      in[128 * v + 64 + lane] = second ? e[0] : e[1];
+      wave_sync();
+      if (rot) wave_lds_fwht128<1>(in + 128 * v, p.had_block, lane);
+    }
+  }
+  lds_barrier();
+  if constexpr (DN) {                                        // learned rotation after the Hadamard (App. A.3)
+    if (p.dense_k) {
+      block_columns_product<G, NW>(in, y, cols, lane);
+      if (with_new) block_columns_product<1, NW>(in + 128 * G, y + 128 * G, cols, lane);
+    } else {
+      for (int i = 64 * wave + lane; i < 128 * (G + 1); i += 64 * NW) y[i] = in[i];
+    }
+    if (p.dense_v && with_new) {
+      block_columns_product<1, NW>(in + 128 * (G + 1), y + 128 * (G + 1), cols, lane);
+    } else {
+      if (wave < 2) y[128 * (G + 1) + 64 * wave + lane] = in[128 * (G + 1) + 64 * wave + lane];
+    }
+    lds_barrier();
+  }
+  const int row16 = lane & 15, grp = lane >> 4;
+  const float qmul = p.rot_k ? p.q_scale * had_norm(p.had_block) : p.q_scale;
+  if constexpr (NW >= 4) {
+    if (wave < 4) aq[64 * wave + lane] = q_operand<G>(y, wave, qmul, row16, grp);
+    lds_barrier();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) a_q[kk] = aq[64 * kk + lane];
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) a_q[kk] = q_operand<G>(y, kk, qmul, row16, grp);
+  }
+  q_sums<G, NH>(a_q, qsum);
+  wave_sync();
+}
+
 // The end of a range that NW wavefronts of a block shared: their running (max, sum, accumulator) states become the partition's
 // record, or the sequence's output.  Every wavefront leaves its state in its own buffers; after one barrier a wavefront takes G / NW
 // heads (some wavefronts none, if there are more of them) and works them out from all states with two channels per lane: weights, hi + lo
@@ -299,6 +402,11 @@ __device__ __forceinline__ void block_epilogue(const DecodeParams& p, uint8_t* c
   static_assert((kM + G) * 4 <= kScr, "a state fits in front of the P buffer");
   static_assert(HPW * 512 <= kPbufBytes && G * 512 <= kPbufBytes + 2 * kMetaBytesOf(HP), "the heads' rows fit behind it");
   const int row16 = lane & 15, grp = lane >> 4;
+  const bool alone = !CUT && p.num_splits == 1;
+  BlockColumns<DN ? NW : 8> cols;                             // (requested now: the exchange of the states hides the trip to L2)
+  if constexpr (DN) {
+    if (alone && p.dense_v) block_columns_load<NW>(p.dense + kDenseD * kDenseD, wave, lane, cols);
+  }
   {
     float* const st = (float*)(lds_all + wave * kWaveLds);
     if (SW == 64 || lane < SW) {
@@ -316,7 +424,6 @@ __device__ __forceinline__ void block_epilogue(const DecodeParams& p, uint8_t* c
   }
   __syncthreads();
   const int h0 = wave * HPW;
-  const bool alone = !CUT && p.num_splits == 1;
   if (h0 >= G && !(DN && alone)) return;                      // (wavefronts without a head help with the learned rotation)
   float* const scr = (float*)(lds_all + wave * kWaveLds + kScr);
   float o0[HPW], o1[HPW];
@@ -382,7 +489,7 @@ __device__ __forceinline__ void block_epilogue(const DecodeParams& p, uint8_t* c
           x[128 * (h0 + j) + 64 + lane] = o1[j];
         }
       __syncthreads();
-      block_lds_product128<G, NW>(x, y, p.dense + kDenseD * kDenseD, wave, lane);
+      block_columns_product<G, NW>(x, y, cols, lane);
       __syncthreads();
       rows = y + 128 * h0;
     }
@@ -501,7 +608,8 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // needs a slot outside the wavefront's own buffers)
   constexpr bool kSpare = PAIR && (NW > 2 || K > 2);
   constexpr int kSpareBytes = kSpare ? (K - 1) * kRecFloats * 4 : 0;
-  __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * kWaveLds + 16 + kSpareBytes];
+  constexpr bool kBP = kBlockPrep<NW, PAIR, HP, DN>;
+  __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * kWaveLds + 16 + kSpareBytes + kPrepBytes<G, NW, PAIR, HP, DN>];
   uint8_t* const kbuf = lds_all + wave * kWaveLds;
   uint8_t* const vbuf_a = kbuf + 4 * kTileBytes;
   uint8_t* const vbuf_b = kbuf + 8 * kTileBytes;
@@ -699,9 +807,14 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     }
   }
   SAW_LOAD_PIDS(pidv_nx, pg_first + 64)
-  // this lane's share of the G query vectors (element lane + 64 j), issued ahead of the code transfers
-  uint32_t qbits[2 * G];
-  {
+  // this lane's share of the G query vectors (element lane + 64 j), issued ahead of the code transfers; a block that prepares
+  // its range together: of this wavefront's share of them and of the new token's vectors
+  uint32_t qbits[kBP ? 1 : 2 * G];
+  uint32_t vbits[kBP ? (G + 1 + NW) / NW : 1][2];
+  const bool block_new = p.append && (CUT ? cut_new : t_begin == 0);     // some wavefront of the block takes the new token
+  if constexpr (kBP) {
+    block_vectors_load<G, NW, HP>(p, b, kvh, block_new, wave, lane, vbits);
+  } else {
     // (the block's G query heads are contiguous: G x 128 values, or G x 64 for a head pair)
     constexpr int NQ = HP ? G : 2 * G;
     const int64_t qoff = ((int64_t)b * p.n_q_heads + kvh * G) * DH + lane;
@@ -718,14 +831,16 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // several share the range); of a batch cut by its lengths the one that ends it, there the wavefront with the fewest
   // batches; so in a block of eight, where over a short context that wavefront has none and works on the token while the others
   // stream (4 sequences of 256 tokens: the step 9.3 -> 9.1 us); its inputs are requested here, with the query
-  const bool takes_new = p.append && (CUT ? cut_new && wave == NW - 1 : t_begin == 0 && first_batch == (NW == 8 ? NW - 1 : 0));
+  const bool takes_new = block_new && (PAIR || wave == (CUT || NW == 8 ? NW - 1 : 0));
   uint32_t new_wk = 0, new_wv = 0;
   int new_pid = -1;
   if (takes_new) {
     // (the block's new K|V values are 128 contiguous elements: one head, or a pair of 64-channel heads)
-    const int64_t e = ((int64_t)b * p.n_kv_heads * DH + (int64_t)kvh * D) / 2 + lane;
-    new_wk = ((const uint32_t*)p.k_new)[e];
-    new_wv = ((const uint32_t*)p.v_new)[e];
+    if (!kBP) {
+      const int64_t e = ((int64_t)b * p.n_kv_heads * DH + (int64_t)kvh * D) / 2 + lane;
+      new_wk = ((const uint32_t*)p.k_new)[e];
+      new_wv = ((const uint32_t*)p.v_new)[e];
+    }
     // (a length beyond the caller's bound was clamped for the attention; storing at the clamped
     // position would overwrite a cached token, so such a token is attended to but not stored)
     if ((seq_len_b >> 4) < p.max_pages && p.seq_lens[b] <= p.bound) new_pid = p.page_table[pt_row + (seq_len_b >> 4)];
@@ -790,6 +905,12 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // restrict-qualified pointers: the compiler then orders none of its LDS accesses behind them.
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0)
+  BlockColumns<DN && kBP ? NW : 8> cols;
+  if constexpr (DN && kBP) {
+    // (in front of the transfers: loads return in order, and behind them R_l's 64 KiB from L2 would wait for HBM)
+    if (p.dense_k || p.dense_v) block_columns_load<NW>(p.dense, wave, lane, cols);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   if (first_batch < nb) {
     SAW_FETCH_V(first_batch, vbuf_a, mbuf_a)
     SAW_FETCH_K(first_batch, kbuf)
@@ -799,8 +920,21 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   float* const qrows = (G <= 4) ? (float*)pbuf : (float*)vbuf_b;
   u32x4 a_q[4];
   float qsum[NH];
-  float qmul;
-  {
+  float new_x[2][2] = {{0.f, 0.f}, {0.f, 0.f}};               // the new token's K and V channels, rotated
+  if constexpr (kBP) {
+    float* const rows = (float*)(lds_all + NW * kWaveLds + 16 + kSpareBytes);
+    // (rows to be multiplied: wavefront 0's second V buffer and what follows, which nobody writes to before the barrier behind the product)
+    block_prepare<G, NW, NH, HP, DN>(p, vbits, block_new, wave, lane, (float*)(lds_all + 8 * kTileBytes), rows,
+                                     (u32x4*)(rows + 128 * (G + 2)), cols, a_q, qsum);
+    if (takes_new) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const f32x2 v = *(const f32x2*)(rows + 128 * (G + t) + 2 * lane);
+        new_x[t][0] = v.x;
+        new_x[t][1] = v.y;
+      }
+    }
+  } else   {
     float qraw[2 * G];
     const bool q_is_f32 = p.q_dtype == SAW_F32, q_is_bf16 = p.q_dtype == SAW_BF16;
 #pragma unroll
@@ -812,9 +946,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       // randomised Hadamard: q diag(sigma) first (element lane + 64 j is channel lane + 64 (j & 1))
       if (p.rot_k && p.has_signs) qraw[j] = apply_sign(p.signs, HP ? lane : lane + 64 * (j & 1), qraw[j]);
     }
-    // (the wavefronts of a block that share a range prepare the same query)
-    prepare_q<G, NH, HP, DN, PAIR ? 1 : NW>(p, qraw, lane, (float*)((uint8_t*)qrows - wave * kWaveLds), kWaveLds / 4, wave,
-                                            a_q, qsum, qmul);
+    prepare_q<G, NH, HP, DN>(p, qraw, lane, qrows, a_q, qsum);
   }
 
   f32x4 oacc[8];
@@ -981,7 +1113,8 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // so nothing is requested).
   if (takes_new) {
     NewToken nt;
-    append_token<G, HP, DN>(p, kvh, lane, seq_len_b, new_pid, new_wk, new_wv, (float*)vbuf_b, kbuf, vbuf_a, mbuf_a, nt);
+    if (!kBP) rotate_token<HP, DN>(p, lane, new_wk, new_wv, (float*)vbuf_b, new_x);
+    append_token<HP>(p, kvh, lane, seq_len_b, new_pid, new_x, kbuf, vbuf_a, mbuf_a, nt);
     body(0x3fffffff, t_end - 1, kbuf, vbuf_a, vbuf_b, pbuf, mbuf_a, mbuf_b);
     append_store<HP>(p, lane, nt);                         // (nobody waits for these: see append_store)
   }

@@ -224,70 +224,56 @@ __device__ __forceinline__ void wave_lds_matvec128(float* x, const float* __rest
   wave_sync();
 }
 
-// r[v] = this wavefront's columns (four per lane) of x[v] M, v < NV, where NW (2, 4 or 8) wavefronts of a block take 128 / NW columns
-// each; returns the lane's first column.  Lanes whose index agrees below 128 / NW / 4 hold the same columns.
-template <int NV, int NW>
-__device__ __forceinline__ int block_columns128(const float* __restrict__ x, const float* __restrict__ M, int wave, int lane, f32x4 (&r)[NV]) {
-  constexpr int QUADS = 32 / NW;                              // column quads of a wavefront, one per lane of a group
-  constexpr int ROWS = 128 / (64 / QUADS);                    // rows of M a lane multiplies
-  const int col = 4 * (QUADS * wave + (lane & (QUADS - 1))), row0 = ROWS * (lane / QUADS);
+// Products x[v] M of vectors in LDS by a block of NW (2, 4 or 8) wavefronts: wavefront `wave` takes 128 / NW columns, so that the
+// block reads M (64 KiB, from L2) once and not once per wavefront.  A lane's part of M, four columns of ROWS rows, is requested by
+// block_columns_load: early, in front of transfers from HBM, because loads return in order.
+template <int NW>
+struct BlockColumns {
+  static constexpr int QUADS = 32 / NW;                       // column quads of a wavefront, one per lane of a group
+  static constexpr int ROWS = 128 / (64 / QUADS);             // rows of M a lane multiplies
   f32x4 m[ROWS];
+  int col, row0;
+};
+template <int NW>
+__device__ __forceinline__ void block_columns_load(const float* __restrict__ M, int wave, int lane, BlockColumns<NW>& k) {
+  using K = BlockColumns<NW>;
+  k.col = 4 * (K::QUADS * wave + (lane & (K::QUADS - 1)));
+  k.row0 = K::ROWS * (lane / K::QUADS);
 #pragma unroll
-  for (int u = 0; u < ROWS; ++u) m[u] = *(const f32x4*)(M + (row0 + u) * 128 + col);
+  for (int u = 0; u < K::ROWS; ++u) k.m[u] = *(const f32x4*)(M + (k.row0 + u) * 128 + k.col);
+}
+// y[v] = x[v] M in this wavefront's columns, v < NV (x and y are different memory; the caller's barriers)
+template <int NV, int NW>
+__device__ __forceinline__ void block_columns_product(const float* __restrict__ x, float* __restrict__ y, const BlockColumns<NW>& k, int lane) {
+  using K = BlockColumns<NW>;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     float acc[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int u4 = 0; u4 < ROWS / 4; ++u4) {
-      const f32x4 xv = *(const f32x4*)(x + v * 128 + row0 + 4 * u4);
+    for (int u4 = 0; u4 < K::ROWS / 4; ++u4) {
+      const f32x4 xv = *(const f32x4*)(x + v * 128 + k.row0 + 4 * u4);
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[k & 1][c] = fmaf(xv[k], m[4 * u4 + k][c], acc[k & 1][c]);
+        for (int c = 0; c < 4; ++c) acc[e & 1][c] = fmaf(xv[e], k.m[4 * u4 + e][c], acc[e & 1][c]);
     }
+    f32x4 r;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       float t = acc[0][c] + acc[1][c];
-      if (QUADS <= 4) t += dpp_f<0x124>(t);                   // row_ror:4, 8: the row's other lanes of the same columns
-      if (QUADS <= 8) t += dpp_f<0x128>(t);
-      r[v][c] = add_xor32(add_xor16(t));
+      if (K::QUADS <= 4) t += dpp_f<0x124>(t);                // row_ror:4, 8: the row's other lanes of the same columns
+      if (K::QUADS <= 8) t += dpp_f<0x128>(t);
+      r[c] = add_xor32(add_xor16(t));
     }
+    if (lane < K::QUADS) *(f32x4*)(y + v * 128 + k.col) = r;
   }
-  return col;
 }
-
-// The same product for a block of NW (2, 4 or 8) wavefronts that all hold the same NV vectors, each in LDS of its own: wavefront
-// `wave` works out 128 / NW columns - it reads that part of M only - and writes them into every wavefront's copy (the copies are
-// `stride` floats apart, `first` is wavefront 0's): a quarter of the L2 traffic and of the arithmetic with four (64 ragged sequences
-// of 512-4096 tokens with a learned rotation, fused step: 52.5 -> 50.7 us).  The barriers wait for LDS, not for transfers in flight.  Every wavefront of
-// the block must get here.
-template <int NV, int NW>
-__device__ __forceinline__ void block_lds_matvec128(float* __restrict__ first, int stride, const float* __restrict__ M, int wave, int lane) {
-  constexpr int QUADS = 32 / NW;
-  f32x4 r[NV];
-  const int col = block_columns128<NV, NW>(first + stride * wave, M, wave, lane, r);
+// a barrier that waits for this wavefront's LDS accesses only, not for transfers in flight
+__device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_waitcnt(0xC07F);                         // lgkmcnt(0)
   wave_sync();
-  __builtin_amdgcn_s_barrier();                               // everybody has read its copy
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-      if (lane / QUADS == w % (64 / QUADS)) *(f32x4*)(first + stride * w + v * 128 + col) = r[v];
-  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_s_barrier();
   wave_sync();
-  __builtin_amdgcn_s_barrier();                               // every copy is complete
-}
-// The same for NV vectors that the block holds once: y[v] = x[v] M (x and y are different memory; the caller's barriers)
-template <int NV, int NW>
-__device__ __forceinline__ void block_lds_product128(const float* __restrict__ x, float* __restrict__ y, const float* __restrict__ M, int wave, int lane) {
-  constexpr int QUADS = 32 / NW;
-  f32x4 r[NV];
-  const int col = block_columns128<NV, NW>(x, M, wave, lane, r);
-  if (lane < QUADS) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) *(f32x4*)(y + v * 128 + col) = r[v];
-  }
 }
 
 }  // namespace saw
