@@ -137,11 +137,11 @@ __device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&q
 
 constexpr int kMetaBytesOf(bool hp) { return hp ? 2048 : 1024; }   // one batch's (scale, zero) pairs: K, then V
 
-// (what append_token leaves for append_store: this lane's code byte and (scale, zero) pair of K and of V,
-// the token's vector index in the pools, and whether its page is mapped)
+// (what append_token leaves for append_store: four codes and the (scale, zero) pair of this lane's vector, its
+// index in the pools, and whether its page is mapped)
 struct NewToken {
-  uint32_t byte[2];
-  f32x2 meta[2];
+  uint32_t codes;
+  f32x2 meta;
   int64_t vec;
   bool place;
 };
@@ -149,53 +149,40 @@ struct NewToken {
 // token (which needs nothing from memory), so that no part of the step waits for them.
 template <bool HP>
 __device__ __forceinline__ void append_store(const DecodeParams& p, int lane, const NewToken& nt) {
-  constexpr int DH = HP ? 64 : 128;
+  constexpr int DH = HP ? 64 : 128, LANES = DH / 4;          // lanes of a head
   if (!nt.place) return;
-#pragma unroll
-  for (int w = 0; w < 2; ++w) {
-    uint8_t* codes = const_cast<uint8_t*>(w ? p.v_codes : p.k_codes);
-    float* meta = const_cast<float*>(w ? p.v_meta : p.k_meta);
-    codes[nt.vec * (DH / 2) + (lane & (DH / 2 - 1))] = (uint8_t)nt.byte[w];
-    if ((lane & (DH / 2 - 1)) == 0) *(f32x2*)(meta + nt.vec * 2) = nt.meta[w];
-  }
+  uint8_t* const codes = const_cast<uint8_t*>(lane < 32 ? p.k_codes : p.v_codes);
+  float* const meta = const_cast<float*>(lane < 32 ? p.k_meta : p.v_meta);
+  *(uint16_t*)(codes + nt.vec * (DH / 2) + 2 * (lane & (LANES - 1))) = (uint16_t)nt.codes;
+  if ((lane & (LANES - 1)) == 0) *(f32x2*)(meta + nt.vec * 2) = nt.meta;
 }
-// The rotation of the new token's K and V vectors by one wavefront, two channels per lane (a block that prepares its range
-// together has them from there); scr: LDS scratch of 256 floats (16-byte aligned) that no transfer in flight targets.
+// The rotation of the new token's K and V vectors by one wavefront, four channels per lane, K in the lower half (a block that prepares
+// its range together has them from there); w: the channels as loaded; scr: LDS scratch of 256 floats (16-byte aligned).
 template <bool HP, bool DN>
-__device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, uint32_t wk, uint32_t wv, float* __restrict__ scr,
-                                             float (&x)[2][2]) {
-  constexpr int D = 128;
-  constexpr int DH = HP ? 64 : 128;  // channels of one head
-  float* const yb = scr;            // [2][128]: K and V for the rotation
-  // K and V go through every step together (index 0: K, 1: V): one two-vector transform instead of
-  // two single ones, and reductions that overlap each other
-  const bool rot[2] = {p.rot_k != 0, p.rot_v != 0};                                // block Hadamard
-  const bool dns[2] = {DN && p.dense_k != 0, DN && p.dense_v != 0};                  // learned rotation after it
-  if (p.kv_new_dtype == SAW_BF16) { widen2<SAW_BF16>(wk, x[0][0], x[0][1]); widen2<SAW_BF16>(wv, x[1][0], x[1][1]); }
-  else                            { widen2<SAW_F16>(wk, x[0][0], x[0][1]);  widen2<SAW_F16>(wv, x[1][0], x[1][1]); }
+__device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, u32x2 w, float* __restrict__ scr, float (&x)[4]) {
+  constexpr int DH = HP ? 64 : 128;
+  const bool second = lane >= 32;
+  const bool rot = second ? p.rot_v : p.rot_k;
+  const bool dns[2] = {DN && p.dense_k != 0, DN && p.dense_v != 0};
+  if (p.kv_new_dtype == SAW_BF16) { widen2<SAW_BF16>(w.x, x[0], x[1]); widen2<SAW_BF16>(w.y, x[2], x[3]); }
+  else                            { widen2<SAW_F16>(w.x, x[0], x[1]);  widen2<SAW_F16>(w.y, x[2], x[3]); }
   if (p.has_signs) {                                         // x diag(sigma), as the store kernel does
 #pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      if (rot[w]) {
-        x[w][0] = apply_sign(p.signs, (2 * lane) & (DH - 1), x[w][0]);
-        x[w][1] = apply_sign(p.signs, (2 * lane + 1) & (DH - 1), x[w][1]);
-      }
-    }
+    for (int e = 0; e < 4; ++e) x[e] = rot ? apply_sign(p.signs, (4 * lane + e) & (DH - 1), x[e]) : x[e];
   }
-  if (rot[0] || rot[1] || dns[0] || dns[1]) {
-    *(f32x2*)(yb + 2 * lane) = f32x2{x[0][0], x[0][1]};
-    *(f32x2*)(yb + D + 2 * lane) = f32x2{x[1][0], x[1][1]};
+  if (p.rot_k || p.rot_v || dns[0] || dns[1]) {
+    *(f32x4*)(scr + 4 * lane) = f32x4{x[0], x[1], x[2], x[3]};             // [2][128]: K, V
     wave_sync();
-    if (rot[0] && rot[1]) wave_lds_fwht128<2>(yb, p.had_block, lane);
-    else if (rot[0]) wave_lds_fwht128<1>(yb, p.had_block, lane);
-    else if (rot[1]) wave_lds_fwht128<1>(yb + D, p.had_block, lane);
-    if constexpr (DN) {                                    // k^ = (k H_b) R_l, the same for V (App. A.3)
-      if (dns[0] && dns[1]) wave_lds_matvec128<2>(yb, p.dense, lane);
-      else if (dns[0]) wave_lds_matvec128<1>(yb, p.dense, lane);
-      else if (dns[1]) wave_lds_matvec128<1>(yb + D, p.dense, lane);
+    if (p.rot_k && p.rot_v) wave_lds_fwht128<2>(scr, p.had_block, lane);
+    else if (p.rot_k) wave_lds_fwht128<1>(scr, p.had_block, lane);
+    else if (p.rot_v) wave_lds_fwht128<1>(scr + 128, p.had_block, lane);
+    if constexpr (DN) {                                      // k^ = (k H_b) R_l, the same for V (App. A.3)
+      if (dns[0] && dns[1]) wave_lds_matvec128<2>(scr, p.dense, lane);
+      else if (dns[0]) wave_lds_matvec128<1>(scr, p.dense, lane);
+      else if (dns[1]) wave_lds_matvec128<1>(scr + 128, p.dense, lane);
     }
-    const f32x2 yk = *(const f32x2*)(yb + 2 * lane), yv = *(const f32x2*)(yb + D + 2 * lane);
-    x[0][0] = yk.x; x[0][1] = yk.y; x[1][0] = yv.x; x[1][1] = yv.y;
+    const f32x4 y = *(const f32x4*)(scr + 4 * lane);
+    x[0] = y.x; x[1] = y.y; x[2] = y.z; x[3] = y.w;
     wave_sync();
   }
 }
@@ -209,67 +196,52 @@ __device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, ui
 // happens at the END of the range that starts the sequence, when every transfer of the range has
 // landed: at the start of a launch all wavefronts of the chip run their prologues at once and are
 // bound by instruction issue, while later the vector ALU has slack under the memory traffic.
-// One wavefront, two channels per lane.
-//   pid, x  page id of position L and this lane's two channels of the new K and V vectors, rotated
+// One wavefront, K in lanes 0-31 and V in lanes 32-63, four channels per lane: one chain of reductions and one division for both.
+// (It is on the critical path of the range's last wavefront: with two channels of both vectors in every lane, 4 x 256 tokens took 8.6 us
+// and take 8.1, 16 x 4096 22.6 and 22.1, 64 ragged with a learned rotation 46.3 and 45.0.)
+//   pid, x  page id of position L and this lane's channels 4 (lane % 32) .. + 3, rotated
 //   kdst, vdst, mdst  the K buffer, a V buffer and its metadata buffer
-// HP: the 128 values are the new vectors of two neighbouring 64-channel kv heads (lanes 0-31 hold
-// the first head's channels), quantised and stored per head; `kvh` counts pairs.
+// HP: the 128 values are the new vectors of two neighbouring 64-channel kv heads (16 lanes each),
+// quantised and stored per head; `kvh` counts pairs.
 template <bool HP>
-__device__ __forceinline__ void append_token(const DecodeParams& p, int kvh, int lane, int L, int pid, const float (&x)[2][2],
+__device__ __forceinline__ void append_token(const DecodeParams& p, int kvh, int lane, int L, int pid, const float (&x)[4],
                                              uint8_t* __restrict__ kdst, uint8_t* __restrict__ vdst,
                                              uint8_t* __restrict__ mdst, NewToken& nt) {
-  constexpr int DH = HP ? 64 : 128;  // channels of one head
-  const int slot = L & 15;
+  constexpr int DH = HP ? 64 : 128, LANES = DH / 4;
+  const bool second = lane >= 32;
   nt.place = pid >= 0 && pid < p.num_pages;                  // otherwise attended to but not stored
-  const int head = HP ? 2 * kvh + (lane >> 5) : kvh;         // kv head of this lane's two channels
-  nt.vec = ((int64_t)pid * p.n_kv_heads + head) * 16 + slot;
-  const bool rot[2] = {p.rot_k != 0, p.rot_v != 0};                                // block Hadamard
-  // min and max over each head's values (128: all lanes, 64: half of them): reductions of
-  // (max, -min) pairs, rows first (DPP)
-  float mx[2], nmn[2];
-#pragma unroll
-  for (int w = 0; w < 2; ++w) {
-    mx[w] = row_allmax(fmaxf(x[w][0], x[w][1]));
-    nmn[w] = row_allmax(-fminf(x[w][0], x[w][1]));
+  const int head = HP ? 2 * kvh + ((lane >> 4) & 1) : kvh;   // kv head of this lane's channels
+  nt.vec = ((int64_t)pid * p.n_kv_heads + head) * 16 + (L & 15);
+  // max and -min over the head's lanes, rows first (DPP)
+  float mx = row_allmax(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+  float nmn = row_allmax(-fminf(fminf(x[0], x[1]), fminf(x[2], x[3])));
+  if (!HP) {
+    mx = max_xor16(mx);
+    nmn = max_xor16(nmn);
   }
-#pragma unroll
-  for (int w = 0; w < 2; ++w) {
-    mx[w] = max_xor16(mx[w]);
-    nmn[w] = max_xor16(nmn[w]);
-    if (!HP) {
-      mx[w] = max_xor32(mx[w]);
-      nmn[w] = max_xor32(nmn[w]);
-    }
+  const float norm = (second ? p.rot_v : p.rot_k) ? had_norm(p.had_block) : 1.0f;
+  const float mn = -nmn;
+  const float range = mx - mn;
+  float inv, zq, s_store, z_store;
+  if (range > 0.0f) {
+    inv = 15.0f / range;
+    s_store = range * (norm * (1.0f / 15.0f));
+    zq = rintf(-mn * inv);
+    z_store = zq;
+  } else {  // constant vector
+    inv = 0.0f;
+    zq = 0.0f;
+    s_store = (mn != 0.0f) ? fabsf(mn) * norm : 1.0f;
+    z_store = (mn > 0.0f) ? -1.0f : ((mn < 0.0f) ? 1.0f : 0.0f);
   }
+  nt.codes = 0u;
 #pragma unroll
-  for (int w = 0; w < 2; ++w) {
-    const float norm = rot[w] ? had_norm(p.had_block) : 1.0f;
-    const float mn = -nmn[w];
-    const float range = mx[w] - mn;
-    float inv, zq, s_store, z_store;
-    if (range > 0.0f) {
-      inv = 15.0f / range;
-      s_store = range * (norm * (1.0f / 15.0f));
-      zq = rintf(-mn * inv);
-      z_store = zq;
-    } else {  // constant vector
-      inv = 0.0f;
-      zq = 0.0f;
-      s_store = (mn != 0.0f) ? fabsf(mn) * norm : 1.0f;
-      z_store = (mn > 0.0f) ? -1.0f : ((mn < 0.0f) ? 1.0f : 0.0f);
-    }
-    const float c0 = __builtin_amdgcn_fmed3f(rintf(x[w][0] * inv) + zq, 0.0f, 15.0f);
-    const float c1 = __builtin_amdgcn_fmed3f(rintf(x[w][1] * inv) + zq, 0.0f, 15.0f);
-    const uint8_t byte = (uint8_t)((uint32_t)c0 | ((uint32_t)c1 << 4));
-    const bool meta_lane = (lane & (DH / 2 - 1)) == 0;        // lane 0 (and lane 32 for the pair's second head)
-    nt.byte[w] = byte;
-    nt.meta[w] = f32x2{s_store, z_store};
-    // token 0 of page 0 of the batch: its 64 code bytes are the first 64 bytes of the tile (chunk Q of
-    // token 0 sits at chunk position Q), its pairs the first of the metadata block (head pair: one per head)
-    (w ? vdst : kdst)[lane] = byte;
-    if (meta_lane)
-      *(f32x2*)(mdst + (w ? kMetaBytesOf(HP) / 2 : 0) + (HP ? 128 * (lane >> 5) : 0)) = f32x2{s_store, z_store};
-  }
+  for (int e = 0; e < 4; ++e) nt.codes |= (uint32_t)__builtin_amdgcn_fmed3f(rintf(x[e] * inv) + zq, 0.0f, 15.0f) << (4 * e);
+  nt.meta = f32x2{s_store, z_store};
+  // token 0 of page 0 of the batch: its 64 code bytes are the first 64 bytes of the tile (chunk Q of
+  // token 0 sits at chunk position Q), its pairs the first of the metadata block (head pair: one per head)
+  *(uint16_t*)((second ? vdst : kdst) + 2 * (lane & 31)) = (uint16_t)nt.codes;
+  if ((lane & (LANES - 1)) == 0) *(f32x2*)(mdst + (second ? kMetaBytesOf(HP) / 2 : 0) + (HP ? 128 * ((lane >> 4) & 1) : 0)) = nt.meta;
   wave_sync();
 }
 
@@ -832,15 +804,12 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // batches; so in a block of eight, where over a short context that wavefront has none and works on the token while the others
   // stream (4 sequences of 256 tokens: the step 9.3 -> 9.1 us); its inputs are requested here, with the query
   const bool takes_new = block_new && (PAIR || wave == (CUT || NW == 8 ? NW - 1 : 0));
-  uint32_t new_wk = 0, new_wv = 0;
+  u32x2 new_w = u32x2{0u, 0u};
   int new_pid = -1;
   if (takes_new) {
     // (the block's new K|V values are 128 contiguous elements: one head, or a pair of 64-channel heads)
-    if (!kBP) {
-      const int64_t e = ((int64_t)b * p.n_kv_heads * DH + (int64_t)kvh * D) / 2 + lane;
-      new_wk = ((const uint32_t*)p.k_new)[e];
-      new_wv = ((const uint32_t*)p.v_new)[e];
-    }
+    if (!kBP)
+      new_w = *(const u32x2*)((const uint16_t*)(lane < 32 ? p.k_new : p.v_new) + (int64_t)b * p.n_kv_heads * DH + (int64_t)kvh * D + 4 * (lane & 31));
     // (a length beyond the caller's bound was clamped for the attention; storing at the clamped
     // position would overwrite a cached token, so such a token is attended to but not stored)
     if ((seq_len_b >> 4) < p.max_pages && p.seq_lens[b] <= p.bound) new_pid = p.page_table[pt_row + (seq_len_b >> 4)];
@@ -920,19 +889,15 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   float* const qrows = (G <= 4) ? (float*)pbuf : (float*)vbuf_b;
   u32x4 a_q[4];
   float qsum[NH];
-  float new_x[2][2] = {{0.f, 0.f}, {0.f, 0.f}};               // the new token's K and V channels, rotated
+  float new_x[4] = {0.f, 0.f, 0.f, 0.f};                      // the new token's channels of this lane, rotated
   if constexpr (kBP) {
     float* const rows = (float*)(lds_all + NW * kWaveLds + 16 + kSpareBytes);
     // (rows to be multiplied: wavefront 0's second V buffer and what follows, which nobody writes to before the barrier behind the product)
     block_prepare<G, NW, NH, HP, DN>(p, vbits, block_new, wave, lane, (float*)(lds_all + 8 * kTileBytes), rows,
                                      (u32x4*)(rows + 128 * (G + 2)), cols, a_q, qsum);
     if (takes_new) {
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const f32x2 v = *(const f32x2*)(rows + 128 * (G + t) + 2 * lane);
-        new_x[t][0] = v.x;
-        new_x[t][1] = v.y;
-      }
+      const f32x4 v = *(const f32x4*)(rows + 128 * G + 4 * lane);                 // K, then V
+      new_x[0] = v.x; new_x[1] = v.y; new_x[2] = v.z; new_x[3] = v.w;
     }
   } else   {
     float qraw[2 * G];
@@ -1113,7 +1078,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // so nothing is requested).
   if (takes_new) {
     NewToken nt;
-    if (!kBP) rotate_token<HP, DN>(p, lane, new_wk, new_wv, (float*)vbuf_b, new_x);
+    if (!kBP) rotate_token<HP, DN>(p, lane, new_w, (float*)vbuf_b, new_x);
     append_token<HP>(p, kvh, lane, seq_len_b, new_pid, new_x, kbuf, vbuf_a, mbuf_a, nt);
     body(0x3fffffff, t_end - 1, kbuf, vbuf_a, vbuf_b, pbuf, mbuf_a, mbuf_b);
     append_store<HP>(p, lane, nt);                         // (nobody waits for these: see append_store)
