@@ -73,6 +73,19 @@ static bool block_ok(const saw_cache_t* c) {
 }
 
 
+// Wavefronts of the INT4 block that takes a whole sequence (one partition), by the number of (kv head, or pair of heads, sequence)
+// items; `nw`: what the bound alone asks for.  Up to 256 items the block of eight above; from 1152 on pair blocks and one wavefront
+// (run_decode).  In between the chip holds four wavefronts for every item up to 512 and two up to 1024, and a wavefront that has only
+// a batch or two is still better than a slot left empty, however short the sequences.  Fused step, 32 query / 8 kv heads, us, one
+// wavefront an item (pair blocks) before: 64 x 250 tokens 17.6, now 10.8; 64 x 750 30 and 16.4; 64 ragged up to 1500 30 and 21; learned
+// 64 x 750 40 and 22.  513 to 575 items: 68 x 250 22 and 13, four wavefronts only from 1024 tokens on, where their second round
+// is paid for (68 x 250 17, x 750 level, 68 ragged up to 1000 20.4 against 24 with two); 1040 ragged up to 750 33 and 24.
+static int whole_waves(int64_t items, int units, int nw) {
+  if (items <= 256 || items >= 1152) return nw;
+  if (items <= 512 || (items < 576 && units >= 16)) return 4;
+  return 2;
+}
+
 // The matrix-core INT4 kernel for rows of 128 channels holds 2048 wavefronts.  `per_seq`: (kv head, or pair of heads) items of a
 // sequence.  What was measured, decode or fused step, 32 query / 8 kv heads, against the fixed partitions (in brackets):
 //   * partitions of four wavefronts, which fold in LDS, leave the merge pass a quarter of the records, where that still gives
@@ -89,13 +102,23 @@ static bool block_ok(const saw_cache_t* c) {
 //     (20 x 2304 19.0 against 21.4, 16 x 2304 18.9 against 19.3 but ragged 18.3 against 17.4), eight from 192 on (24 x 2560 20.7 against
 //     23.9, 28 x 3584 26.2 against 30.3, 28 of up to 1750 under a bound of 3500 16.6 against 18.6; 28 ragged up to 3500 24.4 against
 //     23.1, 24 ragged up to 4000 26.1 against 23.0).  Pairs of 64-channel heads: five from 192 items on (56 x 3584 31.2
-//     against 33.4, but ragged 29.8 against 25.5).
-static void plan_cut(int B, int units, int per_seq, bool pairs, SplitPlan* plan) {
+//     against 33.4, but ragged 29.8 against 25.5);
+//   * from 257 items on four wavefronts over the whole sequence (whole_waves) take its place where each has at most six batches
+//     (40 x 200 tokens 17.6 us, 10.6 with them, 62 x 800 21.1 and 17.7, 48 x 1500 27.5 and 23.4, 33 with a few long ones of 1500
+//     16.3 and 16.6; x 2000 16.3 and 19.2), five for pairs of 64-channel heads (40 x 1200 23.6 and 23.4, x 1500 25.7 and 26.2), eight
+//     with the learned rotation, whose preparation every partition would repeat (33 x 2000 33.3 and 31.6, 62 x 2000 43.7 and 34.5).
+static void plan_cut(int B, int units, int per_seq, bool pairs, bool learned, SplitPlan* plan) {
   const int64_t items = (int64_t)B * per_seq;
   const int per_wave = (units + 7) / 8;
   const int most = pairs ? (items >= 192 ? 5 : 4) : items >= 192 ? 8 : items > 128 ? 5 : 4;
   if (plan->waves_per_item == 8 && per_wave <= most) return;
   if (items >= 512) return;
+  if (items > 256 && (units + 3) / 4 <= (pairs ? 5 : learned ? 8 : 6)) {
+    plan->num_splits = 1;
+    plan->chunk_tokens = units * 64;
+    plan->waves_per_item = whole_waves(items, units, 1);
+    return;
+  }
   if (cut_plan(B, units, 512 / per_seq, 4, plan) && plan->cut >= 8 * B) return;
   plan->cut = 0;
   cut_plan(B, units, 1024 / per_seq, 2, plan);
@@ -212,10 +235,12 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   plan->bound = bound;
   // wavefronts per partition: only when the partitions alone cannot fill the chip (about 2560
   // wavefront slots), and while every wavefront keeps at least 8 batches (512 tokens) of its own
+  // (a sequence in one partition, over 256 items: whole_waves)
   const int64_t blocks = (int64_t)B * decode_items_per_seq(c->head_dim, c->n_kv_heads) * plan->num_splits;
   int nw = 1;
   while (nw < 4 && blocks * nw * 2 <= 2560 && plan->chunk_tokens / (nw * 2) >= 512) nw *= 2;
   if (block_of_eight && plan->num_splits == 1) nw = 8;
+  else if (!kv16 && plan->num_splits == 1) nw = whole_waves(blocks, units, nw);
   plan->waves_per_item = nw;
   plan->cut = plan->cut_min = plan->cut_waves = 0;
   plan->valu16 = valu16;
@@ -225,7 +250,7 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   // (partitions of 256 tokens are the shortest a cut makes: fixed ones that are no longer have the shorter start - 8 ragged up to 8000
   // tokens, 32 query / 8 kv heads, 42 us, 49 cut; above that 40 ragged up to 8000 161 and 131)
   else if (kv16) { if (plan->num_splits > 1 && chunk_units > 4) cut_plan(B, units, 2048 / per_seq, 1, plan); }
-  else plan_cut(B, units, per_seq, c->head_dim == 64, plan);
+  else plan_cut(B, units, per_seq, c->head_dim == 64, c->dense_rot != nullptr, plan);
   return true;
 }
 

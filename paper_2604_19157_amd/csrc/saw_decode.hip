@@ -342,7 +342,13 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
   //     wavefront per item, sequences taken longest first, so the launch ends on the shortest.
   //     (Measured at 288..512 sequences x 8 heads: 173-270 us against 224-332 us in pair mode,
   //     whose equal blocks make the last round as long as the others; 2 or 4 wavefronts per item
-  //     were never better.)
+  //     were never better.);
+  //   * short bounds leave nothing worth evening out: the plan's wavefronts take each sequence as it comes, without the ranking
+  //     and the records (two of them up to 1151 items, one above).  96 x 8 of 250 tokens 20 -> 14 us, ragged up to 500 23 -> 17, 128 x 8
+  //     x 500 25 -> 19; 144 x 8 x 250 25 -> 19, 256 x 8 ragged up to 250 25 -> 20, 512 x 8 x 63 37 -> 25.  Above these bounds the batches
+  //     with a few long sequences lose (128 x 8 up to 750 tokens by 6 %, 192 x 8 up to 500 by 7 %).  The caller's order saves the
+  //     ranking: with it up to 256 tokens and 1024 items only (128 x 8 x 250 18 -> 14 us, up to 500 tokens 16 -> 17; 130 x 8 x 63
+  //     14 -> 17, 400 x 8 ragged up to 250 30 -> 33).
   p.pair = 0;
   p.pair_seqs = 2;
   p.sorted = 0;
@@ -352,7 +358,10 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
       !plan.cut && plan.num_splits == 1 && B <= 1024) {
     const int64_t blocks = (int64_t)((B + 1) / 2) * items;
     const int64_t blocks3 = (int64_t)((B + 2) / 3) * items;
-    if ((int64_t)B * items >= 576 && blocks <= 512) p.pair = 4;
+    const bool crowded = (int64_t)B * items > 1024;
+    const int short_bound = p.order ? (crowded ? 0 : 256) : crowded ? 256 : 512;
+    if ((int64_t)B * items < 576 || p.chunk_tokens <= short_bound) {}   // blocks of the plan's wavefronts
+    else if ((int64_t)B * items >= 576 && blocks <= 512) p.pair = 4;
     else if ((int64_t)B * items >= 1152 && blocks3 <= 512 && !(c->head_dim == 64 && G == 4)) {
       // four wavefronts over three sequences (not for head pairs with eight query rows: two such
       // blocks with their two spare records do not fit a compute unit's LDS)
@@ -360,7 +369,7 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
       p.pair_seqs = 3;
     }
     else if ((int64_t)B * items >= 1152 && blocks <= 1024) p.pair = 2;   // (whatever the plan's wavefronts per item)
-    else if (plan.waves_per_item == 1 && (int64_t)B * items > 256) {
+    else if (crowded && (plan.waves_per_item == 1 || p.chunk_tokens <= 256)) {
       if (blocks <= 1024) p.pair = 2;
       else if ((int64_t)B * items <= 2304 && blocks3 <= 1024 && !(c->head_dim == 64 && G == 4)) {
         // just above 2048 items: blocks of two wavefronts over THREE sequences keep everything resident
