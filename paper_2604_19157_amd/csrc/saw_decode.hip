@@ -387,11 +387,12 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
       order && B <= 1024 && (int64_t)B * c->n_kv_heads > 256)
     p.sorted = 1;
   // the 16-bit matrix-core kernel has the two-wavefront pair mode as well (same conditions), so that
-  // the comparison on a ragged batch is between formats and not between schedules; for the shapes with eight query heads per kv
-  // head or head_dim 64 only from bounds of 1024 tokens on: of shorter sequences the ranking takes longer than it saves (257 x 1
-  // kv heads of 128, eight query heads each, up to 150 tokens 27.6 us with pair blocks, 15.7 without; 256 x 8 of 600 equal
-  // tokens level, ragged up to 1200 with them ahead by 6 %)
-  if (kv16 && !plan.valu16 && !plan.cut && plan.num_splits == 1 && B <= 1024 && ((c->head_dim == 128 && G <= 4) || plan.bound > 1024) &&
+  // the comparison on a ragged batch is between formats and not between schedules; only above bounds of 256 tokens (48 x 8 ragged
+  // up to 250 tokens 26 us with pair blocks, 22 without, 256 x 8 x 250 59 and 53, 96 x 8 x 63 18 and 13; from 500 tokens on level, and 256 x 8
+  // ragged up to 1000 ahead by 8 %), and for the shapes with eight query heads per kv head or head_dim 64 only above 1024: of
+  // shorter sequences the ranking takes longer than it saves (257 x 1 kv heads of 128, eight query heads each, up to 150 tokens
+  // 27.6 us with pair blocks, 15.7 without; 256 x 8 of 600 equal tokens level, ragged up to 1200 with them ahead by 6 %)
+  if (kv16 && !plan.valu16 && !plan.cut && plan.num_splits == 1 && B <= 1024 && plan.bound > (c->head_dim == 128 && G <= 4 ? 256 : 1024) &&
       (int64_t)B * c->n_kv_heads > 256 && (int64_t)((B + 1) / 2) * c->n_kv_heads <= 1024)
     p.pair = 2;
   return launch_decode(p, B, c->head_dim, G, kv16, plan.valu16 != 0, kv_dtype, st);

@@ -1,7 +1,7 @@
 """Short bounds: several wavefronts over each whole sequence instead of partitions, pair blocks and the in-kernel ranking.
 
 Both sides of each line of the rules, in (sequence, kv head) items and in tokens, decode and fused step, with and without the
-caller's order, pairs of 64-channel heads and a learned rotation; lengths from zero to the bound.  The call's own
+caller's order, pairs of 64-channel heads, a learned rotation and the 16-bit cache; lengths from zero to the bound.  The call's own
 plan against two fixed partitions per sequence and their merge pass: the same products, with weights that both sides round to bf16
 against their own running maximum.  One weight p is off by at most 2^-9 p on either side; over n tokens of about equal weight these
 roundings, of either sign, add up to 2^-8 |v| / sqrt(n) in the norm of an output row (twice that is allowed), |v| <= 0.8 sqrt(d) here."""
@@ -67,3 +67,18 @@ def test_short_bounds(saw, B, n_kv, G, d, bound, dense):
         if after is None:
             after = saw.paged_decode_attn(c, q, pt, lens + 1, max_seq_len=bound + 1, num_splits=2).float()
         _same(got, after, lens + 1, ("fused", order is not None))
+
+
+@pytest.mark.parametrize("B,n_kv,G,bound", [(257, 1, 4, 256), (257, 1, 4, 257), (48, 8, 1, 200), (512, 4, 4, 100)])
+def test_short_bounds_kv16(saw, B, n_kv, G, bound):
+    lens = torch.tensor(_lens(B, bound), dtype=torch.int32, device="cuda")
+    need = (bound + 16) // 16
+    g = torch.Generator(device="cuda").manual_seed(bound)
+    c = saw.Kv16Cache(B * need, n_kv, 128, torch.bfloat16)
+    for t in (c.k_pages, c.v_pages):
+        t.normal_(generator=g).mul_(0.5)
+    pt = torch.randperm(B * need, device="cuda", generator=g).to(torch.int32).view(B, need)
+    q = torch.randn((B, n_kv * G, 128), device="cuda", generator=g).bfloat16()
+    ref = saw.kv16_paged_decode_attn(c, q, pt, lens, max_seq_len=bound, num_splits=2).float()
+    out = saw.kv16_paged_decode_attn(c, q, pt, lens, max_seq_len=bound).float()
+    _same(out, ref, lens, "kv16")
