@@ -130,6 +130,10 @@ static void plan_cut(int B, int units, int per_seq, bool pairs, bool learned, Sp
 // gives a sequence two slots on average; beyond that one partition per sequence, of four wavefronts while they fit.  Four
 // wavefronts a slot, 2048 in all, where a sequence gets four slots of those (16 ragged x 8 heads of 300-3000 tokens 17.5 us, 19.1
 // with 3072, 22.4 and 25.3 with one wavefront a slot; 64 ragged 40.0, with one wavefront 32.1, which is why it needs the four).
+// Short bounds of more items are not cut: four wavefronts over the whole sequence, no merge pass, while they fit and have at most
+// six batches each (eight query heads, fused step: 33 x 400 tokens 17 us, 13 so, 64 x 700 22 and 16, 96 ragged up to 1000 26 and 22, 90 x 1535
+// 37 and 32, with a few long ones among short level), and up to 1024 items, where they no longer fit, at most three (110 x 400 24 and
+// 21, 128 x 767 33 and 29; x 1000 level); one or two batches in all still go to one wavefront there (200 tokens 15 and 20).
 static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan) {
   const int64_t items = (int64_t)B * c->n_kv_heads;
   constexpr int kWaves = 3072;
@@ -139,6 +143,12 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
     plan->num_splits = 1;
     plan->chunk_tokens = units * 64;
     plan->waves_per_item = 8;
+    return;
+  }
+  if (items > 256 && (items <= 768 ? units <= 24 : items <= 1024 && B <= kMaxCut && units > 4 && units <= 12)) {
+    plan->num_splits = 1;
+    plan->chunk_tokens = units * 64;
+    plan->waves_per_item = 4;
     return;
   }
   if (cut_plan(B, units, 2048 / 4 / c->n_kv_heads, 4, plan) && plan->cut >= 4 * B) return;

@@ -1,7 +1,7 @@
 """Short bounds: several wavefronts over each whole sequence instead of partitions, pair blocks and the in-kernel ranking.
 
 Both sides of each line of the rules, in (sequence, kv head) items and in tokens, decode and fused step, with and without the
-caller's order, pairs of 64-channel heads, a learned rotation and the 16-bit cache; lengths from zero to the bound.  The call's own
+caller's order, 64-channel heads in pairs and one at a time, a learned rotation and the 16-bit cache; lengths from zero to the bound.  The call's own
 plan against two fixed partitions per sequence and their merge pass: the same products, with weights that both sides round to bf16
 against their own running maximum.  One weight p is off by at most 2^-9 p on either side; over n tokens of about equal weight these
 roundings, of either sign, add up to 2^-8 |v| / sqrt(n) in the norm of an output row (twice that is allowed), |v| <= 0.8 sqrt(d) here."""
@@ -51,7 +51,9 @@ def _same(out, ref, lens, what):
     (171, 3, 4, 128, 961, False), (115, 5, 8, 128, 1025, False), (144, 4, 4, 128, 512, False), (144, 4, 4, 128, 513, False),
     (128, 8, 4, 128, 256, False), (205, 5, 4, 128, 256, False), (205, 5, 4, 128, 257, False), (164, 7, 2, 128, 40, True),
     (144, 8, 4, 128, 256, False), (144, 8, 8, 128, 257, False), (1030, 1, 4, 128, 200, False), (260, 8, 4, 128, 130, False),
-    (33, 16, 4, 64, 1279, False), (33, 16, 2, 64, 1281, False), (64, 16, 4, 64, 400, False), (144, 16, 4, 64, 250, False)])
+    (33, 16, 4, 64, 1279, False), (33, 16, 2, 64, 1281, False), (64, 16, 4, 64, 400, False), (144, 16, 4, 64, 250, False),
+    (33, 8, 8, 64, 1536, False), (33, 8, 8, 64, 1537, False), (96, 8, 8, 64, 300, False), (110, 7, 8, 64, 257, False),
+    (128, 8, 8, 64, 768, False), (257, 3, 1, 64, 400, False), (259, 3, 1, 64, 400, False)])
 def test_short_bounds(saw, B, n_kv, G, d, bound, dense):
     lens = torch.tensor(_lens(B, bound), dtype=torch.int32, device="cuda")
     c, pt, g = _cache(saw, B, n_kv, d, bound, dense)
