@@ -213,6 +213,17 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
     int64_t s = (slots + items - 1) / items;
     const int64_t max_by_min_chunk = (units + 3) / 4;      // partitions of >= 256 tokens
     if (s > max_by_min_chunk) s = max_by_min_chunk;
+    // ... of the 16-bit call 64 or 128 where all of those are resident at once with room to spare (1792 of 2048 wavefronts): its
+    // batches are 32 tokens, eight of them in a row take longer than the merge pass takes for more records (32 query / 8 kv heads, us:
+    // 1 x 400 tokens 17.3 with 256 a partition, 12.1 with 64; 4 x 1000 19.7 and 13.8; 8 x 2000 25.6 and 23.0 with 128; 16 ragged up to 800
+    // 23.0 and 17.7; 32 x 512 25.8 and 22.7 with 128; with 192 level, under loose bounds 5 % slower).  Bounds of up to five units
+    // stay as they are (28 ragged up to 128 under a bound of 256, one query head: 10.1, cut 13.4, the second launch; 32 up to 130 under
+    // 272: 16.8 and 17.5), and so do more than 320 items (48 ragged up to 600 25.9 and 28.2).  Not in the fixed plan, whose
+    // scratch every call has to bring.
+    if (kv16 && !fixed && !valu16 && units > 5 && items <= 320) {
+      const int64_t finer = 1792 / items < units ? 1792 / items : units;
+      if (2 * finer >= units && s < finer) s = finer;
+    }
     if (!kv16 && items >= 512 && B <= 1024) s = 1;
     // Very many partitions (a single long sequence): a quarter of them, each shared by four wavefronts
     // that fold their states in LDS, leaves the merge pass a quarter of the partial records to write

@@ -1,4 +1,5 @@
-"""Short bounds: several wavefronts over each whole sequence instead of partitions, pair blocks and the in-kernel ranking.
+"""Short bounds: several wavefronts over each whole sequence instead of partitions, pair blocks and the in-kernel ranking; the
+16-bit call's shorter partitions.
 
 Both sides of each line of the rules, in (sequence, kv head) items and in tokens, decode and fused step, with and without the
 caller's order, 64-channel heads in pairs and one at a time, a learned rotation and the 16-bit cache; lengths from zero to the bound.  The call's own
@@ -20,7 +21,7 @@ def saw():
 
 def _lens(B, bound):
     v = [(37 * i * i + 11 * i) % (bound + 1) for i in range(B)]
-    v[0], v[B // 2], v[-1] = bound, 0, min(1, bound)
+    v[B // 2], v[-1], v[0] = 0, min(1, bound), bound
     return v
 
 
@@ -71,7 +72,9 @@ def test_short_bounds(saw, B, n_kv, G, d, bound, dense):
         _same(got, after, lens + 1, ("fused", order is not None))
 
 
-@pytest.mark.parametrize("B,n_kv,G,bound", [(257, 1, 4, 256), (257, 1, 4, 257), (48, 8, 1, 200), (512, 4, 4, 100)])
+@pytest.mark.parametrize("B,n_kv,G,bound", [(257, 1, 4, 256), (257, 1, 4, 257), (48, 8, 1, 200), (512, 4, 4, 100),
+                                           (3, 8, 1, 256), (3, 8, 1, 257), (28, 8, 8, 320), (28, 8, 8, 321), (1, 2, 4, 3000),
+                                           (16, 7, 4, 1100), (320, 1, 4, 500), (321, 1, 4, 500)])
 def test_short_bounds_kv16(saw, B, n_kv, G, bound):
     lens = torch.tensor(_lens(B, bound), dtype=torch.int32, device="cuda")
     need = (bound + 16) // 16
