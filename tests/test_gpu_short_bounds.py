@@ -21,7 +21,7 @@ def saw():
 
 def _lens(B, bound):
     v = [(37 * i * i + 11 * i) % (bound + 1) for i in range(B)]
-    v[B // 2], v[-1], v[0] = 0, min(1, bound), bound
+    v[B // 2], v[-1], v[0] = 0, min(1, bound), bound      # (the last one wins in a batch of one)
     return v
 
 
@@ -54,7 +54,8 @@ def _same(out, ref, lens, what):
     (144, 8, 4, 128, 256, False), (144, 8, 8, 128, 257, False), (1030, 1, 4, 128, 200, False), (260, 8, 4, 128, 130, False),
     (33, 16, 4, 64, 1279, False), (33, 16, 2, 64, 1281, False), (64, 16, 4, 64, 400, False), (144, 16, 4, 64, 250, False),
     (33, 8, 8, 64, 1536, False), (33, 8, 8, 64, 1537, False), (96, 8, 8, 64, 300, False), (110, 7, 8, 64, 257, False),
-    (128, 8, 8, 64, 768, False), (257, 3, 1, 64, 400, False), (259, 3, 1, 64, 400, False)])
+    (128, 8, 8, 64, 768, False), (257, 3, 1, 64, 400, False), (259, 3, 1, 64, 400, False),
+    (1, 8, 4, 128, 2600, False), (1, 16, 8, 128, 8191, True), (1, 1, 1, 128, 8192, False), (1, 16, 4, 64, 5000, False)])
 def test_short_bounds(saw, B, n_kv, G, d, bound, dense):
     lens = torch.tensor(_lens(B, bound), dtype=torch.int32, device="cuda")
     c, pt, g = _cache(saw, B, n_kv, d, bound, dense)
