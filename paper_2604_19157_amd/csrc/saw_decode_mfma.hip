@@ -324,14 +324,18 @@ __device__ __forceinline__ void block_prepare(const DecodeParams& p, const uint3
   if constexpr (DN) {                                        // learned rotation after the Hadamard (App. A.3)
     if (p.dense_k) {
       block_columns_product<G, NW>(in, y, cols, lane);
-      if (with_new) block_columns_product<1, NW>(in + 128 * G, y + 128 * G, cols, lane);
     } else {
-      for (int i = 64 * wave + lane; i < 128 * (G + 1); i += 64 * NW) y[i] = in[i];
+      for (int i = 64 * wave + lane; i < 128 * G; i += 64 * NW) y[i] = in[i];
     }
-    if (p.dense_v && with_new) {
-      block_columns_product<1, NW>(in + 128 * (G + 1), y + 128 * (G + 1), cols, lane);
-    } else {
-      if (wave < 2) y[128 * (G + 1) + 64 * wave + lane] = in[128 * (G + 1) + 64 * wave + lane];
+    if (with_new) {
+      if (p.dense_k && p.dense_v) {
+        block_columns_ordered<2, NW>(in + 128 * G, y + 128 * G, cols, lane);
+      } else {
+        if (p.dense_k) block_columns_ordered<1, NW>(in + 128 * G, y + 128 * G, cols, lane);
+        else if (wave < 2) y[128 * G + 64 * wave + lane] = in[128 * G + 64 * wave + lane];
+        if (p.dense_v) block_columns_ordered<1, NW>(in + 128 * (G + 1), y + 128 * (G + 1), cols, lane);
+        else if (wave < 2) y[128 * (G + 1) + 64 * wave + lane] = in[128 * (G + 1) + 64 * wave + lane];
+      }
     }
     lds_barrier();
   }

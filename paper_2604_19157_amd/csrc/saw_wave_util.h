@@ -227,10 +227,14 @@ __device__ __forceinline__ void wave_lds_matvec128(float* x, const float* __rest
 // Products x[v] M of vectors in LDS by a block of NW (2, 4 or 8) wavefronts: wavefront `wave` takes 128 / NW columns, so that the
 // block reads M (64 KiB, from L2) once and not once per wavefront.  A lane's part of M, four columns of ROWS rows, is requested by
 // block_columns_load: early, in front of transfers from HBM, because loads return in order.
+// Which rows: a sum of wave_lds_matvec128 is four chains of 32 terms, the rows of even and of odd index in either half.  Each row
+// of 16 lanes takes one of the chains, SEQ neighbouring groups of lanes the parts of it one after the other, so that
+// block_columns_ordered can add up in that very order.
 template <int NW>
 struct BlockColumns {
   static constexpr int QUADS = 32 / NW;                       // column quads of a wavefront, one per lane of a group
-  static constexpr int ROWS = 128 / (64 / QUADS);             // rows of M a lane multiplies
+  static constexpr int SEQ = 16 / QUADS;                      // groups that share a chain
+  static constexpr int ROWS = 32 / SEQ;                       // rows of M a lane multiplies: row0, row0 + 2, ...
   f32x4 m[ROWS];
   int col, row0;
 };
@@ -238,9 +242,9 @@ template <int NW>
 __device__ __forceinline__ void block_columns_load(const float* __restrict__ M, int wave, int lane, BlockColumns<NW>& k) {
   using K = BlockColumns<NW>;
   k.col = 4 * (K::QUADS * wave + (lane & (K::QUADS - 1)));
-  k.row0 = K::ROWS * (lane / K::QUADS);
+  k.row0 = 64 * (lane >> 5) + ((lane >> 4) & 1) + 2 * K::ROWS * ((lane & 15) / K::QUADS);
 #pragma unroll
-  for (int u = 0; u < K::ROWS; ++u) k.m[u] = *(const f32x4*)(M + (k.row0 + u) * 128 + k.col);
+  for (int u = 0; u < K::ROWS; ++u) k.m[u] = *(const f32x4*)(M + (k.row0 + 2 * u) * 128 + k.col);
 }
 // y[v] = x[v] M in this wavefront's columns, v < NV (x and y are different memory; the caller's barriers)
 template <int NV, int NW>
@@ -250,12 +254,10 @@ __device__ __forceinline__ void block_columns_product(const float* __restrict__ 
   for (int v = 0; v < NV; ++v) {
     float acc[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int u4 = 0; u4 < K::ROWS / 4; ++u4) {
-      const f32x4 xv = *(const f32x4*)(x + v * 128 + k.row0 + 4 * u4);
+    for (int u = 0; u < K::ROWS; ++u) {
+      const float xu = x[v * 128 + k.row0 + 2 * u];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[e & 1][c] = fmaf(xv[e], k.m[4 * u4 + e][c], acc[e & 1][c]);
+      for (int c = 0; c < 4; ++c) acc[u & 1][c] = fmaf(xu, k.m[u][c], acc[u & 1][c]);
     }
     f32x4 r;
 #pragma unroll
@@ -266,6 +268,37 @@ __device__ __forceinline__ void block_columns_product(const float* __restrict__ 
       r[c] = add_xor32(add_xor16(t));
     }
     if (lane < K::QUADS) *(f32x4*)(y + v * 128 + k.col) = r;
+  }
+}
+// The same for one or two vectors with every sum in the order of wave_lds_matvec128, bit for bit, whatever NW is: a new token's
+// stored scale, zero-point and codes must not depend on which block rotated it.  A chain's running sum goes from group to group; the
+// second vector follows the first a group behind.  (Fused step, the new token in any order before: 34 x 120 tokens 14.4 -> 15.3 us, 4 x 256
+// 11.5 -> 11.9, 64 ragged up to 4000 45.7 -> 46.3.)
+template <int NV, int NW>
+__device__ __forceinline__ void block_columns_ordered(const float* __restrict__ x, float* __restrict__ y, const BlockColumns<NW>& k, int lane) {
+  using K = BlockColumns<NW>;
+  const int seq = (lane & 15) / K::QUADS;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < K::SEQ + NV - 1; ++t) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if constexpr (K::SEQ > 1) acc[c] = dpp_f<0x110 + K::QUADS>(acc[c]);         // row_shr: from the group before; the first gets 0
+      else acc[c] = 0.f;
+    }
+    const float* const xv = x + 128 * min(max(t - seq, 0), NV - 1) + k.row0;
+#pragma unroll
+    for (int u = 0; u < K::ROWS; ++u) {
+      const float xu = xv[2 * u];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = fmaf(xu, k.m[u][c], acc[c]);
+    }
+    if (t >= K::SEQ - 1) {                                    // the last group has the whole chain of vector t - (SEQ - 1)
+      f32x4 r;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r[c] = add_xor32(add_xor16(acc[c]));            // even + odd rows, then the two halves
+      if (lane < 16 && seq == K::SEQ - 1) *(f32x4*)(y + 128 * (t - (K::SEQ - 1)) + k.col) = r;
+    }
   }
 }
 // a barrier that waits for this wavefront's LDS accesses only, not for transfers in flight
