@@ -177,6 +177,22 @@ int saw_decode_plan(const saw_cache_t* cache, int32_t B, int32_t max_seq_len, in
                     int32_t* splits_out, int32_t* chunk_tokens_out);
 
 /*
+ * How a decode call of these arguments is handed to the chip (host-side, for inspection and tests; the rules may change from one
+ * version to the next).  cache16: the 16-bit comparison call; with_order: the call brings hints->order.  A fused append of bound
+ * max_seq_len is planned as a decode of max_seq_len + 1.  The workspace is taken to be what saw_decode_workspace_bytes says: with less
+ * a call takes the fixed partitions that saw_decode_plan reports.
+ */
+typedef struct saw_decode_schedule {
+  int32_t partitions;      /* fixed partitions per sequence; 0: the batch is cut by its own lengths into `slots` */
+  int32_t slots;           /* ... partitions of the whole batch per kv head (or pair of 64-channel heads); 0: fixed */
+  int32_t waves;           /* wavefronts of a block */
+  int32_t pair_seqs;       /* sequences that a block takes and shares out among its wavefronts: 2 or 3; 0: one per block */
+  int32_t longest_first;   /* 1: blocks take the sequences longest first */
+} saw_decode_schedule_t;
+int saw_decode_schedule(const saw_cache_t* cache, int32_t B, int32_t n_q_heads, int32_t max_seq_len, int32_t num_splits,
+                        int32_t cache16, int32_t with_order, saw_decode_schedule_t* out);
+
+/*
  * Host-side mirror of the longest-first order in which the decode kernels take a large batch's
  * sequences (they derive it themselves from seq_lens on the device; nothing has to be passed in).
  * For inspection and tests: seq_lens_host and order_out are HOST arrays of B <= 1024 entries;

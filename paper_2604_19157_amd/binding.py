@@ -35,6 +35,10 @@ class SawHints(ctypes.Structure):
     _fields_ = [("order", ctypes.c_void_p)]
 
 
+class SawSchedule(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("partitions", "slots", "waves", "pair_seqs", "longest_first")]
+
+
 class SawError(RuntimeError):
     def __init__(self, code: int, where: str):
         self.code = code
@@ -68,6 +72,7 @@ def lib() -> ctypes.CDLL:
         L.saw_decode_workspace_bytes.restype = sz
         L.saw_decode_workspace_bytes.argtypes = [cp, i32, i32, i32, i32]
         L.saw_decode_plan.argtypes = [cp, i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+        L.saw_decode_schedule.argtypes = [cp, i32, i32, i32, i32, i32, i32, ctypes.POINTER(SawSchedule)]
         L.saw_decode_rank_order.argtypes = [ctypes.POINTER(i32), i32, i32, ctypes.POINTER(i32)]
         L.saw_paged_decode_attn.argtypes = [cp, vp, i32, i32, i32, vp, i32, vp, i32, f32, vp, i32, vp, sz, i32, vp]
         L.saw_paged_decode_attn_static.argtypes = [cp, vp, i32, i32, i32, vp, i32, vp, i32, f32, vp, i32, i32, vp]
@@ -216,6 +221,14 @@ def decode_plan(cache: Cache, B, max_seq_len, num_splits=0):
     _check(lib().saw_decode_plan(ctypes.byref(st), B, max_seq_len, num_splits, ctypes.byref(s), ctypes.byref(c)),
            "saw_decode_plan")
     return s.value, c.value
+
+
+def decode_schedule(cache, B, n_q_heads, max_seq_len, num_splits=0, order=False):
+    """saw_decode_schedule of a decode call on a Cache or Kv16Cache, as a dict; a fused append: max_seq_len + 1."""
+    st, s = cache.struct(), SawSchedule()
+    _check(lib().saw_decode_schedule(ctypes.byref(st), B, n_q_heads, max_seq_len, num_splits, int(isinstance(cache, Kv16Cache)), int(order),
+                                     ctypes.byref(s)), "saw_decode_schedule")
+    return {n: getattr(s, n) for n, _ in s._fields_}
 
 
 def decode_rank_order(seq_lens, max_seq_len=0):

@@ -427,6 +427,28 @@ int saw_decode_plan(const saw_cache_t* c, int32_t B, int32_t max_seq_len, int32_
   return SAW_OK;
 }
 
+int saw_decode_schedule(const saw_cache_t* c, int32_t B, int32_t n_q_heads, int32_t max_seq_len, int32_t num_splits, int32_t cache16,
+                        int32_t with_order, saw_decode_schedule_t* out) {
+  if (!c || !out) return SAW_ENULL;
+  if (!shape_ok(c) || B < 1 || B > 65535 || c->n_kv_heads > 65535 || max_seq_len < 1 || n_q_heads < 1 || n_q_heads % c->n_kv_heads)
+    return SAW_EINVAL;
+  const int G = n_q_heads / c->n_kv_heads;
+  if (!(G == 1 || G == 2 || G == 4 || G == 8)) return SAW_EINVAL;
+  const bool kv16 = cache16 != 0;
+  SplitPlan plan;
+  if (!make_plan(c, B, G, false, (max_seq_len + c->page_size - 1) / c->page_size, max_seq_len, num_splits, kv16, &plan)) return SAW_EINVAL;
+  const BlockPlan blocks = plan_blocks(c, kv16, B, G, plan, with_order && !kv16);
+  out->partitions = plan.cut ? 0 : plan.num_splits;
+  out->slots = plan.cut;
+  // (the 16-bit kernels' blocks are of one wavefront, or two in pair mode; the one for single 64-channel heads has no block of two)
+  const int nw = plan.cut ? plan.cut_waves : plan.waves_per_item;
+  const bool single64 = !kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G);
+  out->waves = blocks.pair ? blocks.pair : kv16 ? 1 : single64 && nw == 2 ? 4 : nw;
+  out->pair_seqs = blocks.pair ? blocks.pair_seqs : 0;
+  out->longest_first = blocks.sorted;
+  return SAW_OK;
+}
+
 int saw_decode_rank_order(const int32_t* seq_lens_host, int32_t B, int32_t max_seq_len, int32_t* order_out) {
   if (!seq_lens_host || !order_out) return SAW_ENULL;
   if (B < 1 || B > 1024) return SAW_EINVAL;

@@ -41,6 +41,15 @@ struct DecodeParams {
   SignBits signs;           // R = diag(sigma) H_blk for every rotated tensor and the query; outputs take R^T
 };
 
+// How a launch with one partition per sequence hands the sequences to its blocks (see plan_blocks)
+struct BlockPlan {
+  int32_t pair;           // blocks of this many wavefronts (2 or 4) over several sequences; 0: a block per (sequence, kv head)
+  int32_t pair_seqs;      // ... 2 or 3 sequences
+  int32_t sorted;         // blocks take the sequences longest first
+};
+// `order`: the caller supplies the longest-first order
+BlockPlan plan_blocks(const saw_cache_t* c, bool kv16, int B, int G, const SplitPlan& plan, bool order);
+
 // Length classes of the in-kernel longest-first ranking (saw_rank.h), shared with the host-side
 // mirror saw_decode_rank_order.  `nbmax` is the batch's longest (clamped) sequence in 64-token
 // units.  Class 63 is for sequences without cached tokens only; the others spread over classes

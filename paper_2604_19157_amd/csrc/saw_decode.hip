@@ -276,6 +276,84 @@ int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, bool va
   return hipGetLastError() == hipSuccess ? SAW_OK : SAW_ELAUNCH;
 }
 
+// How the matrix-core INT4 kernel hands out work when one partition covers each sequence and the
+// batch provides more (sequence, kv head) items than compute units (and at most 16 lengths per
+// lane for the in-kernel ranking).  A compute unit holds 8 wavefronts of this kernel, 2048 on
+// the chip:
+//   * up to 2048 items everything is resident at once and nothing rebalances later, so the
+//     work is evened out up front: pair mode, blocks over (long, short) pairs of sequences, of
+//     four wavefronts while that still fits the 2048 slots and of two beyond.  Four-wavefront
+//     blocks pay off on ragged batches from 576 items on (256 sequences x 4 heads: 82 -> 70 us,
+//     90 x 8: 70 -> 61 us, 72 x 8: 63 -> 57 us against 2 or 4 wavefronts interleaving each
+//     item's batches; equal lengths lose 2-8 us to the ranking and the records; at 528 items
+//     four interleaving wavefronts per item are ahead: 51 against 64 us).  Between 1025 and 1151
+//     items two interleaving wavefronts per item still fit the slots well enough (136 x 8: 79
+//     against 94 us in pair mode); from 1152 on they spill into a second round.  Up to 1536
+//     items blocks of four wavefronts over THREE sequences then fill the chip where blocks of two
+//     over pairs leave a quarter to a half of the slots empty (144 x 8: 93 -> 83 us, 160 x 8:
+//     93 -> 85 us, 176 x 8: 94 -> 89 us, level at 192 x 8), beyond that blocks of two;
+//   * beyond that blocks queue for slots in index order, which is list scheduling: one
+//     wavefront per item, sequences taken longest first, so the launch ends on the shortest.
+//     (Measured at 288..512 sequences x 8 heads: 173-270 us against 224-332 us in pair mode,
+//     whose equal blocks make the last round as long as the others; 2 or 4 wavefronts per item
+//     were never better.);
+//   * short bounds leave nothing worth evening out: the plan's wavefronts take each sequence as it comes, without the ranking
+//     and the records (two of them up to 1151 items, one above).  96 x 8 of 250 tokens 20 -> 14 us, ragged up to 500 23 -> 17, 128 x 8
+//     x 500 25 -> 19; 144 x 8 x 250 25 -> 19, 256 x 8 ragged up to 250 25 -> 20, 512 x 8 x 63 37 -> 25.  Above these bounds the batches
+//     with a few long sequences lose (128 x 8 up to 750 tokens by 6 %, 192 x 8 up to 500 by 7 %).  The caller's order saves the
+//     ranking: with it up to 256 tokens and 1024 items only (128 x 8 x 250 18 -> 14 us, up to 500 tokens 16 -> 17; 130 x 8 x 63
+//     14 -> 17, 400 x 8 ragged up to 250 30 -> 33).
+BlockPlan plan_blocks(const saw_cache_t* c, bool kv16, int B, int G, const SplitPlan& plan, bool order) {
+  BlockPlan r = {0, 2, 0};
+  if (plan.cut || plan.num_splits != 1 || B > 1024 || plan.valu16) return r;
+  const int64_t n_kv = (int64_t)B * c->n_kv_heads;
+  if (kv16) {
+    // the 16-bit matrix-core kernel has the two-wavefront pair mode as well (same conditions), so that
+    // the comparison on a ragged batch is between formats and not between schedules; only above bounds of 256 tokens (48 x 8 ragged
+    // up to 250 tokens 26 us with pair blocks, 22 without, 256 x 8 x 250 59 and 53, 96 x 8 x 63 18 and 13; from 500 tokens on level, and
+    // 256 x 8 ragged up to 1000 ahead by 8 %), and for the shapes with eight query heads per kv head or head_dim 64 only above 1024: of
+    // shorter sequences the ranking takes longer than it saves (257 x 1 kv heads of 128, eight query heads each, up to 150 tokens
+    // 27.6 us with pair blocks, 15.7 without; 256 x 8 of 600 equal tokens level, ragged up to 1200 with them ahead by 6 %)
+    if (plan.bound > (c->head_dim == 128 && G <= 4 ? 256 : 1024) && n_kv > 256 && (int64_t)((B + 1) / 2) * c->n_kv_heads <= 1024) r.pair = 2;
+    return r;
+  }
+  if (c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G)) {
+    r.sorted = order && n_kv > 256;             // one 64-channel head at a time: the caller's order, if there is one
+    return r;
+  }
+  const int per_seq = decode_items_per_seq(c->head_dim, c->n_kv_heads);   // head_dim 64: pairs of kv heads
+  const int64_t items = (int64_t)B * per_seq;
+  const int64_t blocks = (int64_t)((B + 1) / 2) * per_seq, blocks3 = (int64_t)((B + 2) / 3) * per_seq;
+  // (blocks over three sequences: not for head pairs with eight query rows, two such blocks of four with their two spare records do
+  // not fit a compute unit's LDS)
+  const bool threes = !(c->head_dim == 64 && G == 4);
+  const int short_bound = items <= 1024 ? (order ? 256 : 512) : (order ? 0 : 256);
+  if (items < 576 || plan.chunk_tokens <= short_bound) return r;
+  if (blocks <= 512) {
+    r.pair = 4;
+  } else if (items >= 1152 && blocks3 <= 512 && threes) {
+    r.pair = 4;
+    r.pair_seqs = 3;
+  } else if (items >= 1152 && blocks <= 1024) {
+    r.pair = 2;                                 // (whatever the plan's wavefronts per item)
+  } else if (items > 1024 && (plan.waves_per_item == 1 || plan.chunk_tokens <= 256)) {
+    // (1025 to 1151 items get here only with the caller's order, which makes pairs cheap; without it they keep the plan's two wavefronts)
+    if (blocks <= 1024) {
+      r.pair = 2;
+    } else if (items <= 2304 && blocks3 <= 1024 && threes) {
+      // just above 2048 items: blocks of two wavefronts over THREE sequences keep everything resident
+      // (equal lengths, where the longest-first order has nothing to reorder and the last 32 items ran
+      // alone: 260 x 8 sequences of 2304 tokens 165 -> 135 us; ragged batches 137-148 us either way up
+      // to 288 x 8; from 320 x 8 on the longest-first order is ahead: 155 against 166 us)
+      r.pair = 2;
+      r.pair_seqs = 3;
+    } else {
+      r.sorted = 1;
+    }
+  }
+  return r;
+}
+
 int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void* v_pages, int kv_dtype,
                const void* q, int q_dtype, int B, int Hq, const int32_t* pt, int max_pages,
                const int32_t* seq_lens, float sm_scale, void* out, int out_dtype, void* ws,
@@ -315,86 +393,16 @@ int run_decode(const saw_cache_t* c, bool kv16, const void* k_pages, const void*
   p.cut = plan.cut;
   p.cut_min = plan.cut_min;
   p.cut_of = plan.cut ? (int2*)((uint8_t*)ws + partial_bytes(1, Hq, plan.cut, c->head_dim)) : nullptr;
-  // Pair mode: one partition per sequence, enough (sequence, kv head) items that every compute
-  // unit gets several, and at most 16 lengths per lane for the in-kernel ranking.
   p.k_new = k_new;
   p.v_new = v_new;
   p.kv_new_dtype = kv_new_dtype;
   p.append = k_new != nullptr;
   p.batch = B;
-  // How the matrix-core INT4 kernel hands out work when one partition covers each sequence and the
-  // batch provides more (sequence, kv head) items than compute units (and at most 16 lengths per
-  // lane for the in-kernel ranking).  A compute unit holds 8 wavefronts of this kernel, 2048 on
-  // the chip:
-  //   * up to 2048 items everything is resident at once and nothing rebalances later, so the
-  //     work is evened out up front: pair mode, blocks over (long, short) pairs of sequences, of
-  //     four wavefronts while that still fits the 2048 slots and of two beyond.  Four-wavefront
-  //     blocks pay off on ragged batches from 576 items on (256 sequences x 4 heads: 82 -> 70 us,
-  //     90 x 8: 70 -> 61 us, 72 x 8: 63 -> 57 us against 2 or 4 wavefronts interleaving each
-  //     item's batches; equal lengths lose 2-8 us to the ranking and the records; at 528 items
-  //     four interleaving wavefronts per item are ahead: 51 against 64 us).  Between 1025 and 1151
-  //     items two interleaving wavefronts per item still fit the slots well enough (136 x 8: 79
-  //     against 94 us in pair mode); from 1152 on they spill into a second round.  Up to 1536
-  //     items blocks of four wavefronts over THREE sequences then fill the chip where blocks of two
-  //     over pairs leave a quarter to a half of the slots empty (144 x 8: 93 -> 83 us, 160 x 8:
-  //     93 -> 85 us, 176 x 8: 94 -> 89 us, level at 192 x 8), beyond that blocks of two;
-  //   * beyond that blocks queue for slots in index order, which is list scheduling: one
-  //     wavefront per item, sequences taken longest first, so the launch ends on the shortest.
-  //     (Measured at 288..512 sequences x 8 heads: 173-270 us against 224-332 us in pair mode,
-  //     whose equal blocks make the last round as long as the others; 2 or 4 wavefronts per item
-  //     were never better.);
-  //   * short bounds leave nothing worth evening out: the plan's wavefronts take each sequence as it comes, without the ranking
-  //     and the records (two of them up to 1151 items, one above).  96 x 8 of 250 tokens 20 -> 14 us, ragged up to 500 23 -> 17, 128 x 8
-  //     x 500 25 -> 19; 144 x 8 x 250 25 -> 19, 256 x 8 ragged up to 250 25 -> 20, 512 x 8 x 63 37 -> 25.  Above these bounds the batches
-  //     with a few long sequences lose (128 x 8 up to 750 tokens by 6 %, 192 x 8 up to 500 by 7 %).  The caller's order saves the
-  //     ranking: with it up to 256 tokens and 1024 items only (128 x 8 x 250 18 -> 14 us, up to 500 tokens 16 -> 17; 130 x 8 x 63
-  //     14 -> 17, 400 x 8 ragged up to 250 30 -> 33).
-  p.pair = 0;
-  p.pair_seqs = 2;
-  p.sorted = 0;
   const int G = Hq / c->n_kv_heads;
-  const int items = decode_items_per_seq(c->head_dim, c->n_kv_heads);   // head_dim 64: pairs of kv heads
-  if (!kv16 && (c->head_dim == 128 || decode_head_pairs(c->head_dim, c->n_kv_heads, G)) &&
-      !plan.cut && plan.num_splits == 1 && B <= 1024) {
-    const int64_t blocks = (int64_t)((B + 1) / 2) * items;
-    const int64_t blocks3 = (int64_t)((B + 2) / 3) * items;
-    const bool crowded = (int64_t)B * items > 1024;
-    const int short_bound = p.order ? (crowded ? 0 : 256) : crowded ? 256 : 512;
-    if ((int64_t)B * items < 576 || p.chunk_tokens <= short_bound) {}   // blocks of the plan's wavefronts
-    else if ((int64_t)B * items >= 576 && blocks <= 512) p.pair = 4;
-    else if ((int64_t)B * items >= 1152 && blocks3 <= 512 && !(c->head_dim == 64 && G == 4)) {
-      // four wavefronts over three sequences (not for head pairs with eight query rows: two such
-      // blocks with their two spare records do not fit a compute unit's LDS)
-      p.pair = 4;
-      p.pair_seqs = 3;
-    }
-    else if ((int64_t)B * items >= 1152 && blocks <= 1024) p.pair = 2;   // (whatever the plan's wavefronts per item)
-    else if (crowded && (plan.waves_per_item == 1 || p.chunk_tokens <= 256)) {
-      if (blocks <= 1024) p.pair = 2;
-      else if ((int64_t)B * items <= 2304 && blocks3 <= 1024 && !(c->head_dim == 64 && G == 4)) {
-        // just above 2048 items: blocks of two wavefronts over THREE sequences keep everything resident
-        // (equal lengths, where the longest-first order has nothing to reorder and the last 32 items ran
-        // alone: 260 x 8 sequences of 2304 tokens 165 -> 135 us; ragged batches 137-148 us either way up
-        // to 288 x 8; from 320 x 8 on the longest-first order is ahead: 155 against 166 us)
-        p.pair = 2;
-        p.pair_seqs = 3;
-      }
-      else p.sorted = 1;
-    }
-  }
-  // one 64-channel head at a time: the caller's order, if there is one (and one partition covers a sequence)
-  if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G) && !plan.cut && plan.num_splits == 1 &&
-      order && B <= 1024 && (int64_t)B * c->n_kv_heads > 256)
-    p.sorted = 1;
-  // the 16-bit matrix-core kernel has the two-wavefront pair mode as well (same conditions), so that
-  // the comparison on a ragged batch is between formats and not between schedules; only above bounds of 256 tokens (48 x 8 ragged
-  // up to 250 tokens 26 us with pair blocks, 22 without, 256 x 8 x 250 59 and 53, 96 x 8 x 63 18 and 13; from 500 tokens on level, and 256 x 8
-  // ragged up to 1000 ahead by 8 %), and for the shapes with eight query heads per kv head or head_dim 64 only above 1024: of
-  // shorter sequences the ranking takes longer than it saves (257 x 1 kv heads of 128, eight query heads each, up to 150 tokens
-  // 27.6 us with pair blocks, 15.7 without; 256 x 8 of 600 equal tokens level, ragged up to 1200 with them ahead by 6 %)
-  if (kv16 && !plan.valu16 && !plan.cut && plan.num_splits == 1 && B <= 1024 && plan.bound > (c->head_dim == 128 && G <= 4 ? 256 : 1024) &&
-      (int64_t)B * c->n_kv_heads > 256 && (int64_t)((B + 1) / 2) * c->n_kv_heads <= 1024)
-    p.pair = 2;
+  const BlockPlan blocks = plan_blocks(c, kv16, B, G, plan, p.order != nullptr);
+  p.pair = blocks.pair;
+  p.pair_seqs = blocks.pair_seqs;
+  p.sorted = blocks.sorted;
   return launch_decode(p, B, c->head_dim, G, kv16, plan.valu16 != 0, kv_dtype, st);
 }
 

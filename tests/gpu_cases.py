@@ -102,3 +102,23 @@ def compare_store(got: dict, ref: dict, recs: list) -> dict:
         untouched_ok &= not got[which + "_meta"][~written].any()
     total["untouched_ok"] = bool(untouched_ok)
     return total
+
+
+def check_schedule(saw, cache, B, n_q_heads, bound, want, num_splits=0, order=False):
+    """The call that follows is handed out as its test means it to be (`want`: part of saw.decode_schedule; None: whatever)."""
+    if want is not None:
+        got = saw.decode_schedule(cache, B, n_q_heads, bound, num_splits, order)
+        assert {k: got[k] for k in want} == want, (got, want)
+
+
+def pairs(waves, seqs=2):
+    return dict(partitions=1, waves=waves, pair_seqs=seqs)
+
+
+def by_items(items):
+    """Schedule of one-partition batches of long bounds, by (sequence, kv head) items."""
+    if items < 576 or 1024 < items < 1152:
+        return dict(partitions=1, pair_seqs=0, longest_first=0)
+    if items > 2304:
+        return dict(partitions=1, pair_seqs=0, longest_first=1)
+    return pairs(4) if items <= 1024 else pairs(4, 3) if items <= 1536 else pairs(2) if items <= 2048 else pairs(2, 3)

@@ -36,12 +36,15 @@ def _new_tokens(w):
     return torch.cat(ks).contiguous(), torch.cat(vs).contiguous()
 
 
-def _case(saw, w, out_dtype=torch.float32, unmapped=(), max_seq_len=None, order=None):
+def _case(saw, w, out_dtype=torch.float32, unmapped=(), max_seq_len=None, order=None, expect=None):
     """`unmapped`: sequences whose new token's page is taken out of the page table (attended, not stored).
-    `max_seq_len`: the host-side bound handed to the call (None: the longest sequence; 0: the default)."""
+    `max_seq_len`: the host-side bound handed to the call (None: the longest sequence; 0: the default).
+    `expect`: how the call has to be handed out (gc.check_schedule)."""
     B = w.batch
     ref = gc.oracle_fill(w)
     cache = gc.upload_cache(ref, w, saw)
+    bound = int(w.seq_lens.max()) if max_seq_len is None else max_seq_len
+    gc.check_schedule(saw, cache, B, w.n_q_heads, bound + 1 if bound else 16 * w.max_pages_per_seq, expect, order=order is not None)
     page_table = w.page_table.copy()
     for b in unmapped:
         page_table[b, int(w.seq_lens[b]) >> 4] = -1
@@ -115,23 +118,23 @@ def test_small_batch_one_launch(saw):
                                    head_dim=64, had_block=64))                                           # head pairs
 
 
-@pytest.mark.parametrize("B,Hkv", [(70, 8), (129, 4), (150, 8), (191, 8), (200, 8), (300, 8), (260, 8), (288, 8)])
+@pytest.mark.parametrize("B,Hkv", [(72, 8), (144, 4), (150, 8), (191, 8), (200, 8), (300, 8), (260, 8), (288, 8)])
 def test_large_ragged_batch_pair_mode(saw, B, Hkv):
     rng = np.random.default_rng(B)
     lens = rng.integers(0, 330, size=B)
     lens[:6] = [0, 329, 1, 16, 15, 64]                       # empty, page boundaries, batch boundary
-    w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv)
-    _case(saw, w)
+    w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv, table_width=64)
+    _case(saw, w, max_seq_len=0, expect=gc.by_items(B * Hkv))
 
 
-@pytest.mark.parametrize("B,Hkv", [(70, 8), (150, 8), (200, 8), (300, 8)])
+@pytest.mark.parametrize("B,Hkv", [(72, 8), (150, 8), (200, 8), (300, 8)])
 def test_caller_supplied_order(saw, B, Hkv):
     """saw_append_decode_attn_hinted: the same step with the longest-first order supplied by the caller."""
     rng = np.random.default_rng(B + 2)
     lens = rng.integers(0, 330, size=B)
     lens[:6] = [0, 329, 1, 16, 15, 64]
     w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv)
-    _case(saw, w, order=np.argsort(-lens, kind="stable"))
+    _case(saw, w, order=np.argsort(-lens, kind="stable"), expect=gc.by_items(B * Hkv))
 
 
 @pytest.mark.parametrize("h,mask", [(1, 3), (16, 3), (32, 3), (64, 3), (128, 3), (64, 1), (64, 2)])
@@ -175,9 +178,9 @@ def test_several_partitions_with_lengths_on_partition_boundaries(saw):
 
 
 def test_pair_blocks_of_four_with_empty_sequences(saw):
-    """512 items: four-wavefront pair blocks; empty sequences still attend to (and store) their new token."""
-    lens = [0] * 20 + [1] * 10 + [64] * 10 + [200] * 23 + [129]
-    _case(saw, synth.make_workload("highconc", batch=len(lens), seq_lens=lens))
+    """576 items, a page table of 1024 tokens: four-wavefront pair blocks; empty sequences still attend to (and store) their new token."""
+    lens = [0] * 24 + [1] * 12 + [64] * 12 + [200] * 23 + [129]
+    _case(saw, synth.make_workload("highconc", batch=len(lens), seq_lens=lens, table_width=64), max_seq_len=0, expect=gc.pairs(4))
 
 
 @pytest.mark.parametrize("seed", range(100, 112))
@@ -205,7 +208,8 @@ def test_empty_sequence_first_under_a_loose_bound(saw, lens, width):
     share a length class with the non-empty ones and rank ahead of them: blocks of two wavefronts (2048
     items), of four over pairs (1024 items) and of four over three sequences.  The ranking keeps empty
     sequences in a class of their own, so the block's first sequence is never the empty one."""
-    _case(saw, synth.make_workload("highconc", batch=len(lens), seq_lens=lens, table_width=width), max_seq_len=0)
+    _case(saw, synth.make_workload("highconc", batch=len(lens), seq_lens=lens, table_width=width), max_seq_len=0,
+          expect=gc.by_items(8 * len(lens)))
 
 
 def test_length_beyond_the_bound_is_not_stored(saw):

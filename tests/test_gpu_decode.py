@@ -20,13 +20,15 @@ def saw():
 
 
 def _decode_case(saw, w, num_splits=0, out_dtype=torch.float32, sm_scale=0.0, q_dtype=None, end_to_end=True,
-                 max_seq_len=None, order=None):
+                 max_seq_len=None, order=None, expect=None):
     """Criterion: both sides attend over the SAME bytes, the ones the oracle's store wrote (uploaded to
     the device cache), so the decode kernel is compared with the oracle independently of the store.
     `max_seq_len`: the host-side bound handed to the call (None: the longest sequence; 0: the call's
-    default, the page table's capacity)."""
+    default, the page table's capacity).  `expect`: how the call has to be handed out (gc.check_schedule)."""
     ref = gc.oracle_fill(w)
     cache = gc.upload_cache(ref, w, saw)
+    gc.check_schedule(saw, cache, w.batch, w.n_q_heads, (int(w.seq_lens.max()) if max_seq_len is None else max_seq_len) or
+                      16 * w.max_pages_per_seq, expect, num_splits, order is not None)
     pt = torch.from_numpy(w.page_table).cuda()
     q = synth.gen_q(w)
     if q_dtype is not None:
@@ -90,22 +92,22 @@ def test_ragged_lengths_with_empty_and_single(saw):
     assert not o[0].any()                                           # empty sequence -> zero row
 
 
-@pytest.mark.parametrize("B,Hkv", [(70, 8), (129, 4), (300, 2), (65, 8), (130, 8), (162, 8), (191, 8), (383, 4),
+@pytest.mark.parametrize("B,Hkv", [(72, 8), (144, 4), (300, 2), (80, 8), (144, 8), (162, 8), (191, 8), (383, 4),
                                    (200, 8), (255, 8), (300, 8), (257, 8), (260, 8), (288, 8), (575, 4)])
 def test_many_sequences_balanced_item_order(saw, B, Hkv):
     """More (sequence, kv head) items than compute units: the kernel pairs long with short sequences
     (everything resident at once: blocks of four wavefronts per pair from 576 to 1024 items, the first
     four cases, blocks of four over three sequences up to 1536 items, the next four, blocks of two up to
     2048 items, blocks of two over three sequences up to 2304 items, the last four) or, beyond that, takes
-    them longest first.  Every sequence is
+    them longest first.  (Under a bound above 512 tokens: a page table of 1024.)  Every sequence is
     compared, so an item served twice or never shows up; lengths include empty sequences and many ties."""
     rng = np.random.default_rng(B)
     lens = rng.integers(0, 330, size=B)
     lens[rng.integers(0, B, size=B // 5)] = 64                      # ties
     lens[:3] = [0, 329, 1]
-    w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv)
-    _decode_case(saw, w, num_splits=1, end_to_end=False)
-    _decode_case(saw, w, num_splits=0, end_to_end=False)
+    w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv, table_width=64)
+    _decode_case(saw, w, num_splits=1, end_to_end=False, max_seq_len=0, expect=gc.by_items(B * Hkv))
+    _decode_case(saw, w, num_splits=0, end_to_end=False, max_seq_len=0, expect=gc.by_items(B * Hkv))
 
 
 @pytest.mark.parametrize("lens,kw", [([0, 1, 63, 64, 65, 500], {}), ([2304] * 4 + [0, 7], {}), ([2500] * 30, {}),
@@ -228,25 +230,27 @@ def test_kv16_batch_edges(saw, dtype, G, Hkv, d, big):
                                   [200] * 2 + [1] * 62, [129] * 33 + [0] * 32, [256] + [0] * 63,
                                   list(range(64)), [128] * 64, [64 * (i % 5) for i in range(64)]])
 def test_pair_blocks_of_four_share_boundaries(saw, lens):
-    """64 sequences x 8 kv heads = 512 items: blocks of four wavefronts over (long, short) pairs.  The
-    lengths put the cuts between the wavefronts' shares everywhere: fewer batches than wavefronts,
+    """72 sequences x 8 kv heads = 576 items, a page table of 1024 tokens: blocks of four wavefronts over (long, short) pairs.  The
+    lengths (the last eight once more) put the cuts between the wavefronts' shares everywhere: fewer batches than wavefronts,
     empty sequences, the pair's boundary on a cut, inside a share, and a short sequence that is
     itself shared between wavefronts."""
-    w = synth.make_workload("highconc", batch=len(lens), seq_lens=lens)
-    _decode_case(saw, w, end_to_end=False)
+    lens = lens + lens[-8:]
+    w = synth.make_workload("highconc", batch=len(lens), seq_lens=lens, table_width=64)
+    _decode_case(saw, w, end_to_end=False, max_seq_len=0, expect=gc.pairs(4))
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("B,Hq,Hkv", [(70, 32, 8), (129, 4, 4), (255, 16, 8)])
 def test_kv16_comparison_path_pair_mode(saw, dtype, B, Hq, Hkv):
     """The 16-bit kernel's two-wavefront blocks over (long, short) sequence pairs (one partition, 257..2048
-    items): every sequence compared, lengths with empty sequences and ties."""
+    items, bounds above 256 tokens): every sequence compared, lengths with empty sequences and ties."""
     rng = np.random.default_rng(B)
     lens = rng.integers(0, 200, size=B)
     lens[rng.integers(0, B, size=B // 5)] = 32
     lens[:4] = [0, 199, 1, 33]
-    w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=Hq, n_kv_heads=Hkv, dtype=dtype)
+    w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=Hq, n_kv_heads=Hkv, dtype=dtype, table_width=17)
     kc = saw.Kv16Cache(w.num_pages, Hkv, w.head_dim, dtype)
+    gc.check_schedule(saw, kc, B, Hq, 16 * 17, gc.pairs(2), num_splits=1)
     pt = torch.from_numpy(w.page_table).cuda()
     for b in range(w.batch):
         L = int(w.seq_lens[b])
@@ -299,7 +303,7 @@ def test_random_shapes(saw, seed):
     _decode_case(saw, w, num_splits=splits, end_to_end=False)
 
 
-@pytest.mark.parametrize("B,Hkv", [(70, 8), (129, 4), (150, 8), (191, 8), (200, 8), (255, 8), (300, 8), (383, 4)])
+@pytest.mark.parametrize("B,Hkv", [(72, 8), (144, 4), (150, 8), (191, 8), (200, 8), (255, 8), (300, 8), (383, 4)])
 def test_caller_supplied_order(saw, B, Hkv):
     """saw_paged_decode_attn_hinted: the longest-first order comes from the caller (a stable host sort of the
     lengths, empty sequences last) and the kernels skip their own ranking: pair blocks of two and of four,
@@ -310,7 +314,7 @@ def test_caller_supplied_order(saw, B, Hkv):
     lens[:3] = [0, 329, 1]
     w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv)
     order = np.argsort(-lens, kind="stable")
-    o, _ = _decode_case(saw, w, num_splits=1, end_to_end=False, order=order)
+    o, _ = _decode_case(saw, w, num_splits=1, end_to_end=False, order=order, expect=gc.by_items(B * Hkv))
     assert not o[lens == 0].any()
     # entries outside [0, B) are clamped: nothing out of bounds, whatever the rows hold
     cache = gc.upload_cache(gc.oracle_fill(w), w, saw)
@@ -359,7 +363,7 @@ def test_empty_sequences_under_a_loose_bound(saw, lens, Hkv):
     three sequences, and the longest-first order."""
     w = synth.make_workload("highconc", batch=len(lens), seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv,
                             table_width=8192)
-    o, _ = _decode_case(saw, w, end_to_end=False, max_seq_len=0)
+    o, _ = _decode_case(saw, w, end_to_end=False, max_seq_len=0, expect=gc.by_items(len(lens) * Hkv))
     assert not o[np.asarray(lens) == 0].any()
 
 
@@ -370,9 +374,9 @@ def test_blocks_of_two_over_three_sequences(saw, lens):
     """2049..2304 items: a block of two wavefronts takes three sequences laid end to end; the one cut between
     the two shares falls in any of them (a wavefront that holds the head of a shared sequence and an earlier
     sequence after it leaves that record in the block's spare slot), in a gap, or nowhere (empty sequences)."""
-    w = synth.make_workload("highconc", batch=len(lens), seq_lens=lens)
-    _decode_case(saw, w, end_to_end=False)
-    _decode_case(saw, w, end_to_end=False, order=np.argsort(-np.asarray(lens), kind="stable"))
+    w = synth.make_workload("highconc", batch=len(lens), seq_lens=lens, table_width=64)
+    _decode_case(saw, w, end_to_end=False, max_seq_len=0, expect=gc.pairs(2, 3))
+    _decode_case(saw, w, end_to_end=False, max_seq_len=0, expect=gc.pairs(2, 3), order=np.argsort(-np.asarray(lens), kind="stable"))
 
 
 @pytest.mark.parametrize("lens", [[0] * 150, [1] * 150, [64] * 100 + [0] * 50, [200] * 3 + [1] * 147,
@@ -383,8 +387,8 @@ def test_blocks_of_four_over_three_sequences(saw, lens):
     put the cuts everywhere: sequences that fit inside one share (three ranges for one wavefront), empty
     sequences, batches fewer than wavefronts, a batch size that leaves the last block with one or two
     sequences only."""
-    w = synth.make_workload("highconc", batch=len(lens), seq_lens=lens)
-    _decode_case(saw, w, end_to_end=False)
+    w = synth.make_workload("highconc", batch=len(lens), seq_lens=lens, table_width=64)
+    _decode_case(saw, w, end_to_end=False, max_seq_len=0, expect=gc.pairs(4, 3))
 
 
 @pytest.mark.parametrize("seed", range(200, 230))

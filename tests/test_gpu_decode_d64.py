@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+import gpu_cases as gc
 import test_gpu_append as TA
 import test_gpu_decode as TD
 from paper_2604_19157_amd import synth
@@ -63,21 +64,23 @@ def test_head_pairs_ragged_with_empty_and_single(saw):
     assert not o[0].any()
 
 
-@pytest.mark.parametrize("B,Hq,Hkv", [(70, 32, 8), (140, 16, 4), (150, 32, 8), (255, 8, 8), (300, 8, 8), (340, 16, 8),
+@pytest.mark.parametrize("B,Hq,Hkv", [(140, 32, 8), (140, 16, 4), (150, 32, 8), (255, 8, 8), (300, 8, 8), (340, 16, 8),
                                       (340, 32, 8), (600, 8, 8)])
 def test_head_pairs_many_sequences(saw, B, Hq, Hkv):
-    """More (sequence, head pair) items than compute units: pair mode (blocks of two wavefronts, of four
-    from 576 to 1024 items: the third and fourth case; of four over three sequences from 1152 to 1536 items:
-    the sixth, while the seventh, with eight query rows per head pair, stays with blocks of two), longest first
-    beyond 2048 items (the last case).
+    """More (sequence, head pair) items than compute units, under a bound of 1024 tokens: four or two wavefronts a sequence (560 and
+    280 items, the first two cases), pair mode (blocks of four from 576 to 1024 items: the third and fourth case; of four over three
+    sequences from 1152 to 1536 items: the fifth and sixth, while the seventh, with eight query rows per head pair, takes blocks of two),
+    longest first beyond 2304 items (the last case).
     Lengths include empty sequences and many ties."""
     rng = np.random.default_rng(B)
     lens = rng.integers(0, 200, size=B)
     lens[rng.integers(0, B, size=B // 5)] = 64
     lens[:3] = [0, 199, 1]
-    w = _w(batch=B, seq_lens=lens, n_q_heads=Hq, n_kv_heads=Hkv)
-    TD._decode_case(saw, w, num_splits=1, end_to_end=False)
-    TD._decode_case(saw, w, num_splits=0, end_to_end=False)
+    w = _w(batch=B, seq_lens=lens, n_q_heads=Hq, n_kv_heads=Hkv, table_width=64)
+    items = B * Hkv // 2
+    expect = gc.pairs(2) if 1152 <= items <= 2048 and Hq == 4 * Hkv else gc.by_items(items)
+    TD._decode_case(saw, w, num_splits=1, end_to_end=False, max_seq_len=0, expect=expect)
+    TD._decode_case(saw, w, num_splits=0, end_to_end=False, max_seq_len=0, expect=expect)
 
 
 def test_head_pairs_long_context_several_wavefronts(saw):
@@ -130,7 +133,6 @@ def test_one_head_at_a_time_batch_edges(saw, Hq, Hkv, dtype, kw, B):
     the rounding of fp32 sums: Sum w c of up to 15 s, from which about half is taken away again with the zero-points
     (2^-24 a step of that, tens of steps: 2^-20 s), against outputs of a few s that shrink with sqrt(L) as the values
     average out: 4e-6 sqrt(max(L / 300, 1)) of the largest output."""
-    import gpu_cases as gc
     from oracle import saw_oracle as O
     import parity
     rng = np.random.default_rng(B + Hq)
@@ -178,7 +180,6 @@ def test_one_head_at_a_time_batch_edges(saw, Hq, Hkv, dtype, kw, B):
 @pytest.mark.parametrize("B", [2, 40, 300])
 def test_append_of_a_length_below_zero_stores_nothing(saw, Hq, Hkv, B):
     """Such a sequence has no position for its token: its pages stay as they are, and the others' tokens are stored."""
-    import gpu_cases as gc
     lens = [50 + (37 * b) % 900 for b in range(B)]
     w = _w(batch=B, seq_lens=lens, n_q_heads=Hq, n_kv_heads=Hkv, table_width=400)
     cache = gc.upload_cache(gc.oracle_fill(w), w, saw)
@@ -199,7 +200,6 @@ def test_append_of_a_length_below_zero_stores_nothing(saw, Hq, Hkv, B):
 def test_a_bound_beyond_what_can_be_cut_keeps_partitions(saw):
     """256 sequences under the bound of a page table of two million tokens: more 64-token batches than the device's cut
     counts, so the batch is split by that bound, and every partition that runs leaves a record in the workspace."""
-    import gpu_cases as gc
     B, Hq, width = 256, 8, 131072
     w = _w(batch=B, seq_lens=[100 + b for b in range(B)], n_q_heads=Hq, n_kv_heads=1, table_width=32)
     cache = gc.upload_cache(gc.oracle_fill(w), w, saw)

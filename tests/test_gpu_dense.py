@@ -72,14 +72,22 @@ def test_decode_with_learned_rotation(saw, kw, splits):
     TD._decode_case(saw, w, num_splits=splits)
 
 
-@pytest.mark.parametrize("B,Hkv", [(70, 8), (150, 8), (200, 8)])
-def test_decode_with_learned_rotation_pair_mode(saw, B, Hkv):
-    import test_gpu_decode as TD
+# pair blocks of four over two sequences, over three, of two over two, over three; longest first
+PAIRS = [(72, 8, 4), (600, 1, 8), (150, 8, 4), (300, 4, 1), (600, 2, 8), (200, 8, 4), (400, 4, 2), (900, 2, 8), (260, 8, 4), (520, 4, 8),
+         (300, 8, 2)]
+
+
+def _pair_workload(B, Hkv, G):
     rng = np.random.default_rng(B)
     lens = rng.integers(0, 200, size=B)
-    lens[:3] = [0, 199, 1]
-    w = synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=4 * Hkv, n_kv_heads=Hkv, dense_seed=5)
-    TD._decode_case(saw, w, end_to_end=False)
+    lens[:6] = [0, 199, 1, 64, 0, 128]
+    return synth.make_workload("highconc", batch=B, seq_lens=lens, n_q_heads=G * Hkv, n_kv_heads=Hkv, dense_seed=5, table_width=64)
+
+
+@pytest.mark.parametrize("B,Hkv,G", PAIRS)
+def test_decode_with_learned_rotation_pair_mode(saw, B, Hkv, G):
+    import test_gpu_decode as TD
+    TD._decode_case(saw, _pair_workload(B, Hkv, G), end_to_end=False, max_seq_len=0, expect=gc.by_items(B * Hkv))
 
 
 @pytest.mark.parametrize("kw", [dict(batch=3, seq_lens=[0, 47, 200]), dict(batch=3, seq_lens=[5, 64, 130], rotate_mask=1),
@@ -90,11 +98,10 @@ def test_append_with_learned_rotation(saw, kw):
     TA._case(saw, synth.make_workload("llama8b", dense_seed=29, **kw))
 
 
-def test_append_with_learned_rotation_pair_mode(saw):
+@pytest.mark.parametrize("B,Hkv,G", PAIRS)
+def test_append_with_learned_rotation_pair_mode(saw, B, Hkv, G):
     import test_gpu_append as TA
-    rng = np.random.default_rng(12)
-    lens = rng.integers(0, 200, size=150)
-    TA._case(saw, synth.make_workload("highconc", batch=150, seq_lens=lens, dense_seed=31))
+    TA._case(saw, _pair_workload(B, Hkv, G), max_seq_len=0, expect=gc.by_items(B * Hkv))
 
 
 @pytest.mark.parametrize("mask,h", [(3, 128), (1, 64), (2, 16), (3, 1)])

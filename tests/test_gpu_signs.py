@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import gpu_cases as gc
 import test_gpu_append as TA
 import test_gpu_decode as TD
 import test_gpu_flatten as TF
@@ -65,10 +66,12 @@ def test_signs_change_the_codes_and_plain_cache_ignores_them(saw):
                                      ("tiny", dict(batch=2, ctx=(200, 900), rotate_mask=1)),      # K only
                                      ("tiny", dict(batch=2, ctx=(200, 900), rotate_mask=2)),      # V only
                                      ("longctx1", dict(ctx=3000, had_block=64)),                  # G = 8, split-KV + merge
-                                     ("highconc", dict(batch=70, ctx=(1, 200))),                  # pair mode
+                                     ("highconc", dict(batch=72, ctx=(1, 200), table_width=64)),  # pair mode
                                      ("prefill_mha", dict(ctx=150, had_block=16))])               # d = 64 path
 def test_decode_with_signs(saw, name, kw):
     w = synth.make_workload(name, sign_seed=21, **kw)
+    if name == "highconc":
+        TD._decode_case(saw, w, max_seq_len=0, expect=gc.pairs(4))
     TD._decode_case(saw, w)
 
 
@@ -79,11 +82,14 @@ def test_decode_with_signs_forced_splits(saw, splits):
 
 
 @pytest.mark.parametrize("name,kw", [("tiny", dict(batch=3, ctx=(40, 300))),
-                                     ("highconc", dict(batch=70, ctx=(1, 200))),
+                                     ("highconc", dict(batch=72, ctx=(1, 200), table_width=64)),
                                      ("tiny", dict(batch=2, ctx=(100, 400), rotate_mask=1)),
                                      ("prefill_mha", dict(ctx=100, had_block=16))])                # unfused fallback (d = 64)
 def test_fused_append_with_signs(saw, name, kw):
-    TA._case(saw, synth.make_workload(name, sign_seed=23, **kw))
+    w = synth.make_workload(name, sign_seed=23, **kw)
+    if name == "highconc":
+        TA._case(saw, w, max_seq_len=0, expect=gc.pairs(4))
+    TA._case(saw, w)
 
 
 @pytest.mark.parametrize("h,mask", [(16, 3), (64, 3), (128, 3), (128, 1), (32, 2)])
