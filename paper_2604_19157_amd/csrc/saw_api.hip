@@ -218,10 +218,13 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
     // 1 x 400 tokens 17.3 with 256 a partition, 12.1 with 64; 4 x 1000 19.7 and 13.8; 8 x 2000 25.6 and 23.0 with 128; 16 ragged up to 800
     // 23.0 and 17.7; 32 x 512 25.8 and 22.7 with 128; with 192 level, under loose bounds 5 % slower).  Bounds of up to five units
     // stay as they are (28 ragged up to 128 under a bound of 256, one query head: 10.1, cut 13.4, the second launch; 32 up to 130 under
-    // 272: 16.8 and 17.5), and so do more than 320 items (48 ragged up to 600 25.9 and 28.2).  Not in the fixed plan, whose
-    // scratch every call has to bring.
+    // 272: 16.8 and 17.5), and so do more than 320 items (48 ragged up to 600 25.9 and 28.2).  At most 448 partitions, more cost
+    // the merge too much: 2 x 32768 tokens, one kv head 22.3 with 256 a partition, 23.1 with 64 (512 of them), about 20 with 128; 1 x 65536
+    // 24.0, with 64 29.1.  Not in the fixed plan,
+    // whose scratch every call has to bring.
     if (kv16 && !fixed && !valu16 && units > 5 && items <= 320) {
-      const int64_t finer = 1792 / items < units ? 1792 / items : units;
+      int64_t finer = 1792 / items < units ? 1792 / items : units;
+      if (finer > 448) finer = 448;
       if (2 * finer >= units && s < finer) s = finer;
     }
     if (!kv16 && items >= 512 && B <= 1024) s = 1;

@@ -56,6 +56,11 @@ FIRST = dict(partitions=1, waves=1, pair_seqs=0, longest_first=1)
     (pairs(2), (257, 1, 4, 257), dict(cache16=True, splits=1)), (whole(1), (257, 1, 4, 256), dict(cache16=True, splits=1)),
     (pairs(2), (257, 1, 8, 1025), dict(cache16=True, splits=1)), (whole(1), (257, 1, 8, 1024), dict(cache16=True, splits=1)),
     (whole(1), (256, 1, 4, 1025), dict(cache16=True, splits=1)), (whole(1), (1025, 1, 4, 1025), dict(cache16=True, splits=1)),
+    # ... partitions of 64 or 128 tokens, at most 448 of them
+    (dict(partitions=2), (4, 8, 4, 320), dict(cache16=True)), (dict(partitions=6), (4, 8, 4, 321), dict(cache16=True)),
+    (dict(partitions=448), (1, 1, 4, 28672), dict(cache16=True)), (dict(partitions=225), (1, 1, 4, 28673), dict(cache16=True)),
+    (dict(partitions=448), (1, 1, 4, 57344), dict(cache16=True)), (dict(partitions=225), (1, 1, 4, 57345), dict(cache16=True)),
+    (dict(partitions=448), (1, 1, 8, 57344), dict(cache16=True, d=64)),
 ])
 def test_lines_of_the_rules(saw, want, args, kw):
     got = _got(saw, *args, **kw)
