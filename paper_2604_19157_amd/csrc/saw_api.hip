@@ -250,9 +250,11 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
     // A single sequence, which is not cut by its length, takes partitions of 64 or 128 tokens as well (fixed plan as above) up to 8192
     // tokens and 16 items (8 kv heads, decode, four query heads each, us: 2600 tokens 14.2 with 256 a partition, 11.6 with 64, 8000
     // 14.5 and 13.3; 12000 15.6 and 16.0, 28000 17.2 and 19.3, the merge of so many records; 32 items x 3300, eight query heads,
-    // 16.7 and 18.0).
+    // 16.7 and 18.0).  With the learned rotation up to 896 wavefronts of them, because each multiplies the query by all of R_l (eight
+    // query heads: 8 kv heads x 6000 tokens, 752 wavefronts, 25.1 and 24.0; x 8100, 1016, 24.8 and 26.6; 16 x 6000, 1504, 26.5 and 28.5).
     if (!kv16 && !fixed && B == 1 && !block_of_eight && units <= 128 && items <= 16) {
-      const int64_t finer = 1792 / items < units ? 1792 / items : units;
+      const int64_t most = (c->dense_rot ? 896 : 1792) / items;
+      const int64_t finer = most < units ? most : units;
       if (2 * finer >= units && s < finer) s = finer;
     }
     if (s < 1) s = 1;

@@ -52,6 +52,11 @@ FIRST = dict(partitions=1, waves=1, pair_seqs=0, longest_first=1)
     # cut by the lengths: 512 slots of four wavefronts from eight a sequence on, 1024 of two otherwise
     (dict(partitions=0, slots=64, waves=4), (8, 8, 4, 8192), {}), (dict(partitions=0, slots=128, waves=2), (9, 8, 4, 8192), {}),
     (dict(partitions=0, slots=128, waves=2), (63, 8, 4, 4096), {}),
+    # one sequence: partitions of 64 or 128 tokens, of half as many wavefronts with the learned rotation
+    (dict(partitions=127), (1, 8, 4, 8128), {}), (dict(partitions=64), (1, 8, 4, 8128), dict(learned=True)),
+    (dict(partitions=112), (1, 8, 4, 7168), dict(learned=True)), (dict(partitions=57), (1, 8, 4, 7169), dict(learned=True)),
+    (dict(partitions=56), (1, 16, 4, 7168), dict(learned=True)), (dict(partitions=29), (1, 16, 4, 7169), dict(learned=True)),
+    (dict(partitions=128), (1, 1, 1, 8192), {}), (dict(partitions=33), (1, 1, 1, 8193), {}), (dict(partitions=11), (1, 17, 4, 2600), {}),
     # the 16-bit call
     (pairs(2), (257, 1, 4, 257), dict(cache16=True, splits=1)), (whole(1), (257, 1, 4, 256), dict(cache16=True, splits=1)),
     (pairs(2), (257, 1, 8, 1025), dict(cache16=True, splits=1)), (whole(1), (257, 1, 8, 1024), dict(cache16=True, splits=1)),
