@@ -269,18 +269,24 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   plan->bound = bound;
   // wavefronts per partition: only when the partitions alone cannot fill the chip (about 2560
   // wavefront slots), and while every wavefront keeps at least 8 batches (512 tokens) of its own
-  // (a sequence in one partition, over 256 items: whole_waves)
   const int64_t blocks = (int64_t)B * decode_items_per_seq(c->head_dim, c->n_kv_heads) * plan->num_splits;
   int nw = 1;
   while (nw < 4 && blocks * nw * 2 <= 2560 && plan->chunk_tokens / (nw * 2) >= 512) nw *= 2;
-  if (block_of_eight && plan->num_splits == 1) nw = 8;
-  else if (!kv16 && plan->num_splits == 1) nw = whole_waves(blocks, units, nw);
+  // (INT4, a whole sequence in one partition: whole_waves; single 64-channel heads, where the chip holds 3072 wavefronts: four while all of
+  // those fit - 66 x 8, eight query heads x 700 tokens 21.9 and 18.7 us, but 250 x 8 x 200 18 and 27, x 700 34 and 44)
+  const bool single64 = !kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G);
+  if (!kv16 && plan->num_splits == 1) {
+    const int64_t heads = (int64_t)B * c->n_kv_heads;
+    if (block_of_eight) nw = 8;
+    else if (!single64) nw = whole_waves(blocks, units, nw);
+    else if (heads > 256 && heads <= 768) nw = 4;
+  }
   plan->waves_per_item = nw;
   plan->cut = plan->cut_min = plan->cut_waves = 0;
   plan->valu16 = valu16;
   if (num_splits != 0 || fixed || valu16) return true;
   const int per_seq = kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads);
-  if (!kv16 && c->head_dim == 64 && !decode_head_pairs(64, c->n_kv_heads, G)) plan_split64(c, B, units, plan);
+  if (single64) plan_split64(c, B, units, plan);
   // (partitions of 256 tokens are the shortest a cut makes: fixed ones that are no longer have the shorter start - 8 ragged up to 8000
   // tokens, 32 query / 8 kv heads, 42 us, 49 cut; above that 40 ragged up to 8000 161 and 131)
   else if (kv16) { if (plan->num_splits > 1 && chunk_units > 4) cut_plan(B, units, 2048 / per_seq, 1, plan); }

@@ -49,6 +49,10 @@ FIRST = dict(partitions=1, waves=1, pair_seqs=0, longest_first=1)
     (FIRST, (520, 8, 4, 1024), dict(d=64)),
     # one 64-channel head at a time: only the caller's order
     (whole(4), (64, 8, 8, 400), dict(d=64)), (dict(longest_first=1, waves=4), (64, 8, 8, 400), dict(d=64, order=True)),
+    # ... one partition asked for: four wavefronts up to 768 heads, beyond that only where each keeps 512 tokens
+    (whole(1), (32, 8, 8, 400), dict(d=64, splits=1)), (whole(4), (33, 8, 8, 400), dict(d=64, splits=1)), (whole(4), (96, 8, 8, 400), dict(d=64, splits=1)),
+    (whole(1), (97, 8, 8, 400), dict(d=64, splits=1)), (whole(1), (250, 8, 8, 700), dict(d=64, splits=1)), (whole(4), (250, 8, 8, 1024), dict(d=64, splits=1)),
+    (whole(1), (142, 7, 4, 200), dict(d=64, splits=1)), (whole(4), (100, 7, 4, 200), dict(d=64, splits=1)),
     # cut by the lengths: 512 slots of four wavefronts from eight a sequence on, 1024 of two otherwise
     (dict(partitions=0, slots=64, waves=4), (8, 8, 4, 8192), {}), (dict(partitions=0, slots=128, waves=2), (9, 8, 4, 8192), {}),
     (dict(partitions=0, slots=128, waves=2), (63, 8, 4, 4096), {}),
