@@ -39,7 +39,7 @@ FIRST = dict(partitions=1, waves=1, pair_seqs=0, longest_first=1)
     (pairs(4, 3), (192, 8, 4, 4096), {}), (pairs(2), (193, 8, 4, 4096), {}), (pairs(2), (256, 8, 4, 4096), {}),
     (pairs(2, 3), (257, 8, 4, 4096), {}), (pairs(2, 3), (288, 8, 4, 4096), {}), (FIRST, (289, 8, 4, 4096), {}),
     (whole(1), (256, 8, 4, 256), {}), (pairs(2), (256, 8, 4, 257), {}), (whole(1), (400, 8, 4, 256), {}), (FIRST, (400, 8, 4, 257), {}),
-    (whole(1), (1025, 8, 4, 4096), {}),
+    (whole(1), (1025, 8, 4, 4096), {}), (whole(2), (1024, 1, 4, 256), {}), (whole(1), (1025, 1, 4, 256), {}), (whole(1), (1150, 1, 8, 100), {}),
     # ... with the caller's order
     (whole(2), (128, 8, 4, 256), dict(order=True)), (pairs(4), (128, 8, 4, 257), dict(order=True)),
     (pairs(2), (130, 8, 4, 64), dict(order=True)), (whole(2), (130, 8, 4, 320), dict(order=True)), (pairs(2), (256, 8, 4, 64), dict(order=True)),
