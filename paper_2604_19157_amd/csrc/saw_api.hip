@@ -105,17 +105,19 @@ static int whole_waves(int64_t items, int units, int nw) {
 //     23.9, 28 x 3584 26.2 against 30.3, 28 of up to 1750 under a bound of 3500 16.6 against 18.6; 28 ragged up to 3500 24.4 against
 //     23.1, 24 ragged up to 4000 26.1 against 23.0).  Pairs of 64-channel heads: five from 192 items on (56 x 3584 31.2
 //     against 33.4, but ragged 29.8 against 25.5);
-//   * from 257 items on four wavefronts over the whole sequence (whole_waves) take its place where each has at most six batches
-//     (40 x 200 tokens 17.6 us, 10.6 with them, 62 x 800 21.1 and 17.7, 48 x 1500 27.5 and 23.4, 33 with a few long ones of 1500
-//     16.3 and 16.6; x 2000 16.3 and 19.2), five for pairs of 64-channel heads (40 x 1200 23.6 and 23.4, x 1500 25.7 and 26.2), eight
-//     with the learned rotation, whose preparation every partition would repeat (33 x 2000 33.3 and 31.6, 62 x 2000 43.7 and 34.5).
-static void plan_cut(int B, int units, int per_seq, bool pairs, bool learned, SplitPlan* plan) {
+//   * from 257 items on four wavefronts over the whole sequence (whole_waves) take its place where each has at most four batches
+//     (40 x 200 tokens 17.6 us, 10.6 with them, 62 x 800 21.1 and 17.7), three for pairs of 64-channel heads, five with the learned rotation,
+//     whose preparation every partition would repeat, but with eight query heads three.  The line is where a batch with one sequence in
+//     sixteen at the bound and the others an eighth of it does not lose (over the time of the cut: 50 x 1000 0.92, x 1150 1.08, x 1400 1.19;
+//     pairs 100 x 700 0.96, x 850 1.08, x 1150 1.18; learned 50 x 1150 0.99, x 1400 1.05, x 2000 1.18, eight query heads 132 x 2 heads x 700
+//     0.99, x 850 1.10, x 1150 1.15); equal and ragged lengths would gain up to 1500 tokens (48 x 1500 0.85).
+static void plan_cut(int B, int units, int per_seq, int G, bool pairs, bool learned, SplitPlan* plan) {
   const int64_t items = (int64_t)B * per_seq;
   const int per_wave = (units + 7) / 8;
   const int most = pairs ? (items >= 192 ? 5 : 4) : items >= 192 ? 8 : items > 128 ? 5 : 4;
   if (plan->waves_per_item == 8 && per_wave <= most) return;
   if (items >= 512) return;
-  if (items > 256 && (units + 3) / 4 <= (pairs ? 5 : learned ? 8 : 6)) {
+  if (items > 256 && (units + 3) / 4 <= (pairs || (learned && G == 8) ? 3 : learned ? 5 : 4)) {
     plan->num_splits = 1;
     plan->chunk_tokens = units * 64;
     plan->waves_per_item = whole_waves(items, units, 1);
@@ -133,10 +135,11 @@ static void plan_cut(int B, int units, int per_seq, bool pairs, bool learned, Sp
 // wavefronts a slot, 2048 in all, where a sequence gets four slots of those (16 ragged x 8 heads of 300-3000 tokens 17.5 us, 19.1
 // with 3072, 22.4 and 25.3 with one wavefront a slot; 64 ragged 40.0, with one wavefront 32.1, which is why it needs the four).
 // Short bounds of more items are not cut: four wavefronts over the whole sequence, no merge pass, while they fit and have at most
-// six batches each (eight query heads, fused step: 33 x 400 tokens 17 us, 13 so, 64 x 700 22 and 16, 96 ragged up to 1000 26 and 22, 90 x 1535
-// 37 and 32, with a few long ones among short level), and up to 1024 items, where they no longer fit, at most three (110 x 400 24 and
+// six batches each (eight query heads, fused step: 33 x 400 tokens 17 us, 13 so, 64 x 700 22 and 16, 96 ragged up to 1000 26 and 22), four
+// with eight query heads in batches that can be cut (with one sequence in sixteen at the bound, the others an eighth of it: 95 x 1000 level,
+// x 1150 27 % longer than cut, x 1400 40 %; four query heads 0.72 to 0.96 up to 1530), and up to 1024 items, where they no longer fit, at most three (110 x 400 24 and
 // 21, 128 x 767 33 and 29; x 1000 level); one or two batches in all still go to one wavefront there (200 tokens 15 and 20).
-static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan) {
+static void plan_split64(const saw_cache_t* c, int B, int G, int units, SplitPlan* plan) {
   const int64_t items = (int64_t)B * c->n_kv_heads;
   constexpr int kWaves = 3072;
   const int per_wave = (units + 7) / 8;
@@ -147,7 +150,7 @@ static void plan_split64(const saw_cache_t* c, int B, int units, SplitPlan* plan
     plan->waves_per_item = 8;
     return;
   }
-  if (items > 256 && (items <= 768 ? units <= 24 : items <= 1024 && B <= kMaxCut && units > 4 && units <= 12)) {
+  if (items > 256 && (items <= 768 ? units <= (G == 8 && B <= kMaxCut ? 16 : 24) : items <= 1024 && B <= kMaxCut && units > 4 && units <= 12)) {
     plan->num_splits = 1;
     plan->chunk_tokens = units * 64;
     plan->waves_per_item = 4;
@@ -288,11 +291,11 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   plan->valu16 = valu16;
   if (num_splits != 0 || fixed || valu16) return true;
   const int per_seq = kv16 ? c->n_kv_heads : decode_items_per_seq(c->head_dim, c->n_kv_heads);
-  if (single64) plan_split64(c, B, units, plan);
+  if (single64) plan_split64(c, B, G, units, plan);
   // (partitions of 256 tokens are the shortest a cut makes: fixed ones that are no longer have the shorter start - 8 ragged up to 8000
   // tokens, 32 query / 8 kv heads, 42 us, 49 cut; above that 40 ragged up to 8000 161 and 131)
   else if (kv16) { if (plan->num_splits > 1 && chunk_units > 4) cut_plan(B, units, 2048 / per_seq, 1, plan); }
-  else plan_cut(B, units, per_seq, c->head_dim == 64, c->dense_rot != nullptr, plan);
+  else plan_cut(B, units, per_seq, G, c->head_dim == 64, c->dense_rot != nullptr, plan);
   return true;
 }
 

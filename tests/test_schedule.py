@@ -61,6 +61,13 @@ FIRST = dict(partitions=1, waves=1, pair_seqs=0, longest_first=1)
     (dict(partitions=112), (1, 8, 4, 7168), dict(learned=True)), (dict(partitions=57), (1, 8, 4, 7169), dict(learned=True)),
     (dict(partitions=56), (1, 16, 4, 7168), dict(learned=True)), (dict(partitions=29), (1, 16, 4, 7169), dict(learned=True)),
     (dict(partitions=128), (1, 1, 1, 8192), {}), (dict(partitions=33), (1, 1, 1, 8193), {}), (dict(partitions=11), (1, 17, 4, 2600), {}),
+    # ... but four wavefronts over whole sequences of short bounds
+    (whole(4), (40, 8, 4, 1024), {}), (dict(partitions=0), (40, 8, 4, 1025), {}), (whole(4), (80, 8, 4, 768), dict(d=64)),
+    (dict(partitions=0), (80, 8, 4, 769), dict(d=64)), (whole(4), (40, 8, 4, 1280), dict(learned=True)),
+    (dict(partitions=0), (40, 8, 4, 1281), dict(learned=True)), (whole(4), (40, 8, 8, 768), dict(learned=True)),
+    (dict(partitions=0), (40, 8, 8, 769), dict(learned=True)), (whole(4), (40, 8, 8, 1024), dict(d=64)),
+    (dict(partitions=0), (40, 8, 8, 1025), dict(d=64)), (whole(4), (57, 7, 4, 1536), dict(d=64)), (dict(partitions=0), (57, 7, 4, 1537), dict(d=64)),
+    (whole(4), (257, 1, 8, 1536), dict(d=64)),
     # the 16-bit call
     (pairs(2), (257, 1, 4, 257), dict(cache16=True, splits=1)), (whole(1), (257, 1, 4, 256), dict(cache16=True, splits=1)),
     (pairs(2), (257, 1, 8, 1025), dict(cache16=True, splits=1)), (whole(1), (257, 1, 8, 1024), dict(cache16=True, splits=1)),
