@@ -74,17 +74,18 @@ static bool block_ok(const saw_cache_t* c) {
 
 
 // Wavefronts of the INT4 block that takes a whole sequence (one partition), by the number of (kv head, or pair of heads, sequence)
-// items; `nw`: what the bound alone asks for.  Up to 256 items the block of eight above; from 1152 on pair blocks and one wavefront
+// items; `rows`: query heads of a block; `nw`: what the bound alone asks for.  Up to 256 items the block of eight above; from 1152 on pair blocks and one wavefront
 // (run_decode).  In between the chip holds four wavefronts for every item up to 512 and two up to 1024, and a wavefront that has only
 // a batch or two is still better than a slot left empty, however short the sequences.  Fused step, 32 query / 8 kv heads, us, one
 // wavefront an item (pair blocks) before: 64 x 250 tokens 17.6, now 10.8; 64 x 750 30 and 16.4; 64 ragged up to 1500 30 and 21; learned
 // 64 x 750 40 and 22.  513 to 575 items: 68 x 250 22 and 13, four wavefronts only from 1024 tokens on, where their second round
-// is paid for (68 x 250 17, x 750 level, 68 ragged up to 1000 20.4 against 24 with two); 1040 ragged up to 750 33 and 24.  More than
+// is paid for (68 x 250 17, x 750 level, 68 ragged up to 1000 20.4 against 24 with two), with one or two query rows a
+// block from 2048 on (one: 140 x 4 heads x 1400 28.8, 31.5 with four, two: x 1500 30.7 and 33.4; from 2000 on level); 1040 ragged up to 750 33 and 24.  More than
 // 1024 sequences were never in pair blocks, and two wavefronts are no gain over one (1030 x 1 kv head x 100 tokens, four query heads 14.3
 // and 16.9, eight 17.2 and 21.1; x 600 level).
-static int whole_waves(int64_t items, int units, int nw) {
+static int whole_waves(int64_t items, int rows, int units, int nw) {
   if (items <= 256 || items >= 1152) return nw;
-  if (items <= 512 || (items < 576 && units >= 16)) return 4;
+  if (items <= 512 || (items < 576 && units >= (rows <= 2 ? 32 : 16))) return 4;
   return 2;
 }
 
@@ -120,7 +121,7 @@ static void plan_cut(int B, int units, int per_seq, int G, bool pairs, bool lear
   if (items > 256 && (units + 3) / 4 <= (pairs || (learned && G == 8) ? 3 : learned ? 5 : 4)) {
     plan->num_splits = 1;
     plan->chunk_tokens = units * 64;
-    plan->waves_per_item = whole_waves(items, units, 1);
+    plan->waves_per_item = whole_waves(items, pairs ? 2 * G : G, units, 1);
     return;
   }
   if (cut_plan(B, units, 512 / per_seq, 4, plan) && plan->cut >= 8 * B) return;
@@ -283,7 +284,7 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
   if (!kv16 && plan->num_splits == 1) {
     const int64_t heads = (int64_t)B * c->n_kv_heads;
     if (block_of_eight) nw = 8;
-    else if (!single64) nw = B <= 1024 ? whole_waves(blocks, units, nw) : nw;
+    else if (!single64) nw = B <= 1024 ? whole_waves(blocks, c->head_dim == 64 ? 2 * G : G, units, nw) : nw;
     else if (heads > 256 && heads <= 768) nw = 4;
   }
   plan->waves_per_item = nw;

@@ -34,7 +34,8 @@ FIRST = dict(partitions=1, waves=1, pair_seqs=0, longest_first=1)
 @pytest.mark.parametrize("want,args,kw", [
     # 128-channel rows, one partition: by items and bound
     (whole(8), (32, 8, 4, 2304), {}), (whole(4), (33, 8, 4, 512), {}), (whole(4), (64, 8, 4, 4096), {}),
-    (whole(2), (65, 8, 4, 640), {}), (whole(2), (72, 8, 4, 512), {}), (pairs(4), (72, 8, 4, 513), {}), (whole(4), (71, 8, 4, 4096), {}),
+    (whole(2), (65, 8, 4, 960), {}), (whole(4), (65, 8, 4, 961), {}), (whole(2), (140, 4, 1, 1984), {}), (whole(4), (140, 4, 1, 1985), {}), (whole(2), (140, 4, 2, 1984), {}),
+    (whole(2), (140, 8, 1, 1984), dict(d=64)), (whole(4), (140, 8, 2, 1984), dict(d=64)), (whole(2), (72, 8, 4, 512), {}), (pairs(4), (72, 8, 4, 513), {}), (whole(4), (71, 8, 4, 4096), {}),
     (pairs(4), (128, 8, 4, 4096), {}), (whole(2), (129, 8, 4, 4096), {}), (whole(2), (143, 8, 4, 4096), {}), (pairs(4, 3), (144, 8, 4, 4096), {}),
     (pairs(4, 3), (192, 8, 4, 4096), {}), (pairs(2), (193, 8, 4, 4096), {}), (pairs(2), (256, 8, 4, 4096), {}),
     (pairs(2, 3), (257, 8, 4, 4096), {}), (pairs(2, 3), (288, 8, 4, 4096), {}), (FIRST, (289, 8, 4, 4096), {}),
