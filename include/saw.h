@@ -160,6 +160,9 @@ int saw_rotate_quant_store_layers(const saw_cache_t* caches, const void* const* 
 /*
  * Bytes of scratch the decode calls need for these arguments: split-KV partial results of head_dim + 2 float32 per
  * query row and partition.  max_seq_len and num_splits have the meaning below; returns 0 on invalid arguments.
+ * With num_splits 0 the figure covers the many short partitions of calls with fewer sequences or a shorter bound as well, so scratch
+ * can be sized once for the largest call.  (Elsewhere a smaller call may want somewhat more than a larger one; where it finds less
+ * than its plan wants it takes the partitions that saw_decode_plan reports: the same result, its sums in another order.)
  */
 size_t saw_decode_workspace_bytes(const saw_cache_t* cache, int32_t B, int32_t n_q_heads,
                                   int32_t max_seq_len, int32_t num_splits);

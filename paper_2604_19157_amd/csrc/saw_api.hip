@@ -189,6 +189,10 @@ static bool takes_valu16(const saw_cache_t* c, int B, int G, int units) {
   return G == 1 || !(many || long_ones);
 }
 
+// Partitions of 64 or 128 tokens (make_plan): wavefronts in all; of the 16-bit call items and partitions a sequence; of the INT4 call of
+// one sequence items and 64-token units
+constexpr int64_t kFineWaves = 1792, kFineItems16 = 320, kFine16 = 448, kFineItems4 = 16, kFineUnits4 = 128;
+
 // Split-KV plan.  Partitions are whole multiples of 64 tokens so every wavefront pass
 // starts on a page boundary.  The automatic choice aims at about 2048 wavefronts (8 per compute
 // unit): one partition per sequence once the batch alone provides them, otherwise partitions of
@@ -228,9 +232,9 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
     // the merge too much: 2 x 32768 tokens, one kv head 22.3 with 256 a partition, 23.1 with 64 (512 of them), about 20 with 128; 1 x 65536
     // 24.0, with 64 29.1.  Not in the fixed plan,
     // whose scratch every call has to bring.
-    if (kv16 && !fixed && !valu16 && units > 5 && items <= 320) {
-      int64_t finer = 1792 / items < units ? 1792 / items : units;
-      if (finer > 448) finer = 448;
+    if (kv16 && !fixed && !valu16 && units > 5 && items <= kFineItems16) {
+      int64_t finer = kFineWaves / items < units ? kFineWaves / items : units;
+      if (finer > kFine16) finer = kFine16;
       if (2 * finer >= units && s < finer) s = finer;
     }
     if (!kv16 && items >= 512 && B <= 1024) s = 1;
@@ -258,8 +262,8 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
     // 14.5 and 13.3; 12000 15.6 and 16.0, 28000 17.2 and 19.3, the merge of so many records; 32 items x 3300, eight query heads,
     // 16.7 and 18.0).  With the learned rotation up to 896 wavefronts of them, because each multiplies the query by all of R_l (eight
     // query heads: 8 kv heads x 6000 tokens, 752 wavefronts, 25.1 and 24.0; x 8100, 1016, 24.8 and 26.6; 16 x 6000, 1504, 26.5 and 28.5).
-    if (!kv16 && !fixed && B == 1 && !block_of_eight && units <= 128 && items <= 16) {
-      const int64_t most = (c->dense_rot ? 896 : 1792) / items;
+    if (!kv16 && !fixed && B == 1 && !block_of_eight && units <= kFineUnits4 && items <= kFineItems4) {
+      const int64_t most = (c->dense_rot ? kFineWaves / 2 : kFineWaves) / items;
       const int64_t finer = most < units ? most : units;
       if (2 * finer >= units && s < finer) s = finer;
     }
@@ -427,6 +431,24 @@ size_t saw_decode_workspace_bytes(const saw_cache_t* c, int32_t B, int32_t n_q_h
     const bool fixed = G == 0 || (k & 1);
     if (!make_plan(c, B, G, fixed, max_pages, max_seq_len, num_splits, (k & 2) != 0, &plan)) return 0;
     const size_t n = plan_bytes(plan, B, n_q_heads, c->head_dim);
+    if (n > most) most = n;
+  }
+  if (num_splits == 0) {
+    // ... and the partitions of 64 or 128 tokens of calls with fewer sequences or a shorter bound, so that a program that sizes its
+    // scratch once, for the largest call, gets them there (as many as make_plan ever takes)
+    const int64_t units = ((int64_t)max_seq_len + 63) / 64;
+    const int per_seq = decode_items_per_seq(c->head_dim, c->n_kv_heads);
+    int64_t records = 0;
+    if (units > 5 && c->n_kv_heads <= kFineItems16 && !(c->head_dim == 64 && G == 1)) {
+      records = B * (units < kFine16 ? units : kFine16);
+      if (records > kFineWaves / c->n_kv_heads) records = kFineWaves / c->n_kv_heads;
+    }
+    if (per_seq <= kFineItems4) {
+      const int64_t one = units < kFineUnits4 ? units : kFineUnits4;
+      const int64_t r = one < kFineWaves / per_seq ? one : kFineWaves / per_seq;
+      if (units > 40 && r > records) records = r;
+    }
+    const size_t n = partial_bytes(1, n_q_heads, (int)records, c->head_dim);
     if (n > most) most = n;
   }
   return most;

@@ -291,6 +291,30 @@ def test_a_workspace_below_the_reported_geometry_is_refused(saw):
                                         P(16), need - 16, 0, P(0)) == -3
 
 
+def test_scratch_for_the_largest_call_holds_smaller_calls_plans(saw):
+    """A program sizes its scratch once.  A shorter bound never wants more than 5/4 of it (whole partitions), a smaller batch never more
+    than twice (the wavefronts that 257 to 511 items get), and the 64-token partitions of few sequences always fit."""
+    import torch
+    L = saw.lib()
+    bounds = [64, 200, 300, 321, 512, 700, 1024, 2000, 2561, 4096, 7168, 8000, 8256, 12000, 20000, 28672, 40000, 57344, 65536, 131072]
+    batches = [1, 2, 3, 4, 8, 16, 33, 40, 48, 64, 65, 129, 256, 257, 512, 1025]
+    for d, n_kv in [(128, 1), (128, 2), (128, 7), (128, 8), (128, 32), (64, 2), (64, 3), (64, 8), (64, 16)]:
+        for G in (1, 2, 4, 8):
+            st = _struct(saw, n_kv_heads=n_kv, head_dim=d, had_block=64)
+            f = {(B, n): L.saw_decode_workspace_bytes(ctypes.byref(st), B, n_kv * G, n, 0) for B in batches for n in bounds}
+            for i, B in enumerate(batches):
+                for j, n in enumerate(bounds):
+                    assert max(f[B, m] for m in bounds[:j + 1]) <= 1.25 * f[B, n], (d, n_kv, G, B, n)
+                    assert max(f[b, n] for b in batches[:i + 1]) <= 2 * f[B, n], (d, n_kv, G, B, n)
+            shape16 = saw.Kv16Cache(1, n_kv, d, torch.bfloat16, device="cpu")
+            shape = saw.Cache(1, n_kv, d, 64, device="cpu")
+            for B, n in [(1, 2600), (1, 8000), (1, 28672), (2, 900), (4, 3000), (16, 1100)]:
+                for c in (shape, shape16):
+                    s = saw.decode_schedule(c, B, n_kv * G, n)
+                    if s["partitions"] * 256 > n:                       # (shorter than 256 tokens)
+                        assert min(f[b, m] for b in batches if b >= B for m in bounds if m >= n) >= B * n_kv * G * s["partitions"] * (d + 2) * 4
+
+
 class _SplitPlan(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("num_splits", "chunk_tokens", "bound", "waves_per_item", "cut", "cut_min", "cut_waves", "valu16")]
 
