@@ -67,8 +67,8 @@ def test_head_pairs_ragged_with_empty_and_single(saw):
 @pytest.mark.parametrize("B,Hq,Hkv", [(140, 32, 8), (140, 16, 4), (150, 32, 8), (255, 8, 8), (300, 8, 8), (340, 16, 8),
                                       (340, 32, 8), (600, 8, 8)])
 def test_head_pairs_many_sequences(saw, B, Hq, Hkv):
-    """More (sequence, head pair) items than compute units, under a bound of 1024 tokens: four or two wavefronts a sequence (560 and
-    280 items, the first two cases), pair mode (blocks of four from 576 to 1024 items: the third and fourth case; of four over three
+    """More (sequence, head pair) items than compute units, under a bound of 1024 tokens: four wavefronts a sequence (560 and
+    280 items, the first two cases; the second by itself is cut by its lengths), pair mode (blocks of four from 576 to 1024 items: the third and fourth case; of four over three
     sequences from 1152 to 1536 items: the fifth and sixth, while the seventh, with eight query rows per head pair, takes blocks of two),
     longest first beyond 2304 items (the last case).
     Lengths include empty sequences and many ties."""
@@ -80,7 +80,7 @@ def test_head_pairs_many_sequences(saw, B, Hq, Hkv):
     items = B * Hkv // 2
     expect = gc.pairs(2) if 1152 <= items <= 2048 and Hq == 4 * Hkv else gc.by_items(items)
     TD._decode_case(saw, w, num_splits=1, end_to_end=False, max_seq_len=0, expect=expect)
-    TD._decode_case(saw, w, num_splits=0, end_to_end=False, max_seq_len=0, expect=expect)
+    TD._decode_case(saw, w, num_splits=0, end_to_end=False, max_seq_len=0, expect=dict(partitions=0) if items < 512 else expect)
 
 
 def test_head_pairs_long_context_several_wavefronts(saw):
