@@ -237,8 +237,10 @@ int saw_paged_decode_attn(const saw_cache_t* cache, const void* q, int32_t q_dty
  * this order at no cost; with it the kernels of a large batch skip their own length ranking (the first
  * microseconds of every wavefront).  Entries outside [0, B) are clamped; an order that is not a permutation
  * or not sorted gives unbalanced work or wrong rows, never an out-of-bounds access.  The order is only
- * read where the launch needs one (one partition per sequence and more than 256 (sequence, kv head)
- * items); hints == NULL or order == NULL: the kernels rank the sequences themselves, which is what
+ * read where the launch deals sequences out by their lengths (saw_decode_schedule with with_order 1: pair_seqs or
+ * longest_first): one partition per sequence, at most 1024 sequences, 576 or more (sequence, kv head) items (pairs of heads for
+ * head_dim 64; where single heads are taken one at a time more than 256 of them), mostly under bounds above 256 tokens;
+ * hints == NULL or order == NULL: the kernels rank the sequences themselves, which is what
  * saw_paged_decode_attn / saw_append_decode_attn do.  Everything else as in those calls.
  */
 /*

@@ -74,15 +74,15 @@ static bool block_ok(const saw_cache_t* c) {
 
 
 // Wavefronts of the INT4 block that takes a whole sequence (one partition), by the number of (kv head, or pair of heads, sequence)
-// items; `rows`: query heads of a block; `nw`: what the bound alone asks for.  Up to 256 items the block of eight above; from 1152 on pair blocks and one wavefront
-// (run_decode).  In between the chip holds four wavefronts for every item up to 512 and two up to 1024, and a wavefront that has only
-// a batch or two is still better than a slot left empty, however short the sequences.  Fused step, 32 query / 8 kv heads, us, one
-// wavefront an item (pair blocks) before: 64 x 250 tokens 17.6, now 10.8; 64 x 750 30 and 16.4; 64 ragged up to 1500 30 and 21; learned
-// 64 x 750 40 and 22.  513 to 575 items: 68 x 250 22 and 13, four wavefronts only from 1024 tokens on, where their second round
-// is paid for (68 x 250 17, x 750 level, 68 ragged up to 1000 20.4 against 24 with two), with one or two query rows a
-// block from 2048 on (one: 140 x 4 heads x 1400 28.8, 31.5 with four, two: x 1500 30.7 and 33.4; from 2000 on level); 1040 ragged up to 750 33 and 24.  More than
-// 1024 sequences were never in pair blocks, and two wavefronts are no gain over one (1030 x 1 kv head x 100 tokens, four query heads 14.3
-// and 16.9, eight 17.2 and 21.1; x 600 level).
+// items; `rows`: query heads of a block; `nw`: what the bound alone asks for.  Up to 256 items the block of eight above; from 1152
+// on pair blocks and one wavefront (plan_blocks).  In between the chip holds four wavefronts for every item up to 512 and two up to
+// 1024, and a wavefront that has only a batch or two is still better than a slot left empty, however short the sequences.  Fused
+// step, 32 query / 8 kv heads, us, one wavefront an item (pair blocks) before: 64 x 250 tokens 17.6, now 10.8; 64 x 750 30 and 16.4; 64
+// ragged up to 1500 30 and 21; learned 64 x 750 40 and 22.  513 to 575 items: 68 x 250 22 and 13, four wavefronts only from 1024
+// tokens on, where their second round is paid for (68 x 250 17, x 750 level, 68 ragged up to 1000 20.4 against 24 with two), with one or
+// two query rows a block from 2048 on (one: 140 x 4 heads x 1400 28.8, 31.5 with four, two: x 1500 30.7 and 33.4; from 2000 on level);
+// 1040 ragged up to 750 33 and 24.  More than 1024 sequences were never in pair blocks, and two wavefronts are no gain over one
+// (1030 x 1 kv head x 100 tokens, four query heads 14.3 and 16.9, eight 17.2 and 21.1; x 600 level).
 static int whole_waves(int64_t items, int rows, int units, int nw) {
   if (items <= 256 || items >= 1152) return nw;
   if (items <= 512 || (items < 576 && units >= (rows <= 2 ? 32 : 16))) return 4;
@@ -229,9 +229,8 @@ static bool make_plan(const saw_cache_t* c, int B, int G, bool fixed, int max_pa
     // 23.0 and 17.7; 32 x 512 25.8 and 22.7 with 128; with 192 level, under loose bounds 5 % slower).  Bounds of up to five units
     // stay as they are (28 ragged up to 128 under a bound of 256, one query head: 10.1, cut 13.4, the second launch; 32 up to 130 under
     // 272: 16.8 and 17.5), and so do more than 320 items (48 ragged up to 600 25.9 and 28.2).  At most 448 partitions, more cost
-    // the merge too much: 2 x 32768 tokens, one kv head 22.3 with 256 a partition, 23.1 with 64 (512 of them), about 20 with 128; 1 x 65536
-    // 24.0, with 64 29.1.  Not in the fixed plan,
-    // whose scratch every call has to bring.
+    // the merge too much: 2 x 32768 tokens, one kv head 22.4 with 256 a partition, 23.1 with 64 (512 of them), 20.9 with 128; 1 x 65536
+    // 24.0, with 64 29.1.  Not in the fixed plan, whose scratch every call has to bring.
     if (kv16 && !fixed && !valu16 && units > 5 && items <= kFineItems16) {
       int64_t finer = kFineWaves / items < units ? kFineWaves / items : units;
       if (finer > kFine16) finer = kFine16;

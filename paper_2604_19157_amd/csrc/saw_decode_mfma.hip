@@ -192,10 +192,10 @@ __device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, u3
 // App. A.1; append_store writes them to the pools), and place its codes and (scale, zero) pairs in LDS as token 0 of page 0 of a
 // batch, in the layout the transfers produce.  The caller then runs one more batch in which only that
 // token is valid, so the new token goes through the very code path of the cached ones (same q~ limbs,
-// same softmax update) and nothing this launch writes to the cache is read back by it.  All of this
-// happens at the END of the range that starts the sequence, when every transfer of the range has
-// landed: at the start of a launch all wavefronts of the chip run their prologues at once and are
-// bound by instruction issue, while later the vector ALU has slack under the memory traffic.
+// same softmax update) and nothing this launch writes to the cache is read back by it.  This happens at
+// the END of the range that starts the sequence, when every transfer of the range has landed and the buffers
+// are idle: in the middle of the loop, where wavefronts have no slack, it costs 1-2 us.  The rotation in front of it
+// runs there too (rotate_token), or, in a block that prepares its range together, with the query's at the start (block_prepare).
 // One wavefront, K in lanes 0-31 and V in lanes 32-63, four channels per lane: one chain of reductions and one division for both.
 // (It is on the critical path of the range's last wavefront: with two channels of both vectors in every lane, 4 x 256 tokens took 8.6 us
 // and take 8.1, 16 x 4096 22.6 and 22.1, 64 ragged with a learned rotation 46.3 and 45.0.)
@@ -258,7 +258,8 @@ template <int G, bool HP> constexpr int kWaveLdsG = 12 * kTileBytes + kPbufBytes
 // was 1.6 us of instructions, two wavefronts a SIMD, in front of the first batch.  With a learned rotation the new token costs its
 // rows in a product that runs anyway, instead of one wavefront's product at the end of the longest range.
 // Blocks of two only do this with a learned rotation: theirs is hidden by the first transfers (16 x 4096 tokens).
-// (fused steps, each wavefront for itself and then together: 4 x 256 tokens 8.9 -> 8.6 us, 64 ragged with a learned rotation 47.8 -> 46.3.)
+// (fused steps, each wavefront for itself and then together: 4 x 256 tokens 8.9 -> 8.6 us, 64 ragged with a learned rotation 47.8 -> 46.3,
+// of which the fixed order of the new token's sums took 0.6 back: block_columns_ordered.)
 template <int NW, bool PAIR, bool HP, bool DN>
 constexpr bool kBlockPrep = !PAIR && (NW == 8 || (NW == 4 && !HP) || (DN && NW > 1));
 // LDS for it beside the wavefronts' buffers, which transfers may target: the rotated rows, then the A operands
@@ -487,7 +488,7 @@ __device__ __forceinline__ void block_epilogue(const DecodeParams& p, uint8_t* c
 #pragma unroll
   for (int j = 0; j < HPW; ++j) {
     const int h = h0 + j;
-    if (h >= G) break;                                        // (three heads or fewer left over: wavefront-uniform)
+    if (h >= G) break;                                        // (wavefront-uniform)
     // two consecutive channels per lane: a whole row per store (head pair: the 32 lanes of the head's own half)
     if (HP && (lane >> 5) != h / GK) continue;
     const f32x2 o2 = *(const f32x2*)(rows + 128 * j + 2 * lane);
@@ -806,7 +807,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // fused append: the range that starts the sequence also takes the step's new token (wavefront 0 of the block when
   // several share the range); of a batch cut by its lengths the one that ends it, there the wavefront with the fewest
   // batches; so in a block of eight, where over a short context that wavefront has none and works on the token while the others
-  // stream (4 sequences of 256 tokens: the step 9.3 -> 9.1 us); its inputs are requested here, with the query
+  // stream (4 sequences of 256 tokens: the step 9.3 -> 8.9 us); its inputs are requested here, with the query
   const bool takes_new = block_new && (PAIR || wave == (CUT || NW == 8 ? NW - 1 : 0));
   u32x2 new_w = u32x2{0u, 0u};
   int new_pid = -1;
@@ -903,7 +904,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       const f32x4 v = *(const f32x4*)(rows + 128 * G + 4 * lane);                 // K, then V
       new_x[0] = v.x; new_x[1] = v.y; new_x[2] = v.z; new_x[3] = v.w;
     }
-  } else   {
+  } else {
     float qraw[2 * G];
     const bool q_is_f32 = p.q_dtype == SAW_F32, q_is_bf16 = p.q_dtype == SAW_BF16;
 #pragma unroll
@@ -1325,8 +1326,8 @@ static void launch_g(const DecodeParams& p, int B, int nw, dim3 grid, hipStream_
   else decode_int4_mfma_kernel<G, 1, false, HP, 2, DN><<<grid, dim3(64), 0, st>>>(p);
 }
 
-// `G`: query heads per kv head.  `nw`: wavefronts per (sequence, kv head, partition) block: 1, 2 or
-// 4 (ignored in pair mode).  `head_pairs`: head_dim 64, grid.y = n_kv_heads / 2 blocks of two kv
+// `G`: query heads per kv head.  `nw`: wavefronts per (sequence, kv head, partition) block: 1, 2, 4
+// or 8 (ignored in pair mode).  `head_pairs`: head_dim 64, grid.y = n_kv_heads / 2 blocks of two kv
 // heads each (2 G rows), G <= 4; otherwise head_dim 128 and grid.y = n_kv_heads.
 int launch_decode_int4_mfma(const DecodeParams& p, int G, int B, int nw, bool head_pairs, dim3 grid, hipStream_t st) {
   if (head_pairs) {
