@@ -4,23 +4,28 @@
 //
 // A wavefront walks its share of one (sequence, kv head) in batches of four pages (64 tokens: 512 bytes of K and of
 // V codes and 128 bytes of (scale, zero) pairs a page).  Everything is loaded into registers, two batches ahead:
-//   * K codes: lane (token = lane % 16, k-group = lane / 16) loads the 16 codes it feeds to the logit MFMA;
+//   * K codes: lane (token = lane % 16, k-group = lane / 16) loads the 16 codes it feeds to the logit product;
 //   * V codes: 16 bytes per lane, two pages a load; written to LDS when their batch is due and read back by
 //     ds_read_b64_tr_b4 (a 16x16 nibble transpose) with tokens along the contraction;
-//   * the pairs: each lane loads those of its own token(s) of the softmax layout.
+//   * the pairs: each lane loads those of one token; LDS hands them to the lanes that have its logits.
 // With a fifth of the bytes of an LDS-DMA double buffer per wavefront in LDS, registers set the occupancy: three
 // wavefronts per SIMD with two batches each in flight, which is what a 5 KiB batch needs to keep HBM busy.
 //
-// Numerics.  A nibble c, as a byte, is the fp8 (e4m3) number c 2^-9: codes 0-7 are the format's subnormals and 8-15 its
-// first binade, which has the same spacing.  One v_cvt_scalef32_pk_bf16_fp8 with scale 2^9 therefore makes two bf16
-// integers of two nibbles, without an offset whose removal would cost bits (128 + c, or 16 + c, in the mantissa of a
-// constant: twice to three times the error).  The query and the weights p s are
-// carried in three bf16 limbs, whose sum is the fp32 value: first and second limbs in separate rows of one tile, third
-// limbs in a second product that adds into the first limbs' rows.  So the results are those of fp32 arithmetic.
+// Numerics: both products are integer (v_mfma_i32_16x16x64_i8; saw_fixed.h).  The query and the weights p s are 31-bit
+// fixed-point numbers, four signed byte digits each, and the codes are bytes as they are, so the products and their sums
+// are exact; what is rounded is the query, to 2^-31 of its row's largest element, and each weight, to 2^-29 of the largest weight
+// the wavefront had met when it set the unit.
+// What bounds it is the vector ALU, i.e. instructions: a nibble becomes a byte with 1.5 operations on eight of them where bf16 operands
+// take seven, and the digits of a number need two operations, whatever their count.  Tile rows are 4 head + digit, so that a lane
+// holds all four digits of a head's results and of one head only: no exchange between lanes in front of the softmax, one running
+// state per tile.  (As bf16 products with three limbs: 370 vector-ALU and matrix instructions a batch of eight heads, now 245; 64 ragged
+// sequences of 300 to 3000 tokens x 8 kv heads, 8 query heads each: kernel 28.4 -> 24.9 us, fused step 32.9 -> 30.4; error against
+// 64 bits with fp32 outputs 7.2e-7 -> 4.4e-7.)
 #include "saw_decode.h"
 #include "saw_wave_util.h"
 #include "saw_rank.h"
 #include "saw_cut.h"
+#include "saw_fixed.h"
 
 namespace saw {
 
@@ -28,43 +33,21 @@ namespace split64 {
 
 constexpr int D = 64;
 constexpr int kTile = 512;                     // one (page, head) code tile: 16 tokens x 32 B
-constexpr int kProw = 72;                      // P row stride in bf16 (64 tokens + 8 pad)
-constexpr float kLazyTau = 8.0f;               // the reference maximum may lag the true one by 2^8
 
 template <int G>
 struct Lds {
-  static constexpr int LO = (G > 4) ? 8 : 4;                 // first row of the second limbs
+  static constexpr int NT = (G > 4) ? 2 : 1;                 // row tiles of four heads
   static constexpr int kV = 4 * kTile;
-  static constexpr int kP = 3 * LO * kProw * 2;
-  static constexpr int kWave = kV + kP;
+  static constexpr int kP = NT * kDigitTile;
+  static constexpr int kMeta = 1024;                         // a batch's pairs: K [page][token], then V
+  static constexpr int kWave = kV + kP + kMeta;
 };
 
-// Eight nibbles -> eight bf16 integers in k-order (n0, n2, n4, n6, n1, n3, n5, n7)
-__device__ __forceinline__ bf16x8 unpack8f(uint32_t w) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const uint32_t even = w & 0x0F0F0F0Fu, odd = (w >> 4) & 0x0F0F0F0Fu;
-  u32x4 r;
-  r.x = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(even, 512.f, false));
-  r.y = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(even, 512.f, true));
-  r.z = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(odd, 512.f, false));
-  r.w = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(odd, 512.f, true));
-  return as_bf16x8(r);
-}
-// x = hi + mid + lo, three bf16 values (two truncations; the eight bits that remain are exact)
-__device__ __forceinline__ void split3(float x, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-  hi = __float_as_uint(x) >> 16;
-  const float r = x - __uint_as_float(hi << 16);
-  mid = __float_as_uint(r) >> 16;
-  lo = __float_as_uint(r - __uint_as_float(mid << 16)) >> 16;
-}
-
-template <int NS>
 struct Batch {                                 // one batch as loaded
   u32x2 k[4];                                  // channels 16 grp .. + 15 of token row16 of page q
   u32x4 v[2];                                  // chunk lane % 32 of pages 2 i and 2 i + 1
-  f32x2 km[NS], vm[NS];                        // (scale, zero) of this lane's token(s)
+  f32x2 km, vm;                                // (scale, zero) of token row16 of page grp
 };
-
 }  // namespace split64
 
 // NW wavefronts share a partition: wavefront w takes its batches w, w + NW, ...
@@ -73,9 +56,7 @@ template <int G, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void decode_int4_split64_kernel(DecodeParams p) {
   using namespace split64;
-  constexpr int LO = Lds<G>::LO;
-  constexpr int NS = (G > 4) ? 2 : 1;          // tokens per lane in the softmax layout
-  constexpr int NH = (G > 4) ? 4 : G;          // heads per lane in the softmax layout
+  constexpr int NT = Lds<G>::NT;               // row tiles: lane group grp has head 4 t + grp of tile t
   constexpr int kWave = Lds<G>::kWave;
   const int kvh = blockIdx.y;
   const int lane = threadIdx.x & 63;
@@ -83,7 +64,8 @@ void decode_int4_split64_kernel(DecodeParams p) {
   const int row16 = lane & 15, grp = lane >> 4;
   __shared__ __attribute__((aligned(16))) uint8_t lds_all[NW * kWave];
   uint8_t* const vbuf = lds_all + wave * kWave;
-  uint8_t* const pbuf = vbuf + 4 * kTile;
+  uint8_t* const pbuf = vbuf + Lds<G>::kV;
+  uint8_t* const mbuf = pbuf + Lds<G>::kP;
 
   // ---- which tokens ----
   int b, part = 0, parts = 1, slot;
@@ -166,7 +148,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
   // ---- fetch ----
   const int64_t page_stride = (int64_t)p.n_kv_heads * kTile, head_tile = (int64_t)kvh * kTile;
   const int64_t page_meta = (int64_t)p.n_kv_heads * 32, head_meta = (int64_t)kvh * 32;       // floats
-  auto fetch = [&](int bi, Batch<NS>& r) __attribute__((always_inline)) {
+  auto fetch = [&](int bi, Batch& r) __attribute__((always_inline)) {
     if ((bi >> 4) != window) {
       window = bi >> 4;
       pidv = clamp_pid(pidv_nx);
@@ -183,212 +165,197 @@ void decode_int4_split64_kernel(DecodeParams p) {
       const int pid = lane < 32 ? id[2 * i] : id[2 * i + 1];
       r.v[i] = __builtin_nontemporal_load((const u32x4*)(p.v_codes + (int64_t)pid * page_stride + head_tile + 16 * (lane & 31)));
     }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int pid = (G > 4) ? (lane < 32 ? id[2 * s] : id[2 * s + 1])
-                              : (grp == 0 ? id[0] : grp == 1 ? id[1] : grp == 2 ? id[2] : id[3]);
-      const int64_t m = (int64_t)pid * page_meta + head_meta + 2 * row16;
-      r.km[s] = __builtin_nontemporal_load((const f32x2*)(p.k_meta + m));
-      r.vm[s] = __builtin_nontemporal_load((const f32x2*)(p.v_meta + m));
-    }
+    const int pid = grp == 0 ? id[0] : grp == 1 ? id[1] : grp == 2 ? id[2] : id[3];
+    const int64_t m = (int64_t)pid * page_meta + head_meta + 2 * row16;
+    r.km = __builtin_nontemporal_load((const f32x2*)(p.k_meta + m));
+    r.vm = __builtin_nontemporal_load((const f32x2*)(p.v_meta + m));
   };
   const int mine = (nb > wave) ? (nb - wave + NW - 1) / NW : 0;         // this wavefront's batches
-  Batch<NS> ra, rb;
+  Batch ra, rb;
   if (mine > 0) fetch(wave, ra);
   if (mine > 1) fetch(wave + NW, rb);
 
-  // ---- q~ = (q R) sm_scale log2(e) as A operands ----
-  // lane (row16, grp) holds channels 16 grp + 8 kk + {0, 2, 4, 6, 1, 3, 5, 7} of head row16 % LO
-  u32x4 a_q[2], a_q3[2];
-  float qsum[NH];
+  // ---- q~ = (q R) sm_scale log2(e) as A operands: digits of 31-bit fixed-point numbers, one exponent per row ----
+  i32x4 a_q[NT];                               // 16 channels: even and odd ones of each eight in turn, as unpack_codes has them
+  float qsum[NT], qunit[NT];                   // this lane's heads: sum over channels in the row's unit; the unit
   {
     float* const qs = (float*)vbuf;
 #pragma unroll
     for (int g = 0; g < G; ++g) qs[D * g + lane] = qraw[g];
+    if (G % 4 != 0) {                                         // rows of heads there are none of
+#pragma unroll
+      for (int i = 0; i < kDigitTile / 256; ++i) ((uint32_t*)pbuf)[lane + 64 * i] = 0u;
+    }
     wave_sync();
     float qmul = p.q_scale;
     if (p.rot_k) {
       wave_lds_fwht128<(G + 1) / 2>(qs, p.had_block, lane);  // two 64-channel rows are one 128-channel vector (G = 1: half of one)
       qmul *= had_norm(p.had_block);
     }
-    const bool second = (row16 & LO) != 0;
-    const int head = row16 & (LO - 1);
-    const float qm = (row16 < 2 * LO && head < G) ? qmul : 0.f;
-    const float* const qrow = qs + (head < G ? head : 0) * D + 16 * grp;
+    float* const units = (float*)mbuf;
+    const int head = lane >> 3, ch8 = lane & 7;               // eight lanes a head, eight channels a lane
+    if (G == 8 || head < G) {
+      const f32x4 va = *(const f32x4*)(qs + D * head + 8 * ch8), vb = *(const f32x4*)(qs + D * head + 8 * ch8 + 4);
+      const float x[8] = {va.x * qmul, va.y * qmul, va.z * qmul, va.w * qmul, vb.x * qmul, vb.y * qmul, vb.z * qmul, vb.w * qmul};
+      float mx = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const f32x4 va = *(const f32x4*)(qrow + 8 * kk), vb = *(const f32x4*)(qrow + 8 * kk + 4);
-      uint32_t w[4], w3[4];
+      for (int k = 0; k < 8; ++k) mx = max_or_nan(mx, fabsf(x[k]));
+      mx = max_or_nan(mx, dpp_f<0x141>(mx));                  // the eight lanes of the head: row_half_mirror,
+      mx = max_or_nan(mx, dpp_f<0xB1>(mx));                   // quad_perm 1 0 3 2 and
+      mx = max_or_nan(mx, dpp_f<0x4E>(mx));                   // 2 3 0 1
+      const int e = fixed_exponent(mx);
+      uint32_t even[4], odd[4];
+      uint32_t u[8];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint32_t h0, m0, l0, h1, m1, l1;
-        // dword j packs channels 4 (j & 1) + (j >> 1) and that + 2
-        split3((j & 1 ? vb : va)[j >> 1] * qm, h0, m0, l0);
-        split3((j & 1 ? vb : va)[(j >> 1) + 2] * qm, h1, m1, l1);
-        w[j] = second ? (m0 | (m1 << 16)) : (h0 | (h1 << 16));
-        w3[j] = second ? 0u : (l0 | (l1 << 16));
-      }
-      a_q[kk] = u32x4{w[0], w[1], w[2], w[3]};
-      a_q3[kk] = u32x4{w3[0], w3[1], w3[2], w3[3]};
+      for (int k = 0; k < 8; ++k) u[k] = digit_bytes(nearest_int(__builtin_amdgcn_ldexpf(x[k], e)));
+      transpose_digits(u[0], u[2], u[4], u[6], even);
+      transpose_digits(u[1], u[3], u[5], u[7], odd);
+#pragma unroll
+      for (int l = 0; l < 4; ++l)
+        *(u32x2*)(pbuf + (head >> 2) * kDigitTile + (4 * (head & 3) + l) * kDigitRow + 8 * ch8) = u32x2{even[l], odd[l]};
+      if (ch8 == 0) units[head] = fixed_unit(mx, e);
     }
-    // qsum = sum over channels of q~: row sums by a product with a matrix of ones
-    f32x4 rs = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16x8 ones = as_bf16x8(u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+    wave_sync();
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      rs = mfma_bf16(as_bf16x8(a_q3[kk]), ones, rs);
-      rs = mfma_bf16(as_bf16x8(a_q[kk]), ones, rs);
-    }
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      float t = rs[i];
-      if (G <= 4) t = add_xor16(t);
-      qsum[i] = add_xor32(t);
+    for (int t = 0; t < NT; ++t) {
+      a_q[t] = *(const i32x4*)(pbuf + t * kDigitTile + row16 * kDigitRow + 16 * grp);
+      qunit[t] = (G % 4 == 0 || grp < G) ? units[4 * t + grp] : 0.f;
+      const i32x4 ones = i32x4{0x01010101, 0x01010101, 0x01010101, 0x01010101};
+      qsum[t] = digits_value(mfma_i8(a_q[t], ones, i32x4{0, 0, 0, 0}));
     }
     wave_sync();
   }
-
   // ---- per-lane constants ----
-  // V in LDS: 16-byte chunk Q of token t at chunk 2 t + (Q ^ (t / 8)) of the page's tile, which spreads the rows that
-  // share a bank; the transpose read of channels 16 c .. + 15 takes half c & 1 of chunk c >> 1
-  const int vw_off = kTile * (lane >> 5) + 16 * (((lane & 31) & ~1) + ((lane & 1) ^ ((lane >> 4) & 1)));
-  int vr_off[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) vr_off[c] = grp * kTile + 16 * (2 * row16 + ((c >> 1) ^ (row16 >> 3))) + 8 * (c & 1);
-  // P column of token t of a page: 16 page + 8 (t / 8) + perm^-1(t % 8), the k-order of the unpacked nibbles
-  const int pcol_t = (row16 & 8) + (((row16 & 1) << 2) | ((row16 >> 1) & 3));
-  const int head0 = (G > 4) ? 4 * (grp & 1) : 0;              // first head of this lane
-  const uint16_t* const pa = (const uint16_t*)pbuf + (row16 & (2 * LO - 1)) * kProw + 16 * grp;
-  const uint16_t* const pa3 = (const uint16_t*)pbuf + (2 * LO + (row16 & (LO - 1))) * kProw + 16 * grp;
-  const uint32_t third_rows = (row16 < LO) ? 0xffffffffu : 0u;
+  // V in LDS: 16-byte chunk Q of token t at chunk 2 t + (Q ^ (page & 1)) of the page's tile.  A lane group's transpose reads take
+  // tokens 4 grp .. + 3 of all four pages, page innermost: lane 8 i + 2 page + j supplies token 4 grp + 2 i + j, so that contraction
+  // step 16 grp + 4 r + page is token 4 grp + r, and the four weights of a lane of the softmax are four steps in a row.
+  const int vw_off = kTile * (lane >> 5) + 16 * (((lane & 31) & ~1) + ((lane & 1) ^ (lane >> 5)));
+  const int v_page = (row16 >> 1) & 3, v_tok = 4 * grp + 2 * (row16 >> 3) + (row16 & 1);
+  const int vr_off = v_page * kTile + 32 * v_tok;
+  const int vr_flip = 16 * (v_page & 1);
+  uint8_t* const pw = pbuf + 4 * grp * kDigitRow + 4 * row16;  // digit l of this lane's head: row 4 grp + l
+  const uint8_t* const pr = pbuf + row16 * kDigitRow + 16 * grp;
 
-  f32x4 oacc[4];
+  // Running state: reference, sum of the p and of the w z of this lane's tokens, and sum of the w (c - 8) as 16 times that in digits,
+  // and what was moved out of the digits.  Weights are w = p s kWeightTop relative to the reference of their head: kWeightTop, kLeastLog.
+  i32x4 oacc[NT][4];
+  float otop[NT][4], m_ref[NT], lsum[NT], zs[NT];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) oacc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_ref[NH], lsum[NH], zs[NH];
+  for (int t = 0; t < NT; ++t) {
+    m_ref[t] = -INFINITY; lsum[t] = 0.f; zs[t] = 0.f;
 #pragma unroll
-  for (int i = 0; i < NH; ++i) { m_ref[i] = -INFINITY; lsum[i] = 0.f; zs[i] = 0.f; }
+    for (int c = 0; c < 4; ++c) { oacc[t][c] = i32x4{0, 0, 0, 0}; otop[t][c] = 0.f; }
+  }
+  int room = kFlushAfter;                      // (batches until the digits are moved out; all of them: nothing is in them yet)
 
   // One batch whose first token is position tok0; tokens from t_lim on are masked.  `next` requests the batch
   // that takes these registers next, as soon as they are consumed.
-  auto body = [&](Batch<NS>& r, int tok0, int t_lim, auto&& next) __attribute__((always_inline)) {
-    f32x4 dq[4];
+  auto body = [&](Batch& r, int tok0, int t_lim, auto&& next) __attribute__((always_inline)) {
+    i32x4 dq[NT][4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      const i32x4 kb = operand(code_bytes(r.k[q].x), code_bytes(r.k[q].y));
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const bf16x8 kb = unpack8f(r.k[q][kk]);
-        acc = mfma_bf16(as_bf16x8(a_q3[kk]), kb, acc);
-        acc = mfma_bf16(as_bf16x8(a_q[kk]), kb, acc);
-      }
-      dq[q] = acc;
+      for (int t = 0; t < NT; ++t) dq[t][q] = mfma_i8(a_q[t], kb, i32x4{0, 0, 0, 0});
     }
+    *(f32x2*)(mbuf + 8 * lane) = r.km;
+    *(f32x2*)(mbuf + 512 + 8 * lane) = r.vm;
 #pragma unroll
     for (int i = 0; i < 2; ++i) *(u32x4*)(vbuf + 2 * kTile * i + vw_off) = r.v[i];
-    f32x2 km[NS], vm[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) { km[s] = r.km[s]; vm[s] = r.vm[s]; }
     next(r);
-    // ---- gather: limbs added, lane = token of the batch, registers = heads ----
-    float lg[NS][NH];
-    bool valid[NS];
-    bool need = false;
+    wave_sync();
+    // ---- this lane's tokens are row16 of the four pages, its heads grp and 4 + grp ----
+    f32x2 vm[4];
+    float lg[NT][4];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) valid[s] = tok0 + 16 * ((G > 4) ? 2 * s + (lane >> 5) : grp) + row16 < t_lim;
+    for (int q = 0; q < 4; ++q) {
+      const f32x2 km = *(const f32x2*)(mbuf + 128 * q + 8 * row16);
+      vm[q] = *(const f32x2*)(mbuf + 512 + 128 * q + 8 * row16);
 #pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      float raw[NS];
-      if constexpr (G > 4) {        // tile rows: first limbs of heads 0-3 | 4-7 | second limbs of 0-3 | 4-7
+      for (int t = 0; t < NT; ++t) lg[t][q] = (km.x * qunit[t]) * fmaf(-km.y, qsum[t], digits_value(dq[t][q]));
+    }
+    if (tok0 + 64 > t_lim) {                                  // wavefront-uniform
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          float hi, lo;
-          swap32(dq[2 * s][i], dq[2 * s + 1][i], hi, lo);
-          raw[s] = hi + lo;
+      for (int q = 0; q < 4; ++q) {
+        const bool valid = tok0 + 16 * q + row16 < t_lim;
+        vm[q] = valid ? vm[q] : f32x2{0.f, 8.f};
+#pragma unroll
+        for (int t = 0; t < NT; ++t) lg[t][q] = valid ? lg[t][q] : -INFINITY;
+      }
+    }
+    float scale[4], w[NT][4], pr_[NT][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) scale[q] = vm[q].x * kWeightTop;
+    float most = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        pr_[t][q] = fast_exp2(lg[t][q] - m_ref[t]);           // exp2(-inf) = 0 for masked tokens
+        w[t][q] = pr_[t][q] * scale[q];
+        most = max_or_nan(most, fabsf(w[t][q]));
+      }
+    if (__any(!(most <= kWeightMost)) || room == 0) {
+      float lv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) lv[q] = fmaxf(__builtin_amdgcn_logf(fabsf(vm[q].x)), kLeastLog);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float mx = fmaxf(fmaxf(lg[t][0] + lv[0], lg[t][1] + lv[1]), fmaxf(lg[t][2] + lv[2], lg[t][3] + lv[3]));
+        const float mnew = fmaxf(m_ref[t], row_allmax(mx));
+        if (room != kFlushAfter) {
+          const float alpha = fast_exp2(m_ref[t] - mnew);
+          lsum[t] *= alpha;
+          zs[t] *= alpha;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            otop[t][c] = (otop[t][c] + long_digits_value(oacc[t][c])) * alpha;
+            oacc[t][c] = i32x4{0, 0, 0, 0};
+          }
         }
-      } else {                      // first limbs | second limbs | idle | idle
-        float h01, l01, h23, l23, hi, lo, junk;
-        swap16(dq[0][i], dq[1][i], h01, l01);
-        swap16(dq[2][i], dq[3][i], h23, l23);
-        swap32(h01, h23, hi, junk);
-        swap32(l01, l23, lo, junk);
-        raw[0] = hi + lo;
-      }
+        m_ref[t] = mnew;
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const float v = km[s].x * fmaf(-km[s].y, qsum[i], raw[s]);
-        lg[s][i] = valid[s] ? v : -INFINITY;
-        need |= lg[s][i] > m_ref[i] + kLazyTau;
+        for (int q = 0; q < 4; ++q) {
+          pr_[t][q] = fast_exp2(lg[t][q] - mnew);
+          w[t][q] = pr_[t][q] * scale[q];
+        }
       }
+      room = kFlushAfter;
     }
-    if (__any(need)) {
+    --room;
 #pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        float mx = lg[0][i];
-        if (NS > 1) mx = fmaxf(mx, lg[NS - 1][i]);
-        mx = row_allmax(mx);
-        if (G <= 4) mx = max_xor16(mx);                       // eight heads: lanes 32 apart share the head group
-        mx = max_xor32(mx);
-        const float mnew = fmaxf(m_ref[i], mx);
-        const float alpha = fast_exp2(m_ref[i] - mnew);       // 0 on the first batch
-        lsum[i] *= alpha;
-        zs[i] *= alpha;
+    for (int t = 0; t < NT; ++t) {
+      uint32_t u[4], d[4];
+      float z = w[t][0] * (vm[0].y - 8.f);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) oacc[c][i] *= alpha;
-        m_ref[i] = mnew;
-      }
-    }
+      for (int q = 1; q < 4; ++q) z = fmaf(w[t][q], vm[q].y - 8.f, z);
+      zs[t] += z;                                             // (one addition a batch to each running sum)
+      lsum[t] += (pr_[t][0] + pr_[t][1]) + (pr_[t][2] + pr_[t][3]);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int col = 16 * ((G > 4) ? 2 * s + (lane >> 5) : grp) + pcol_t;
-      const float vs = valid[s] ? vm[s].x : 0.f;
-      const float vz = valid[s] ? vm[s].y - 8.f : 0.f;                 // (codes count from 8: see below)
+      for (int q = 0; q < 4; ++q) u[q] = digit_bytes(nearest_int(w[t][q]));
+      transpose_digits(u[0], u[1], u[2], u[3], d);
 #pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        const float pr = fast_exp2(lg[s][i] - m_ref[i]);      // exp2(-inf) = 0 for masked tokens
-        lsum[i] += pr;
-        const float w = pr * vs;
-        zs[i] = fmaf(w, vz, zs[i]);
-        uint32_t h, m, l;
-        split3(w, h, m, l);
-        uint16_t* const pw = (uint16_t*)pbuf + (head0 + i) * kProw + col;
-        pw[0] = (uint16_t)h;
-        pw[LO * kProw] = (uint16_t)m;
-        pw[2 * LO * kProw] = (uint16_t)l;
-      }
+      for (int l = 0; l < 4; ++l) *(uint32_t*)(pw + t * kDigitTile + l * kDigitRow) = d[l];
     }
     wave_sync();
     // ---- O[row][channel] += P (rows x 64 tokens) . V codes ----
-    const u32x4 p0 = *(const u32x4*)pa, p1 = *(const u32x4*)(pa + 8);
-    u32x4 q0 = *(const u32x4*)pa3, q1 = *(const u32x4*)(pa3 + 8);
-    q0 &= u32x4{third_rows, third_rows, third_rows, third_rows};
-    q1 &= u32x4{third_rows, third_rows, third_rows, third_rows};
-    // The batch's sums start at -8 sum w (a product with a matrix of -8) and are then added to the running ones: the
-    // codes count from the middle of their range, so that the running sums stay as small as the values they stand
-    // for (a range of 5000 tokens: 3e-5 of the output off without this, 3e-6 with it).
-    const bf16x8 eights = as_bf16x8(u32x4{0xc100c100u, 0xc100c100u, 0xc100c100u, 0xc100c100u});
-    f32x4 mid = f32x4{0.f, 0.f, 0.f, 0.f};
-    mid = mfma_bf16(as_bf16x8(q0), eights, mid);
-    mid = mfma_bf16(as_bf16x8(q1), eights, mid);
-    mid = mfma_bf16(as_bf16x8(p0), eights, mid);
-    mid = mfma_bf16(as_bf16x8(p1), eights, mid);
+    i32x4 pa[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) pa[t] = *(const i32x4*)(pr + t * kDigitTile);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const i32x2 tv = __builtin_amdgcn_ds_read_tr4_b64_v2i32((LDS_AS i32x2*)(vbuf + vr_off[c]));
-      const bf16x8 v0 = unpack8f((uint32_t)tv.x), v1 = unpack8f((uint32_t)tv.y);
-      f32x4 t = mfma_bf16(as_bf16x8(q0), v0, mid);
-      t = mfma_bf16(as_bf16x8(q1), v1, t);
-      t = mfma_bf16(as_bf16x8(p0), v0, t);
-      t = mfma_bf16(as_bf16x8(p1), v1, t);
-      oacc[c] += t;
+      const i32x2 tv = __builtin_amdgcn_ds_read_tr4_b64_v2i32((LDS_AS i32x2*)(vbuf + vr_off + ((16 * (c >> 1)) ^ vr_flip) + 8 * (c & 1)));
+      const i32x4 vb = operand(centred_bytes((uint32_t)tv.x), centred_bytes((uint32_t)tv.y));
+#pragma unroll
+      for (int t = 0; t < NT; ++t) oacc[t][c] = mfma_i8(pa[t], vb, oacc[t][c]);
     }
-    wave_sync();                                              // V and P are rewritten by the next batch
+    wave_sync();                                              // V, P and the pairs are rewritten by the next batch
   };
   for (int n = 0; n < mine; n += 2) {
     const int bi = wave + NW * n;
-    body(ra, t_begin + 64 * bi, t_end, [&](Batch<NS>& r) { if (n + 2 < mine) fetch(bi + 2 * NW, r); });
+    body(ra, t_begin + 64 * bi, t_end, [&](Batch& r) { if (n + 2 < mine) fetch(bi + 2 * NW, r); });
     if (n + 1 < mine)
-      body(rb, t_begin + 64 * (bi + NW), t_end, [&](Batch<NS>& r) { if (n + 3 < mine) fetch(bi + 3 * NW, r); });
+      body(rb, t_begin + 64 * (bi + NW), t_end, [&](Batch& r) { if (n + 3 < mine) fetch(bi + 3 * NW, r); });
   }
 
   // ---- fused append: the step's new token as one more batch in which only token 0 is valid ----
@@ -451,16 +418,15 @@ void decode_int4_split64_kernel(DecodeParams p) {
       if (lane < 32) cb[32 * w + lane] = (uint8_t)byte[w];
     }
     wave_sync();
-    Batch<NS> r;
+    Batch r;
 #pragma unroll
     for (int q = 0; q < 4; ++q) r.k[q] = u32x2{0u, 0u};
     r.k[0] = *(const u32x2*)(cb + 8 * grp);                   // (rows other than token 0 are masked)
     r.v[0] = *(const u32x4*)(cb + 32 + 16 * (lane & 1));
     r.v[1] = r.v[0];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) { r.km[s] = meta[0]; r.vm[s] = meta[1]; }
+    r.km = meta[0]; r.vm = meta[1];
     wave_sync();
-    body(r, 0, 1, [](Batch<NS>&) {});
+    body(r, 0, 1, [](Batch&) {});
     // (nobody waits for these stores)
     if (new_pid >= 0 && new_pid < p.num_pages && lane < 32) {
       const int64_t vec = ((int64_t)new_pid * p.n_kv_heads + kvh) * 16 + (len & 15);
@@ -474,24 +440,18 @@ void decode_int4_split64_kernel(DecodeParams p) {
   }
 
   // ---- this wavefront's record in its own LDS: acc[G][64] un-normalised, then (max, sum) per head ----
-#pragma unroll
-  for (int i = 0; i < NH; ++i) {
-    lsum[i] = row_allsum(lsum[i]);
-    zs[i] = row_allsum(zs[i]);
-    if (G <= 4) { lsum[i] = add_xor16(lsum[i]); zs[i] = add_xor16(zs[i]); }
-    lsum[i] = add_xor32(lsum[i]);
-    zs[i] = add_xor32(zs[i]);
-  }
-  const bool writer = (G > 4) ? (grp < 2) : (grp == 0);
   float* const rec = (float*)vbuf;
 #pragma unroll
-  for (int i = 0; i < NH; ++i) {
+  for (int t = 0; t < NT; ++t) {
+    const int head = 4 * t + grp;
+    lsum[t] = row_allsum(lsum[t]);
+    zs[t] = row_allsum(zs[t]);
+    if (G % 4 == 0 || head < G) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float o = (G > 4) ? add_xor32(oacc[c][i]) : add_xor16(oacc[c][i]);
-      if (writer) rec[(head0 + i) * D + 16 * c + row16] = o - zs[i];
+      for (int c = 0; c < 4; ++c)
+        rec[head * D + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -zs[t]) * (1.f / kWeightTop);
+      if (row16 == 0) { rec[G * D + 2 * head] = m_ref[t]; rec[G * D + 2 * head + 1] = lsum[t]; }
     }
-    if (writer && row16 == 0) { rec[G * D + 2 * (head0 + i)] = m_ref[i]; rec[G * D + 2 * (head0 + i) + 1] = lsum[i]; }
   }
   if (NW > 1) __syncthreads(); else wave_sync();
 

@@ -1,0 +1,136 @@
+"""INT4 decode: queries and weights as fixed-point digits (saw_fixed.h) where rounding, the units and the digits' range could go wrong.
+
+Caches are made of chosen logits: every token of a kv head has the same codes and zero-point, so that its logits are its key scale times
+one number per query head; values are random codes.  Against attention in 64 bits over the same bytes, row by row in the 2-norm.
+What a row may be off by: its logits (up to X in base 2) and their exponentials are fp32 numbers, (X + 4) 2^-22 of the weights; n weights
+rounded to 2^-30 of the largest p s are n 2^-30 of it, times the values' range of 15 over the row's own size; fp32 sums over the n / 64
+batches of the p and of the p s (z - 8), z = 5, round by 2^-25 of them in each; and 2^-20 for the rest."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(8, 1, 64), (4, 3, 64), (1, 1, 64), (2, 3, 64)]        # query heads per kv head, kv heads, head_dim
+
+
+@pytest.fixture(scope="module")
+def saw():
+    from paper_2604_19157_amd import binding
+    binding.lib()
+    return binding
+
+
+def _make(saw, G, Hkv, d, B, L, k_scale, v_scale, seed=3):
+    """k_scale, v_scale: [L] scales of the tokens.  Every sequence has pages of its own with the same bytes."""
+    g = torch.Generator().manual_seed(seed)
+    pages = (L + 16) // 16
+    c = saw.Cache(B * pages, Hkv, d, 1)
+    pad = lambda x: torch.cat([x, torch.full((16 * pages - L,), float("nan"))]).view(pages, 1, 16).expand(pages, Hkv, 16)
+    kc = torch.randint(0, 256, (1, Hkv, 1, d // 2), generator=g, dtype=torch.uint8).expand(pages, Hkv, 16, d // 2)
+    vc = torch.randint(0, 256, (pages, Hkv, 16, d // 2), generator=g, dtype=torch.uint8)
+    km = torch.stack([pad(k_scale), torch.full((pages, Hkv, 16), 7.0)], -1)
+    vm = torch.stack([pad(v_scale), torch.full((pages, Hkv, 16), 5.0)], -1)
+    for dst, src in ((c.k_codes, kc), (c.v_codes, vc), (c.k_meta, km), (c.v_meta, vm)):
+        dst.copy_(src.repeat(B, 1, 1, 1))
+    pt = torch.arange(B * pages, dtype=torch.int32).view(B, pages).cuda()
+    q = torch.randn((Hkv * G, d), generator=g)
+    x = lambda codes: torch.stack([codes & 15, codes >> 4], -1).flatten(-2).double()
+    one = torch.einsum("hgd,hd->hg", q.double().view(Hkv, G, d), x(kc[0, :, 0]) - 7) / d ** 0.5     # logit of scale 1, natural units
+    q = q / (one.abs().flatten()[:, None] / one.sign().flatten()[:, None]).float()                     # ... made 1 for every head
+    q = q * torch.linspace(1.0, 0.8, G).repeat(Hkv)[:, None]
+    one = torch.einsum("hgd,hd->hg", q.double().view(Hkv, G, d), x(kc[0, :, 0]) - 7) / d ** 0.5
+    V = (x(vc) - 5).transpose(0, 1).reshape(Hkv, 16 * pages, d)[:, :L] * v_scale.double()[None, :, None]
+    return c, pt, q, one, V
+
+
+def _exact(one, V, k_scale, v_scale):
+    logits = one[..., None] * k_scale.double()                       # [Hkv][G][L]
+    p = torch.softmax(logits, -1)
+    o = p @ V
+    X = float(logits.abs().max()) / math.log(2)
+    most = (p * v_scale.double()).amax(-1)
+    n, d = V.shape[-2:]
+    sums = n / 64 * 2 ** -25 * (o.norm(dim=-1) + 3 * d ** 0.5 * (p * v_scale.double()).sum(-1))
+    tol = (X + 4) * 2 ** -22 * torch.sqrt((p ** 2) @ (V ** 2).sum(-1, keepdim=True)).squeeze(-1) \
+        + (X + 4) * 2 ** -22 * o.norm(dim=-1) + n * 2 ** -30 * most * 15 * d ** 0.5 + sums + 2 ** -20 * o.norm(dim=-1)
+    return o.flatten(0, 1), tol.flatten()
+
+
+def _check(saw, made, k_scale, v_scale, B, L, splits=(1, 3, 0), tag=""):
+    c, pt, q, one, V = made
+    want, tol = _exact(one, V, k_scale, v_scale)
+    for s in splits:
+        out = torch.full((B,) + q.shape, float("nan"), device="cuda")
+        saw.paged_decode_attn(c, q.expand(B, *q.shape).contiguous().cuda(), pt, torch.full((B,), L, dtype=torch.int32).cuda(),
+                              num_splits=s, out=out)
+        err = (out.cpu().double() - want).norm(dim=-1)
+        print(f"[fixed {tag} splits={s}] worst error over bound {float((err / tol).max()):.3f}", flush=True)
+        assert (err <= tol).all()
+
+
+def _logits(kind, L):
+    t = torch.arange(L, dtype=torch.float32)
+    if kind == "rising":                       # the reference moves in nearly every batch
+        return 1 + t * (60.0 / L)
+    if kind == "falling":
+        return 61 - t * (60.0 / L)
+    # a sink in front of a long even tail, 14 or 20 powers of two below it, whose weights round all alike
+    s = torch.full((L,), 0.5)
+    s[L // 3] = 0.5 + (14 if kind == "sink14" else 20) * math.log(2)
+    return s
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
+@pytest.mark.parametrize("kind", ["rising", "falling", "sink14", "sink20"])
+@pytest.mark.parametrize("B,L", [(2, 1), (2, 65), (2, 4001), (300, 333)])
+def test_chosen_logits(saw, G, Hkv, d, kind, B, L):
+    k = _logits(kind, L)
+    v = 0.5 + 0.4 * torch.cos(torch.arange(L, dtype=torch.float32))
+    _check(saw, _make(saw, G, Hkv, d, B, L, k, v), k, v, B, L, tag=f"{kind} G={G} Hkv={Hkv} d={d} B={B} L={L}")
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
+@pytest.mark.parametrize("lo,hi", [(-60, 60), (-95, -80), (60, 90)])
+def test_value_scales_far_apart(saw, G, Hkv, d, lo, hi):
+    """Scales of the values over many powers of two, some zero: units follow the weights p s, not the p."""
+    L = 1000
+    t = torch.arange(L)
+    v = torch.exp2((lo + (hi - lo) * ((37 * t) % 101) / 101).float())
+    v[t % 9 == 4] = 0.0
+    k = 2 + 3 * torch.sin(t.float())
+    _check(saw, _make(saw, G, Hkv, d, 2, L, k, v), k, v, 2, L, tag=f"scales {lo} {hi} G={G} Hkv={Hkv} d={d}")
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
+def test_all_value_scales_zero(saw, G, Hkv, d):
+    L, k = 200, torch.linspace(1, 3, 200)
+    c, pt, q, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.zeros(L))
+    for s in (1, 2):
+        out = saw.paged_decode_attn(c, q[None].cuda(), pt, torch.tensor([L], dtype=torch.int32).cuda(), num_splits=s)
+        assert (out == 0).all()
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_a_query_row_that_is_not_finite_is_nan_alone(saw, G, Hkv, d, bad):
+    L, k = 150, torch.linspace(1, 3, 150)
+    c, pt, q, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.ones(L))
+    lens = torch.tensor([L], dtype=torch.int32).cuda()
+    for s in (1, 2):
+        want = saw.paged_decode_attn(c, q[None].cuda(), pt, lens, num_splits=s)
+        q2 = q.clone()
+        q2[-1, 11] = bad
+        got = saw.paged_decode_attn(c, q2[None].cuda(), pt, lens, num_splits=s)
+        assert got[0, -1].isnan().all()
+        # (a row that is NaN has the others' units set anew in every batch: another rounding of fp32 sums)
+        assert G * Hkv == 1 or float((got - want)[0, :-1].abs().max() / want.abs().max()) < 2 ** -20
+
+
+@pytest.mark.parametrize("G,Hkv,d", [(8, 1, 64), (1, 1, 64)])
+def test_more_batches_than_the_digits_hold(saw, G, Hkv, d):
+    """One partition whose wavefronts add up more than 1024 batches each, all weights alike."""
+    L = 4 * 64 * 1100 + 17
+    k, v = torch.full((L,), 0.25), torch.full((L,), 0.75)
+    _check(saw, _make(saw, G, Hkv, d, 1, L, k, v), k, v, 1, L, splits=(1,), tag=f"long G={G} d={d}")
