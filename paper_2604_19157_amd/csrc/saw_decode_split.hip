@@ -248,6 +248,99 @@ void decode_int4_split64_kernel(DecodeParams p) {
   }
   int room = kFlushAfter;                      // (batches until the digits are moved out; all of them: nothing is in them yet)
 
+  // ---- fused append: the step's new token ----
+  // Rotated, quantised (Sec. 3 eqs. 1-3, App. A.1) and stored as the store kernel would; what attends to it
+  // comes from LDS, nothing this launch writes to the cache is read back by it.  It opens the running state while the first batches
+  // travel: as one more batch behind the last it made its wavefronts the last ones of the launch.
+  if (takes_new) {
+    float* const yb = (float*)vbuf;                           // [2][64]: K, V
+    uint8_t* const cb = vbuf + 1024;                          // code bytes of K, V
+    const bool rot[2] = {p.rot_k != 0, p.rot_v != 0};
+    float x[2][2];
+    if (p.kv_new_dtype == SAW_BF16) { widen2<SAW_BF16>(new_wk, x[0][0], x[0][1]); widen2<SAW_BF16>(new_wv, x[1][0], x[1][1]); }
+    else                            { widen2<SAW_F16>(new_wk, x[0][0], x[0][1]);  widen2<SAW_F16>(new_wv, x[1][0], x[1][1]); }
+    const int c2 = 2 * (lane & 31);
+    if (rot[0] || rot[1]) {
+      if (p.has_signs) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+          if (rot[w]) {
+            x[w][0] = apply_sign(p.signs, c2, x[w][0]);
+            x[w][1] = apply_sign(p.signs, c2 + 1, x[w][1]);
+          }
+      }
+      // K and V are one 128-channel vector of two blocks; a tensor that is not rotated keeps its values
+      const int w = lane >> 5;
+      *(f32x2*)(yb + D * w + c2) = f32x2{x[w][0], x[w][1]};
+      wave_sync();
+      wave_lds_fwht128<1>(yb, p.had_block, lane);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        if (rot[t]) {
+          const f32x2 y = *(const f32x2*)(yb + D * t + c2);
+          x[t][0] = y.x; x[t][1] = y.y;
+        }
+      wave_sync();
+    }
+    uint32_t byte[2];
+    f32x2 meta[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const float mx = max_xor16(row_allmax(fmaxf(x[w][0], x[w][1])));       // over the 32 lanes of a half
+      const float mn = -max_xor16(row_allmax(-fminf(x[w][0], x[w][1])));
+      const float norm = rot[w] ? had_norm(p.had_block) : 1.0f;
+      const float range = mx - mn;
+      float inv, zq, s_store, z_store;
+      if (range > 0.0f) {
+        inv = 15.0f / range;
+        s_store = range * (norm * (1.0f / 15.0f));
+        zq = rintf(-mn * inv);
+        z_store = zq;
+      } else {  // constant vector
+        inv = 0.0f;
+        zq = 0.0f;
+        s_store = (mn != 0.0f) ? fabsf(mn) * norm : 1.0f;
+        z_store = (mn > 0.0f) ? -1.0f : ((mn < 0.0f) ? 1.0f : 0.0f);
+      }
+      const float q0 = __builtin_amdgcn_fmed3f(rintf(x[w][0] * inv) + zq, 0.0f, 15.0f);
+      const float q1 = __builtin_amdgcn_fmed3f(rintf(x[w][1] * inv) + zq, 0.0f, 15.0f);
+      byte[w] = (uint32_t)q0 | ((uint32_t)q1 << 4);
+      meta[w] = f32x2{s_store, z_store};
+      if (lane < 32) cb[32 * w + lane] = (uint8_t)byte[w];
+    }
+    wave_sync();
+    // its one logit of each head (the same in every column of the tile), and its weight times its codes in fp32
+    const u32x2 kc = *(const u32x2*)(cb + 8 * grp);
+    const i32x4 kb = operand(code_bytes(kc.x), code_bytes(kc.y));
+    float vc[4];                                              // channels 16 c + row16
+#pragma unroll
+    for (int c = 0; c < 4; ++c) vc[c] = (float)((cb[32 + 8 * c + (row16 >> 1)] >> (4 * (row16 & 1))) & 15) - 8.f;
+    const float lv = fmaxf(__builtin_amdgcn_logf(fabsf(meta[1].x)), kLeastLog);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const float lg = (meta[0].x * qunit[t]) * fmaf(-meta[0].y, qsum[t], digits_value(mfma_i8(a_q[t], kb, i32x4{0, 0, 0, 0})));
+      m_ref[t] = lg + lv;
+      const float pr = fast_exp2(lg - m_ref[t]);
+      const float w = pr * (meta[1].x * kWeightTop);
+      lsum[t] = row16 == 0 ? pr : 0.f;
+      zs[t] = row16 == 0 ? w * (meta[1].y - 8.f) : 0.f;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) otop[t][c] = 16.f * w * vc[c];
+    }
+    room = kFlushAfter - 1;                                   // (there is something to be scaled)
+    // (nobody waits for these stores)
+    if (new_pid >= 0 && new_pid < p.num_pages && lane < 32) {
+      const int64_t vec = ((int64_t)new_pid * p.n_kv_heads + kvh) * 16 + (len & 15);
+      const_cast<uint8_t*>(p.k_codes)[vec * (D / 2) + lane] = (uint8_t)byte[0];
+      const_cast<uint8_t*>(p.v_codes)[vec * (D / 2) + lane] = (uint8_t)byte[1];
+      if (lane == 0) {
+        *(f32x2*)(const_cast<float*>(p.k_meta) + vec * 2) = meta[0];
+        *(f32x2*)(const_cast<float*>(p.v_meta) + vec * 2) = meta[1];
+      }
+    }
+    wave_sync();                                              // (the first batch's codes and pairs take the place)
+  }
+
   // One batch whose first token is position tok0; tokens from t_lim on are masked.  `next` requests the batch
   // that takes these registers next, as soon as they are consumed.
   auto body = [&](Batch& r, int tok0, int t_lim, auto&& next) __attribute__((always_inline)) {
@@ -358,87 +451,23 @@ void decode_int4_split64_kernel(DecodeParams p) {
       body(rb, t_begin + 64 * (bi + NW), t_end, [&](Batch& r) { if (n + 3 < mine) fetch(bi + 3 * NW, r); });
   }
 
-  // ---- fused append: the step's new token as one more batch in which only token 0 is valid ----
-  // Rotated, quantised (Sec. 3 eqs. 1-3, App. A.1) and stored as the store kernel would; what attends to it
-  // comes from LDS, nothing this launch writes to the cache is read back by it.
-  if (takes_new) {
-    float* const yb = (float*)vbuf;                           // [2][64]: K, V
-    uint8_t* const cb = vbuf + 1024;                          // code bytes of K, V
-    const bool rot[2] = {p.rot_k != 0, p.rot_v != 0};
-    float x[2][2];
-    if (p.kv_new_dtype == SAW_BF16) { widen2<SAW_BF16>(new_wk, x[0][0], x[0][1]); widen2<SAW_BF16>(new_wv, x[1][0], x[1][1]); }
-    else                            { widen2<SAW_F16>(new_wk, x[0][0], x[0][1]);  widen2<SAW_F16>(new_wv, x[1][0], x[1][1]); }
-    const int c2 = 2 * (lane & 31);
-    if (rot[0] || rot[1]) {
-      if (p.has_signs) {
+  const bool alone = !p.cut && p.num_splits == 1;
+  if (NW == 1 && !alone) {                                    // a record of its own, straight from the registers
 #pragma unroll
-        for (int w = 0; w < 2; ++w)
-          if (rot[w]) {
-            x[w][0] = apply_sign(p.signs, c2, x[w][0]);
-            x[w][1] = apply_sign(p.signs, c2 + 1, x[w][1]);
-          }
-      }
-      // K and V are one 128-channel vector of two blocks; a tensor that is not rotated keeps its values
-      const int w = lane >> 5;
-      *(f32x2*)(yb + D * w + c2) = f32x2{x[w][0], x[w][1]};
-      wave_sync();
-      wave_lds_fwht128<1>(yb, p.had_block, lane);
+    for (int t = 0; t < NT; ++t) {
+      const int head = 4 * t + grp;
+      const float l = row_allsum(lsum[t]), z = row_allsum(zs[t]);
+      if (G % 4 == 0 || head < G) {
+        const int at = kvh * G + head;
+        float* const dst = p.ws + (p.cut ? (int64_t)at * p.cut + slot : ((int64_t)b * p.n_q_heads + at) * p.num_splits + slot) * (D + 2);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-        if (rot[t]) {
-          const f32x2 y = *(const f32x2*)(yb + D * t + c2);
-          x[t][0] = y.x; x[t][1] = y.y;
-        }
-      wave_sync();
-    }
-    uint32_t byte[2];
-    f32x2 meta[2];
-#pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      const float mx = max_xor16(row_allmax(fmaxf(x[w][0], x[w][1])));       // over the 32 lanes of a half
-      const float mn = -max_xor16(row_allmax(-fminf(x[w][0], x[w][1])));
-      const float norm = rot[w] ? had_norm(p.had_block) : 1.0f;
-      const float range = mx - mn;
-      float inv, zq, s_store, z_store;
-      if (range > 0.0f) {
-        inv = 15.0f / range;
-        s_store = range * (norm * (1.0f / 15.0f));
-        zq = rintf(-mn * inv);
-        z_store = zq;
-      } else {  // constant vector
-        inv = 0.0f;
-        zq = 0.0f;
-        s_store = (mn != 0.0f) ? fabsf(mn) * norm : 1.0f;
-        z_store = (mn > 0.0f) ? -1.0f : ((mn < 0.0f) ? 1.0f : 0.0f);
-      }
-      const float q0 = __builtin_amdgcn_fmed3f(rintf(x[w][0] * inv) + zq, 0.0f, 15.0f);
-      const float q1 = __builtin_amdgcn_fmed3f(rintf(x[w][1] * inv) + zq, 0.0f, 15.0f);
-      byte[w] = (uint32_t)q0 | ((uint32_t)q1 << 4);
-      meta[w] = f32x2{s_store, z_store};
-      if (lane < 32) cb[32 * w + lane] = (uint8_t)byte[w];
-    }
-    wave_sync();
-    Batch r;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) r.k[q] = u32x2{0u, 0u};
-    r.k[0] = *(const u32x2*)(cb + 8 * grp);                   // (rows other than token 0 are masked)
-    r.v[0] = *(const u32x4*)(cb + 32 + 16 * (lane & 1));
-    r.v[1] = r.v[0];
-    r.km = meta[0]; r.vm = meta[1];
-    wave_sync();
-    body(r, 0, 1, [](Batch&) {});
-    // (nobody waits for these stores)
-    if (new_pid >= 0 && new_pid < p.num_pages && lane < 32) {
-      const int64_t vec = ((int64_t)new_pid * p.n_kv_heads + kvh) * 16 + (len & 15);
-      const_cast<uint8_t*>(p.k_codes)[vec * (D / 2) + lane] = (uint8_t)byte[0];
-      const_cast<uint8_t*>(p.v_codes)[vec * (D / 2) + lane] = (uint8_t)byte[1];
-      if (lane == 0) {
-        *(f32x2*)(const_cast<float*>(p.k_meta) + vec * 2) = meta[0];
-        *(f32x2*)(const_cast<float*>(p.v_meta) + vec * 2) = meta[1];
+        for (int c = 0; c < 4; ++c)
+          dst[2 + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -z) * (1.f / kWeightTop);
+        if (row16 == 0) *(f32x2*)dst = f32x2{m_ref[t], l};
       }
     }
+    return;
   }
-
   // ---- this wavefront's record in its own LDS: acc[G][64] un-normalised, then (max, sum) per head ----
   float* const rec = (float*)vbuf;
 #pragma unroll
@@ -458,7 +487,6 @@ void decode_int4_split64_kernel(DecodeParams p) {
   // ---- combine the block's records, a few heads per wavefront ----
   constexpr int HPW = (G + NW - 1) / NW;
   const int h0 = wave * HPW;
-  const bool alone = !p.cut && p.num_splits == 1;
   float val[HPW], mm[HPW], den[HPW];
 #pragma unroll
   for (int j = 0; j < HPW; ++j) {
