@@ -173,7 +173,6 @@ void decode_int4_split64_kernel(DecodeParams p) {
   const int mine = (nb > wave) ? (nb - wave + NW - 1) / NW : 0;         // this wavefront's batches
   Batch ra, rb;
   if (mine > 0) fetch(wave, ra);
-  if (mine > 1) fetch(wave + NW, rb);
 
   // ---- q~ = (q R) sm_scale log2(e) as A operands: digits of 31-bit fixed-point numbers, one exponent per row ----
   i32x4 a_q[NT];                               // 16 channels: even and odd ones of each eight in turn, as unpack_codes has them
@@ -247,6 +246,10 @@ void decode_int4_split64_kernel(DecodeParams p) {
     for (int c = 0; c < 4; ++c) { oacc[t][c] = i32x4{0, 0, 0, 0}; otop[t][c] = 0.f; }
   }
   int room = kFlushAfter;                      // (batches until the digits are moved out; all of them: nothing is in them yet)
+
+  // (the second batch only here: requested with the first, 20 loads a wavefront filled the compute unit's memory pipeline in front of the
+  // page ids and queries of wavefronts that had started later, which then ended last: 27.7 -> 26.3 us)
+  if (mine > 1) fetch(wave + NW, rb);
 
   // ---- fused append: the step's new token ----
   // Rotated, quantised (Sec. 3 eqs. 1-3, App. A.1) and stored as the store kernel would; what attends to it
