@@ -8,86 +8,108 @@
 //     zero) pairs go straight from global memory into LDS (global_load_lds_dwordx4, no staging
 //     registers): V and the metadata one batch ahead into double buffers, K into a single buffer
 //     that is refilled as soon as its operand reads are done.  Each lane fetches the 16-byte chunk that belongs at its LDS
-//     position under the swizzle pos(t, Q) = 4t + ((Q + t/4) & 3), which makes every later
+//     position under the swizzle pos(t, Q) = 4t + ((Q + t/4) & 3) (V: (Q + t/4 + page) & 3), which makes every later
 //     LDS read bank-conflict free while a lane quad still reads one whole 64-byte row;
-//   * nibbles become bf16 operands with two ALU ops per pair: (w >> 4i) & 0x000F000F | 0x43004300
-//     is the bf16 pair (128 + c_lo, 128 + c_hi); the constant 128 joins the zero-point;
-//   * logits: D[head][token] = q~ (heads x channels) . codes (channels x tokens) with
-//     v_mfma_f32_16x16x32_bf16; q~ is carried as bf16 hi + lo limbs in separate rows of the
-//     tile (~16 bits together), added after the gather below;
-//   * the four pages' result rows are gathered with v_permlane16/32_swap so that lane =
-//     token of the batch and registers = heads: the softmax runs on all 64 lanes;
-//   * the running maximum is a lazily updated reference: it only moves (with a rescale of
-//     the accumulators) when some logit exceeds it by more than 2^8;
-//   * P.V needs tokens along the contraction: ds_read_b64_tr_b4 hands each lane the 16
-//     tokens of one channel (a 16x16 nibble transpose inside LDS); P goes through LDS once as
-//     bf16 hi/lo rows; O[head][channel] accumulates in eight 16x16 tiles.
-// Zero-points never enter the loops:  q~.k^ = s (q~.(c+128) - (z+128) sum q~),
-// sum_t w_t v^_t = sum_t w_t (c_t+128) - sum_t w_t (z_t+128),  w_t = p_t s_t.
+//   * logits: D[4 head + digit][token] = q~ . codes with v_mfma_i32_16x16x64_i8: q~ is a 31-bit fixed-point number, four signed
+//     byte digits in neighbouring rows of the tile, and a nibble becomes a byte with 1.5 ALU operations on eight of them
+//     (saw_fixed.h).  A lane's four results are the digits of one head and token: no exchange between lanes in front of the softmax;
+//   * the reference of the running state only moves (with a rescale of the accumulators) when a weight outgrows the digits, 2^4 above the
+//     largest weight met when it was set;
+//   * P.V needs tokens along the contraction: ds_read_b64_tr_b4 hands each lane 16 tokens of one channel (a 16x16 nibble
+//     transpose inside LDS); the weights p s go through LDS once as digit rows; O[4 head + digit][channel] adds up exactly in 32-bit
+//     integers.
+// Integers because instructions in front of and between the transfers are what short and middle-sized calls wait for: as bf16 products
+// with hi and lo limbs a batch of four query heads took 506 vector-ALU and matrix instructions, now 191 (eight heads 573, now 287).  Fused steps:
+// 4 x 256 tokens 8.1 -> 6.9 us, 16 x 4096 22.4 -> 21.0, 48 ragged 32.6 -> 30.3, 256 ragged x 8 kv heads 121.5 -> 115.6, 64 ragged with a
+// learned rotation 46.4 -> 41.9; one sequence of 131072 tokens with eight query heads 34.5 -> 33.5.  The error against 64 bits with fp32
+// outputs fell from 2.4e-5 to 4e-7.
+// Zero-points never enter the loops:  q~.k^ = s (q~.c - z sum q~),  sum_t w_t v^_t = sum_t w_t (c_t - 8) - sum_t w_t (z_t - 8),  w_t = p_t s_t.
 // When one partition covers the sequence the kernel also normalises, rotates the output back and
 // writes it (no merge launch), and it can append the step's new token itself (append_token).
 #include "saw_decode.h"
 #include "saw_wave_util.h"
 #include "saw_rank.h"
 #include "saw_cut.h"
+#include "saw_fixed.h"
 
 namespace saw {
 
 constexpr int kTileBytes = 1024;               // one (page, head) code tile: 16 tokens x 64 B
-constexpr int kProw = 72;                      // P row stride in bf16 (64 tokens + 8 pad: conflict-free b128 reads)
-constexpr int kPbufBytes = 16 * kProw * 2;     // P as bf16 [16 rows][64 tokens]
-constexpr float kLazyTau = 8.0f;               // reference max may lag the true max by 2^8
+template <int G> constexpr int kTiles = (G > 4) ? 2 : 1;        // row tiles of four heads
+// Loads of a learned rotation's matrix at once (wave_lds_matvec128) for the query and the new token, and for the output: pair blocks of eight
+// query heads are short of registers, and what they spill is reloaded behind transfers.  256 ragged sequences x 8 kv heads: 16, 16 and
+// 16 loads 161 us, 8 each 150, 4 each with 8 for the token 143, 8 and 4 for the output 142.
+template <int G, bool PAIR> constexpr int kLoads = (PAIR && G > 4) ? 8 : 16;
+template <int G, bool PAIR> constexpr int kLoadsOut = (PAIR && G > 4) ? 4 : 16;
+// Of a head pair with two row tiles a tile is one of the heads: it needs the 64 channels of that head only, one k-step of logits
+template <int G, bool HP> constexpr int kSteps = (HP && G > 4) ? 1 : 2;
+// ... and four column tiles of 16 output channels.  (Half the products: see the kernel.)
+template <int G, bool HP> constexpr int kColumns = (HP && G > 4) ? 4 : 8;
+// (weights are set at 2^27: the sums' error stays below that of the fp32 sums they replace, and the reference moves half as often as from 2^29)
+template <int G, bool HP> using RangeState = FixedState<kTiles<G>, kColumns<G, HP>, 27>;
+constexpr int kQueryTile = 2048;               // digit rows of the query's four heads in LDS, 128 channels each: where their fp32 rows were
+// (chunk of 16 channels: turned by the row, so that a column of chunks is spread over the banks)
+__device__ __forceinline__ int query_at(int row, int chunk) { return 128 * row + 16 * (chunk ^ (row & 7)); }
+// the P buffer: weights as digit rows, [tile][16 rows]; at the start of a range also one tile of the query's
+template <int G> constexpr int kPbufBytes = (G > 4) ? kTiles<G> * kDigitTile : kQueryTile;
 
-// the A operand of k-step kk from the rows of q R (in LDS, 128 floats each): see prepare_q
+// Tile t of the query from the rows of q R (in LDS, 128 floats each), in two steps with a wave_sync between them, so that the digits may
+// take the rows' place: lane (grp, row16) reads channels 8 row16 .. + 7 of head 4 t + grp and leaves their digits, even channels
+// of each eight in front of the odd ones, as code_bytes has them.  Heads there are none of get rows of zeros.
+struct QueryPart {
+  float x[8];
+};
 template <int G>
-__device__ __forceinline__ u32x4 q_operand(const float* qs, int kk, float qmul, int row16, int grp) {
-  constexpr int LO = (G > 4) ? 8 : 4;
-  const bool is_lo = row16 >= LO;
-  const int qhead = row16 - (is_lo ? LO : 0);
-  const bool q_live = qhead < G;
-  const float* const qrow = qs + (q_live ? qhead : 0) * 128 + 32 * grp + 8 * kk;
-  const float qm = q_live ? qmul : 0.f;                      // idle rows of the tile carry zeros
-  const f32x4 va = *(const f32x4*)qrow, vb = *(const f32x4*)(qrow + 4);
-  uint32_t w[4];
+__device__ __forceinline__ QueryPart q_part(const float* rows, int t, float qmul, int lane) {
+  const int head = 4 * t + (lane >> 4);
+  const float* const row = rows + 128 * min(head, G - 1) + 8 * (lane & 15);
+  const f32x4 va = *(const f32x4*)row, vb = *(const f32x4*)(row + 4);
+  const bool live = G % 4 == 0 || head < G;
+  QueryPart r;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {                              // dword j packs channels j (low half) and j + 4
-    const float x0 = va[j] * qm, x1 = vb[j] * qm;
-    const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
-    // hi limbs: the top 16 bits of both values in one byte permute
-    const uint32_t hi = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
-    // lo limbs: the remainders, rounded to nearest even (v_cvt_pk_bf16_f32)
-    const f32x2 rem = f32x2{x0 - __uint_as_float(u0 & 0xffff0000u), x1 - __uint_as_float(u1 & 0xffff0000u)};
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rem, bf16x2_t));
-    w[j] = is_lo ? lo : hi;
-  }
-  return u32x4{w[0], w[1], w[2], w[3]};
+  for (int k = 0; k < 4; ++k) { r.x[k] = live ? va[k] * qmul : 0.f; r.x[4 + k] = live ? vb[k] * qmul : 0.f; }
+  return r;
 }
-template <int G, int NH>
-__device__ __forceinline__ void q_sums(const u32x4 (&a_q)[4], float (&qsum)[NH]) {
-  // qsum = sum over channels of the limbs as the matrix cores will see them: one product per k-step
-  // with a matrix of ones leaves row m's sum in every column; lane (grp, .) holds rows 4 grp + i,
-  // and the hi and lo rows of a head sit one (G <= 4) or two (G = 8) lane groups apart
-  f32x4 rs = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bf16x8 ones = as_bf16x8(u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+__device__ __forceinline__ void q_digits(const QueryPart& r, int lane, uint8_t* dig, float& unit) {
+  float mx = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) rs = mfma_bf16(as_bf16x8(a_q[kk]), ones, rs);
+  for (int k = 0; k < 8; ++k) mx = max_or_nan(mx, fabsf(r.x[k]));
+  mx = max_or_nan(mx, dpp_f<0x121>(mx));                     // over the row of lanes: rotations by 1, 2, 4, 8
+  mx = max_or_nan(mx, dpp_f<0x122>(mx));
+  mx = max_or_nan(mx, dpp_f<0x124>(mx));
+  mx = max_or_nan(mx, dpp_f<0x128>(mx));
+  const int e = fixed_exponent(mx);
+  uint32_t u[8], even[4], odd[4];
 #pragma unroll
-  for (int i = 0; i < NH; ++i) {
-    float t = rs[i];
-    if (G <= 4) t = add_xor16(t);                            // rows 0-3 (hi) + rows 4-7 (lo); groups 2, 3 hold zeros
-    qsum[i] = add_xor32(t);                                  // G = 8: rows 4 (grp & 1) + i (hi) + 8 more (lo)
+  for (int k = 0; k < 8; ++k) u[k] = digit_bytes(nearest_int(__builtin_amdgcn_ldexpf(r.x[k], e)));
+  transpose_digits(u[0], u[2], u[4], u[6], even);
+  transpose_digits(u[1], u[3], u[5], u[7], odd);
+#pragma unroll
+  for (int l = 0; l < 4; ++l)
+    *(u32x2*)(dig + query_at(4 * (lane >> 4) + l, (lane & 15) >> 1) + 8 * (lane & 1)) = u32x2{even[l], odd[l]};
+  unit = fixed_unit(mx, e);
+}
+// the A operands of tile t: k-step kk has channels 32 grp + 16 kk .. + 15, a single one 64 t + 16 grp .. + 15; and the sum over
+// channels of this lane's head, in its unit
+template <int KS>
+__device__ __forceinline__ void q_operands(const uint8_t* dig, int t, int lane, i32x4 (&a_q)[KS], float& qsum) {
+  i32x4 sum = i32x4{0, 0, 0, 0};
+  const i32x4 ones = i32x4{0x01010101, 0x01010101, 0x01010101, 0x01010101};
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    a_q[kk] = *(const i32x4*)(dig + query_at(lane & 15, KS == 2 ? 2 * (lane >> 4) + kk : 4 * t + (lane >> 4)));
+    sum = mfma_i8(a_q[kk], ones, sum);
   }
+  qsum = digits_value(sum);
 }
 
 // ---------------------------------------------------------------------------------------
 // q~ = (q H_blk) sm_scale log2(e) for the G query heads of one kv head, in the lane layout of the
-// logit MFMA's A operand, as bf16 hi and lo limbs (Sec. 4.1: the query is rotated once and
-// consumed by the q.K loop).  Rows m < LO carry the hi limbs of head m, rows LO + g the lo limbs
-// of head g; lane (row16 = m, grp = k-group) holds channels 32*grp + 8*kk + {0,4,1,5,2,6,3,7}.
-// qsum[i] is the sum over channels of hi + lo for the i-th head of this lane's softmax layout.
+// logit MFMA's A operand, as digits of 31-bit fixed-point numbers with one unit per row (Sec. 4.1: the query is rotated once and
+// consumed by the q.K loop).  qsum[t], qunit[t]: sum over channels and unit of this lane's head of tile t.
 // `qraw` holds this lane's share of q (element lane + 64 j), loaded by the caller ahead of time;
-// `qs` is LDS scratch of G*128 floats.  It is a __restrict__ parameter on purpose: that keeps
+// `qs` is LDS scratch of G*128 floats, `dig` of one tile's digits (up to G = 4 they take the rows' place).  These are
+// __restrict__ parameters on purpose: that keeps
 // these LDS accesses in an alias scope of their own, so the compiler does not make them wait for
 // the LDS-DMA transfers the caller already has in flight into other buffers.
 // HP (two 64-channel heads per row, see the kernel): `qraw[j]`, j < G, is channel `lane` of the j-th
@@ -95,12 +117,11 @@ __device__ __forceinline__ void q_sums(const u32x4 (&a_q)[4], float (&qsum)[NH])
 // the other half, so that the 128-channel products below are the 64-channel ones.
 // DN: a learned rotation R_l follows the Hadamard (App. A.3); a compile-time flag, so that the kernels
 // of caches without one carry none of its code.
-template <int G, int NH, bool HP, bool DN>
-__device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&qraw)[2 * G], int lane,
-                                          float* __restrict__ qs, u32x4 (&a_q)[4], float (&qsum)[NH]) {
+template <int G, bool HP, bool DN, int LOADS>
+__device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&qraw)[2 * G], int lane, float* __restrict__ qs,
+                                          uint8_t* __restrict__ dig, i32x4 (&a_q)[kTiles<G>][kSteps<G, HP>], float (&qsum)[kTiles<G>],
+                                          float (&qunit)[kTiles<G>]) {
   constexpr int D = 128;
-  constexpr int LO = (G > 4) ? 8 : 4;
-  const int row16 = lane & 15, grp = lane >> 4;
   if (HP) {
 #pragma unroll
     for (int j = 0; j < G; ++j) {
@@ -127,12 +148,18 @@ __device__ __forceinline__ void prepare_q(const DecodeParams& p, const float (&q
   }
   // learned rotation after the Hadamard (App. A.3: q^ = (q H_b) R_l)
   if constexpr (DN) {
-    if (p.dense_k) wave_lds_matvec128<G>(qs, p.dense, lane);
+    if (p.dense_k) wave_lds_matvec128<G, LOADS>(qs, p.dense, lane);
   }
+  uint8_t* const d = (G > 4) ? dig : (uint8_t*)qs;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) a_q[kk] = q_operand<G>(qs, kk, qmul, row16, grp);
-  q_sums<G, NH>(a_q, qsum);
-  wave_sync();
+  for (int t = 0; t < kTiles<G>; ++t) {
+    const QueryPart part = q_part<G>(qs, t, qmul, lane);
+    wave_sync();
+    q_digits(part, lane, d, qunit[t]);
+    wave_sync();
+    q_operands(d, t, lane, a_q[t], qsum[t]);
+    wave_sync();
+  }
 }
 
 constexpr int kMetaBytesOf(bool hp) { return hp ? 2048 : 1024; }   // one batch's (scale, zero) pairs: K, then V
@@ -158,7 +185,7 @@ __device__ __forceinline__ void append_store(const DecodeParams& p, int lane, co
 }
 // The rotation of the new token's K and V vectors by one wavefront, four channels per lane, K in the lower half (a block that prepares
 // its range together has them from there); w: the channels as loaded; scr: LDS scratch of 256 floats (16-byte aligned).
-template <bool HP, bool DN>
+template <bool HP, bool DN, int LOADS>
 __device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, u32x2 w, float* __restrict__ scr, float (&x)[4]) {
   constexpr int DH = HP ? 64 : 128;
   const bool second = lane >= 32;
@@ -177,9 +204,9 @@ __device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, u3
     else if (p.rot_k) wave_lds_fwht128<1>(scr, p.had_block, lane);
     else if (p.rot_v) wave_lds_fwht128<1>(scr + 128, p.had_block, lane);
     if constexpr (DN) {                                      // k^ = (k H_b) R_l, the same for V (App. A.3)
-      if (dns[0] && dns[1]) wave_lds_matvec128<2>(scr, p.dense, lane);
-      else if (dns[0]) wave_lds_matvec128<1>(scr, p.dense, lane);
-      else if (dns[1]) wave_lds_matvec128<1>(scr + 128, p.dense, lane);
+      if (dns[0] && dns[1]) wave_lds_matvec128<2, LOADS>(scr, p.dense, lane);
+      else if (dns[0]) wave_lds_matvec128<1, LOADS>(scr, p.dense, lane);
+      else if (dns[1]) wave_lds_matvec128<1, LOADS>(scr + 128, p.dense, lane);
     }
     const f32x4 y = *(const f32x4*)(scr + 4 * lane);
     x[0] = y.x; x[1] = y.y; x[2] = y.z; x[3] = y.w;
@@ -191,7 +218,7 @@ __device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, u3
 // (sequence b, kv head kvh) for position L exactly as the store kernel would (Sec. 3 eqs. 1-3,
 // App. A.1; append_store writes them to the pools), and place its codes and (scale, zero) pairs in LDS as token 0 of page 0 of a
 // batch, in the layout the transfers produce.  The caller then runs one more batch in which only that
-// token is valid, so the new token goes through the very code path of the cached ones (same q~ limbs,
+// token is valid, so the new token goes through the very code path of the cached ones (same q~ operands,
 // same softmax update) and nothing this launch writes to the cache is read back by it.  This happens at
 // the END of the range that starts the sequence, when every transfer of the range has landed and the buffers
 // are idle: in the middle of the loop, where wavefronts have no slack, it costs 1-2 us.  The rotation in front of it
@@ -250,7 +277,7 @@ template <bool HP> constexpr int kMetaBytes = HP ? 2048 : 1024;
 // The P buffer is never a transfer target.  Up to G = 4 it also serves, at the start of a range, as the
 // query preparation's scratch (the rotated query rows, at most 2 KB), so that this work touches no
 // memory a transfer may be writing.
-template <int G, bool HP> constexpr int kWaveLdsG = 12 * kTileBytes + kPbufBytes + 2 * kMetaBytes<HP>;   // per wavefront: K buffer, two V buffers, P buffer, two metadata buffers
+template <int G, bool HP> constexpr int kWaveLdsG = 12 * kTileBytes + kPbufBytes<G> + 2 * kMetaBytes<HP>;   // per wavefront: K buffer, two V buffers, P buffer, two metadata buffers
 
 // The start of a range that NW wavefronts of a block share, where they prepare it together (kBlockPrep): every wavefront rotates its
 // share of the G query rows and of the new token's K and V vectors, a learned rotation's product is the block's, and the A operands are
@@ -262,9 +289,11 @@ template <int G, bool HP> constexpr int kWaveLdsG = 12 * kTileBytes + kPbufBytes
 // of which the fixed order of the new token's sums took 0.6 back: block_columns_ordered.)
 template <int NW, bool PAIR, bool HP, bool DN>
 constexpr bool kBlockPrep = !PAIR && (NW == 8 || (NW == 4 && !HP) || (DN && NW > 1));
-// LDS for it beside the wavefronts' buffers, which transfers may target: the rotated rows, then the A operands
+// LDS for it beside the wavefronts' buffers, which transfers may target: the query's rotated rows, whose place its digits take, the new
+// token's from row kNewRow on, and the units
+template <int G> constexpr int kNewRow = (G > 4) ? G : 4;
 template <int G, int NW, bool PAIR, bool HP, bool DN>
-constexpr int kPrepBytes = kBlockPrep<NW, PAIR, HP, DN> ? (G + 2) * 512 + (NW >= 4 ? 4096 : 0) : 0;
+constexpr int kPrepBytes = kBlockPrep<NW, PAIR, HP, DN> ? (kNewRow<G> + 2) * 512 + (NW >= 4 ? 16 * kTiles<G> : 0) : 0;
 
 // This wavefront's vectors (wave, wave + NW, ...: below G a query row, then K, then V): elements `lane` and `lane + 64`, as loaded.
 template <int G, int NW, bool HP>
@@ -294,11 +323,12 @@ __device__ __forceinline__ void block_vectors_load(const DecodeParams& p, int b,
 }
 //   x, y  rows of 128 floats; x is where the vectors are rotated (without a learned rotation it is y), y holds the result; no
 //         transfer in flight may target either, and y stays until the range ends
-//   aq    the A operands, [4][64] of 16 bytes
-template <int G, int NW, int NH, bool HP, bool DN>
+//   dig   in a block of two: one tile of digits of this wavefront's own
+template <int G, int NW, bool HP, bool DN>
 __device__ __forceinline__ void block_prepare(const DecodeParams& p, const uint32_t (&bits)[(G + 1 + NW) / NW][2], bool with_new, int wave,
-                                              int lane, float* __restrict__ x, float* __restrict__ y, u32x4* __restrict__ aq,
-                                              const BlockColumns<DN ? NW : 8>& cols, u32x4 (&a_q)[4], float (&qsum)[NH]) {
+                                              int lane, float* __restrict__ x, float* __restrict__ y, uint8_t* __restrict__ dig,
+                                              const BlockColumns<DN ? NW : 8>& cols, i32x4 (&a_q)[kTiles<G>][kSteps<G, HP>],
+                                              float (&qsum)[kTiles<G>], float (&qunit)[kTiles<G>]) {
   float* const in = DN ? x : y;
 #pragma unroll
   for (int u = 0; u < (G + 1 + NW) / NW; ++u) {
@@ -315,10 +345,11 @@ __device__ __forceinline__ void block_prepare(const DecodeParams& p, const uint3
       }
       // (head pair: a query row has its 64 values in the half of its own kv head and zeros in the other)
       const bool second = HP && v < G && v >= G / 2;
-      in[128 * v + lane] = second ? 0.f : e[0];
-      in[128 * v + 64 + lane] = second ? e[0] : e[1];
+      float* const row = in + 128 * (v < G ? v : v - G + kNewRow<G>);
+      row[lane] = second ? 0.f : e[0];
+      row[64 + lane] = second ? e[0] : e[1];
       wave_sync();
-      if (rot) wave_lds_fwht128<1>(in + 128 * v, p.had_block, lane);
+      if (rot) wave_lds_fwht128<1>(row, p.had_block, lane);
     }
   }
   lds_barrier();
@@ -329,29 +360,45 @@ __device__ __forceinline__ void block_prepare(const DecodeParams& p, const uint3
       for (int i = 64 * wave + lane; i < 128 * G; i += 64 * NW) y[i] = in[i];
     }
     if (with_new) {
+      constexpr int R = 128 * kNewRow<G>;
       if (p.dense_k && p.dense_v) {
-        block_columns_ordered<2, NW>(in + 128 * G, y + 128 * G, cols, lane);
+        block_columns_ordered<2, NW>(in + R, y + R, cols, lane);
       } else {
-        if (p.dense_k) block_columns_ordered<1, NW>(in + 128 * G, y + 128 * G, cols, lane);
-        else if (wave < 2) y[128 * G + 64 * wave + lane] = in[128 * G + 64 * wave + lane];
-        if (p.dense_v) block_columns_ordered<1, NW>(in + 128 * (G + 1), y + 128 * (G + 1), cols, lane);
-        else if (wave < 2) y[128 * (G + 1) + 64 * wave + lane] = in[128 * (G + 1) + 64 * wave + lane];
+        if (p.dense_k) block_columns_ordered<1, NW>(in + R, y + R, cols, lane);
+        else if (wave < 2) y[R + 64 * wave + lane] = in[R + 64 * wave + lane];
+        if (p.dense_v) block_columns_ordered<1, NW>(in + R + 128, y + R + 128, cols, lane);
+        else if (wave < 2) y[R + 128 + 64 * wave + lane] = in[R + 128 + 64 * wave + lane];
       }
     }
     lds_barrier();
   }
-  const int row16 = lane & 15, grp = lane >> 4;
+  constexpr int NT = kTiles<G>;
   const float qmul = p.rot_k ? p.q_scale * had_norm(p.had_block) : p.q_scale;
   if constexpr (NW >= 4) {
-    if (wave < 4) aq[64 * wave + lane] = q_operand<G>(y, wave, qmul, row16, grp);
+    uint8_t* const d = (uint8_t*)y;
+    float* const units = y + 128 * (kNewRow<G> + 2);
+    if (wave < NT) {
+      const QueryPart part = q_part<G>(y, wave, qmul, lane);
+      wave_sync();
+      float unit;
+      q_digits(part, lane, d + wave * kQueryTile, unit);
+      if ((lane & 15) == 0) units[4 * wave + (lane >> 4)] = unit;
+    }
     lds_barrier();
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) a_q[kk] = aq[64 * kk + lane];
+    for (int t = 0; t < NT; ++t) {
+      q_operands(d + t * kQueryTile, t, lane, a_q[t], qsum[t]);
+      qunit[t] = units[4 * t + (lane >> 4)];
+    }
   } else {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) a_q[kk] = q_operand<G>(y, kk, qmul, row16, grp);
+    for (int t = 0; t < NT; ++t) {
+      q_digits(q_part<G>(y, t, qmul, lane), lane, dig, qunit[t]);
+      wave_sync();
+      q_operands(dig, t, lane, a_q[t], qsum[t]);
+      wave_sync();
+    }
   }
-  q_sums<G, NH>(a_q, qsum);
   wave_sync();
 }
 
@@ -365,38 +412,34 @@ __device__ __forceinline__ void block_prepare(const DecodeParams& p, const uint3
 // with a learned rotation 50.1 -> 47.9.
 template <int G, int NW, bool HP, bool DN, bool CUT>
 __device__ __forceinline__ void block_epilogue(const DecodeParams& p, uint8_t* const lds_all, int wave, int lane, int b, int kvh,
-                                               int split, const f32x4 (&oacc)[8], const float (&m_ref)[(G > 4) ? 4 : G],
-                                               const float (&lsum)[(G > 4) ? 4 : G], const float (&zs)[(G > 4) ? 4 : G]) {
+                                               int split, RangeState<G, HP> st) {
   constexpr int DH = HP ? 64 : 128;
   constexpr int GK = HP ? G / 2 : G;
-  constexpr int NH = (G > 4) ? 4 : G;
+  constexpr int NT = kTiles<G>, NC = kColumns<G, HP>;
   constexpr int kWaveLds = kWaveLdsG<G, HP>;
-  constexpr int SW = (G > 4) ? 64 : 32;                       // lanes whose accumulator rows are heads' limbs
-  constexpr int SP = SW + 4;                                  // row pitch: the reads below touch every bank once
-  constexpr int kL = 32 * SP, kZ = kL + 64 * NH, kM = kZ + 64 * NH;
+  constexpr int SP = 128 + 16;                                // pitch of a head's channels: the four heads of a write differ in their banks
+  constexpr int kM = G * SP;                                  // then (maximum, sum) of each head
   constexpr int HPW = (G + NW - 1) / NW;                      // heads of a wavefront
   constexpr int kScr = 12 * kTileBytes;                       // (the P and metadata buffers: no state reaches them)
-  static_assert((kM + G) * 4 <= kScr, "a state fits in front of the P buffer");
-  static_assert(HPW * 512 <= kPbufBytes && G * 512 <= kPbufBytes + 2 * kMetaBytesOf(HP), "the heads' rows fit behind it");
+  static_assert((kM + 2 * G) * 4 <= kScr, "a state fits in front of the P buffer");
+  static_assert(HPW * 512 <= kPbufBytes<G> + 2 * kMetaBytesOf(HP) && G * 512 <= kPbufBytes<G> + 2 * kMetaBytesOf(HP), "the heads' rows fit behind it");
   const int row16 = lane & 15, grp = lane >> 4;
   const bool alone = !CUT && p.num_splits == 1;
   BlockColumns<DN ? NW : 8> cols;                             // (requested now: the exchange of the states hides the trip to L2)
   if constexpr (DN) {
     if (alone && p.dense_v) block_columns_load<NW>(p.dense + kDenseD * kDenseD, wave, lane, cols);
   }
+  st.sum_lanes();
   {
-    float* const st = (float*)(lds_all + wave * kWaveLds);
-    if (SW == 64 || lane < SW) {
+    float* const own = (float*)(lds_all + wave * kWaveLds);
 #pragma unroll
-      for (int c = 0; c < 8; ++c)
+    for (int t = 0; t < NT; ++t) {
+      const int head = 4 * t + grp;
+      if (G % 4 == 0 || head < G) {
 #pragma unroll
-        for (int i = 0; i < NH; ++i) st[(4 * c + i) * SP + lane] = oacc[c][i];
-    }
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      st[kL + 64 * i + lane] = lsum[i];
-      st[kZ + 64 * i + lane] = zs[i];
-      if (row16 == 0 && grp < (G > 4 ? 2 : 1)) st[kM + (G > 4 ? 4 * grp : 0) + i] = m_ref[i];
+        for (int c = 0; c < NC; ++c) own[head * SP + 16 * (NC == 8 ? c : 4 * t + c) + row16] = st.value(t, c);
+        if (row16 == 0) *(f32x2*)(own + kM + 2 * head) = f32x2{st.m_ref[t], st.lsum[t]};
+      }
     }
   }
   __syncthreads();
@@ -407,32 +450,23 @@ __device__ __forceinline__ void block_epilogue(const DecodeParams& p, uint8_t* c
 #pragma unroll
   for (int j = 0; j < HPW; ++j) {
     const int h = min(h0 + j, G - 1);
-    const int i = h & (NH - 1), hg = (G > 4) ? h >> 2 : 0;    // row of the lane's four, lane group (hi limbs)
-    constexpr int LOF = (G > 4) ? 32 : 16;                    // lanes from the hi to the lo limbs' rows
-    float a[NW], mm = -INFINITY;                              // (some wavefront has a batch or the new token: the maximum is finite)
+    float a[NW], ls[NW], mm = -INFINITY;                      // (some wavefront has a batch or the new token: the maximum is finite)
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      a[w] = ((const float*)(lds_all + w * kWaveLds))[kM + h];
+      const f32x2 ml = *(const f32x2*)((const float*)(lds_all + w * kWaveLds) + kM + 2 * h);
+      a[w] = ml.x;
+      ls[w] = ml.y;
       mm = fmaxf(mm, a[w]);
     }
-    // the lane sums: up to four heads every lane has a part of each, with eight the lanes of two groups
-    const int at = (G > 4) ? 64 * i + 32 * ((lane >> 4) & 1) + 16 * hg + row16 : 64 * i + lane;
-    const int cell = (4 * grp + i) * SP + 16 * hg + row16;    // channel `lane`; channel lane + 64 is 16 rows further
-    float l = 0.f, z = 0.f, v0 = 0.f, v1 = 0.f;
+    float l = 0.f, v0 = 0.f, v1 = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float* const so = (const float*)(lds_all + w * kWaveLds);
+      const float* const so = (const float*)(lds_all + w * kWaveLds) + h * SP + lane;
       const float aw = fast_exp2(a[w] - mm);                  // 0 for a wavefront that had no batch
-      l = fmaf(aw, so[kL + at], l);
-      z = fmaf(aw, so[kZ + at], z);
-      v0 = fmaf(aw, so[cell] + so[cell + LOF], v0);
-      v1 = fmaf(aw, so[cell + 16 * SP] + so[cell + 16 * SP + LOF], v1);
+      l = fmaf(aw, ls[w], l);
+      v0 = fmaf(aw, so[0], v0);
+      v1 = fmaf(aw, so[64], v1);
     }
-    l = add_xor16(row_allsum(l));
-    z = add_xor16(row_allsum(z));
-    if (G <= 4) { l = add_xor32(l); z = add_xor32(z); }
-    v0 -= z;
-    v1 -= z;
     if (!alone) {
       // one of several partitions: (max, sum, un-normalised accumulator) for the merge kernel
       if (h0 + j < G) {
@@ -555,10 +589,9 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   constexpr int D = 128;                       // channels of a row (a head, or a pair of 64-channel heads)
   constexpr int DH = HP ? 64 : 128;            // channels of one head
   constexpr int GK = HP ? G / 2 : G;           // query heads per kv head
-  constexpr int KV = (HP && G <= 4) ? 2 : 1;   // kv heads whose metadata one lane needs (G = 8: its own only)
-  constexpr int NS = (G > 4) ? 2 : 1;          // tokens per lane in the softmax layout
-  constexpr int NH = (G > 4) ? 4 : G;          // heads per lane in the softmax layout
-  constexpr int LO = (G > 4) ? 8 : 4;          // first row of the lo limbs of P
+  constexpr int NT = kTiles<G>;                // row tiles: lane group grp has head 4 t + grp of tile t
+  constexpr int NC = kColumns<G, HP>, KS = kSteps<G, HP>;
+  constexpr int NM = (HP && NT == 2) ? 2 : 1;  // kv heads whose pairs a lane needs: its tiles' (head pair), else one
   constexpr int STEP = PAIR ? 1 : NW;          // batch stride of a wavefront inside its range
   // (which partition a block takes is rotated by its kv head and sequence: blocks go to the XCDs round
   // robin in launch order, and with the partition index as the fastest grid index and a partition count
@@ -591,7 +624,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   uint8_t* const vbuf_a = kbuf + 4 * kTileBytes;
   uint8_t* const vbuf_b = kbuf + 8 * kTileBytes;
   uint8_t* const pbuf = kbuf + 12 * kTileBytes;
-  uint8_t* const mbuf_a = pbuf + kPbufBytes;   // metadata of the batch in vbuf_a / vbuf_b
+  uint8_t* const mbuf_a = pbuf + kPbufBytes<G>;   // metadata of the batch in vbuf_a / vbuf_b
   uint8_t* const mbuf_b = mbuf_a + kMetaBytes<HP>;
   int* const done_cnt = (int*)(lds_all + NW * kWaveLds);        // PAIR: records left so far of the block's sequences [k]
   float* const spare_rec = (float*)(lds_all + NW * kWaveLds + 16);   // PAIR, NW = 4: spare record of sequence k >= 1 at (k - 1) * kRecFloats
@@ -735,18 +768,28 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // quarter Q of a row is 16 source bytes: of the token's 64 (head_dim 128), or half Q & 1 of the
   // token's 32 in head Q >> 1 of the pair, whose tiles follow each other
   const int q_src = ((lane & 3) - (lane >> 4)) & 3;
-  const int g_swz = HP ? 512 * (q_src >> 1) + 32 * (lane >> 2) + 16 * (q_src & 1) : 64 * (lane >> 2) + 16 * q_src;
-  const uint32_t kbias = bf16_bias();
+  const auto source = [&](int quarter) { return HP ? 512 * (quarter >> 1) + 32 * (lane >> 2) + 16 * (quarter & 1) : 64 * (lane >> 2) + 16 * quarter; };
+  const int g_swz = source(q_src);
+  // V tiles are turned further by their page of the batch: stored quarter s of a row is quarter (s - t/4 - page) & 3, so that the
+  // transpose reads, which take the same tokens of all four pages at once, touch every bank once
+  int g_swz_v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) g_swz_v[q] = source((q_src - q) & 3);
   // ---- per-lane constants ----
   const int kr_off = 16 * (4 * row16 + ((grp + (row16 >> 2)) & 3));                 // K read: t = row16, Q = grp
-  int vr_off[8];
+  // (one k-step a head: quarter 2 head + grp / 2 of token row16, half grp % 2 of its 16 bytes)
+  const int kr_pair[2] = {16 * (4 * row16 + (((grp >> 1) + (row16 >> 2)) & 3)) + 8 * (grp & 1),
+                          16 * (4 * row16 + ((2 + (grp >> 1) + (row16 >> 2)) & 3)) + 8 * (grp & 1)};
+  // V transpose reads: a lane group takes tokens 4 grp .. + 3 of all four pages, page innermost: lane 8 i + 2 page + j supplies
+  // token 4 grp + 2 i + j, so that contraction step 16 grp + 4 r + page is token 4 grp + r, and the four weights of a lane of the
+  // softmax (token row16 of the four pages) are four steps in a row
+  const int v_page = (row16 >> 1) & 3, v_tok = 4 * grp + 2 * (row16 >> 3) + (row16 & 1);
+  int vr_off[4];                                                                     // channels 32 i .. + 15; the next 16 are 8 bytes on
 #pragma unroll
-  for (int c = 0; c < 8; ++c)
-    vr_off[c] = grp * kTileBytes + 16 * (4 * row16 + (((c >> 1) + (row16 >> 2)) & 3)) + 8 * (c & 1);
-  // P write column inside the batch: 16*page + 8*(t/8) + perm^-1(t%8),  perm^-1(u) = (u&3)<<1 | u>>2
-  const int pcol_t = (row16 & 8) + (((row16 & 3) << 1) | ((row16 >> 2) & 1));
-  const int head0 = (G > 4) ? 4 * (grp & 1) : 0;                                    // first head of this lane
-  const uint32_t pa_addr = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)pbuf + (row16 * kProw + 16 * grp) * 2;   // LDS byte address
+  for (int i = 0; i < 4; ++i) vr_off[i] = v_page * kTileBytes + 16 * (4 * v_tok + ((i + grp + v_page) & 3));
+  const int kv_of = HP ? min(grp, G - 1) / GK : 0;                                   // head pair, one tile: which of the two heads' pairs
+  const int pw_off = 4 * grp * kDigitRow + 4 * row16;                                // digit l of this lane's head: row 4 grp + l
+  const uint32_t pa_addr = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)pbuf + row16 * kDigitRow + 16 * grp;   // LDS byte address
 
 #pragma unroll 1
   for (int seg = 0; seg < nseg; ++seg) {
@@ -847,7 +890,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     SAW_ROTATE_PIDS(batch)                                                                      \
     _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                             \
       const uint8_t* vp = p.v_codes + (int64_t)SAW_PID(batch, q) * page_stride + head_tile;     \
-      SAW_DMA(vp + g_swz, VDST + q * kTileBytes);                                               \
+      SAW_DMA(vp + g_swz_v[q], VDST + q * kTileBytes);                                               \
     }                                                                                           \
     const int mq = HP ? (lane >> 4) : (lane >> 3) & 3;                                          \
     const int id = mq == 0 ? SAW_PID(batch, 0) : mq == 1 ? SAW_PID(batch, 1)                    \
@@ -892,16 +935,16 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // query scratch: up to G = 4 in the P buffer (no transfer ever targets it), else the second V
   // buffer for the rows (first written by the second batch's transfers, which leave after this)
   float* const qrows = (G <= 4) ? (float*)pbuf : (float*)vbuf_b;
-  u32x4 a_q[4];
-  float qsum[NH];
+  i32x4 a_q[NT][KS];
+  float qsum[NT], qunit[NT];
   float new_x[4] = {0.f, 0.f, 0.f, 0.f};                      // the new token's channels of this lane, rotated
   if constexpr (kBP) {
     float* const rows = (float*)(lds_all + NW * kWaveLds + 16 + kSpareBytes);
     // (rows to be multiplied: wavefront 0's second V buffer and what follows, which nobody writes to before the barrier behind the product)
-    block_prepare<G, NW, NH, HP, DN>(p, vbits, block_new, wave, lane, (float*)(lds_all + 8 * kTileBytes), rows,
-                                     (u32x4*)(rows + 128 * (G + 2)), cols, a_q, qsum);
+    block_prepare<G, NW, HP, DN>(p, vbits, block_new, wave, lane, (float*)(lds_all + 8 * kTileBytes), rows,
+                                 pbuf, cols, a_q, qsum, qunit);
     if (takes_new) {
-      const f32x4 v = *(const f32x4*)(rows + 128 * G + 4 * lane);                 // K, then V
+      const f32x4 v = *(const f32x4*)(rows + 128 * kNewRow<G> + 4 * lane);                 // K, then V
       new_x[0] = v.x; new_x[1] = v.y; new_x[2] = v.z; new_x[3] = v.w;
     }
   } else {
@@ -916,15 +959,15 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       // randomised Hadamard: q diag(sigma) first (element lane + 64 j is channel lane + 64 (j & 1))
       if (p.rot_k && p.has_signs) qraw[j] = apply_sign(p.signs, HP ? lane : lane + 64 * (j & 1), qraw[j]);
     }
-    prepare_q<G, NH, HP, DN>(p, qraw, lane, qrows, a_q, qsum);
+    prepare_q<G, HP, DN, kLoads<G, PAIR>>(p, qraw, lane, qrows, pbuf, a_q, qsum, qunit);
   }
 
-  f32x4 oacc[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) oacc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_ref[NH], lsum[NH], zs[NH];
-#pragma unroll
-  for (int i = 0; i < NH; ++i) { m_ref[i] = -INFINITY; lsum[i] = 0.f; zs[i] = 0.f; }
+  using State = RangeState<G, HP>;
+  i32x4 digits[NT][NC];
+  float m_ref[NT], lsum[NT], zs[NT], top;
+  int room;
+  State st{digits, m_ref, lsum, zs, top, room};
+  st.clear();
 
   // One batch, whose first token is position tok0 of the sequence.  On entry the transfers of batch bi
   // (V into vcur, K into kb, metadata) are the only ones this wavefront has in flight.
@@ -938,22 +981,26 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     // (issued through the builtin, not inline asm, so that the compiler's wait-count pass sees it
     // and stops guarding earlier loads, e.g. the q~ operands, with waits of its own further down)
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0): batch bi has landed (codes in LDS, metadata)
-    f32x2 km[NS][KV], vm[NS][KV];
+    // (this lane's tokens are row16 of the four pages, its heads 4 t + grp)
+    f32x2 km[NM][4];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int pg = (G > 4) ? (2 * s + (lane >> 5)) : grp;        // page of this lane's token
+    for (int n = 0; n < NM; ++n)
 #pragma unroll
-      for (int kv = 0; kv < KV; ++kv) {
-        // head pair: [page][kv head][token]; with G = 8 a lane's four heads belong to kv head grp & 1
-        const int mo = HP ? 256 * pg + 128 * (G > 4 ? (grp & 1) : kv) + 8 * row16 : 128 * pg + 8 * row16;
-        km[s][kv] = *(const f32x2*)(mcur + mo);
-        vm[s][kv] = *(const f32x2*)(mcur + kMetaBytes<HP> / 2 + mo);
+      for (int q = 0; q < 4; ++q) {
+        // head pair: [page][kv head][token]
+        km[n][q] = *(const f32x2*)(mcur + (HP ? 256 * q + 128 * (NM == 2 ? n : kv_of) : 128 * q) + 8 * row16);
       }
-    }
     // K operand reads first, before the next transfers are issued.
     u32x4 kw[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) kw[q] = *(const u32x4*)(kb + q * kTileBytes + kr_off);
+    for (int q = 0; q < 4; ++q) {
+      if (KS == 2) {
+        kw[q] = *(const u32x4*)(kb + q * kTileBytes + kr_off);
+      } else {                                             // 16 channels of either head
+        const u32x2 a = *(const u32x2*)(kb + q * kTileBytes + kr_pair[0]), b2 = *(const u32x2*)(kb + q * kTileBytes + kr_pair[1]);
+        kw[q] = u32x4{a.x, a.y, b2.x, b2.y};
+      }
+    }
     __builtin_amdgcn_s_waitcnt(0xC07F);                    // lgkmcnt(0): ... and they have returned: kb is free
     // The next batch of this wavefront, if it has one (the branch is wavefront-uniform and the
     // wait at the top of a batch is a full vmcnt(0), so the number of transfers in flight may
@@ -964,108 +1011,56 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       SAW_FETCH_K(nxt, kb)
     }
 
-    // ---- logits: D_q[head][token of page q] ----
-    f32x4 dq[4];
+    // ---- logits of this lane's tokens and heads ----
+    float lg[NT][4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      const i32x4 k0 = operand(code_bytes(kw[q].x), code_bytes(kw[q].y)), k1 = operand(code_bytes(kw[q].z), code_bytes(kw[q].w));
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        acc = mfma_bf16(as_bf16x8(a_q[kk]), unpack8(kw[q][kk], kbias), acc);
-      }
-      dq[q] = acc;
-    }
-    // ---- gather: lane = token of the batch, registers = heads ----
-    float sraw[NS][NH];
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      float hi, lo, junk;
-      if (G > 4) {      // tile rows: hi heads 0-3 | hi 4-7 | lo 0-3 | lo 4-7
-        swap32(dq[0][i], dq[1][i], hi, lo);
-        sraw[0][i] = hi + lo;
-        swap32(dq[2][i], dq[3][i], hi, lo);
-        sraw[NS - 1][i] = hi + lo;
-      } else {          // tile rows: hi heads | lo heads | idle | idle
-        float h01, l01, h23, l23;
-        swap16(dq[0][i], dq[1][i], h01, l01);
-        swap16(dq[2][i], dq[3][i], h23, l23);
-        swap32(h01, h23, hi, junk);
-        swap32(l01, l23, lo, junk);
-        sraw[0][i] = hi + lo;
+      for (int t = 0; t < NT; ++t) {
+        const i32x4 none = i32x4{0, 0, 0, 0};
+        const i32x4 dq = KS == 2 ? mfma_i8(a_q[t][KS - 1], k1, mfma_i8(a_q[t][0], k0, none)) : mfma_i8(a_q[t][0], t == 0 ? k0 : k1, none);
+        const f32x2 m = km[t * (NM - 1)][q];
+        lg[t][q] = (m.x * qunit[t]) * fmaf(-m.y, qsum[t], digits_value(dq));
       }
     }
-    // ---- softmax with a lazily updated reference maximum ----
-    float lg[NS][NH];
-    bool valid[NS];
-    bool need = false;
+    f32x2 vm[NM][4];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int pg = (G > 4) ? (2 * s + (lane >> 5)) : grp;
-      valid[s] = (tok0 + 16 * pg + row16) < t_end;
+    for (int n = 0; n < NM; ++n)
 #pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        const int kv = (KV == 2 && i >= G / 2) ? 1 : 0;
-        const float kz = km[s][kv].y + 128.f;
-        const float v = km[s][kv].x * fmaf(-kz, qsum[i], sraw[s][i]);
-        lg[s][i] = valid[s] ? v : -INFINITY;
-        need |= lg[s][i] > m_ref[i] + kLazyTau;
+      for (int q = 0; q < 4; ++q)
+        vm[n][q] = *(const f32x2*)(mcur + kMetaBytes<HP> / 2 + (HP ? 256 * q + 128 * (NM == 2 ? n : kv_of) : 128 * q) + 8 * row16);
+    if (tok0 + 64 > t_end) {                                  // wavefront-uniform
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool valid = tok0 + 16 * q + row16 < t_end;
+#pragma unroll
+        for (int n = 0; n < NM; ++n) vm[n][q] = valid ? vm[n][q] : f32x2{0.f, 8.f};
+#pragma unroll
+        for (int t = 0; t < NT; ++t) lg[t][q] = valid ? lg[t][q] : -INFINITY;
       }
     }
-    if (__any(need)) {
-#pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        float mx = lg[0][i];
-        if (NS > 1) mx = fmaxf(mx, lg[NS - 1][i]);
-        mx = row_allmax(mx);
-        if (G > 4) {
-          mx = max_xor32(mx);      // lanes 32 apart share the head group
-        } else {
-          mx = max_xor16(mx);
-          mx = max_xor32(mx);
-        }
-        const float mnew = fmaxf(m_ref[i], mx);
-        const float alpha = fast_exp2(m_ref[i] - mnew);      // 0 on the first batch
-        lsum[i] *= alpha;
-        zs[i] *= alpha;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) oacc[c][i] *= alpha;
-        m_ref[i] = mnew;
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int pg = (G > 4) ? (2 * s + (lane >> 5)) : grp;
-      const int col = 16 * pg + pcol_t;
-#pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        const int kv = (KV == 2 && i >= G / 2) ? 1 : 0;
-        const float vs = valid[s] ? vm[s][kv].x : 0.f;
-        const float vz = valid[s] ? vm[s][kv].y + 128.f : 0.f;
-        const float pr = fast_exp2(lg[s][i] - m_ref[i]);     // exp2(-inf) = 0 for masked tokens
-        lsum[i] += pr;
-        uint32_t h16, l16;
-        float wsum;
-        split_bf16(pr * vs, h16, l16, wsum);
-        zs[i] = fmaf(wsum, vz, zs[i]);
-        ((uint16_t*)pb)[(head0 + i) * kProw + col] = (uint16_t)h16;
-        ((uint16_t*)pb)[(LO + head0 + i) * kProw + col] = (uint16_t)l16;
-      }
-    }
+    st.weigh(lg, vm, pb + pw_off);
     wave_sync();
     // ---- O[row][channel] += P (rows x 64 tokens) . V codes ----
-    // The two P operand reads are issued by hand: written as ordinary LDS loads, the compiler's
+    // The P operand reads are issued by hand: written as ordinary LDS loads, the compiler's
     // wait insertion cannot tell them from the buffers the LDS-DMA prefetch is filling and would
     // drain every transfer in flight (s_waitcnt vmcnt(0)) right here.
-    u32x4 pa0, pa1;
-    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(pa0), "=&v"(pa1)
-                 : "v"(pa_addr)
-                 : "memory");
+    i32x4 pa[NT];
+    if constexpr (NT == 2)
+      asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:%c3\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(pa[0]), "=&v"(pa[1])
+                   : "v"(pa_addr), "i"(kDigitTile)
+                   : "memory");
+    else
+      asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(pa[0]) : "v"(pa_addr) : "memory");
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      const i32x2 tv = __builtin_amdgcn_ds_read_tr4_b64_v2i32((LDS_AS i32x2*)(vcur + vr_off[c]));
-      oacc[c] = mfma_bf16(as_bf16x8(pa0), unpack8((uint32_t)tv.x, kbias), oacc[c]);
-      oacc[c] = mfma_bf16(as_bf16x8(pa1), unpack8((uint32_t)tv.y, kbias), oacc[c]);
+      const i32x2 tv = __builtin_amdgcn_ds_read_tr4_b64_v2i32((LDS_AS i32x2*)(vcur + vr_off[c >> 1] + 8 * (c & 1)));
+      const i32x4 vb = operand(centred_bytes((uint32_t)tv.x), centred_bytes((uint32_t)tv.y));
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        if (NC == 8 || (c >> 2) == t) st.digits[t][c & (NC - 1)] = mfma_i8(pa[t], vb, st.digits[t][c & (NC - 1)]);
     }
   };
   for (int bi = first_batch; bi < nb; bi += 2 * STEP) {
@@ -1083,7 +1078,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // so nothing is requested).
   if (takes_new) {
     NewToken nt;
-    if (!kBP) rotate_token<HP, DN>(p, lane, new_w, (float*)vbuf_b, new_x);
+    if (!kBP) rotate_token<HP, DN, kLoads<G, PAIR>>(p, lane, new_w, (float*)vbuf_b, new_x);
     append_token<HP>(p, kvh, lane, seq_len_b, new_pid, new_x, kbuf, vbuf_a, mbuf_a, nt);
     body(0x3fffffff, t_end - 1, kbuf, vbuf_a, vbuf_b, pbuf, mbuf_a, mbuf_b);
     append_store<HP>(p, lane, nt);                         // (nobody waits for these: see append_store)
@@ -1091,41 +1086,27 @@ void decode_int4_mfma_kernel(DecodeParams p) {
 
   // ---- fold the wavefronts of the block together: heads are dealt out to the wavefronts ----
   if constexpr (!PAIR && NW > 1) {
-    block_epilogue<G, NW, HP, DN, CUT>(p, lds_all, wave, lane, b, kvh, split, oacc, m_ref, lsum, zs);
+    block_epilogue<G, NW, HP, DN, CUT>(p, lds_all, wave, lane, b, kvh, split, st);
     return;
   }
 
-  // ---- epilogue: reduce the per-lane sums, fold hi + lo rows ----
-#pragma unroll
-  for (int i = 0; i < NH; ++i) {
-    lsum[i] = row_allsum(lsum[i]);
-    zs[i] = row_allsum(zs[i]);
-    if (G > 4) {
-      lsum[i] = add_xor32(lsum[i]);
-      zs[i] = add_xor32(zs[i]);
-    } else {
-      lsum[i] = add_xor16(lsum[i]);
-      lsum[i] = add_xor32(lsum[i]);
-      zs[i] = add_xor16(zs[i]);
-      zs[i] = add_xor32(zs[i]);
-    }
-  }
-  // (the lanes holding the lo rows sit 16 lanes above the hi rows, 32 for G = 8)
-  const bool writer = (G > 4) ? (grp < 2) : (grp == 0);
+  // ---- epilogue: reduce the per-lane sums ----
+  st.sum_lanes();
   const int emode = PAIR ? mode : (p.num_splits == 1 ? (int)kSegAlone : (int)kSegSplitKV);
   if (emode == kSegSplitKV) {
     // one of several partitions: (max, sum, un-normalised accumulator) for the merge kernel
 #pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      const int head = head0 + i;
-      float* dst = p.ws + (((int64_t)b * p.n_q_heads + kvh * G + head) * p.num_splits + split) * (DH + 2);
+    for (int t = 0; t < NT; ++t) {
+      const int head = 4 * t + grp;
+      if (G % 4 != 0 && head >= G) continue;
+      float* const dst = p.ws + (((int64_t)b * p.n_q_heads + kvh * G + head) * p.num_splits + split) * (DH + 2);
       const int own = head / GK;                  // head pair: the half of the row that is this head's
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float o = (G > 4) ? add_xor32(oacc[c][i]) : add_xor16(oacc[c][i]);   // hi rows + lo rows
-        if (writer && i < G && (!HP || (c >> 2) == own)) dst[2 + 16 * (HP ? (c & 3) : c) + row16] = o - zs[i];
+      for (int c = 0; c < NC; ++c) {
+        const float o = st.value(t, c);
+        if (!HP || NC == 4 || (c >> 2) == own) dst[2 + 16 * (HP ? (c & 3) : c) + row16] = o;
       }
-      if (writer && row16 == 0 && i < G) { dst[0] = m_ref[i]; dst[1] = lsum[i]; }
+      if (row16 == 0) { dst[0] = st.m_ref[t]; dst[1] = st.lsum[t]; }
     }
     return;
   }
@@ -1140,15 +1121,14 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   float* const ml = rec + G * D;
   wave_sync();
 #pragma unroll
-  for (int i = 0; i < NH; ++i) {
+  for (int t = 0; t < NT; ++t) {
+    const int head = 4 * t + grp;
+    if (G % 4 != 0 && head >= G) continue;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const float o = (G > 4) ? add_xor32(oacc[c][i]) : add_xor16(oacc[c][i]);   // hi rows + lo rows
-      if (writer && i < G) rec[(head0 + i) * D + 16 * c + row16] = o - zs[i];
-    }
-    if (writer && row16 == 0 && i < G) {
-      ml[2 * (head0 + i)] = m_ref[i];
-      ml[2 * (head0 + i) + 1] = lsum[i];
+    for (int c = 0; c < NC; ++c) rec[head * D + 16 * (NC == 8 ? c : 4 * t + c) + row16] = st.value(t, c);
+    if (row16 == 0) {
+      ml[2 * head] = st.m_ref[t];
+      ml[2 * head + 1] = st.lsum[t];
     }
   }
   // the records that make up the sequence's result: this one, or with a shared sequence those of
@@ -1239,7 +1219,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // rotate back once for V (App. A.4; a learned rotation's transpose first, App. A.3), write the output
   float onorm = 1.0f;
   if constexpr (DN) {
-    if (p.dense_v) wave_lds_matvec128<G>(fb, p.dense + kDenseD * kDenseD, lane);
+    if (p.dense_v) wave_lds_matvec128<G, kLoadsOut<G, PAIR>>(fb, p.dense + kDenseD * kDenseD, lane);
   }
   if (p.rot_v) {
     wave_lds_fwht128<G>(fb, p.had_block, lane);

@@ -14,11 +14,11 @@ constexpr int kDigitTile = 16 * kDigitRow;     // four heads
 
 __device__ __forceinline__ i32x4 mfma_i8(i32x4 a, i32x4 b, i32x4 c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
 
-// Weights p s as fixed-point numbers: relative to a reference that puts the largest one met when it was set at kWeightTop, and set anew
-// when one outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-30 of the largest or finer, and
-// where the n weights of a range fall short of that altogether its result is off by n 2^-30 at most; the matrix cores' fp32 sums, cut off at 2^-23
-// twice a batch, made that up to n 2^-28.  A reference further up would have to be set anew more often.
-constexpr float kWeightTop = 536870912.f, kWeightMost = 2.1e9f;
+// Weights p s as fixed-point numbers: relative to a reference that puts the largest one met when it was set at 2^TOP, and set anew
+// when one outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-(TOP + 1) of the largest or finer, and
+// where the n weights of a range fall short of that altogether its result is off by n 2^-(TOP + 1) at most; the matrix cores' fp32 sums, cut
+// off at 2^-23 twice a batch, made that up to n 2^-28.  A reference further up has to be set anew more often.
+constexpr float kWeightTop = 536870912.f, kWeightMost = 2.1e9f;                // (kWeightTop: TOP = 29, single 64-channel heads)
 constexpr float kLeastLog = -100.f;            // log2 of the smallest scale that counts for the reference: p stays finite
 constexpr int kFlushAfter = 1024;              // batches whose digits, 64 x 128 x 128 at most, add up to less than 2^31
 
@@ -47,6 +47,11 @@ __device__ __forceinline__ float digits_value(i32x4 d) {
 __device__ __forceinline__ float long_digits_value(i32x4 d) {
   return fmaf(fmaf(fmaf((float)d[3], 256.f, (float)d[2]), 256.f, (float)d[1]), 256.f, (float)d[0]);
 }
+// ... and a number below 2^54 as such a sum, rounded to a whole one
+__device__ __forceinline__ i32x4 long_digits(float x) {
+  const int hi = (int)__builtin_rintf(x * 0x1p-24f);
+  return i32x4{(int)__builtin_rintf(fmaf((float)hi, -0x1p24f, x)), 0, 0, hi};
+}
 // the largest of |x|, |y|, .. with a NaN winning
 __device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 // The exponent e that takes a row whose largest element is mx to below 2^30; the row's unit 2^-e (NaN if mx is: an infinity or NaN has
@@ -61,5 +66,113 @@ __device__ __forceinline__ u32x2 centred_bytes(uint32_t w) {
   return u32x2{((w << 4) & 0xF0F0F0F0u) ^ 0x80808080u, (w & 0xF0F0F0F0u) ^ 0x80808080u};
 }
 __device__ __forceinline__ i32x4 operand(u32x2 a, u32x2 b) { return i32x4{(int)a.x, (int)a.y, (int)b.x, (int)b.y}; }
+
+// The running state of a range: NT tiles of four heads, a lane's head in tile t being 4 t + grp, NC column tiles of 16 channels.
+// Sums are relative to a reference per head, m_ref: p = 2^(logit - m_ref), weights w = p s top with the largest p s met when it was set
+// at 1.  Accumulators hold 16 times the sum of w (c - 8) as digits.  When the reference moves they are scaled as fp32 numbers and put back
+// as whole numbers; every kFlushAfter batches it moves by one at least, so that they stay below 2^31: a half of what 1024 batches
+// can make of what was there, and 1024 batches' 2^30 on top.
+template <int NT, int NC, int TOP>
+struct FixedState {
+  static constexpr float kTop = (float)(1u << TOP);
+  // (references to arrays of the kernel's: as members of one object some of them end up in memory)
+  i32x4 (&digits)[NT][NC];
+  float (&m_ref)[NT], (&lsum)[NT], (&zs)[NT];                 // ... lsum, zs: of the p and of the w (z - 8), of this lane's tokens
+  float& top;
+  int& room;                                                  // batches until the digits could fill up
+
+  __device__ __forceinline__ void clear() {
+    top = kTop;
+    room = kFlushAfter;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      m_ref[t] = -INFINITY; lsum[t] = 0.f; zs[t] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) digits[t][c] = i32x4{0, 0, 0, 0};
+    }
+  }
+
+  // A batch's logits (-infinity: masked; then its (scale, zero) is (0, 8)) of this lane's four tokens and its heads become weights, whose
+  // digits go to rows 4 grp + l of tile t.  vm: the tokens' pairs, NM = 1 for all tiles or one set for each.
+  template <int NM>
+  __device__ __forceinline__ void weigh(const float (&lg)[NT][4], const f32x2 (&vm)[NM][4], uint8_t* pw) {
+    float w[NT][4], p[NT][4];
+    const bool first = room == kFlushAfter;                   // (wavefront-uniform; nothing is in the state yet)
+    bool move = first || room == 0;
+    if (!move) {
+      float most = 0.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          p[t][q] = fast_exp2(lg[t][q] - m_ref[t]);           // exp2(-inf) = 0 for masked tokens
+          w[t][q] = p[t][q] * (vm[t * (NM - 1)][q].x * top);
+          most = max_or_nan(most, fabsf(w[t][q]));
+        }
+      move = __any(!(most <= kWeightMost));
+    }
+    if (move) {
+      float lv[NM][4], big = 0.f;
+#pragma unroll
+      for (int n = 0; n < NM; ++n)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          lv[n][q] = __builtin_amdgcn_logf(fabsf(vm[n][q].x));
+          big = fmaxf(big, lv[n][q]);
+        }
+      // (scales beyond 2^62: weights 2^64 further down, so that neither they overflow nor the p beside them vanish)
+      const bool lower = top == kTop && __any(big > 62.f);
+      if (lower) top = kTop * 0x1p-64f;
+      const float drop = top == kTop ? 0.f : 64.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, lg[t][q] + fmaxf(lv[t * (NM - 1)][q] - drop, kLeastLog));
+        const float mnew = fmaxf(m_ref[t] + (room == 0 ? 1.f : 0.f), row_allmax(mx));
+        if (!first) {
+          const float alpha = fast_exp2(m_ref[t] - mnew), beta = lower ? alpha * 0x1p-64f : alpha;
+          lsum[t] *= alpha;
+          zs[t] *= beta;
+#pragma unroll
+          for (int c = 0; c < NC; ++c) digits[t][c] = long_digits(long_digits_value(digits[t][c]) * beta);
+        }
+        m_ref[t] = mnew;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          p[t][q] = fast_exp2(lg[t][q] - mnew);
+          w[t][q] = p[t][q] * (vm[t * (NM - 1)][q].x * top);
+        }
+      }
+      if (room == 0) room = kFlushAfter;
+    }
+    --room;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      uint32_t u[4], d[4];
+      const f32x2 (&m)[4] = vm[t * (NM - 1)];
+      float z = w[t][0] * (m[0].y - 8.f);
+#pragma unroll
+      for (int q = 1; q < 4; ++q) z = fmaf(w[t][q], m[q].y - 8.f, z);
+      zs[t] += z;                                             // (one addition a batch to each running sum)
+      lsum[t] += (p[t][0] + p[t][1]) + (p[t][2] + p[t][3]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) u[q] = digit_bytes(nearest_int(w[t][q]));
+      transpose_digits(u[0], u[1], u[2], u[3], d);
+#pragma unroll
+      for (int l = 0; l < 4; ++l) *(uint32_t*)(pw + t * kDigitTile + l * kDigitRow) = d[l];
+    }
+  }
+
+  // the lanes' sums of a head together, in all of its lanes
+  __device__ __forceinline__ void sum_lanes() {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) { lsum[t] = row_allsum(lsum[t]); zs[t] = row_allsum(zs[t]); }
+  }
+  // ... and then channel 16 c + row16 of this lane's head, not normalised
+  __device__ __forceinline__ float value(int t, int c) const {
+    return fmaf(long_digits_value(digits[t][c]), 1.f / 16.f, -zs[t]) * (top == kTop ? 1.f / kTop : 0x1p64f / kTop);
+  }
+};
 
 }  // namespace saw

@@ -1,6 +1,5 @@
-// Wavefront-level helpers shared by the MFMA decode kernels (gfx950): operand types, the nibble ->
-// bf16 expansion, bf16 hi/lo splitting, lane-row exchanges, DPP row reductions, barrier-free LDS
-// hand-over inside one wavefront, and an LDS Walsh-Hadamard transform.
+// Wavefront-level helpers shared by the MFMA decode kernels (gfx950): operand types, bf16 hi/lo splitting,
+// lane-row exchanges, DPP row reductions, barrier-free LDS hand-over inside one wavefront, and an LDS Walsh-Hadamard transform.
 #pragma once
 
 #include "saw_common.h"
@@ -16,29 +15,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 #define LDS_AS __attribute__((address_space(3)))
 #define GLOBAL_AS __attribute__((address_space(1)))
-
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-// Eight packed nibbles -> eight bf16 values 128 + c, in k-order (n0, n4, n1, n5, n2, n6, n3, n7).
-// `k` holds 0x43004300 in a VGPR (see bf16_bias()), which lets each mask-and-bias be one
-// v_and_or_b32 with a single scalar operand.
-__device__ __forceinline__ bf16x8 unpack8(uint32_t w, uint32_t k) {
-  u32x4 r;
-  r.x = (w & 0x000F000Fu) | k;
-  r.y = ((w >> 4) & 0x000F000Fu) | k;
-  r.z = ((w >> 8) & 0x000F000Fu) | k;
-  r.w = ((w >> 12) & 0x000F000Fu) | k;
-  return as_bf16x8(r);
-}
-__device__ __forceinline__ uint32_t bf16_bias() {
-  uint32_t k;
-  asm volatile("v_mov_b32 %0, 0x43004300" : "=v"(k));
-  return k;
-}
-
-__device__ __forceinline__ f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 
 // x = hi + lo with hi a truncated bf16 and lo a rounded bf16 of the remainder.
 __device__ __forceinline__ void split_bf16(float x, uint32_t& hi16, uint32_t& lo16, float& sum) {
@@ -181,8 +157,8 @@ __device__ __forceinline__ void wave_lds_fwht128(float* x, int h, int lane) {
 // of M, and the 64 loads of a lane go out in four rounds of 16 (what bounds this routine is the latency
 // of M coming from L2 while every wavefront of the chip asks for it, so few, wide rounds matter).  Two
 // partial sums per output and half (rows of even and odd index), added pairwise at the end, keep the
-// rounding error near that of a pairwise sum.
-template <int NV>
+// rounding error near that of a pairwise sum.  LOADS: of a round, 8 where registers are short (the same sums).
+template <int NV, int LOADS = 16>
 __device__ __forceinline__ void wave_lds_matvec128(float* x, const float* __restrict__ M, int lane) {
   const int half = lane >> 5, cq = lane & 31;
   float acc[NV][2][4];
@@ -194,15 +170,15 @@ __device__ __forceinline__ void wave_lds_matvec128(float* x, const float* __rest
       for (int c = 0; c < 4; ++c) acc[v][e][c] = 0.f;
   const float* const mbase = M + (64 * half) * 128 + 4 * cq;
 #pragma unroll 1
-  for (int t = 0; t < 4; ++t) {
-    f32x4 m[16];
+  for (int t = 0; t < 64 / LOADS; ++t) {
+    f32x4 m[LOADS];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) m[u] = *(const f32x4*)(mbase + (16 * t + u) * 128);
+    for (int u = 0; u < LOADS; ++u) m[u] = *(const f32x4*)(mbase + (LOADS * t + u) * 128);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      const float* xr = x + v * 128 + 64 * half + 16 * t;
+      const float* xr = x + v * 128 + 64 * half + LOADS * t;
 #pragma unroll
-      for (int u4 = 0; u4 < 4; ++u4) {
+      for (int u4 = 0; u4 < LOADS / 4; ++u4) {
         const f32x4 xv = *(const f32x4*)(xr + 4 * u4);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
