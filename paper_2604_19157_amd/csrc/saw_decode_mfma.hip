@@ -45,8 +45,7 @@ template <int G, bool PAIR> constexpr int kLoadsOut = (PAIR && G > 4) ? 4 : 16;
 template <int G, bool HP> constexpr int kSteps = (HP && G > 4) ? 1 : 2;
 // ... and four column tiles of 16 output channels.  (Half the products: see the kernel.)
 template <int G, bool HP> constexpr int kColumns = (HP && G > 4) ? 4 : 8;
-// (weights are set at 2^27: the sums' error stays below that of the fp32 sums they replace, and the reference moves half as often as from 2^29)
-template <int G, bool HP> using RangeState = FixedState<kTiles<G>, kColumns<G, HP>, 27>;
+template <int G, bool HP> using RangeState = FixedState<kTiles<G>, kColumns<G, HP>>;
 constexpr int kQueryTile = 2048;               // digit rows of the query's four heads in LDS, 128 channels each: where their fp32 rows were
 // (chunk of 16 channels: turned by the row, so that a column of chunks is spread over the banks)
 __device__ __forceinline__ int query_at(int row, int chunk) { return 128 * row + 16 * (chunk ^ (row & 7)); }

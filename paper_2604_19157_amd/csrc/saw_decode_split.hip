@@ -13,7 +13,7 @@
 //
 // Numerics: both products are integer (v_mfma_i32_16x16x64_i8; saw_fixed.h).  The query and the weights p s are 31-bit
 // fixed-point numbers, four signed byte digits each, and the codes are bytes as they are, so the products and their sums
-// are exact; what is rounded is the query, to 2^-31 of its row's largest element, and each weight, to 2^-29 of the largest weight
+// are exact; what is rounded is the query, to 2^-31 of its row's largest element, and each weight, to 2^-28 of the largest weight
 // the wavefront had met when it set the unit.
 // What bounds it is the vector ALU, i.e. instructions: a nibble becomes a byte with 1.5 operations on eight of them where bf16 operands
 // take seven, and the digits of a number need two operations, whatever their count.  Tile rows are 4 head + digit, so that a lane
@@ -245,6 +245,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) { oacc[t][c] = i32x4{0, 0, 0, 0}; otop[t][c] = 0.f; }
   }
+  int low = 0;                                 // wavefront-uniform: weights are kLower further down
   int room = kFlushAfter;                      // (batches until the digits are moved out; all of them: nothing is in them yet)
 
   // (the second batch only here: requested with the first, 20 loads a wavefront filled the compute unit's memory pipeline in front of the
@@ -318,13 +319,15 @@ void decode_int4_split64_kernel(DecodeParams p) {
     float vc[4];                                              // channels 16 c + row16
 #pragma unroll
     for (int c = 0; c < 4; ++c) vc[c] = (float)((cb[32 + 8 * c + (row16 >> 1)] >> (4 * (row16 & 1))) & 15) - 8.f;
-    const float lv = fmaxf(__builtin_amdgcn_logf(fabsf(meta[1].x)), kLeastLog);
+    float lv = __builtin_amdgcn_logf(fabsf(meta[1].x));
+    if (__any(lv > kMostLog)) { low = 1; lv += kLowerLog; }   // (the same in every lane)
+    lv = fmaxf(lv, kLeastLog);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const float lg = (meta[0].x * qunit[t]) * fmaf(-meta[0].y, qsum[t], digits_value(mfma_i8(a_q[t], kb, i32x4{0, 0, 0, 0})));
       m_ref[t] = lg + lv;
       const float pr = fast_exp2(lg - m_ref[t]);
-      const float w = pr * (meta[1].x * kWeightTop);
+      const float w = pr * (meta[1].x * (low ? kWeightTop * kLower : kWeightTop));
       lsum[t] = row16 == 0 ? pr : 0.f;
       zs[t] = row16 == 0 ? w * (meta[1].y - 8.f) : 0.f;
 #pragma unroll
@@ -379,9 +382,10 @@ void decode_int4_split64_kernel(DecodeParams p) {
         for (int t = 0; t < NT; ++t) lg[t][q] = valid ? lg[t][q] : -INFINITY;
       }
     }
+    float top = __uint_as_float(__builtin_amdgcn_readfirstlane(low ? __float_as_uint(kWeightTop * kLower) : __float_as_uint(kWeightTop)));
     float scale[4], w[NT][4], pr_[NT][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) scale[q] = vm[q].x * kWeightTop;
+    for (int q = 0; q < 4; ++q) scale[q] = vm[q].x * top;
     float most = 0.f;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -394,18 +398,24 @@ void decode_int4_split64_kernel(DecodeParams p) {
     if (__any(!(most <= kWeightMost)) || room == 0) {
       float lv[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) lv[q] = fmaxf(__builtin_amdgcn_logf(fabsf(vm[q].x)), kLeastLog);
+      for (int q = 0; q < 4; ++q) lv[q] = __builtin_amdgcn_logf(fabsf(vm[q].x));
+      // (such scales, met for the first time: what there is, and the weights from now on, further down)
+      float down = 1.f;
+      if (!low && __any(fmaxf(fmaxf(lv[0], lv[1]), fmaxf(lv[2], lv[3])) > kMostLog)) { low = 1; top = kWeightTop * kLower; down = kLower; }
+      const float by = low ? kLowerLog : 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { lv[q] = fmaxf(lv[q] + by, kLeastLog); scale[q] = vm[q].x * top; }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const float mx = fmaxf(fmaxf(lg[t][0] + lv[0], lg[t][1] + lv[1]), fmaxf(lg[t][2] + lv[2], lg[t][3] + lv[3]));
         const float mnew = fmaxf(m_ref[t], row_allmax(mx));
         if (room != kFlushAfter) {
-          const float alpha = fast_exp2(m_ref[t] - mnew);
+          const float alpha = fast_exp2(m_ref[t] - mnew), beta = alpha * down;
           lsum[t] *= alpha;
-          zs[t] *= alpha;
+          zs[t] *= beta;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            otop[t][c] = (otop[t][c] + long_digits_value(oacc[t][c])) * alpha;
+            otop[t][c] = (otop[t][c] + long_digits_value(oacc[t][c])) * beta;
             oacc[t][c] = i32x4{0, 0, 0, 0};
           }
         }
@@ -455,6 +465,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
   }
 
   const bool alone = !p.cut && p.num_splits == 1;
+  const float unit = low ? 1.f / (kWeightTop * kLower) : 1.f / kWeightTop;
   if (NW == 1 && !alone) {                                    // a record of its own, straight from the registers
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -465,7 +476,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
         float* const dst = p.ws + (p.cut ? (int64_t)at * p.cut + slot : ((int64_t)b * p.n_q_heads + at) * p.num_splits + slot) * (D + 2);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          dst[2 + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -z) * (1.f / kWeightTop);
+          dst[2 + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -z) * unit;
         if (row16 == 0) *(f32x2*)dst = f32x2{m_ref[t], l};
       }
     }
@@ -481,7 +492,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
     if (G % 4 == 0 || head < G) {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        rec[head * D + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -zs[t]) * (1.f / kWeightTop);
+        rec[head * D + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -zs[t]) * unit;
       if (row16 == 0) { rec[G * D + 2 * head] = m_ref[t]; rec[G * D + 2 * head + 1] = lsum[t]; }
     }
   }

@@ -14,12 +14,15 @@ constexpr int kDigitTile = 16 * kDigitRow;     // four heads
 
 __device__ __forceinline__ i32x4 mfma_i8(i32x4 a, i32x4 b, i32x4 c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
 
-// Weights p s as fixed-point numbers: relative to a reference that puts the largest one met when it was set at 2^TOP, and set anew
-// when one outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-(TOP + 1) of the largest or finer, and
-// where the n weights of a range fall short of that altogether its result is off by n 2^-(TOP + 1) at most; the matrix cores' fp32 sums, cut
-// off at 2^-23 twice a batch, made that up to n 2^-28.  A reference further up has to be set anew more often.
-constexpr float kWeightTop = 536870912.f, kWeightMost = 2.1e9f;                // (kWeightTop: TOP = 29, single 64-channel heads)
+// Weights p s as fixed-point numbers: relative to a reference that puts the largest one met when it was set at kWeightTop, and set anew
+// when one outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-28 of the largest or finer, and
+// where the n weights of a range fall short of that altogether its result is off by n 2^-28 at most; the matrix cores' fp32 sums, cut
+// off at 2^-23 twice a batch, made that up to n 2^-28 too.  A reference further up has to be set anew more often (2^29: 64 ragged
+// sequences x 8 single 64-channel heads, eight query heads 26.5 -> 26.1 us, 256 of them 53.4 -> 51.8).
+constexpr float kWeightTop = 134217728.f, kWeightMost = 2.1e9f;
 constexpr float kLeastLog = -100.f;            // log2 of the smallest scale that counts for the reference: p stays finite
+// Scales beyond 2^kMostLog: weights are kLower of that, so that neither they overflow nor the p beside them vanish
+constexpr float kMostLog = 62.f, kLowerLog = -64.f, kLower = 0x1p-64f;
 constexpr int kFlushAfter = 1024;              // batches whose digits, 64 x 128 x 128 at most, add up to less than 2^31
 
 // u = d0 + 256 d1 + 65536 d2 + 2^24 d3 with -128 <= d0, d1, d2 < 128, |u| <= 2.13e9: the digits as bytes
@@ -72,9 +75,8 @@ __device__ __forceinline__ i32x4 operand(u32x2 a, u32x2 b) { return i32x4{(int)a
 // at 1.  Accumulators hold 16 times the sum of w (c - 8) as digits.  When the reference moves they are scaled as fp32 numbers and put back
 // as whole numbers; every kFlushAfter batches it moves by one at least, so that they stay below 2^31: a half of what 1024 batches
 // can make of what was there, and 1024 batches' 2^30 on top.
-template <int NT, int NC, int TOP>
+template <int NT, int NC>
 struct FixedState {
-  static constexpr float kTop = (float)(1u << TOP);
   // (references to arrays of the kernel's: as members of one object some of them end up in memory)
   i32x4 (&digits)[NT][NC];
   float (&m_ref)[NT], (&lsum)[NT], (&zs)[NT];                 // ... lsum, zs: of the p and of the w (z - 8), of this lane's tokens
@@ -82,7 +84,7 @@ struct FixedState {
   int& room;                                                  // batches until the digits could fill up
 
   __device__ __forceinline__ void clear() {
-    top = kTop;
+    top = kWeightTop;
     room = kFlushAfter;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -120,18 +122,17 @@ struct FixedState {
           lv[n][q] = __builtin_amdgcn_logf(fabsf(vm[n][q].x));
           big = fmaxf(big, lv[n][q]);
         }
-      // (scales beyond 2^62: weights 2^64 further down, so that neither they overflow nor the p beside them vanish)
-      const bool lower = top == kTop && __any(big > 62.f);
-      if (lower) top = kTop * 0x1p-64f;
-      const float drop = top == kTop ? 0.f : 64.f;
+      const bool lower = top == kWeightTop && __any(big > kMostLog);
+      if (lower) top = kWeightTop * kLower;
+      const float by = top == kWeightTop ? 0.f : kLowerLog;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         float mx = -INFINITY;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, lg[t][q] + fmaxf(lv[t * (NM - 1)][q] - drop, kLeastLog));
+        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, lg[t][q] + fmaxf(lv[t * (NM - 1)][q] + by, kLeastLog));
         const float mnew = fmaxf(m_ref[t] + (room == 0 ? 1.f : 0.f), row_allmax(mx));
         if (!first) {
-          const float alpha = fast_exp2(m_ref[t] - mnew), beta = lower ? alpha * 0x1p-64f : alpha;
+          const float alpha = fast_exp2(m_ref[t] - mnew), beta = lower ? alpha * kLower : alpha;
           lsum[t] *= alpha;
           zs[t] *= beta;
 #pragma unroll
@@ -171,7 +172,7 @@ struct FixedState {
   }
   // ... and then channel 16 c + row16 of this lane's head, not normalised
   __device__ __forceinline__ float value(int t, int c) const {
-    return fmaf(long_digits_value(digits[t][c]), 1.f / 16.f, -zs[t]) * (top == kTop ? 1.f / kTop : 0x1p64f / kTop);
+    return fmaf(long_digits_value(digits[t][c]), 1.f / 16.f, -zs[t]) * (top == kWeightTop ? 1.f / kWeightTop : 1.f / (kWeightTop * kLower));
   }
 };
 

@@ -15,10 +15,7 @@ pytestmark = pytest.mark.gpu
 # query heads per kv head, kv heads, head_dim: single 64-channel heads, head_dim 128, pairs of 64-channel heads
 SHAPES = [(8, 1, 64), (4, 3, 64), (1, 1, 64), (2, 3, 64), (4, 2, 128), (8, 1, 128), (1, 3, 128), (2, 1, 128), (4, 4, 64), (2, 2, 64), (1, 2, 64)]
 
-
-def _top(G, Hkv, d):
-    """log2 of the largest weight when the reference is set"""
-    return 29 if d == 64 and (G == 8 or Hkv % 2) else 27
+TOP = 27                                   # log2 of the largest weight when the reference is set
 
 
 @pytest.fixture(scope="module")
@@ -48,10 +45,10 @@ def _make(saw, G, Hkv, d, B, L, k_scale, v_scale, seed=3):
     q = q * torch.linspace(1.0, 0.8, G).repeat(Hkv)[:, None]
     one = torch.einsum("hgd,hd->hg", q.double().view(Hkv, G, d), x(kc[0, :, 0]) - 7) / d ** 0.5
     V = (x(vc) - 5).transpose(0, 1).reshape(Hkv, 16 * pages, d)[:, :L] * v_scale.double()[None, :, None]
-    return c, pt, q, one, V, _top(G, Hkv, d)
+    return c, pt, q, one, V
 
 
-def _exact(one, V, k_scale, v_scale, top):
+def _exact(one, V, k_scale, v_scale):
     logits = one[..., None] * k_scale.double()                       # [Hkv][G][L]
     p = torch.softmax(logits, -1)
     o = p @ V
@@ -60,13 +57,13 @@ def _exact(one, V, k_scale, v_scale, top):
     n, d = V.shape[-2:]
     sums = n / 64 * 2 ** -25 * (o.norm(dim=-1) + 3 * d ** 0.5 * (p * v_scale.double()).sum(-1))
     tol = (X + 4) * 2 ** -22 * torch.sqrt((p ** 2) @ (V ** 2).sum(-1, keepdim=True)).squeeze(-1) \
-        + (X + 4) * 2 ** -22 * o.norm(dim=-1) + n * 2.0 ** -(top + 1) * most * 15 * d ** 0.5 + sums + 2 ** -20 * o.norm(dim=-1)
+        + (X + 4) * 2 ** -22 * o.norm(dim=-1) + n * 2.0 ** -(TOP + 1) * most * 15 * d ** 0.5 + sums + 2 ** -20 * o.norm(dim=-1)
     return o.flatten(0, 1), tol.flatten()
 
 
 def _check(saw, made, k_scale, v_scale, B, L, splits=(1, 3, 0), tag=""):
-    c, pt, q, one, V, top = made
-    want, tol = _exact(one, V, k_scale, v_scale, top)
+    c, pt, q, one, V = made
+    want, tol = _exact(one, V, k_scale, v_scale)
     for s in splits:
         out = torch.full((B,) + q.shape, float("nan"), device="cuda")
         saw.paged_decode_attn(c, q.expand(B, *q.shape).contiguous().cuda(), pt, torch.full((B,), L, dtype=torch.int32).cuda(),
@@ -98,7 +95,7 @@ def test_chosen_logits(saw, G, Hkv, d, kind, B, L):
 
 
 @pytest.mark.parametrize("G,Hkv,d", SHAPES)
-@pytest.mark.parametrize("lo,hi", [(-60, 60), (-95, -80), (60, 90)])
+@pytest.mark.parametrize("lo,hi", [(-60, 60), (-95, -80), (60, 90), (90, 120)])
 def test_value_scales_far_apart(saw, G, Hkv, d, lo, hi):
     """Scales of the values over many powers of two, some zero: units follow the weights p s, not the p."""
     L = 1000
@@ -112,7 +109,7 @@ def test_value_scales_far_apart(saw, G, Hkv, d, lo, hi):
 @pytest.mark.parametrize("G,Hkv,d", SHAPES)
 def test_all_value_scales_zero(saw, G, Hkv, d):
     L, k = 200, torch.linspace(1, 3, 200)
-    c, pt, q, _, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.zeros(L))
+    c, pt, q, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.zeros(L))
     for s in (1, 2):
         out = saw.paged_decode_attn(c, q[None].cuda(), pt, torch.tensor([L], dtype=torch.int32).cuda(), num_splits=s)
         assert (out == 0).all()
@@ -122,7 +119,7 @@ def test_all_value_scales_zero(saw, G, Hkv, d):
 @pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
 def test_a_query_row_that_is_not_finite_is_nan_alone(saw, G, Hkv, d, bad):
     L, k = 150, torch.linspace(1, 3, 150)
-    c, pt, q, _, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.ones(L))
+    c, pt, q, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.ones(L))
     lens = torch.tensor([L], dtype=torch.int32).cuda()
     for s in (1, 2):
         want = saw.paged_decode_attn(c, q[None].cuda(), pt, lens, num_splits=s)
