@@ -216,12 +216,12 @@ __device__ __forceinline__ void rotate_token(const DecodeParams& p, int lane, u3
 // and written" folded into the attention launch): rotate and quantise the new K and V vectors of
 // (sequence b, kv head kvh) for position L exactly as the store kernel would (Sec. 3 eqs. 1-3,
 // App. A.1; append_store writes them to the pools), and place its codes and (scale, zero) pairs in LDS as token 0 of page 0 of a
-// batch, in the layout the transfers produce.  The caller then runs one more batch in which only that
-// token is valid, so the new token goes through the very code path of the cached ones (same q~ operands,
-// same softmax update) and nothing this launch writes to the cache is read back by it.  This happens at
-// the END of the range that starts the sequence, when every transfer of the range has landed and the buffers
-// are idle: in the middle of the loop, where wavefronts have no slack, it costs 1-2 us.  The rotation in front of it
-// runs there too (rotate_token), or, in a block that prepares its range together, with the query's at the start (block_prepare).
+// batch, in the layout the transfers produce; nothing this launch writes to the cache is read back by it.
+// In pair blocks and single wavefronts the caller then runs one more batch in which only that token is valid, at the END of the range that
+// starts the sequence, when every transfer of the range has landed and the buffers are idle: those launches fill the chip, every
+// wavefront starts at once, bound by instructions, and in the middle of the loop, where wavefronts have no slack, it costs 1-2 us.  The
+// rotation in front of it runs there too (rotate_token).  Blocks that share a range open the last wavefront's state with it
+// instead (open_with_token); theirs is rotated with the query where they prepare it together (block_prepare).
 // One wavefront, K in lanes 0-31 and V in lanes 32-63, four channels per lane: one chain of reductions and one division for both.
 // (It is on the critical path of the range's last wavefront: with two channels of both vectors in every lane, 4 x 256 tokens took 8.6 us
 // and take 8.1, 16 x 4096 22.6 and 22.1, 64 ragged with a learned rotation 46.3 and 45.0.)
@@ -269,6 +269,43 @@ __device__ __forceinline__ void append_token(const DecodeParams& p, int kvh, int
   *(uint16_t*)((second ? vdst : kdst) + 2 * (lane & 31)) = (uint16_t)nt.codes;
   if ((lane & (LANES - 1)) == 0) *(f32x2*)(mdst + (second ? kMetaBytesOf(HP) / 2 : 0) + (HP ? 128 * ((lane >> 4) & 1) : 0)) = nt.meta;
   wave_sync();
+}
+
+// Blocks of several wavefronts over one range (not pair blocks): the new token is quantised and opens the running state of the last
+// wavefront, which has the fewest batches, while the first batch travels.  scr: 2 KiB of LDS that no transfer in flight targets.
+// As one more batch behind the last it made the range longer by a microsecond (fused steps, at the end and here: 96 x 200 tokens x 8 kv
+// heads 11.4 -> 10.2 us, 64 x 700 14.8 -> 13.7, 40 ragged 22.7 -> 21.6, 64 ragged 28.7 -> 27.6, one sequence of 300 7.2 -> 6.7).
+template <int G, bool HP>
+__device__ __forceinline__ void open_with_token(const DecodeParams& p, int kvh, int lane, int L, int pid, const float (&x)[4],
+                                                uint8_t* __restrict__ scr, const i32x4 (&a_q)[kTiles<G>][kSteps<G, HP>],
+                                                const float (&qsum)[kTiles<G>], const float (&qunit)[kTiles<G>], RangeState<G, HP> st,
+                                                NewToken& nt) {
+  constexpr int NT = kTiles<G>, NC = kColumns<G, HP>, KS = kSteps<G, HP>;
+  constexpr int GK = HP ? G / 2 : G;
+  const int row16 = lane & 15, grp = lane >> 4;
+  uint8_t* const kdst = scr;                                 // token 0 of a page: 64 bytes; then its V codes and its pairs
+  uint8_t* const vdst = scr + 64;
+  uint8_t* const mdst = scr + 128;                           // [K, V][kv head]
+  append_token<HP>(p, kvh, lane, L, pid, x, kdst, vdst, mdst, nt);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const i32x4 none = i32x4{0, 0, 0, 0};
+    i32x4 dq;
+    if constexpr (KS == 2) {
+      const u32x4 kw = *(const u32x4*)(kdst + 16 * grp);
+      dq = mfma_i8(a_q[t][KS - 1], operand(code_bytes(kw.z), code_bytes(kw.w)), mfma_i8(a_q[t][0], operand(code_bytes(kw.x), code_bytes(kw.y)), none));
+    } else {
+      const u32x2 kw = *(const u32x2*)(kdst + 32 * t + 8 * grp);
+      dq = mfma_i8(a_q[t][0], operand(code_bytes(kw.x), code_bytes(kw.y)), none);
+    }
+    const int kv = HP ? (NC == 4 ? t : min(grp, G - 1) / GK) : 0;
+    const f32x2 km = *(const f32x2*)(mdst + 128 * kv), vm = *(const f32x2*)(mdst + kMetaBytesOf(HP) / 2 + 128 * kv);
+    float code[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) code[c] = (float)((vdst[8 * (NC == 4 ? 4 * t + c : c) + (row16 >> 1)] >> (4 * (row16 & 1))) & 15) - 8.f;
+    st.open(t, (km.x * qunit[t]) * fmaf(-km.y, qsum[t], digits_value(dq)), vm, code, row16 == 0);
+  }
+  wave_sync();                                               // (the second batch's transfers take the place)
 }
 
 // one batch's (scale, zero) pairs: K 4 pages x 128 B, then V (twice that for a pair of 64-channel heads)
@@ -846,11 +883,11 @@ void decode_int4_mfma_kernel(DecodeParams p) {
     }
   }
 
-  // fused append: the range that starts the sequence also takes the step's new token (wavefront 0 of the block when
-  // several share the range); of a batch cut by its lengths the one that ends it, there the wavefront with the fewest
-  // batches; so in a block of eight, where over a short context that wavefront has none and works on the token while the others
-  // stream (4 sequences of 256 tokens: the step 9.3 -> 8.9 us); its inputs are requested here, with the query
-  const bool takes_new = block_new && (PAIR || wave == (CUT || NW == 8 ? NW - 1 : 0));
+  // fused append: the range that starts the sequence also takes the step's new token (of a batch cut by its lengths the one that ends
+  // it, which has the fewest batches), in a block that shares it the last wavefront, for the same reason; its inputs are requested
+  // here, with the query
+  constexpr bool kOpen = !PAIR && NW > 1;
+  const bool takes_new = block_new && (PAIR || wave == NW - 1);
   u32x2 new_w = u32x2{0u, 0u};
   int new_pid = -1;
   if (takes_new) {
@@ -967,6 +1004,13 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   int room;
   State st{digits, m_ref, lsum, zs, top, room};
   st.clear();
+  NewToken nt;
+  if constexpr (kOpen) {
+    if (takes_new) {
+      if (!kBP) rotate_token<HP, DN, kLoads<G, PAIR>>(p, lane, new_w, (float*)vbuf_b, new_x);
+      open_with_token<G, HP>(p, kvh, lane, seq_len_b, new_pid, new_x, vbuf_b, a_q, qsum, qunit, st, nt);
+    }
+  }
 
   // One batch, whose first token is position tok0 of the sequence.  On entry the transfers of batch bi
   // (V into vcur, K into kb, metadata) are the only ones this wavefront has in flight.
@@ -1071,15 +1115,16 @@ void decode_int4_mfma_kernel(DecodeParams p) {
   // when it began, and a wavefront without a batch has requested none: this waits for nothing, it states the rule).
   __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0)
 
-  // Fused append: the step's new token is quantised and stored now, placed in the (idle) buffers as
+  // Fused append, if the range did not open with it: the step's new token is quantised now, placed in the (idle) buffers as
   // token 0 of a batch, and attended to by one more pass of the batch code in which only that token is
   // valid (tok0 = t_end - 1: only position tok0 + 0 lies below t_end; the batch index is past the range,
   // so nothing is requested).
   if (takes_new) {
-    NewToken nt;
-    if (!kBP) rotate_token<HP, DN, kLoads<G, PAIR>>(p, lane, new_w, (float*)vbuf_b, new_x);
-    append_token<HP>(p, kvh, lane, seq_len_b, new_pid, new_x, kbuf, vbuf_a, mbuf_a, nt);
-    body(0x3fffffff, t_end - 1, kbuf, vbuf_a, vbuf_b, pbuf, mbuf_a, mbuf_b);
+    if constexpr (!kOpen) {
+      rotate_token<HP, DN, kLoads<G, PAIR>>(p, lane, new_w, (float*)vbuf_b, new_x);
+      append_token<HP>(p, kvh, lane, seq_len_b, new_pid, new_x, kbuf, vbuf_a, mbuf_a, nt);
+      body(0x3fffffff, t_end - 1, kbuf, vbuf_a, vbuf_b, pbuf, mbuf_a, mbuf_b);
+    }
     append_store<HP>(p, lane, nt);                         // (nobody waits for these: see append_store)
   }
 

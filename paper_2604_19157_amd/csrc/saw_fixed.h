@@ -94,6 +94,32 @@ struct FixedState {
     }
   }
 
+  // The state of tile t opens with one token: its logit, its pair, the codes (c - 8) of this lane's channels 16 c + row16; one: this
+  // lane counts it for the head.  Pairs that are not finite carry on into lsum and zs.
+  __device__ __forceinline__ void open(int t, float lg, f32x2 m, const float (&code)[NC], bool one) {
+    float lv = __builtin_amdgcn_logf(fabsf(m.x));
+    if (t == 0) {
+      top = kWeightTop;
+      room = kFlushAfter - 1;                                 // (there is something to be scaled)
+    }
+    if (top == kWeightTop && __any(lv > kMostLog)) {          // (head pairs: tile 0 may have been opened further up)
+      top = kWeightTop * kLower;
+#pragma unroll
+      for (int u = 0; u < t; ++u) {
+        zs[u] *= kLower;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) digits[u][c] = long_digits(long_digits_value(digits[u][c]) * kLower);
+      }
+    }
+    lv = fmaxf(lv + (top == kWeightTop ? 0.f : kLowerLog), kLeastLog);
+    m_ref[t] = lg + lv;
+    const float p = fast_exp2(lg - m_ref[t]), w = p * (m.x * top);
+    lsum[t] = one ? p : 0.f;
+    zs[t] = one ? w * (m.y - 8.f) : 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) digits[t][c] = long_digits(16.f * w * code[c]);
+  }
+
   // A batch's logits (-infinity: masked; then its (scale, zero) is (0, 8)) of this lane's four tokens and its heads become weights, whose
   // digits go to rows 4 grp + l of tile t.  vm: the tokens' pairs, NM = 1 for all tiles or one set for each.
   template <int NM>

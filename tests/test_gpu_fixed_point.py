@@ -137,3 +137,31 @@ def test_more_batches_than_the_digits_hold(saw, G, Hkv, d):
     L = 4 * 64 * 1100 + 17
     k, v = torch.full((L,), 0.25), torch.full((L,), 0.75)
     _check(saw, _make(saw, G, Hkv, d, 1, L, k, v), k, v, 1, L, splits=(1,), tag=f"long G={G} d={d}")
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES + [(8, 2, 128), (4, 8, 128), (4, 8, 64), (8, 8, 64)])
+@pytest.mark.parametrize("size", [1.0, 2.0 ** -90, 2.0 ** 80])
+@pytest.mark.parametrize("B", [4, 40, 66])
+def test_new_token_opens_the_state(saw, G, Hkv, d, size, B):
+    """The fused step against a decode of what it stored: the new token first in a wavefront's running state, or one of a batch's, its
+    values as large as the cached ones, far below or far above.  Both are within 2^-20 (n 2^-28 included) of attention in 64 bits, row by row;
+    with scales of 2^-90 beside ordinary ones references are up to 128 apart, and such differences are fp32 numbers in units of 2^-17: weights
+    are off by half a unit times ln 2 in either call."""
+    tol = 2 ** -19 + (0.0 if size == 1 else 2 * 2 ** -18 * math.log(2))
+    g = torch.Generator().manual_seed(B)
+    lens = [(0, 1, 64, 65, 700, 1300)[b % 6] for b in range(B)]
+    pages = 1301 // 16 + 1
+    c = saw.Cache(B * pages, Hkv, d, min(d, 64))
+    pt = torch.arange(B * pages, dtype=torch.int32).view(B, pages).cuda()
+    for codes, meta in ((c.k_codes, c.k_meta), (c.v_codes, c.v_meta)):
+        codes.copy_(torch.randint(0, 256, codes.shape, generator=g, dtype=torch.uint8))
+        meta.copy_(torch.stack([torch.rand(meta.shape[:-1], generator=g) * 0.2 + 0.05, torch.full(meta.shape[:-1], 7.0)], -1))
+    q = torch.randn((B, Hkv * G, d), generator=g).cuda()
+    k, v = (torch.randn((B, Hkv, d), generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    n = torch.tensor(lens, dtype=torch.int32).cuda()
+    got = saw.append_decode_attn(c, k, (v.float() * size).to(torch.bfloat16), q, pt, n, out=torch.empty_like(q))
+    for s in (0, 1):
+        want = saw.paged_decode_attn(c, q, pt, n + 1, num_splits=s, out=torch.empty_like(q))
+        err = (got - want).double().norm(dim=-1) / want.double().norm(dim=-1)
+        print(f"[open G={G} Hkv={Hkv} d={d} size={size:.1e} B={B} splits={s}] worst {float(err.max()):.2e}", flush=True)
+        assert (err <= tol).all()
