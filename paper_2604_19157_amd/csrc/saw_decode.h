@@ -67,7 +67,7 @@ __host__ __device__ inline int rank_class(int len, float kscale) {
 int launch_decode_int4_mfma(const DecodeParams& p, int G, int B, int nw, bool head_pairs, dim3 grid, hipStream_t st);
 
 // head_dim 64 runs on the matrix cores when the kv heads can be taken two at a time (rows of 128
-// channels again) and the pair's query heads fit the 16-row tile as hi and lo limbs.
+// channels again) and the pair's query heads fit two row tiles of four heads.
 inline bool decode_head_pairs(int head_dim, int n_kv_heads, int G) {
   return head_dim == 64 && n_kv_heads % 2 == 0 && (G == 1 || G == 2 || G == 4);
 }

@@ -440,8 +440,8 @@ __device__ __forceinline__ void block_prepare(const DecodeParams& p, const uint3
 
 // The end of a range that NW wavefronts of a block shared: their running (max, sum, accumulator) states become the partition's
 // record, or the sequence's output.  Every wavefront leaves its state in its own buffers; after one barrier a wavefront takes G / NW
-// heads (some wavefronts none, if there are more of them) and works them out from all states with two channels per lane: weights, hi + lo
-// rows, the lane sums, normalising, the way back through the rotation and the store.  What this costs is instructions of the last
+// heads (some wavefronts none, if there are more of them) and works them out from all states with two channels per lane: weights,
+// sums, normalising, the way back through the rotation and the store.  What this costs is instructions of the last
 // wavefront to arrive, one every 4-5 cycles: as a fold of accumulator tiles by all, then the rest by wavefront 0, it took 2.5 us from
 // the last batch to the end of the kernel for a record (16 sequences of 4096 tokens) and 3.2 us for an output (4 of 256); now 1.7 and
 // 2.1.  Whole calls: 4 x 256 tokens 10.8 -> 9.3 us, 16 x 4096 23.7 -> 22.6, 48 ragged 34.2 -> 33.1, 1 x 131072 37.3 -> 35.3, 64 ragged
