@@ -13,8 +13,8 @@
 //   * logits: D[4 head + digit][token] = q~ . codes with v_mfma_i32_16x16x64_i8: q~ is a 31-bit fixed-point number, four signed
 //     byte digits in neighbouring rows of the tile, and a nibble becomes a byte with 1.5 ALU operations on eight of them
 //     (saw_fixed.h).  A lane's four results are the digits of one head and token: no exchange between lanes in front of the softmax;
-//   * the reference of the running state only moves (with a rescale of the accumulators) when a weight outgrows the digits, 2^4 above the
-//     largest weight met when it was set;
+//   * reference and unit of the running state only move (with a rescale of the accumulators) when a weight outgrows the digits, 2^4 above
+//     the largest weight met when they were set;
 //   * P.V needs tokens along the contraction: ds_read_b64_tr_b4 hands each lane 16 tokens of one channel (a 16x16 nibble
 //     transpose inside LDS); the weights p s go through LDS once as digit rows; O[4 head + digit][channel] adds up exactly in 32-bit
 //     integers.
@@ -1000,9 +1000,9 @@ void decode_int4_mfma_kernel(DecodeParams p) {
 
   using State = RangeState<G, HP>;
   i32x4 digits[NT][NC];
-  float m_ref[NT], lsum[NT], zs[NT], top;
+  float m_ref[NT], unit[NT], lsum[NT], zs[NT];
   int room;
-  State st{digits, m_ref, lsum, zs, top, room};
+  State st{digits, m_ref, unit, lsum, zs, room};
   st.clear();
   NewToken nt;
   if constexpr (kOpen) {

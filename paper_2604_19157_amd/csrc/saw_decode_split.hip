@@ -14,7 +14,7 @@
 // Numerics: both products are integer (v_mfma_i32_16x16x64_i8; saw_fixed.h).  The query and the weights p s are 31-bit
 // fixed-point numbers, four signed byte digits each, and the codes are bytes as they are, so the products and their sums
 // are exact; what is rounded is the query, to 2^-31 of its row's largest element, and each weight, to 2^-28 of the largest weight
-// the wavefront had met when it set the unit.
+// the wavefront had met of its head when it set the unit.
 // What bounds it is the vector ALU, i.e. instructions: a nibble becomes a byte with 1.5 operations on eight of them where bf16 operands
 // take seven, and the digits of a number need two operations, whatever their count.  Tile rows are 4 head + digit, so that a lane
 // holds all four digits of a head's results and of one head only: no exchange between lanes in front of the softmax, one running
@@ -235,17 +235,16 @@ void decode_int4_split64_kernel(DecodeParams p) {
   uint8_t* const pw = pbuf + 4 * grp * kDigitRow + 4 * row16;  // digit l of this lane's head: row 4 grp + l
   const uint8_t* const pr = pbuf + row16 * kDigitRow + 16 * grp;
 
-  // Running state: reference, sum of the p and of the w z of this lane's tokens, and sum of the w (c - 8) as 16 times that in digits,
-  // and what was moved out of the digits.  Weights are w = p s kWeightTop relative to the reference of their head: kWeightTop, kLeastLog.
+  // Running state: reference and unit (saw_fixed.h), sum of the p and of the w (z - 8) of this lane's tokens, and sum of the w (c - 8) as
+  // 16 times that in digits, and what was moved out of the digits.
   i32x4 oacc[NT][4];
-  float otop[NT][4], m_ref[NT], lsum[NT], zs[NT];
+  float otop[NT][4], m_ref[NT], unit[NT], lsum[NT], zs[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    m_ref[t] = -INFINITY; lsum[t] = 0.f; zs[t] = 0.f;
+    m_ref[t] = -INFINITY; unit[t] = 1.f; lsum[t] = 0.f; zs[t] = 0.f;
 #pragma unroll
     for (int c = 0; c < 4; ++c) { oacc[t][c] = i32x4{0, 0, 0, 0}; otop[t][c] = 0.f; }
   }
-  int low = 0;                                 // wavefront-uniform: weights are kLower further down
   int room = kFlushAfter;                      // (batches until the digits are moved out; all of them: nothing is in them yet)
 
   // (the second batch only here: requested with the first, 20 loads a wavefront filled the compute unit's memory pipeline in front of the
@@ -319,15 +318,13 @@ void decode_int4_split64_kernel(DecodeParams p) {
     float vc[4];                                              // channels 16 c + row16
 #pragma unroll
     for (int c = 0; c < 4; ++c) vc[c] = (float)((cb[32 + 8 * c + (row16 >> 1)] >> (4 * (row16 & 1))) & 15) - 8.f;
-    float lv = __builtin_amdgcn_logf(fabsf(meta[1].x));
-    if (__any(lv > kMostLog)) { low = 1; lv += kLowerLog; }   // (the same in every lane)
-    lv = fmaxf(lv, kLeastLog);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const float lg = (meta[0].x * qunit[t]) * fmaf(-meta[0].y, qsum[t], digits_value(mfma_i8(a_q[t], kb, i32x4{0, 0, 0, 0})));
-      m_ref[t] = lg + lv;
-      const float pr = fast_exp2(lg - m_ref[t]);
-      const float w = pr * (meta[1].x * (low ? kWeightTop * kLower : kWeightTop));
+      m_ref[t] = fmaxf(lg, kLeastLogit);
+      const float pr = fast_exp2(lg - m_ref[t]), ps = pr * meta[1].x;
+      unit[t] = __builtin_amdgcn_ldexpf(1.f, unit_exponent(fabsf(ps)));
+      const float w = ps * unit[t];
       lsum[t] = row16 == 0 ? pr : 0.f;
       zs[t] = row16 == 0 ? w * (meta[1].y - 8.f) : 0.f;
 #pragma unroll
@@ -382,35 +379,22 @@ void decode_int4_split64_kernel(DecodeParams p) {
         for (int t = 0; t < NT; ++t) lg[t][q] = valid ? lg[t][q] : -INFINITY;
       }
     }
-    float top = __uint_as_float(__builtin_amdgcn_readfirstlane(low ? __float_as_uint(kWeightTop * kLower) : __float_as_uint(kWeightTop)));
-    float scale[4], w[NT][4], pr_[NT][4];
+    float w[NT][4], pr_[NT][4], most = 0.f;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) scale[q] = vm[q].x * top;
-    float most = 0.f;
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < NT; ++t) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         pr_[t][q] = fast_exp2(lg[t][q] - m_ref[t]);           // exp2(-inf) = 0 for masked tokens
-        w[t][q] = pr_[t][q] * scale[q];
+        w[t][q] = pr_[t][q] * (vm[q].x * unit[t]);
         most = max_or_nan(most, fabsf(w[t][q]));
       }
+    }
     if (__any(!(most <= kWeightMost)) || room == 0) {
-      float lv[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) lv[q] = __builtin_amdgcn_logf(fabsf(vm[q].x));
-      // (such scales, met for the first time: what there is, and the weights from now on, further down)
-      float down = 1.f;
-      if (!low && __any(fmaxf(fmaxf(lv[0], lv[1]), fmaxf(lv[2], lv[3])) > kMostLog)) { low = 1; top = kWeightTop * kLower; down = kLower; }
-      const float by = low ? kLowerLog : 0.f;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { lv[q] = fmaxf(lv[q] + by, kLeastLog); scale[q] = vm[q].x * top; }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const float mx = fmaxf(fmaxf(lg[t][0] + lv[0], lg[t][1] + lv[1]), fmaxf(lg[t][2] + lv[2], lg[t][3] + lv[3]));
-        const float mnew = fmaxf(m_ref[t], row_allmax(mx));
+        float alpha, beta;
+        set_reference(lg[t], vm, room == kFlushAfter, false, m_ref[t], unit[t], pr_[t], w[t], alpha, beta);
         if (room != kFlushAfter) {
-          const float alpha = fast_exp2(m_ref[t] - mnew), beta = alpha * down;
           lsum[t] *= alpha;
           zs[t] *= beta;
 #pragma unroll
@@ -418,12 +402,6 @@ void decode_int4_split64_kernel(DecodeParams p) {
             otop[t][c] = (otop[t][c] + long_digits_value(oacc[t][c])) * beta;
             oacc[t][c] = i32x4{0, 0, 0, 0};
           }
-        }
-        m_ref[t] = mnew;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          pr_[t][q] = fast_exp2(lg[t][q] - mnew);
-          w[t][q] = pr_[t][q] * scale[q];
         }
       }
       room = kFlushAfter;
@@ -465,7 +443,9 @@ void decode_int4_split64_kernel(DecodeParams p) {
   }
 
   const bool alone = !p.cut && p.num_splits == 1;
-  const float unit = low ? 1.f / (kWeightTop * kLower) : 1.f / kWeightTop;
+  const auto value = [&](int t, int c, float z) {              // channel 16 c + row16 of this lane's head, not normalised
+    return __builtin_amdgcn_ldexpf(fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -z), -exponent_of(unit[t]));
+  };
   if (NW == 1 && !alone) {                                    // a record of its own, straight from the registers
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -476,7 +456,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
         float* const dst = p.ws + (p.cut ? (int64_t)at * p.cut + slot : ((int64_t)b * p.n_q_heads + at) * p.num_splits + slot) * (D + 2);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          dst[2 + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -z) * unit;
+          dst[2 + 16 * c + row16] = value(t, c, z);
         if (row16 == 0) *(f32x2*)dst = f32x2{m_ref[t], l};
       }
     }
@@ -492,7 +472,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
     if (G % 4 == 0 || head < G) {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        rec[head * D + 16 * c + row16] = fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -zs[t]) * unit;
+        rec[head * D + 16 * c + row16] = value(t, c, zs[t]);
       if (row16 == 0) { rec[G * D + 2 * head] = m_ref[t]; rec[G * D + 2 * head + 1] = lsum[t]; }
     }
   }

@@ -14,15 +14,18 @@ constexpr int kDigitTile = 16 * kDigitRow;     // four heads
 
 __device__ __forceinline__ i32x4 mfma_i8(i32x4 a, i32x4 b, i32x4 c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
 
-// Weights p s as fixed-point numbers: relative to a reference that puts the largest one met when it was set at kWeightTop, and set anew
-// when one outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-28 of the largest or finer, and
+// Weights w = p s u as fixed-point numbers: p = 2^(logit - m) with a reference m per head, the largest logit met when it was set, and a
+// unit u per head, a power of two that puts the largest p s met then at 2^(kWeightBits - 1) to 2^kWeightBits.  Both are set anew when
+// a weight outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-28 of the largest or finer, and
 // where the n weights of a range fall short of that altogether its result is off by n 2^-28 at most; the matrix cores' fp32 sums, cut
-// off at 2^-23 twice a batch, made that up to n 2^-28 too.  A reference further up has to be set anew more often (2^29: 64 ragged
-// sequences x 8 single 64-channel heads, eight query heads 26.5 -> 26.1 us, 256 of them 53.4 -> 51.8).
-constexpr float kWeightTop = 134217728.f, kWeightMost = 2.1e9f;
-constexpr float kLeastLog = -100.f;            // log2 of the smallest scale that counts for the reference: p stays finite
-// Scales beyond 2^kMostLog: weights are kLower of that, so that neither they overflow nor the p beside them vanish
-constexpr float kMostLog = 62.f, kLowerLog = -64.f, kLower = 0x1p-64f;
+// off at 2^-23 twice a batch, made that up to n 2^-28 too.  A unit further up has to be set anew more often; one
+// further down rounds to 2^-27 (64 ragged sequences x 8 single 64-channel heads, eight query heads: 26.9 us and 26.7).
+// The unit is the head's own, and the scales are in it and not in the reference: scales of other heads cannot reach a head's weights, and
+// denominators, sums of p, are at least 1 however far apart the scales of ranges, partitions and batches are.
+constexpr int kWeightBits = 28;
+constexpr float kWeightMost = 2.1e9f;
+constexpr int kLeastScale = -99;                // exponent of the smallest p s that the unit follows: 2^127 at most
+constexpr float kLeastLogit = -3.402823466e38f;  // references are finite: a logit of -infinity is a weight of 0
 constexpr int kFlushAfter = 1024;              // batches whose digits, 64 x 128 x 128 at most, add up to less than 2^31
 
 // u = d0 + 256 d1 + 65536 d2 + 2^24 d3 with -128 <= d0, d1, d2 < 128, |u| <= 2.13e9: the digits as bytes
@@ -70,25 +73,53 @@ __device__ __forceinline__ u32x2 centred_bytes(uint32_t w) {
 }
 __device__ __forceinline__ i32x4 operand(u32x2 a, u32x2 b) { return i32x4{(int)a.x, (int)a.y, (int)b.x, (int)b.y}; }
 
+// Exponent of the unit for weights whose largest p s is big (0, NaN or infinity: any will do)
+__device__ __forceinline__ int unit_exponent(float big) {
+  return kWeightBits - (big > 0.f ? max(__builtin_amdgcn_frexp_expf(big), kLeastScale) : kLeastScale);
+}
+__device__ __forceinline__ int exponent_of(float unit) { return __builtin_amdgcn_frexp_expf(unit) - 1; }     // of a power of two
+
+// A head's reference and unit set anew for a batch's logits lg and pairs vm of this lane's four tokens, whose p and w it returns;
+// alpha, beta <= 1: what that makes of sums of p and of w.  none: there are no sums yet.  lower: beta is 1/2 at most.
+// (The weights as (p s) u: s u may overflow where p is small, p s is in range of the unit.)
+__device__ __forceinline__ void set_reference(const float (&lg)[4], const f32x2 (&vm)[4], bool none, bool lower, float& m, float& unit,
+                                              float (&p)[4], float (&w)[4], float& alpha, float& beta) {
+  const float mx = row_allmax(fmaxf(fmaxf(lg[0], lg[1]), fmaxf(lg[2], lg[3])));
+  const float mnew = fmaxf(fmaxf(m, kLeastLogit), mx);
+  float big = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    p[q] = fast_exp2(lg[q] - mnew);                           // exp2(-inf) = 0 for masked tokens
+    w[q] = p[q] * vm[q].x;
+    big = fmaxf(big, fabsf(w[q]));
+  }
+  int e = unit_exponent(row_allmax_positive(big));
+  const int was = exponent_of(unit);
+  if (!none) e = min(e, was + (int)fminf(mnew - m, 1000.f) - (lower ? 1 : 0));
+  alpha = fast_exp2(m - mnew);
+  beta = __builtin_amdgcn_ldexpf(alpha, e - was);
+  m = mnew;
+  unit = __builtin_amdgcn_ldexpf(1.f, e);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) w[q] *= unit;
+}
+
 // The running state of a range: NT tiles of four heads, a lane's head in tile t being 4 t + grp, NC column tiles of 16 channels.
-// Sums are relative to a reference per head, m_ref: p = 2^(logit - m_ref), weights w = p s top with the largest p s met when it was set
-// at 1.  Accumulators hold 16 times the sum of w (c - 8) as digits.  When the reference moves they are scaled as fp32 numbers and put back
-// as whole numbers; every kFlushAfter batches it moves by one at least, so that they stay below 2^31: a half of what 1024 batches
+// Accumulators hold 16 times the sum of w (c - 8) as digits.  When the unit or the reference moves they are scaled as fp32 numbers and put
+// back as whole numbers; every kFlushAfter batches by a half at least, so that they stay below 2^31: a half of what 1024 batches
 // can make of what was there, and 1024 batches' 2^30 on top.
 template <int NT, int NC>
 struct FixedState {
   // (references to arrays of the kernel's: as members of one object some of them end up in memory)
   i32x4 (&digits)[NT][NC];
-  float (&m_ref)[NT], (&lsum)[NT], (&zs)[NT];                 // ... lsum, zs: of the p and of the w (z - 8), of this lane's tokens
-  float& top;
+  float (&m_ref)[NT], (&unit)[NT], (&lsum)[NT], (&zs)[NT];    // ... lsum, zs: of the p and of the w (z - 8), of this lane's tokens
   int& room;                                                  // batches until the digits could fill up
 
   __device__ __forceinline__ void clear() {
-    top = kWeightTop;
     room = kFlushAfter;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      m_ref[t] = -INFINITY; lsum[t] = 0.f; zs[t] = 0.f;
+      m_ref[t] = -INFINITY; unit[t] = 1.f; lsum[t] = 0.f; zs[t] = 0.f;
 #pragma unroll
       for (int c = 0; c < NC; ++c) digits[t][c] = i32x4{0, 0, 0, 0};
     }
@@ -97,23 +128,11 @@ struct FixedState {
   // The state of tile t opens with one token: its logit, its pair, the codes (c - 8) of this lane's channels 16 c + row16; one: this
   // lane counts it for the head.  Pairs that are not finite carry on into lsum and zs.
   __device__ __forceinline__ void open(int t, float lg, f32x2 m, const float (&code)[NC], bool one) {
-    float lv = __builtin_amdgcn_logf(fabsf(m.x));
-    if (t == 0) {
-      top = kWeightTop;
-      room = kFlushAfter - 1;                                 // (there is something to be scaled)
-    }
-    if (top == kWeightTop && __any(lv > kMostLog)) {          // (head pairs: tile 0 may have been opened further up)
-      top = kWeightTop * kLower;
-#pragma unroll
-      for (int u = 0; u < t; ++u) {
-        zs[u] *= kLower;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) digits[u][c] = long_digits(long_digits_value(digits[u][c]) * kLower);
-      }
-    }
-    lv = fmaxf(lv + (top == kWeightTop ? 0.f : kLowerLog), kLeastLog);
-    m_ref[t] = lg + lv;
-    const float p = fast_exp2(lg - m_ref[t]), w = p * (m.x * top);
+    room = kFlushAfter - 1;                                   // (there is something to be scaled)
+    m_ref[t] = fmaxf(lg, kLeastLogit);
+    const float p = fast_exp2(lg - m_ref[t]), ps = p * m.x;
+    unit[t] = __builtin_amdgcn_ldexpf(1.f, unit_exponent(fabsf(ps)));
+    const float w = ps * unit[t];
     lsum[t] = one ? p : 0.f;
     zs[t] = one ? w * (m.y - 8.f) : 0.f;
 #pragma unroll
@@ -130,45 +149,26 @@ struct FixedState {
     if (!move) {
       float most = 0.f;
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+      for (int t = 0; t < NT; ++t) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           p[t][q] = fast_exp2(lg[t][q] - m_ref[t]);           // exp2(-inf) = 0 for masked tokens
-          w[t][q] = p[t][q] * (vm[t * (NM - 1)][q].x * top);
+          w[t][q] = p[t][q] * (vm[t * (NM - 1)][q].x * unit[t]);
           most = max_or_nan(most, fabsf(w[t][q]));
         }
+      }
       move = __any(!(most <= kWeightMost));
     }
     if (move) {
-      float lv[NM][4], big = 0.f;
-#pragma unroll
-      for (int n = 0; n < NM; ++n)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          lv[n][q] = __builtin_amdgcn_logf(fabsf(vm[n][q].x));
-          big = fmaxf(big, lv[n][q]);
-        }
-      const bool lower = top == kWeightTop && __any(big > kMostLog);
-      if (lower) top = kWeightTop * kLower;
-      const float by = top == kWeightTop ? 0.f : kLowerLog;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, lg[t][q] + fmaxf(lv[t * (NM - 1)][q] + by, kLeastLog));
-        const float mnew = fmaxf(m_ref[t] + (room == 0 ? 1.f : 0.f), row_allmax(mx));
+        float alpha, beta;
+        set_reference(lg[t], vm[t * (NM - 1)], first, room == 0, m_ref[t], unit[t], p[t], w[t], alpha, beta);
         if (!first) {
-          const float alpha = fast_exp2(m_ref[t] - mnew), beta = lower ? alpha * kLower : alpha;
           lsum[t] *= alpha;
           zs[t] *= beta;
 #pragma unroll
           for (int c = 0; c < NC; ++c) digits[t][c] = long_digits(long_digits_value(digits[t][c]) * beta);
-        }
-        m_ref[t] = mnew;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          p[t][q] = fast_exp2(lg[t][q] - mnew);
-          w[t][q] = p[t][q] * (vm[t * (NM - 1)][q].x * top);
         }
       }
       if (room == 0) room = kFlushAfter;
@@ -198,7 +198,7 @@ struct FixedState {
   }
   // ... and then channel 16 c + row16 of this lane's head, not normalised
   __device__ __forceinline__ float value(int t, int c) const {
-    return fmaf(long_digits_value(digits[t][c]), 1.f / 16.f, -zs[t]) * (top == kWeightTop ? 1.f / kWeightTop : 1.f / (kWeightTop * kLower));
+    return __builtin_amdgcn_ldexpf(fmaf(long_digits_value(digits[t][c]), 1.f / 16.f, -zs[t]), -exponent_of(unit[t]));
   }
 };
 

@@ -63,10 +63,11 @@ __device__ __forceinline__ float max_xor32(float v) {
   return fmaxf(x, y);
 }
 
+// (every lane has a source in the rotations, mirrors and permutations used here; with bound_ctrl the move is folded into its user)
 template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, false));
-}
+__device__ __forceinline__ int dpp_i(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) { return __uint_as_float(dpp_i<CTRL>((int)__float_as_uint(v))); }
 // max over the 16 lanes of each row (rotations by 1, 2, 4, 8)
 __device__ __forceinline__ float row_allmax(float v) {
   v = fmaxf(v, dpp_f<0x121>(v));
@@ -74,6 +75,15 @@ __device__ __forceinline__ float row_allmax(float v) {
   v = fmaxf(v, dpp_f<0x124>(v));
   v = fmaxf(v, dpp_f<0x128>(v));
   return v;
+}
+// the same of numbers from 0 on, as integers: no instructions to quiet NaNs, one of which may be the result
+__device__ __forceinline__ float row_allmax_positive(float v) {
+  int u = (int)__float_as_uint(v);
+  u = max(u, dpp_i<0x121>(u));
+  u = max(u, dpp_i<0x122>(u));
+  u = max(u, dpp_i<0x124>(u));
+  u = max(u, dpp_i<0x128>(u));
+  return __uint_as_float((uint32_t)u);
 }
 __device__ __forceinline__ float row_allsum(float v) {
   v += dpp_f<0x121>(v);

@@ -25,12 +25,13 @@ def saw():
     return binding
 
 
-def _make(saw, G, Hkv, d, B, L, k_scale, v_scale, seed=3):
-    """k_scale, v_scale: [L] scales of the tokens.  Every sequence has pages of its own with the same bytes."""
+def _make(saw, G, Hkv, d, B, L, k_scale, v_scale, seed=3, sizes=None):
+    """k_scale, v_scale: [L] or [Hkv, L] scales of the tokens.  Every sequence has pages of its own with the same bytes.
+    sizes: [Hkv, G] logits of a key scale of 1."""
     g = torch.Generator().manual_seed(seed)
     pages = (L + 16) // 16
     c = saw.Cache(B * pages, Hkv, d, 1)
-    pad = lambda x: torch.cat([x, torch.full((16 * pages - L,), float("nan"))]).view(pages, 1, 16).expand(pages, Hkv, 16)
+    pad = lambda x: torch.cat([x.expand(Hkv, L), torch.full((Hkv, 16 * pages - L), float("nan"))], 1).view(Hkv, pages, 16).transpose(0, 1)
     kc = torch.randint(0, 256, (1, Hkv, 1, d // 2), generator=g, dtype=torch.uint8).expand(pages, Hkv, 16, d // 2)
     vc = torch.randint(0, 256, (pages, Hkv, 16, d // 2), generator=g, dtype=torch.uint8)
     km = torch.stack([pad(k_scale), torch.full((pages, Hkv, 16), 7.0)], -1)
@@ -42,35 +43,54 @@ def _make(saw, G, Hkv, d, B, L, k_scale, v_scale, seed=3):
     x = lambda codes: torch.stack([codes & 15, codes >> 4], -1).flatten(-2).double()
     one = torch.einsum("hgd,hd->hg", q.double().view(Hkv, G, d), x(kc[0, :, 0]) - 7) / d ** 0.5     # logit of scale 1, natural units
     q = q / (one.abs().flatten()[:, None] / one.sign().flatten()[:, None]).float()                     # ... made 1 for every head
-    q = q * torch.linspace(1.0, 0.8, G).repeat(Hkv)[:, None]
+    q = q * (torch.linspace(1.0, 0.8, G).repeat(Hkv) if sizes is None else sizes.flatten())[:, None]
     one = torch.einsum("hgd,hd->hg", q.double().view(Hkv, G, d), x(kc[0, :, 0]) - 7) / d ** 0.5
-    V = (x(vc) - 5).transpose(0, 1).reshape(Hkv, 16 * pages, d)[:, :L] * v_scale.double()[None, :, None]
+    V = (x(vc) - 5).transpose(0, 1).reshape(Hkv, 16 * pages, d)[:, :L] * v_scale.double().expand(Hkv, L)[..., None]
     return c, pt, q, one, V
 
 
-def _exact(one, V, k_scale, v_scale):
-    logits = one[..., None] * k_scale.double()                       # [Hkv][G][L]
+def _logit_error(made):
+    """[Hkv, G] what a logit may be off by, relative, in 2^-24: the query times its scale and log2(e) (three roundings an element), q.c and sum q as two
+    halves each (two and two), their difference, the pair's scale times the unit and the product (three)."""
+    c, q, one = made[0], made[2].double(), made[3]
+    kc = c.k_codes[0, :, 0].cpu()
+    codes = torch.stack([kc & 15, kc >> 4], -1).flatten(-2).double()[:, None]
+    q = q.view(one.shape + (-1,))
+    parts = 3 * (q * (codes - 7)).abs().sum(-1) + 2 * (q * codes).sum(-1).abs() + 2 * 7 * q.sum(-1).abs()
+    return parts / q.shape[-1] ** 0.5 / one.abs() + 3
+
+
+def _exact(one, V, k_scale, v_scale, logit_error=4.0):
+    """logit_error: of the logits, relative, in 2^-24."""
+    Hkv, L = V.shape[:2]
+    v_scale = v_scale.expand(Hkv, L)[:, None]
+    logits = one[..., None] * k_scale.double().expand(Hkv, L)[:, None]        # [Hkv][G][L]
     p = torch.softmax(logits, -1)
     o = p @ V
     X = float(logits.abs().max()) / math.log(2)
     most = (p * v_scale.double()).amax(-1)
     n, d = V.shape[-2:]
     sums = n / 64 * 2 ** -25 * (o.norm(dim=-1) + 3 * d ** 0.5 * (p * v_scale.double()).sum(-1))
-    tol = (X + 4) * 2 ** -22 * torch.sqrt((p ** 2) @ (V ** 2).sum(-1, keepdim=True)).squeeze(-1) \
-        + (X + 4) * 2 ** -22 * o.norm(dim=-1) + n * 2.0 ** -(TOP + 1) * most * 15 * d ** 0.5 + sums + 2 ** -20 * o.norm(dim=-1)
+    w = (X * logit_error + 16) * 2 ** -24                              # of a weight, relative
+    tol = w * torch.sqrt((p ** 2) @ (V ** 2).sum(-1, keepdim=True)).squeeze(-1) + w * o.norm(dim=-1) + n * 2.0 ** -(TOP + 1) * most * 15 * d ** 0.5 + sums + 2 ** -20 * o.norm(dim=-1)
     return o.flatten(0, 1), tol.flatten()
 
 
-def _check(saw, made, k_scale, v_scale, B, L, splits=(1, 3, 0), tag=""):
+def _check(saw, made, k_scale, v_scale, B, L, splits=(1, 3, 0), tag="", lost=(), logit_error=4.0):
+    """lost: kv heads whose values are not finite, nor are their outputs."""
     c, pt, q, one, V = made
-    want, tol = _exact(one, V, k_scale, v_scale)
+    want, tol = _exact(one, V, k_scale, v_scale, logit_error)
+    rows = torch.ones(one.shape, dtype=torch.bool)
+    rows[list(lost)] = False
+    rows = rows.flatten()
     for s in splits:
         out = torch.full((B,) + q.shape, float("nan"), device="cuda")
         saw.paged_decode_attn(c, q.expand(B, *q.shape).contiguous().cuda(), pt, torch.full((B,), L, dtype=torch.int32).cuda(),
                               num_splits=s, out=out)
-        err = (out.cpu().double() - want).norm(dim=-1)
-        print(f"[fixed {tag} splits={s}] worst error over bound {float((err / tol).max()):.3f}", flush=True)
-        assert (err <= tol).all()
+        err = (out.cpu().double() - want)[:, rows].norm(dim=-1)
+        print(f"[fixed {tag} splits={s}] worst error over bound {float((err / tol[rows]).max()):.3f}", flush=True)
+        assert (err <= tol[rows]).all()
+        assert not out.cpu()[:, ~rows].isfinite().any()
 
 
 def _logits(kind, L):
@@ -104,6 +124,58 @@ def test_value_scales_far_apart(saw, G, Hkv, d, lo, hi):
     v[t % 9 == 4] = 0.0
     k = 2 + 3 * torch.sin(t.float())
     _check(saw, _make(saw, G, Hkv, d, 2, L, k, v), k, v, 2, L, tag=f"scales {lo} {hi} G={G} Hkv={Hkv} d={d}")
+
+
+def _late(kind, Hkv, G, L):
+    """Key and value scales [Hkv, L] (logits in base 2 before the head's size), sizes [Hkv, G], and the kv heads whose outputs are not
+    finite.  The first half of the tokens sets the references of every wavefront and opens the first partitions."""
+    t = torch.arange(L)
+    late = t >= L // 2
+    k = 2 + torch.sin(t.float())
+    v = (0.5 + 0.4 * torch.cos(t.float())).repeat(Hkv, 1)
+    sizes = torch.linspace(1.0, 0.8, G).repeat(Hkv, 1)
+    lost = ()
+    outlier = late & (t % 97 == 5)
+    if kind == "unattended":                   # far below the others even times its scale
+        k[outlier] = -180.0
+        v[:, outlier] = 2.0 ** 102
+    elif kind == "outweighs":                  # 2^-50 of the attention, 2^14 of the output
+        k[outlier] = -50.0
+        v[:, outlier] = 2.0 ** 64
+    elif kind == "one head's":                 # what one query head attends to and the next one of the same kv head does not
+        k[outlier] = 100.0
+        v[:, outlier] = 2.0 ** 70
+        sizes[:, 1::2] *= -1
+    elif kind == "neighbour's":                # in every second kv head
+        v[1::2, late] = 2.0 ** 100
+    elif kind == "neighbour's infinity":
+        v[1::2, outlier] = float("inf")
+        lost = range(1, Hkv, 2)
+    elif kind == "zero, then large":           # equal logits: denominators of both halves count alike
+        k[:] = 2.0
+        v[:, ~late], v[:, late] = 0.0, 2.0 ** 28
+    elif kind == "tiny, then large":
+        k[:] = 2.0
+        v[:, ~late], v[:, late] = 2.0 ** -95, 2.0 ** 60
+    elif kind == "large, then tiny":
+        k[:] = 2.0
+        v[:, ~late], v[:, late] = 2.0 ** 60, 2.0 ** -95
+    elif kind == "zero rising":                # weights of 0 whose denominators grow by 2^27, then ordinary tokens
+        k[:] = torch.where(t < L // 4, 1.0, 28.0)
+        v[:, t < L - L // 4] = 0.0
+        sizes[:] = 1.0
+    return (k * math.log(2)).repeat(Hkv, 1), v, sizes, lost
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
+@pytest.mark.parametrize("kind", ["unattended", "outweighs", "one head's", "neighbour's", "neighbour's infinity", "zero, then large",
+                                  "tiny, then large", "large, then tiny", "zero rising"])
+@pytest.mark.parametrize("B,L", [(1, 2100), (300, 520)])
+def test_value_scales_that_change_within_a_range(saw, G, Hkv, d, kind, B, L):
+    """A head's outputs follow its own values only, whatever its neighbours' are and whatever comes late in a range."""
+    k, v, sizes, lost = _late(kind, Hkv, G, L)
+    made = _make(saw, G, Hkv, d, B, L, k, v, sizes=sizes)
+    _check(saw, made, k, v, B, L, lost=lost, logit_error=_logit_error(made), tag=f"{kind} G={G} Hkv={Hkv} d={d} B={B}")
 
 
 @pytest.mark.parametrize("G,Hkv,d", SHAPES)
