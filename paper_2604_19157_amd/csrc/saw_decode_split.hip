@@ -379,7 +379,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
         for (int t = 0; t < NT; ++t) lg[t][q] = valid ? lg[t][q] : -INFINITY;
       }
     }
-    float w[NT][4], pr_[NT][4], most = 0.f;
+    float w[NT][4], pr_[NT][4], sum[NT], most = 0.f;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
 #pragma unroll
@@ -388,6 +388,8 @@ void decode_int4_split64_kernel(DecodeParams p) {
         w[t][q] = pr_[t][q] * (vm[q].x * unit[t]);
         most = max_or_nan(most, fabsf(w[t][q]));
       }
+      sum[t] = (pr_[t][0] + pr_[t][1]) + (pr_[t][2] + pr_[t][3]);
+      most = max_or_nan(most, sum[t]);
     }
     if (__any(!(most <= kWeightMost)) || room == 0) {
 #pragma unroll
@@ -403,6 +405,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
             oacc[t][c] = i32x4{0, 0, 0, 0};
           }
         }
+        sum[t] = (pr_[t][0] + pr_[t][1]) + (pr_[t][2] + pr_[t][3]);
       }
       room = kFlushAfter;
     }
@@ -414,7 +417,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
 #pragma unroll
       for (int q = 1; q < 4; ++q) z = fmaf(w[t][q], vm[q].y - 8.f, z);
       zs[t] += z;                                             // (one addition a batch to each running sum)
-      lsum[t] += (pr_[t][0] + pr_[t][1]) + (pr_[t][2] + pr_[t][3]);
+      lsum[t] += sum[t];
 #pragma unroll
       for (int q = 0; q < 4; ++q) u[q] = digit_bytes(nearest_int(w[t][q]));
       transpose_digits(u[0], u[1], u[2], u[3], d);

@@ -141,9 +141,10 @@ struct FixedState {
 
   // A batch's logits (-infinity: masked; then its (scale, zero) is (0, 8)) of this lane's four tokens and its heads become weights, whose
   // digits go to rows 4 grp + l of tile t.  vm: the tokens' pairs, NM = 1 for all tiles or one set for each.
+  // (Sums of the p are checked with the weights: where the scales are small or 0 they would grow without a weight that shows it.)
   template <int NM>
   __device__ __forceinline__ void weigh(const float (&lg)[NT][4], const f32x2 (&vm)[NM][4], uint8_t* pw) {
-    float w[NT][4], p[NT][4];
+    float w[NT][4], p[NT][4], sum[NT];
     const bool first = room == kFlushAfter;                   // (wavefront-uniform; nothing is in the state yet)
     bool move = first || room == 0;
     if (!move) {
@@ -156,6 +157,8 @@ struct FixedState {
           w[t][q] = p[t][q] * (vm[t * (NM - 1)][q].x * unit[t]);
           most = max_or_nan(most, fabsf(w[t][q]));
         }
+        sum[t] = (p[t][0] + p[t][1]) + (p[t][2] + p[t][3]);
+        most = max_or_nan(most, sum[t]);
       }
       move = __any(!(most <= kWeightMost));
     }
@@ -170,6 +173,7 @@ struct FixedState {
 #pragma unroll
           for (int c = 0; c < NC; ++c) digits[t][c] = long_digits(long_digits_value(digits[t][c]) * beta);
         }
+        sum[t] = (p[t][0] + p[t][1]) + (p[t][2] + p[t][3]);
       }
       if (room == 0) room = kFlushAfter;
     }
@@ -182,7 +186,7 @@ struct FixedState {
 #pragma unroll
       for (int q = 1; q < 4; ++q) z = fmaf(w[t][q], m[q].y - 8.f, z);
       zs[t] += z;                                             // (one addition a batch to each running sum)
-      lsum[t] += (p[t][0] + p[t][1]) + (p[t][2] + p[t][3]);
+      lsum[t] += sum[t];
 #pragma unroll
       for (int q = 0; q < 4; ++q) u[q] = digit_bytes(nearest_int(w[t][q]));
       transpose_digits(u[0], u[1], u[2], u[3], d);

@@ -164,12 +164,16 @@ def _late(kind, Hkv, G, L):
         k[:] = torch.where(t < L // 4, 1.0, 28.0)
         v[:, t < L - L // 4] = 0.0
         sizes[:] = 1.0
+    elif kind == "zero rising far":            # ... by 2^127.5: every p is finite, the sum of a few is not
+        k[:] = torch.where(t < L // 4, 1.0, 128.5)
+        v[:, t < L - L // 4] = 0.0
+        sizes[:] = 1.0
     return (k * math.log(2)).repeat(Hkv, 1), v, sizes, lost
 
 
 @pytest.mark.parametrize("G,Hkv,d", SHAPES)
 @pytest.mark.parametrize("kind", ["unattended", "outweighs", "one head's", "neighbour's", "neighbour's infinity", "zero, then large",
-                                  "tiny, then large", "large, then tiny", "zero rising"])
+                                  "tiny, then large", "large, then tiny", "zero rising", "zero rising far"])
 @pytest.mark.parametrize("B,L", [(1, 2100), (300, 520)])
 def test_value_scales_that_change_within_a_range(saw, G, Hkv, d, kind, B, L):
     """A head's outputs follow its own values only, whatever its neighbours' are and whatever comes late in a range."""
