@@ -183,6 +183,24 @@ def test_value_scales_that_change_within_a_range(saw, G, Hkv, d, kind, B, L):
 
 
 @pytest.mark.parametrize("G,Hkv,d", SHAPES)
+@pytest.mark.parametrize("B", [1, 4, 300])
+def test_new_token_whose_logit_is_minus_infinity(saw, G, Hkv, d, B):
+    """It counts for nothing: the step's output is that of the cached tokens (key scales of 2^-120 make ordinary logits of such queries)."""
+    L = 200
+    k = (2 + torch.sin(torch.arange(L).float())) * 2.0 ** -120
+    made = _make(saw, G, Hkv, d, B, L, k, torch.ones(L), sizes=torch.linspace(1.0, 0.8, G).repeat(Hkv, 1) * 2.0 ** 120)
+    c, pt, q, one, V = made
+    want, tol = _exact(one, V, k, torch.ones(L), _logit_error(made))
+    x = (q.view(Hkv, G, d)[:, 0].sign() * -1024).to(torch.bfloat16).expand(B, Hkv, d).contiguous().cuda()
+    rows = torch.arange(Hkv) * G                   # (the heads whose signs the new keys have)
+    out = saw.append_decode_attn(c, x, torch.ones_like(x), q.expand(B, *q.shape).contiguous().cuda(), pt,
+                                 torch.full((B,), L, dtype=torch.int32).cuda(), out=torch.empty((B,) + q.shape, device="cuda"))
+    err = (out.cpu().double() - want)[:, rows].norm(dim=-1)
+    print(f"[-inf G={G} Hkv={Hkv} d={d} B={B}] worst error over bound {float((err / tol[rows]).max()):.3f}", flush=True)
+    assert (err <= tol[rows]).all()
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
 def test_all_value_scales_zero(saw, G, Hkv, d):
     L, k = 200, torch.linspace(1, 3, 200)
     c, pt, q, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.zeros(L))
