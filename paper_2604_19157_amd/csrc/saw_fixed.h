@@ -60,9 +60,9 @@ __device__ __forceinline__ i32x4 long_digits(float x) {
 }
 // the largest of |x|, |y|, .. with a NaN winning
 __device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
-// The exponent e that takes a row whose largest element is mx to below 2^30; the row's unit 2^-e (NaN if mx is: an infinity or NaN has
-// no digits, the unit carries it on into everything that is made of the row)
-__device__ __forceinline__ int fixed_exponent(float mx) { return 30 - __builtin_amdgcn_frexp_expf(mx); }
+// The exponent e that takes a row whose largest element is mx to below 2^30, as far as its unit 2^-e is a number: with 2^-149 every element
+// is a whole one as it is (NaN if mx is: an infinity or NaN has no digits, the unit carries it on into everything that is made of the row)
+__device__ __forceinline__ int fixed_exponent(float mx) { return min(30 - __builtin_amdgcn_frexp_expf(mx), 149); }
 __device__ __forceinline__ float fixed_unit(float mx, int e) { return mx <= 3.402823466e38f ? __builtin_amdgcn_ldexpf(1.f, -e) : __builtin_nanf(""); }
 
 // Eight nibbles n0 .. n7 -> bytes (n0, n2, n4, n6) and (n1, n3, n5, n7)

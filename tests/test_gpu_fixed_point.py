@@ -201,6 +201,15 @@ def test_new_token_whose_logit_is_minus_infinity(saw, G, Hkv, d, B):
 
 
 @pytest.mark.parametrize("G,Hkv,d", SHAPES)
+def test_smallest_queries(saw, G, Hkv, d):
+    """A query row below 2^-119 (its unit is the smallest fp32 number then) with key scales that make ordinary logits of it."""
+    L = 300
+    k = (2 + torch.sin(torch.arange(L).float())) * 2.0 ** 118
+    made = _make(saw, G, Hkv, d, 2, L, k, torch.ones(L), sizes=torch.linspace(1.0, 0.8, G).repeat(Hkv, 1) * 2.0 ** -118)
+    _check(saw, made, k, torch.ones(L), 2, L, logit_error=_logit_error(made), tag=f"smallest G={G} Hkv={Hkv} d={d}")
+
+
+@pytest.mark.parametrize("G,Hkv,d", SHAPES)
 def test_all_value_scales_zero(saw, G, Hkv, d):
     L, k = 200, torch.linspace(1, 3, 200)
     c, pt, q, _, _ = _make(saw, G, Hkv, d, 1, L, k, torch.zeros(L))
