@@ -1000,8 +1000,8 @@ void decode_int4_mfma_kernel(DecodeParams p) {
 
   using State = RangeState<G, HP>;
   i32x4 digits[NT][NC];
-  float m_ref[NT], unit[NT], lsum[NT], zs[NT];
-  int room;
+  float m_ref[NT], lsum[NT], zs[NT];
+  int unit[NT], room;
   State st{digits, m_ref, unit, lsum, zs, room};
   st.clear();
   NewToken nt;
@@ -1078,7 +1078,7 @@ void decode_int4_mfma_kernel(DecodeParams p) {
       for (int q = 0; q < 4; ++q) {
         const bool valid = tok0 + 16 * q + row16 < t_end;
 #pragma unroll
-        for (int n = 0; n < NM; ++n) vm[n][q] = valid ? vm[n][q] : f32x2{0.f, 8.f};
+        for (int n = 0; n < NM; ++n) vm[n][q] = valid ? vm[n][q] : f32x2{0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < NT; ++t) lg[t][q] = valid ? lg[t][q] : -INFINITY;
       }

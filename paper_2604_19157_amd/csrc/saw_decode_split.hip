@@ -238,10 +238,11 @@ void decode_int4_split64_kernel(DecodeParams p) {
   // Running state: reference and unit (saw_fixed.h), sum of the p and of the w (z - 8) of this lane's tokens, and sum of the w (c - 8) as
   // 16 times that in digits, and what was moved out of the digits.
   i32x4 oacc[NT][4];
-  float otop[NT][4], m_ref[NT], unit[NT], lsum[NT], zs[NT];
+  float otop[NT][4], m_ref[NT], lsum[NT], zs[NT];
+  int unit[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    m_ref[t] = -INFINITY; unit[t] = 1.f; lsum[t] = 0.f; zs[t] = 0.f;
+    m_ref[t] = -INFINITY; unit[t] = 0; lsum[t] = 0.f; zs[t] = 0.f;
 #pragma unroll
     for (int c = 0; c < 4; ++c) { oacc[t][c] = i32x4{0, 0, 0, 0}; otop[t][c] = 0.f; }
   }
@@ -323,8 +324,8 @@ void decode_int4_split64_kernel(DecodeParams p) {
       const float lg = (meta[0].x * qunit[t]) * fmaf(-meta[0].y, qsum[t], digits_value(mfma_i8(a_q[t], kb, i32x4{0, 0, 0, 0})));
       m_ref[t] = fmaxf(lg, kLeastLogit);
       const float pr = fast_exp2(lg - m_ref[t]), ps = pr * meta[1].x;
-      unit[t] = __builtin_amdgcn_ldexpf(1.f, unit_exponent(fabsf(ps)));
-      const float w = ps * unit[t];
+      unit[t] = unit_exponent(fabsf(ps));
+      const float w = __builtin_amdgcn_ldexpf(ps, unit[t]);
       lsum[t] = row16 == 0 ? pr : 0.f;
       zs[t] = row16 == 0 ? w * (meta[1].y - 8.f) : 0.f;
 #pragma unroll
@@ -374,7 +375,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const bool valid = tok0 + 16 * q + row16 < t_lim;
-        vm[q] = valid ? vm[q] : f32x2{0.f, 8.f};
+        vm[q] = valid ? vm[q] : f32x2{0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < NT; ++t) lg[t][q] = valid ? lg[t][q] : -INFINITY;
       }
@@ -385,7 +386,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         pr_[t][q] = fast_exp2(lg[t][q] - m_ref[t]);           // exp2(-inf) = 0 for masked tokens
-        w[t][q] = pr_[t][q] * (vm[q].x * unit[t]);
+        w[t][q] = pr_[t][q] * __builtin_amdgcn_ldexpf(vm[q].x, unit[t]);
         most = max_or_nan(most, fabsf(w[t][q]));
       }
       sum[t] = (pr_[t][0] + pr_[t][1]) + (pr_[t][2] + pr_[t][3]);
@@ -447,7 +448,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
 
   const bool alone = !p.cut && p.num_splits == 1;
   const auto value = [&](int t, int c, float z) {              // channel 16 c + row16 of this lane's head, not normalised
-    return __builtin_amdgcn_ldexpf(fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -z), -exponent_of(unit[t]));
+    return __builtin_amdgcn_ldexpf(fmaf(otop[t][c] + long_digits_value(oacc[t][c]), 1.f / 16.f, -z), -unit[t]);
   };
   if (NW == 1 && !alone) {                                    // a record of its own, straight from the registers
 #pragma unroll

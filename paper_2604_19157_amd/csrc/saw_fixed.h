@@ -14,8 +14,8 @@ constexpr int kDigitTile = 16 * kDigitRow;     // four heads
 
 __device__ __forceinline__ i32x4 mfma_i8(i32x4 a, i32x4 b, i32x4 c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
 
-// Weights w = p s u as fixed-point numbers: p = 2^(logit - m) with a reference m per head, the largest logit met when it was set, and a
-// unit u per head, a power of two that puts the largest p s met then at 2^(kWeightBits - 1) to 2^kWeightBits.  Both are set anew when
+// Weights w = 2^u p s as fixed-point numbers: p = 2^(logit - m) with a reference m per head, the largest logit met when it was set, and a
+// unit per head, 2^-u, that puts the largest p s met then at 2^(kWeightBits - 1) to 2^kWeightBits.  Both are set anew when
 // a weight outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-28 of the largest or finer, and
 // where the n weights of a range fall short of that altogether its result is off by n 2^-28 at most; the matrix cores' fp32 sums, cut
 // off at 2^-23 twice a batch, made that up to n 2^-28 too.  A unit further up has to be set anew more often; one
@@ -24,7 +24,6 @@ __device__ __forceinline__ i32x4 mfma_i8(i32x4 a, i32x4 b, i32x4 c) { return __b
 // denominators, sums of p, are at least 1 however far apart the scales of ranges, partitions and batches are.
 constexpr int kWeightBits = 28;
 constexpr float kWeightMost = 2.1e9f;
-constexpr int kLeastScale = -99;                // exponent of the smallest p s that the unit follows: 2^127 at most
 constexpr float kLeastLogit = -3.402823466e38f;  // references are finite: a logit of -infinity is a weight of 0
 constexpr int kFlushAfter = 1024;              // batches whose digits, 64 x 128 x 128 at most, add up to less than 2^31
 
@@ -73,16 +72,16 @@ __device__ __forceinline__ u32x2 centred_bytes(uint32_t w) {
 }
 __device__ __forceinline__ i32x4 operand(u32x2 a, u32x2 b) { return i32x4{(int)a.x, (int)a.y, (int)b.x, (int)b.y}; }
 
-// Exponent of the unit for weights whose largest p s is big (0, NaN or infinity: any will do)
+// The u of weights whose largest p s is big >= 0 (an exponent, because 2^u may be no fp32 number).  0 counts as the smallest number, so that
+// whatever follows moves it; of an infinity or NaN any will do.
 __device__ __forceinline__ int unit_exponent(float big) {
-  return kWeightBits - (big > 0.f ? max(__builtin_amdgcn_frexp_expf(big), kLeastScale) : kLeastScale);
+  return kWeightBits - __builtin_amdgcn_frexp_expf(__uint_as_float((uint32_t)max((int)__float_as_uint(big), 1)));
 }
-__device__ __forceinline__ int exponent_of(float unit) { return __builtin_amdgcn_frexp_expf(unit) - 1; }     // of a power of two
 
 // A head's reference and unit set anew for a batch's logits lg and pairs vm of this lane's four tokens, whose p and w it returns;
 // alpha, beta <= 1: what that makes of sums of p and of w.  none: there are no sums yet.  lower: beta is 1/2 at most.
-// (The weights as (p s) u: s u may overflow where p is small, p s is in range of the unit.)
-__device__ __forceinline__ void set_reference(const float (&lg)[4], const f32x2 (&vm)[4], bool none, bool lower, float& m, float& unit,
+// (The weights as 2^u (p s): 2^u s may overflow where p is small, p s is in range of the unit.)
+__device__ __forceinline__ void set_reference(const float (&lg)[4], const f32x2 (&vm)[4], bool none, bool lower, float& m, int& unit,
                                               float (&p)[4], float (&w)[4], float& alpha, float& beta) {
   const float mx = row_allmax(fmaxf(fmaxf(lg[0], lg[1]), fmaxf(lg[2], lg[3])));
   const float mnew = fmaxf(fmaxf(m, kLeastLogit), mx);
@@ -94,14 +93,13 @@ __device__ __forceinline__ void set_reference(const float (&lg)[4], const f32x2 
     big = fmaxf(big, fabsf(w[q]));
   }
   int e = unit_exponent(row_allmax_positive(big));
-  const int was = exponent_of(unit);
-  if (!none) e = min(e, was + (int)fminf(mnew - m, 1000.f) - (lower ? 1 : 0));
+  if (!none) e = min(e, unit + (int)fminf(mnew - m, 1000.f) - (lower ? 1 : 0));
   alpha = fast_exp2(m - mnew);
-  beta = __builtin_amdgcn_ldexpf(alpha, e - was);
+  beta = __builtin_amdgcn_ldexpf(alpha, e - unit);
   m = mnew;
-  unit = __builtin_amdgcn_ldexpf(1.f, e);
+  unit = e;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) w[q] *= unit;
+  for (int q = 0; q < 4; ++q) w[q] = __builtin_amdgcn_ldexpf(w[q], e);
 }
 
 // The running state of a range: NT tiles of four heads, a lane's head in tile t being 4 t + grp, NC column tiles of 16 channels.
@@ -112,14 +110,16 @@ template <int NT, int NC>
 struct FixedState {
   // (references to arrays of the kernel's: as members of one object some of them end up in memory)
   i32x4 (&digits)[NT][NC];
-  float (&m_ref)[NT], (&unit)[NT], (&lsum)[NT], (&zs)[NT];    // ... lsum, zs: of the p and of the w (z - 8), of this lane's tokens
+  float (&m_ref)[NT];
+  int (&unit)[NT];
+  float (&lsum)[NT], (&zs)[NT];                               // ... lsum, zs: of the p and of the w (z - 8), of this lane's tokens
   int& room;                                                  // batches until the digits could fill up
 
   __device__ __forceinline__ void clear() {
     room = kFlushAfter;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      m_ref[t] = -INFINITY; unit[t] = 1.f; lsum[t] = 0.f; zs[t] = 0.f;
+      m_ref[t] = -INFINITY; unit[t] = 0; lsum[t] = 0.f; zs[t] = 0.f;
 #pragma unroll
       for (int c = 0; c < NC; ++c) digits[t][c] = i32x4{0, 0, 0, 0};
     }
@@ -131,15 +131,15 @@ struct FixedState {
     room = kFlushAfter - 1;                                   // (there is something to be scaled)
     m_ref[t] = fmaxf(lg, kLeastLogit);
     const float p = fast_exp2(lg - m_ref[t]), ps = p * m.x;
-    unit[t] = __builtin_amdgcn_ldexpf(1.f, unit_exponent(fabsf(ps)));
-    const float w = ps * unit[t];
+    unit[t] = unit_exponent(fabsf(ps));
+    const float w = __builtin_amdgcn_ldexpf(ps, unit[t]);
     lsum[t] = one ? p : 0.f;
     zs[t] = one ? w * (m.y - 8.f) : 0.f;
 #pragma unroll
     for (int c = 0; c < NC; ++c) digits[t][c] = long_digits(16.f * w * code[c]);
   }
 
-  // A batch's logits (-infinity: masked; then its (scale, zero) is (0, 8)) of this lane's four tokens and its heads become weights, whose
+  // A batch's logits (-infinity: masked; then its scale is 0) of this lane's four tokens and its heads become weights, whose
   // digits go to rows 4 grp + l of tile t.  vm: the tokens' pairs, NM = 1 for all tiles or one set for each.
   // (Sums of the p are checked with the weights: where the scales are small or 0 they would grow without a weight that shows it.)
   template <int NM>
@@ -154,7 +154,7 @@ struct FixedState {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           p[t][q] = fast_exp2(lg[t][q] - m_ref[t]);           // exp2(-inf) = 0 for masked tokens
-          w[t][q] = p[t][q] * (vm[t * (NM - 1)][q].x * unit[t]);
+          w[t][q] = p[t][q] * __builtin_amdgcn_ldexpf(vm[t * (NM - 1)][q].x, unit[t]);
           most = max_or_nan(most, fabsf(w[t][q]));
         }
         sum[t] = (p[t][0] + p[t][1]) + (p[t][2] + p[t][3]);
@@ -202,7 +202,7 @@ struct FixedState {
   }
   // ... and then channel 16 c + row16 of this lane's head, not normalised
   __device__ __forceinline__ float value(int t, int c) const {
-    return __builtin_amdgcn_ldexpf(fmaf(long_digits_value(digits[t][c]), 1.f / 16.f, -zs[t]), -exponent_of(unit[t]));
+    return __builtin_amdgcn_ldexpf(fmaf(long_digits_value(digits[t][c]), 1.f / 16.f, -zs[t]), -unit[t]);
   }
 };
 

@@ -115,7 +115,7 @@ def test_chosen_logits(saw, G, Hkv, d, kind, B, L):
 
 
 @pytest.mark.parametrize("G,Hkv,d", SHAPES)
-@pytest.mark.parametrize("lo,hi", [(-60, 60), (-95, -80), (60, 90), (90, 120)])
+@pytest.mark.parametrize("lo,hi", [(-60, 60), (-95, -80), (-126, -122), (60, 90), (90, 120)])
 def test_value_scales_far_apart(saw, G, Hkv, d, lo, hi):
     """Scales of the values over many powers of two, some zero: units follow the weights p s, not the p."""
     L = 1000
