@@ -322,7 +322,7 @@ void decode_int4_split64_kernel(DecodeParams p) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const float lg = (meta[0].x * qunit[t]) * fmaf(-meta[0].y, qsum[t], digits_value(mfma_i8(a_q[t], kb, i32x4{0, 0, 0, 0})));
-      m_ref[t] = fmaxf(lg, kLeastLogit);
+      m_ref[t] = fmaxf(ceilf(lg), kLeastLogit);
       const float pr = fast_exp2(lg - m_ref[t]), ps = pr * meta[1].x;
       unit[t] = unit_exponent(fabsf(ps));
       const float w = __builtin_amdgcn_ldexpf(ps, unit[t]);

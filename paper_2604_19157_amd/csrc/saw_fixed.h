@@ -14,14 +14,15 @@ constexpr int kDigitTile = 16 * kDigitRow;     // four heads
 
 __device__ __forceinline__ i32x4 mfma_i8(i32x4 a, i32x4 b, i32x4 c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
 
-// Weights w = 2^u p s as fixed-point numbers: p = 2^(logit - m) with a reference m per head, the largest logit met when it was set, and a
-// unit per head, 2^-u, that puts the largest p s met then at 2^(kWeightBits - 1) to 2^kWeightBits.  Both are set anew when
-// a weight outgrows kWeightMost, the most that four digits hold.  So every weight is rounded to 2^-28 of the largest or finer, and
-// where the n weights of a range fall short of that altogether its result is off by n 2^-28 at most; the matrix cores' fp32 sums, cut
-// off at 2^-23 twice a batch, made that up to n 2^-28 too.  A unit further up has to be set anew more often; one
-// further down rounds to 2^-27 (64 ragged sequences x 8 single 64-channel heads, eight query heads: 26.9 us and 26.7).
+// Weights w = 2^u p s as fixed-point numbers: p = 2^(logit - m) with a reference m per head, the largest logit met when it was set, rounded
+// up to a whole number so that sums are scaled by exact powers of two when it moves; and a unit 2^-u per head that puts the largest p s met
+// then at 2^(kWeightBits - 1) to 2^kWeightBits.  Both are set anew when a weight outgrows kWeightMost, the most that four digits hold.
+// So every weight is rounded to 2^-28 of the largest or finer, and where the n weights of a range fall short of that altogether its
+// result is off by n 2^-28 at most; the matrix cores' fp32 sums, cut off at 2^-23 twice a batch, made that up to n 2^-28 too.  A unit
+// further up has to be set anew more often; one further down rounds to 2^-27 (64 ragged sequences x 8 single 64-channel heads, eight query
+// heads: 26.9 us and 26.7).
 // The unit is the head's own, and the scales are in it and not in the reference: scales of other heads cannot reach a head's weights, and
-// denominators, sums of p, are at least 1 however far apart the scales of ranges, partitions and batches are.
+// denominators, sums of p, are at least 1/2 however far apart the scales of ranges, partitions and batches are.
 constexpr int kWeightBits = 28;
 constexpr float kWeightMost = 2.1e9f;
 constexpr float kLeastLogit = -3.402823466e38f;  // references are finite: a logit of -infinity is a weight of 0
@@ -84,7 +85,7 @@ __device__ __forceinline__ int unit_exponent(float big) {
 __device__ __forceinline__ void set_reference(const float (&lg)[4], const f32x2 (&vm)[4], bool none, bool lower, float& m, int& unit,
                                               float (&p)[4], float (&w)[4], float& alpha, float& beta) {
   const float mx = row_allmax(fmaxf(fmaxf(lg[0], lg[1]), fmaxf(lg[2], lg[3])));
-  const float mnew = fmaxf(fmaxf(m, kLeastLogit), mx);
+  const float mnew = fmaxf(fmaxf(m, kLeastLogit), ceilf(mx));
   float big = 0.f;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -93,9 +94,10 @@ __device__ __forceinline__ void set_reference(const float (&lg)[4], const f32x2 
     big = fmaxf(big, fabsf(w[q]));
   }
   int e = unit_exponent(row_allmax_positive(big));
-  if (!none) e = min(e, unit + (int)fminf(mnew - m, 1000.f) - (lower ? 1 : 0));
-  alpha = fast_exp2(m - mnew);
-  beta = __builtin_amdgcn_ldexpf(alpha, e - unit);
+  const int up = (int)fminf(mnew - m, 1000.f);
+  if (!none) e = min(e, unit + up - (lower ? 1 : 0));
+  alpha = __builtin_amdgcn_ldexpf(1.f, -up);
+  beta = __builtin_amdgcn_ldexpf(1.f, e - unit - up);
   m = mnew;
   unit = e;
 #pragma unroll
@@ -129,7 +131,7 @@ struct FixedState {
   // lane counts it for the head.  Pairs that are not finite carry on into lsum and zs.
   __device__ __forceinline__ void open(int t, float lg, f32x2 m, const float (&code)[NC], bool one) {
     room = kFlushAfter - 1;                                   // (there is something to be scaled)
-    m_ref[t] = fmaxf(lg, kLeastLogit);
+    m_ref[t] = fmaxf(ceilf(lg), kLeastLogit);
     const float p = fast_exp2(lg - m_ref[t]), ps = p * m.x;
     unit[t] = unit_exponent(fabsf(ps));
     const float w = __builtin_amdgcn_ldexpf(ps, unit[t]);
