@@ -276,6 +276,7 @@ int launch_decode(const DecodeParams& p, int B, int D, int G, bool kv16, bool va
   return hipGetLastError() == hipSuccess ? SAW_OK : SAW_ELAUNCH;
 }
 
+// (Times as the lines were drawn by, with products of bf16 limbs.)
 // How the matrix-core INT4 kernel hands out work when one partition covers each sequence and the
 // batch provides more (sequence, kv head) items than compute units (and at most 16 lengths per
 // lane for the in-kernel ranking).  A compute unit holds 8 wavefronts of this kernel, 2048 on
